@@ -424,7 +424,14 @@ int64_t pent_size(pent_handle h); /* n, or -1 for a bad handle */
  *           the blocks of one 64-system tile could not all be resident at
  *           once.  Its waits are bounded; a wait that runs out (only possible
  *           when other work holds most of the device) leaves wrong values in
- *           that solve and is reported by pent_check.  The number of
+ *           that solve and is reported by pent_check.  With 64-row
+ *           segments and at least 5120 systems, and where the matrix carries
+ *           a back substitution's state less than 2^-72 of itself over some
+ *           512 rows, the same one pass runs as streaming sweeps instead:
+ *           a workgroup walks down the rows of whole tiles, waits only
+ *           inside itself and needs no scratch (a form of this kind; the
+ *           automatic schedule also takes it for smaller systems in large
+ *           batches).  The number of
  *           segments per workgroup (4) can be set to 2, 4 or 8 with the
  *           environment variable PENT_ONEPASS_WAVES, read once per process
  *           (tuning).

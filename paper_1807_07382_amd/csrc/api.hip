@@ -102,6 +102,7 @@ void free_plan(pent_plan *p)
         if (c.d_grp) (void)hipFree(c.d_grp);
     if (p->d_scan) (void)hipFree(p->d_scan);
     if (p->d_trec) (void)hipFree(p->d_trec);
+    if (p->d_trunc) (void)hipFree(p->d_trunc);
     if (p->d_err) (void)hipFree(p->d_err);
     p->magic = 0;
     delete p;
@@ -131,12 +132,17 @@ pent_plan *new_plan(int64_t n, int *st)
     p->d_scan = nullptr;
     p->d_trec = nullptr;
     p->scan_rows = 0;
+    p->d_trunc = nullptr;
+    p->strm_depth[0] = p->strm_depth[1] = 0;
+    p->cus = 0;
     p->d_err = nullptr;
     p->onepass_cap[0] = p->onepass_cap[1] = 0;
     p->fix_cap = 0;
     p->t_cap = 0;
     p->tst_cap = 0;
     hipError_t e = hipGetDevice(&p->device);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (e == hipSuccess) e = hipMalloc(&p->d_diag, sizeof(double) * 5 * n);
     if (e == hipSuccess) e = hipMalloc(&p->d_fac, sizeof(double) * 4 * n);
     if (e == hipSuccess) e = hipMalloc(&p->d_anorm, sizeof(double));
@@ -174,37 +180,44 @@ bool tile_cache(pent_plan *p, int rows, const ScanRec **scan, const double **tre
 pent_handle finish_factor(pent_plan *p)
 {
     int64_t *d_bad = nullptr;
-    int64_t bad = -1;
+    int64_t bad[3] = {-1, 0, 0};  // the pivot check, then the streaming sweeps' two depths
     int st = PENT_OK;
-    hipError_t e = hipMalloc(&d_bad, sizeof(int64_t));
+    hipError_t e = hipMalloc(&d_bad, sizeof(bad));
     if (e == hipSuccess) e = launch_factor(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, d_bad, 0);
     if (e == hipSuccess) e = launch_anorm(p->d_diag, p->n, p->d_anorm, 0);
     if (e == hipSuccess) {
         std::lock_guard<std::mutex> lk(p->mu);
-        // and the group constants of the many-matrix single pass (64-row
-        // segments, four per group)
-        if (!seg_cache_locked(p, 64, &st, false) || !seg_cache_locked(p, 32, &st, false) ||
-            !grp_cache_locked(p, 64, 4, &st, false))
+        if (!seg_cache_locked(p, 64, &st, false) || !seg_cache_locked(p, 32, &st, false))
             e = hipErrorUnknown;
+    }
+    const bool strm = p->n <= kStreamMaxRows;
+    if (e == hipSuccess && strm) {
+        const SegCache &s32 = p->seg[seg_slot(32)], &s64 = p->seg[seg_slot(64)];
+        e = hipMalloc(&p->d_trunc, sizeof(double) * 4 * (s32.nseg + s64.nseg));
+        if (e == hipSuccess)
+            e = launch_stream_prep(s32.d_seg, s32.nseg, p->d_trunc, s64.d_seg, s64.nseg, p->d_trunc + 4 * s32.nseg,
+                                   d_bad + 1, 0);
     }
     if (e == hipSuccess && tile_rows_for(p->n) > 0) {
         const ScanRec *sc;
         const double *tr;
         if (!tile_cache(p, tile_rows_for(p->n), &sc, &tr, &st, false)) e = hipErrorUnknown;
     }
-    if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int64_t), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(bad, d_bad, strm ? sizeof(bad) : sizeof(bad[0]), hipMemcpyDeviceToHost);
     if (d_bad) (void)hipFree(d_bad);
     if (e != hipSuccess) {
         free_plan(p);
         ret(st != PENT_OK ? st : hip_status(e));
         return nullptr;
     }
-    if (bad >= 0) {
+    if (bad[0] >= 0) {
         free_plan(p);
-        g_pivot_row = bad;
+        g_pivot_row = bad[0];
         ret(PENT_ZERO_PIVOT);
         return nullptr;
     }
+    p->strm_depth[0] = (int)bad[1];
+    p->strm_depth[1] = (int)bad[2];
     query_onepass_cap(p, 64);  // occupancy only; lets the default pick the single pass
     p->magic = kMagic;
     ret(PENT_OK);
@@ -391,6 +404,38 @@ void io_schedule(const pent_plan *p, int64_t batch, bool inplace64, int *kind, i
     }
 }
 
+// Whether a solve that io_schedule gave (kind, seg_rows) runs as the
+// streaming sweeps instead, which need no scratch: 32-row blocks where their
+// depth allows, else 64-row ones.  They put a tile on one compute unit and
+// walk down its rows, about 0.65 us per 32 of them at the least, so they want
+// many systems.  In the places of the single pass (and of the partitioned
+// form where that stands in for it below n = 1024) they win from about 5000
+// systems at every n (us, streaming / before: n = 2048 58 / 56 at 5003, 57 /
+// 81 at 8192; n = 4096 110 / 112 and 110 / 159; n = 8192 230 / 224 and 214 /
+// 290).  In the resident tile's place, from a batch that grows with n (n = 64
+// 8 / 22 at 5003; n = 256 10.5 / 16.5 at 2500; n = 1000 25 / 25 at 2500, 27 /
+// 57 at 5003; n = 4096 not at all within its sizes: 90 / 42 at 1024).  A
+// schedule forced to 64-row single pass streams by the same rule; any other
+// forced schedule is run as asked.
+bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, StreamPlan *p)
+{
+    const bool single = kind == 4 && seg_rows == 64;
+    if ((!single && h->sched_kind != 0) || onepass_waves_override()) return false;
+    const int i = h->strm_depth[0] > 0 ? 0 : h->strm_depth[1] > 0 ? 1 : -1;
+    if (i < 0 || (batch + 31) / 32 > INT32_MAX) return false;
+    const int64_t nblk = (h->n + 31) / 32;
+    if (batch < (kind == 3 ? std::min<int64_t>(80 * nblk, 2560) : 5120)) return false;
+    const SegCache &c = h->seg[seg_slot(i == 0 ? 32 : 64)];
+    p->fwd = h->d_fwd;
+    p->bwd = h->d_bwd;
+    p->seg = c.d_seg;
+    p->trunc = h->d_trunc + (i == 0 ? 0 : 4 * h->seg[seg_slot(32)].nseg);
+    p->rows = i == 0 ? 32 : 64;
+    p->depth = h->strm_depth[i];
+    p->cus = h->cus;
+    return true;
+}
+
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
 // summ_bytes() for the chosen schedule.
 int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int64_t ldx,
@@ -399,6 +444,11 @@ int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int6
     const bool inplace64 = !f32 && (const void *)x == f && ldx == ldf;
     int kind, seg_rows, st;
     io_schedule(h, batch, inplace64, &kind, &seg_rows);
+    StreamPlan sp;
+    if (stream_route(h, kind, seg_rows, batch, &sp)) {
+        const int cw = stream_tile_width(batch, h->cus);
+        return hip_status(launch_stream(sp, h->n, f, f32, ldf, cw, x, ldx, cw, batch, cw, h->d_err, s));
+    }
     if (kind == 1)
         return hip_status(launch_lane_sweep(h->d_fwd, h->d_bwd, h->n, x, batch, ldx, seg_rows, s));
     if (kind == 3) {
@@ -424,7 +474,8 @@ int solve_io_scratch(pent_plan *h, const double *f, int64_t ldf, double *x, int6
 {
     int kind, seg_rows;
     io_schedule(h, batch, (const void *)f == (const void *)x && ldf == ldx, &kind, &seg_rows);
-    const size_t bytes = summ_bytes(h, kind, seg_rows, batch);
+    StreamPlan sp;
+    const size_t bytes = stream_route(h, kind, seg_rows, batch, &sp) ? 0 : summ_bytes(h, kind, seg_rows, batch);
     void *summ = nullptr;
     if (bytes) {
         hipError_t e = scratch_alloc(&summ, bytes, s);
@@ -780,8 +831,6 @@ int group_bind(pent_group g, double *const *F, const int64_t *batch, const int64
         pent_plan *p = g->plans[k];
         const SegRec *seg64 = seg_cache(p, 64, &st);
         if (!seg64) return st;
-        const GrpRec *grp64 = grp_cache(p, 64, 4, &st);
-        if (!grp64) return st;
         const SegRec *segp = seg_cache(p, kGroupSegRows, &st);
         if (!segp) return st;
         const GrpRec *grpp = grp_cache(p, kGroupSegRows, 4, &st);
@@ -794,7 +843,7 @@ int group_bind(pent_group g, double *const *F, const int64_t *batch, const int64
             const double *tr;
             if (!tile_cache(p, tile_rows_for(p->n), &sc, &tr, &st)) return st;
         }
-        mats[k] = GroupMat{p->d_fwd, p->d_bwd, seg64, grp64, F[k], p->n, p->npad, ld[k], batch[k],
+        mats[k] = GroupMat{p->d_fwd, p->d_bwd, seg64, F[k], p->n, p->npad, ld[k], batch[k],
                            segp, grpp};
     }
     for (size_t k = 0; k < cnt; k++)
@@ -1115,9 +1164,13 @@ int pent_solve_tiled(pent_handle h, double *F, int64_t batch, int64_t ld, int64_
     int kind, seg_rows, st;
     io_schedule(h, batch, true, &kind, &seg_rows);
     if (kind != 4) return ret(PENT_NOT_SUPPORTED);
+    hipStream_t s = (hipStream_t)stream;
+    StreamPlan sp;
+    if (stream_route(h, kind, seg_rows, batch, &sp))
+        return ret(hip_status(launch_stream(sp, h->n, F, false, ld, tile_stride, F, ld, tile_stride, batch, 64,
+                                            h->d_err, s)));
     const SegRec *seg = seg_cache(h, seg_rows, &st);
     if (!seg) return ret(st);
-    hipStream_t s = (hipStream_t)stream;
     void *summ = nullptr;
     hipError_t e = scratch_alloc(&summ, summ_bytes(h, kind, seg_rows, batch), s);
     if (e != hipSuccess) return ret(hip_status(e));
@@ -1558,7 +1611,9 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
     // status words, and the step needs no clearing kernel between the two
     int ykind, yseg;
     io_schedule(hy, ybatch, false, &ykind, &yseg);
-    const size_t ybytes = summ_bytes(hy, ykind, yseg, ybatch);
+    StreamPlan ysp;
+    const bool ystream = stream_route(hy, ykind, yseg, ybatch, &ysp);  // needs no scratch
+    const size_t ybytes = ystream ? 0 : summ_bytes(hy, ykind, yseg, ybatch);
     void *ybuf = nullptr;
     if (ybytes) {
         const hipError_t e = scratch_alloc(&ybuf, ybytes, s);
@@ -1577,7 +1632,7 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
             void *xbuf = nullptr;
             hipError_t e = scratch_alloc(&xbuf, onepass_t_scratch_bytes(nx, batch), s);
             if (e == hipSuccess) {
-                const bool clear = ykind == 4 &&
+                const bool clear = ykind == 4 && !ystream &&
                                    onepass_words(hy->n, yseg, ybatch) <= onepass_t_threads(nx, batch);
                 e = launch_onepass_t_ch2d(hx->d_fwd, hx->d_bwd, seg64, nx, C, R, ny, ninst, dt, h, xbuf,
                                           hx->d_err, s, clear ? (unsigned int *)ybuf : nullptr,

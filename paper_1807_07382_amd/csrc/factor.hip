@@ -256,7 +256,7 @@ __global__ void k_records(const double *__restrict__ diag, const double *__restr
 //           incoming states (1,0) and (0,1).
 // The recurrences are the same prescaled ones the sweeps use.
 template <int K>
-__global__ void k_seg_prep(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd,
+__global__ __launch_bounds__(64) void k_seg_prep(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd,
                            int64_t n, int64_t nseg, SegRec *__restrict__ seg)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -265,13 +265,16 @@ __global__ void k_seg_prep(const FwdRec *__restrict__ fwd, const BwdRec *__restr
     const int L = (int)((n - r0) < K ? (n - r0) : K);
     double u[K], v[K];
     SegRec out;
+    // Every record of the segment is loaded (the table is padded), and only
+    // used where its row exists: latency-bound, one load a row under a
+    // condition was waited for row by row (30 us for 64 rows at N = 4096, now 21).
     // forward responses
     {
         double up2 = 1.0, up1 = 0.0, vp2 = 0.0, vp1 = 1.0;
 #pragma unroll
         for (int k = 0; k < K; k++) {
+            const FwdRec r = fwd[r0 + k];
             if (k < L) {
-                const FwdRec r = fwd[r0 + k];
                 const double gu = fma(-r.bp, up1, -r.ap * up2);
                 const double gv = fma(-r.bp, vp1, -r.ap * vp2);
                 u[k] = gu; v[k] = gv;
@@ -290,8 +293,8 @@ __global__ void k_seg_prep(const FwdRec *__restrict__ fwd, const BwdRec *__restr
         double aq1 = 1.0, aq2 = 0.0, bq1 = 0.0, bq2 = 1.0;
 #pragma unroll
         for (int k = K - 1; k >= 0; k--) {
+            const BwdRec q = bwd[r0 + k];
             if (k < L) {
-                const BwdRec q = bwd[r0 + k];
                 const double xu = fma(-q.gm, uq1, fma(-q.dl, uq2, u[k]));
                 const double xv = fma(-q.gm, vq1, fma(-q.dl, vq2, v[k]));
                 const double xa = fma(-q.gm, aq1, -q.dl * aq2);
@@ -326,7 +329,7 @@ __device__ __forceinline__ void mat2_mul(const double *a, const double *b, doubl
 // segments [G*W, G*W + W) of each group G (the segment table is padded with
 // all-zero records past the matrix).  One lane, serial over the groups; a
 // few hundred matrix products per matrix, once per handle.
-__global__ void k_grp_prep(const SegRec *__restrict__ seg, int W, int64_t ngroups,
+__global__ __launch_bounds__(64) void k_grp_prep(const SegRec *__restrict__ seg, int W, int64_t ngroups,
                            GrpRec *__restrict__ grp)
 {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;

@@ -120,7 +120,6 @@ struct GroupMat {
     const FwdRec *fwd;
     const BwdRec *bwd;
     const SegRec *seg64;  // transfer matrices for 64-row segments
-    const GrpRec *grp64;  // group constants for 64-row segments, four per group
     double *F;          // right-hand sides, batch-fastest, overwritten in place
     int64_t n, npad, ld, batch;
     const SegRec *segp;  // the single pass's segments (kGroupSegRows rows) ...
@@ -185,6 +184,27 @@ struct GrpCache {
     GrpRec *d_grp = nullptr;
 };
 
+// Streaming sweeps (stream.hip): a block waits for the next `depth` blocks
+// below it and neglects the state beyond, which the matrix carries up to it
+// by less than kTruncTarget.  Below that a neglected state vanishes against
+// the one it is left out of as long as the two are within 2^18 of each
+// other; where they are not, the kernel adds it.
+constexpr double kTruncTarget = 0x1p-72;
+// Depths up to which the streams run: of the 16 waves that hold a tile's
+// 32-row blocks (12 of 64 rows) enough must be left to load.  N = 4096,
+// 65536 systems: 776 us at 10 blocks of 32 (in place; 774 us FP32 N = 8192 x
+// 32768 at 12, against 603 at 10), 833 us at 8 of 64 (868 at 9).
+constexpr int kStreamDepth32 = 10, kStreamDepth64 = 8, kStreamMaxDepth = 10;
+constexpr int64_t kStreamMaxRows = (int64_t)1 << 20;  // past it the depth is not searched for
+
+struct StreamPlan {
+    const FwdRec *fwd = nullptr;
+    const BwdRec *bwd = nullptr;
+    const SegRec *seg = nullptr;     // of `rows`-row segments
+    const double *trunc = nullptr;   // P_b of every segment (stream.h)
+    int rows = 0, depth = 0, cus = 0;
+};
+
 }  // namespace pent
 
 struct pent_plan {
@@ -210,6 +230,9 @@ struct pent_plan {
     pent::SegCache seg[pent::kMaxSegCaches];
     pent::GrpCache grp[pent::kMaxGrpCaches];  // lazily built, guarded by mu
     pent::ScanRec *d_scan;   // resident-tile scan constants (64 records), lazily built
+    double *d_trunc;         // truncation products of the streaming sweeps: 32-row segments, then 64-row
+    int strm_depth[2];       // their depths (32, 64 rows), 0: too deep to stream
+    int cus;                 // compute units of the device
     double *d_trec;          // resident-tile record image (5 x 64 x rows doubles)
     int scan_rows;           // rows per lane they were built for
 };
@@ -391,6 +414,15 @@ hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *se
                           int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
                           hipStream_t s, int64_t tsf = 64, int64_t tsx = 64,
                           bool words_clear = false);  // words_clear: the status words are zero already
+
+// ---- streaming sweeps (stream.hip) ----
+// p32, p64: 4 doubles per segment; depth[0..1] (device): the two depths.
+hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
+                              double *p64, int64_t *depth, hipStream_t s);
+int stream_tile_width(int64_t batch, int cus);
+// Tile t of cw <= 64 systems starts at F + t * tsf and X + t * tsx.
+hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
+                         int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
 
 // ---- measurement (copy.hip): dst = src through the single pass's blocks ----
 hipError_t launch_block_copy(const double *src, double *dst, int64_t n, int64_t batch, int64_t lds,

@@ -1,0 +1,184 @@
+// stream.hip -- the sweeps of Sec. 2.4 as one stream down the rows of each
+// tile of systems (stream.h): f read once, x written once, nothing exchanged
+// through memory and nothing to clear before the launch.
+#include "stream.h"
+
+namespace pent {
+namespace {
+
+using namespace st;
+
+// Tiles of cw <= 64 systems, tile t's first column at t * tsf (f) and t * tsx
+// (x).  HBM-bound: a wave's 32-row block lives 23 us of which its four sweeps
+// take 1.5; 10 are spent waiting for the blocks below to load and 12 issuing
+// loads and stores into a memory pipeline that is full (trace by the 100 MHz
+// counter, N = 4096 x 65536).  That solve takes 800 us, 5.4 TB/s, as does a
+// bare copy through the same persistent blocks (770 to 830 us for any block
+// shape on this layout); the look-back single pass took 950.
+template <int K, int NW, int EU, bool NT, typename TI>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU))) void k_stream(
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, int64_t n, int nblk,
+    const TI *F, int64_t ldf, int64_t tsf, double *X, int64_t ldx, int64_t tsx, int64_t batch, int cw, int ntiles,
+    unsigned int *err)
+{
+    __shared__ StreamLds<NW> sh;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    const int lane = threadIdx.x & 63;
+    stream_init(sh);
+    const Tiles mine = my_tiles(ntiles);
+    int t = mine.t0, b = w, par = 0;
+    auto skip = [&]() {  // block index into tile and block
+        while (b >= nblk) {
+            b -= nblk;
+            t += mine.step;
+        }
+    };
+    skip();
+    for (unsigned int q = w; t < mine.end; q += NW, par ^= 1) {
+        const bool act = lane < cw && (int64_t)t * cw + lane < batch;
+        const int64_t r0 = (int64_t)b * K;
+        const int L = (int)(n - r0 < K ? n - r0 : K);
+        double v[K];
+        Rec<K> rc = load_rec<K>(fwd, bwd, r0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_sched_barrier(0);  // the records first: the first sweep needs them with its first row
+        // idle lanes repeat the tile's first column
+        load_block<K, NT, TI>(v, F + (int64_t)t * tsf + r0 * ldf, act ? lane : 0, ldf, L);
+        stream_phases<K, NW>(v, rc, (CSeg)seg, (CTrunc)trunc, b, nblk, D, q, w, par, sh, err);
+        if (act) store_block<K, NT>(v, X + (int64_t)t * tsx + r0 * ldx, lane, ldx, L);
+        b += NW;
+        skip();
+    }
+    store_fence();  // every wave's x is in memory before the repair reads it
+    __syncthreads();
+    if (sh.repair)
+        for (t = mine.t0 + w * mine.step; t < mine.end; t += NW * mine.step) {
+            const bool act = lane < cw && (int64_t)t * cw + lane < batch;
+            stream_repair<K>(X + (int64_t)t * tsx + (act ? lane : 0), ldx, act, n, nblk, D, (CBwd)bwd, (CTrunc)trunc);
+        }
+}
+
+// The truncation depth of one segment table and its products P_b: D is the
+// smallest depth at which every P_b with a state left to neglect (b + D <
+// nseg - 1) has all entries below kTruncTarget, 0 if that takes more than
+// dmax segments.  One workgroup per table, a thread per segment: latency-
+// bound, so all of a product's factors are fetched before the first is used
+// and the maxima stay in registers until the end (8 us at N = 4096; 100 us
+// with the loads in the loop and a shared maximum per product).
+__global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, int da, double *pa, const SegRec *sb,
+                                                     int nb, int db, double *pb, int64_t *depth)
+{
+    constexpr int M = kStreamMaxDepth;
+    const SegRec *seg = blockIdx.x == 0 ? sa : sb;
+    const int nseg = blockIdx.x == 0 ? na : nb, dmax = blockIdx.x == 0 ? da : db;
+    double *out = blockIdx.x == 0 ? pa : pb;
+    __shared__ double mx[4][M];
+    typedef double D2 __attribute__((ext_vector_type(2)));
+    // f(i, m) for i = 1 .. M: m the product of the i segments after b
+    auto products = [&](int b, auto f) {
+        D2 t[M][2];
+#pragma unroll
+        for (int i = 0; i < M; i++) {
+            const D2 *p = (const D2 *)seg[b + 1 + i < nseg ? b + 1 + i : nseg - 1].tb;
+            t[i][0] = p[0];
+            t[i][1] = p[1];
+        }
+        double m[4] = {1.0, 0.0, 0.0, 1.0};
+#pragma unroll
+        for (int i = 0; i < M; i++) {
+            const double n0 = fma(m[2], t[i][0].y, m[0] * t[i][0].x), n1 = fma(m[3], t[i][0].y, m[1] * t[i][0].x);
+            const double n2 = fma(m[2], t[i][1].y, m[0] * t[i][1].x), n3 = fma(m[3], t[i][1].y, m[1] * t[i][1].x);
+            m[0] = n0;
+            m[1] = n1;
+            m[2] = n2;
+            m[3] = n3;
+            f(i + 1, m);
+        }
+    };
+    double top[M];
+#pragma unroll
+    for (int i = 0; i < M; i++) top[i] = 0.0;
+    for (int b = threadIdx.x; b < nseg - 1; b += 256)
+        products(b, [&](int i, const double(&m)[4]) {
+            if (b + i < nseg - 1)
+#pragma unroll
+                for (int k = 0; k < 4; k++) top[i - 1] = nan_max(top[i - 1], fabs(m[k]));
+        });
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        for (int d = 32; d > 0; d >>= 1) top[i] = nan_max(top[i], __shfl_xor(top[i], d, 64));
+        mx[threadIdx.x / 64][i] = top[i];
+    }
+    __syncthreads();
+    int D = 0;
+#pragma unroll
+    for (int i = M; i >= 1; i--) {
+        const double v = nan_max(nan_max(mx[0][i - 1], mx[1][i - 1]), nan_max(mx[2][i - 1], mx[3][i - 1]));
+        if (i <= dmax && v <= kTruncTarget) D = i;
+    }
+    if (threadIdx.x == 0) depth[blockIdx.x] = D;
+    if (D == 0) return;
+    for (int b = threadIdx.x; b < nseg; b += 256)
+        products(b, [&](int i, const double(&m)[4]) {
+            if (i == D)
+#pragma unroll
+                for (int k = 0; k < 4; k++) out[4 * (int64_t)b + k] = b + D < nseg - 1 ? m[k] : 0.0;
+        });
+}
+
+template <int K, int NW, int EU, bool NT, typename TI>
+hipError_t launch_k(const StreamPlan &p, int64_t n, const void *F, int64_t ldf, int64_t tsf, double *X, int64_t ldx,
+                    int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
+{
+    const int64_t ntiles = (batch + cw - 1) / cw, nblk = (n + K - 1) / K;
+    const int64_t grid = (ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8;
+    hipLaunchKernelGGL((k_stream<K, NW, EU, NT, TI>), dim3((unsigned)grid), dim3(64 * NW), 0, s, p.fwd, p.bwd, p.seg,
+                       p.trunc, p.depth, n, (int)nblk, (const TI *)F, ldf, tsf, X, ldx, tsx, batch, cw, (int)ntiles, err);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
+                              double *p64, int64_t *depth, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_stream_prep, dim3(2), dim3(256), 0, s, seg32, (int)n32, kStreamDepth32, p32, seg64, (int)n64,
+                       kStreamDepth64, p64, depth);
+    return hipGetLastError();
+}
+
+// Systems per tile: the width with the fewest systems in a compute unit's
+// turns (tiles are dealt whole; the rate of a compute unit, not of the
+// memory, bounds one that has a tile more than the others).  Multiples of 16
+// keep tiles on 128-byte lines of an aligned row.
+int stream_tile_width(int64_t batch, int cus)
+{
+    int best = 64;
+    int64_t cost = 0;
+    for (int cw = 64; cw >= 32; cw -= 16) {
+        const int64_t tiles = (batch + cw - 1) / cw, turns = (tiles + cus - 1) / cus;
+        if (cw == 64 || turns * cw < cost) {
+            best = cw;
+            cost = turns * cw;
+        }
+    }
+    return best;
+}
+
+hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
+                         int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
+{
+    const size_t ef = f32 ? sizeof(float) : sizeof(double);
+    const bool nt = (uintptr_t)F % 128 == 0 && (uintptr_t)X % 128 == 0 && ldf * ef % 128 == 0 && ldx * 8 % 128 == 0 &&
+                    tsf * ef % 64 == 0 && tsx * 8 % 128 == 0;
+#define PENT_STREAM_GO(K, NW, EU)                                                                                       \
+    return f32 ? (nt ? launch_k<K, NW, EU, true, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s)                \
+                     : launch_k<K, NW, EU, false, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s))              \
+               : (nt ? launch_k<K, NW, EU, true, double>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s)               \
+                     : launch_k<K, NW, EU, false, double>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s))
+    if (p.rows == 32) PENT_STREAM_GO(32, 16, 4);
+    PENT_STREAM_GO(64, 12, 3);
+#undef PENT_STREAM_GO
+}
+
+}  // namespace pent

@@ -1,0 +1,147 @@
+"""Streaming sweeps (the automatic schedule of large batches): block and tile
+edges, row strides and types, truncation depths, and right-hand sides for
+which the truncated backward chain alone would lose values."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1807_07382_amd import pentbatch as pb
+from tests._gpu import colerr, d4_tol, print_case, torch_dev
+from tests.test_oracle_pins import random_dd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    return torch_dev()
+
+
+def rand(torch, shape, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.rand(shape, dtype=torch.float64, device="cuda", generator=g) * 2 - 1
+
+
+def probes(m, width):
+    cols = {0, 1, width - 1, width, m // 2, m - 2, m - 1}
+    return np.array(sorted(c for c in cols if 0 <= c < m))
+
+
+# n: one block, block edges of 32 and 64 rows, a partial last block, more
+# blocks than waves; m: tiles of 32, 48 and 64 systems, partial last tiles;
+# sigma: depths from 1 block up to the 64-row form (1000) and past it (1e4:
+# the look-back single pass)
+@pytest.mark.parametrize("n,m,pad,sigma", [
+    (31, 700, 0, 50.0), (32, 701, 3, 0.1), (33, 2600, 0, 1e4), (64, 5120, 16, 50.0), (65, 5123, 0, 200.0),
+    (1000, 5003, 5, 1.0), (1023, 9000, 0, 50.0), (1025, 12300, 4, 50.0), (2049, 5121, 0, 300.0),
+    (2113, 6000, 16, 1000.0), (4096, 16385, 0, 50.0), (4099, 5120, 1, 0.01), (1536, 5150, 0, 1e4)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_stream_matches_oracle(torch, n, m, pad, sigma, f32):
+    print_case(test="stream", n=n, m=m, pad=pad, sigma=sigma, f32=f32)
+    B = rand(torch, (n, m + pad), n + m)
+    if f32:
+        B = B.float()
+    X = torch.full((n, m + pad), 7.0, dtype=torch.float64, device="cuda")
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_mixed(B[:, :m], X[:, :m])
+        if not f32:
+            F = B.clone()
+            p.solve_(F[:, :m])
+            assert torch.equal(F[:, :m], X[:, :m])          # in place: the same bits
+            assert torch.equal(F[:, m:], B[:, m:])          # the padding is left alone
+        p.check()
+    assert bool((X[:, m:] == 7.0).all())
+    c = probes(m, 64)
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(B[:, c].double().cpu().numpy()))
+    assert np.max(colerr(X[:, c].cpu().numpy(), ref)) <= d4_tol(sigma)
+
+
+def test_stream_general_matrix_and_bits_by_column(torch):
+    """A non-symmetric matrix; every system has the same bits wherever it
+    sits in the batch."""
+    n, m = 777, 6001
+    print_case(test="stream_general", n=n, m=m)
+    dg = random_dd(n, seed=5)
+    F = rand(torch, (n, m), 3)
+    perm = torch.randperm(m, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    with pb.Plan.factor(*dg) as p:
+        X = p.solve_(F.clone())
+        Y = p.solve_(F[:, perm].contiguous())
+        p.check()
+    assert torch.equal(X[:, perm], Y)
+    c = probes(m, 48)
+    ref = oracle.solve(dg, np.ascontiguousarray(F[:, c].cpu().numpy()))
+    assert np.max(colerr(X[:, c].cpu().numpy(), ref)) <= 1e-13
+
+
+@pytest.mark.parametrize("n,sigma", [(2050, 30.0), (2050, 700.0), (96, 0.1), (4096, 2.0)])
+@pytest.mark.parametrize("where", ["top", "middle", "bottom"])
+def test_stream_keeps_far_tails(torch, n, sigma, where):
+    """A right-hand side that is zero but for one row: far from it the
+    solution is many orders smaller, and still right in each stretch of rows
+    on its own.  The neighbours in the tile are ordinary systems.  A row
+    adds a few roundings (d4_tol) to the relative error of such a tail."""
+    m = 5120
+    print_case(test="stream_tail", n=n, sigma=sigma, where=where)
+    F = rand(torch, (n, m), 9)
+    c = np.array([0, 17, 63, 64, m - 1])
+    row = {"top": 1, "middle": n // 2, "bottom": n - 1}[where]
+    F[:, c] = 0.0
+    F[row, c] = 1.0
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(F[:, c].cpu().numpy()))
+    other = np.array([1, 18, 62, 65])
+    ref2 = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(F[:, other].cpu().numpy()))
+    with pb.Plan.factor_d4(n, sigma) as p:
+        X = p.solve_(F)
+        p.check()
+    X2 = X[:, other].cpu().numpy()
+    X = X[:, c].cpu().numpy()
+    assert np.max(colerr(X2, ref2)) <= d4_tol(sigma)
+    for r in range(0, n, 128):
+        big = np.max(np.abs(ref[r:r + 128]), axis=0)
+        err = np.max(np.abs(X[r:r + 128] - ref[r:r + 128]), axis=0)
+        assert np.all(err <= n * d4_tol(sigma) * big + 1e-290)
+
+
+@pytest.mark.parametrize("n,sigma", [(2050, 30.0), (2050, 700.0)])
+def test_stream_non_finite_systems(torch, n, sigma):
+    """A NaN or an infinity anywhere in a right-hand side leaves no finite
+    value in that system (as in the other schedules) and the others alone."""
+    m = 5120
+    print_case(test="stream_nan", n=n, sigma=sigma)
+    F = rand(torch, (n, m), 4)
+    with pb.Plan.factor_d4(n, sigma) as p:
+        clean = p.solve_(F.clone())
+        bad = {3: (n - 1, np.nan), 64: (n // 2, np.inf), 65: (0, np.nan), 5119: (n - 1, -np.inf)}
+        for col, (row, val) in bad.items():
+            F[row, col] = val
+        X = p.solve_(F)
+        p.check()
+    cols = list(bad)
+    assert not bool(torch.isfinite(X[:, cols]).any())
+    keep = [j for j in range(m) if j not in bad]
+    assert torch.equal(X[:, keep], clean[:, keep])
+
+
+def test_stream_tiled_layout_same_bits(torch):
+    """64-system tiles stored one after the other: the bits pent_solve gives
+    the same systems, and nothing written past a partial last tile's columns
+    or between tiles."""
+    n, m = 2100, 5150  # large enough for the single pass, which this layout wants
+    print_case(test="stream_tiled", n=n, m=m)
+    F = rand(torch, (n, m), 8)
+    nt, ts = (m + 63) // 64, 64 * n + 32
+    T = torch.full((nt, ts), 3.0, dtype=torch.float64, device="cuda")
+    for t in range(nt):
+        w = min(64, m - 64 * t)
+        T[t, :64 * n].view(n, 64)[:, :w] = F[:, 64 * t:64 * t + w]
+    with pb.Plan.factor_d4(n, 50.0) as p:
+        st = pb.lib().pent_solve_tiled(p.handle, T.data_ptr(), m, 64, ts, torch.cuda.current_stream().cuda_stream)
+        assert st == pb.OK
+        X = p.solve_(F.clone())
+        p.check()
+    for t in range(nt):
+        w = min(64, m - 64 * t)
+        V = T[t, :64 * n].view(n, 64)
+        assert torch.equal(V[:, :w], X[:, 64 * t:64 * t + w])
+        assert bool((V[:, w:] == 3.0).all()) and bool((T[t, 64 * n:] == 3.0).all())
