@@ -133,7 +133,7 @@ pent_plan *new_plan(int64_t n, int *st)
     p->d_trec = nullptr;
     p->scan_rows = 0;
     p->d_trunc = nullptr;
-    p->strm_depth[0] = p->strm_depth[1] = 0;
+    p->strm_depth[0] = p->strm_depth[1] = p->strm_depth[2] = 0;
     p->cus = 0;
     p->d_err = nullptr;
     p->onepass_cap[0] = p->onepass_cap[1] = 0;
@@ -180,7 +180,7 @@ bool tile_cache(pent_plan *p, int rows, const ScanRec **scan, const double **tre
 pent_handle finish_factor(pent_plan *p)
 {
     int64_t *d_bad = nullptr;
-    int64_t bad[3] = {-1, 0, 0};  // the pivot check, then the streaming sweeps' two depths
+    int64_t bad[4] = {-1, 0, 0, 0};  // the pivot check, then the streaming sweeps' depths
     int st = PENT_OK;
     hipError_t e = hipMalloc(&d_bad, sizeof(bad));
     if (e == hipSuccess) e = launch_factor(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, d_bad, 0);
@@ -218,6 +218,7 @@ pent_handle finish_factor(pent_plan *p)
     }
     p->strm_depth[0] = (int)bad[1];
     p->strm_depth[1] = (int)bad[2];
+    p->strm_depth[2] = (int)bad[3];
     query_onepass_cap(p, 64);  // occupancy only; lets the default pick the single pass
     p->magic = kMagic;
     ret(PENT_OK);
@@ -1242,7 +1243,17 @@ int pent_solve_mixed(pent_handle h, const void *f, int f_dtype, int64_t ld_f, do
     // fused correction fits on the device, each correction is one fused pass
     // too (residual, solve and update of x in one kernel); else residual,
     // solve, x += d.
-    if (refine_steps > 0 && L.fused) {
+    StreamPlan sp;
+    int kind, seg_rows;
+    io_schedule(h, batch, alias, &kind, &seg_rows);
+    if (refine_steps > 0 && h->strm_depth[2] > 0 && stream_route(h, kind, seg_rows, batch, &sp)) {
+        sp.seg = h->seg[seg_slot(32)].d_seg;
+        for (int it = 0; it < refine_steps; it++) {
+            hipError_t e = launch_stream_fix(sp, h->strm_depth[2], h->n, h->d_diag, f, f32, ld_f, x, ld_x, batch,
+                                             stream_tile_width(batch, h->cus), h->d_err, s);
+            if (e != hipSuccess) return ret(hip_status(e));
+        }
+    } else if (refine_steps > 0 && L.fused) {
         const SegRec *seg64 = seg_cache(h, 64, &st);
         if (!seg64) return ret(st);
         for (int it = 0; it < refine_steps; it++) {

@@ -195,6 +195,9 @@ constexpr double kTruncTarget = 0x1p-72;
 // 65536 systems: 776 us at 10 blocks of 32 (in place; 774 us FP32 N = 8192 x
 // 32768 at 12, against 603 at 10), 833 us at 8 of 64 (868 at 9).
 constexpr int kStreamDepth32 = 10, kStreamDepth64 = 8, kStreamMaxDepth = 10;
+// ... and of a refinement correction, whose 12 waves hold two arrays each.
+constexpr double kTruncFix = 0x1p-36;
+constexpr int kStreamDepthFix = 8;
 constexpr int64_t kStreamMaxRows = (int64_t)1 << 20;  // past it the depth is not searched for
 
 struct StreamPlan {
@@ -231,7 +234,7 @@ struct pent_plan {
     pent::GrpCache grp[pent::kMaxGrpCaches];  // lazily built, guarded by mu
     pent::ScanRec *d_scan;   // resident-tile scan constants (64 records), lazily built
     double *d_trunc;         // truncation products of the streaming sweeps: 32-row segments, then 64-row
-    int strm_depth[2];       // their depths (32, 64 rows), 0: too deep to stream
+    int strm_depth[3];       // their depths (32, 64 rows; corrections, 32), 0: too deep to stream
     int cus;                 // compute units of the device
     double *d_trec;          // resident-tile record image (5 x 64 x rows doubles)
     int scan_rows;           // rows per lane they were built for
@@ -416,13 +419,18 @@ hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *se
                           bool words_clear = false);  // words_clear: the status words are zero already
 
 // ---- streaming sweeps (stream.hip) ----
-// p32, p64: 4 doubles per segment; depth[0..1] (device): the two depths.
+// p32, p64: 4 doubles per segment; depth[0..2] (device): the two depths and
+// the corrections' (32-row segments).
 hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
                               double *p64, int64_t *depth, hipStream_t s);
 int stream_tile_width(int64_t batch, int cus);
 // Tile t of cw <= 64 systems starts at F + t * tsf and X + t * tsx.
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
                          int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
+
+// One refinement correction by 32-row blocks (p of 32-row segments).
+hipError_t launch_stream_fix(const StreamPlan &p, int depth, int64_t n, const double *diag, const void *F, bool f32,
+                             int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
 
 // ---- measurement (copy.hip): dst = src through the single pass's blocks ----
 hipError_t launch_block_copy(const double *src, double *dst, int64_t n, int64_t batch, int64_t lds,

@@ -225,18 +225,18 @@ __device__ __forceinline__ void sweep_backward(double (&v)[K], Rec<K> &r, double
 // every wave but this one has finished its block before q + NW: the readers
 // of y (block q + 1) and a (blocks before q) are done by then.  z is read by
 // block q + D, which may be later, so its slots alternate.
-template <int NW>
+template <int NW, bool CHECK = true>
 struct StreamLds {
-    double y[NW][2][64];     // state leaving the block downward
-    double a[NW][2][64];     // top state of the zero-start back substitution
-    double z[2][NW][2][64];  // state taken to enter the block from below
-    unsigned int fdone;      // blocks swept forward
+    double y[NW][2][64];                 // state leaving the block downward
+    double a[NW][2][64];                 // top state of the zero-start back substitution
+    double z[CHECK ? 2 : 1][CHECK ? NW : 1][2][64];  // state taken to enter the block from below
+    unsigned int fdone;                  // blocks swept forward
     unsigned int aflag[NW], zflag[2][NW];
-    unsigned int repair;     // some neglected state was not negligible
+    unsigned int repair;                 // some neglected state was not negligible
 };
 
-template <int NW>
-__device__ __forceinline__ void stream_init(StreamLds<NW> &sh)
+template <int NW, bool CHECK>
+__device__ __forceinline__ void stream_init(StreamLds<NW, CHECK> &sh)
 {
     if (threadIdx.x < NW) {
         sh.aflag[threadIdx.x] = 0;
@@ -280,9 +280,10 @@ typedef __attribute__((address_space(4))) const double *CTrunc;  // P_b, four do
 
 // Both sweeps of block q of the workgroup (block b of nblk of its tile, wave
 // w's par-th round): v holds the right-hand side on entry and x on exit.
-template <int K, int NW>
+// CHECK false: what is left out is known not to matter (the caller says why).
+template <int K, int NW, bool CHECK = true>
 __device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, CSeg seg, CTrunc trunc, int b, int nblk,
-                                              int D, unsigned int q, int w, int par, StreamLds<NW> &sh,
+                                              int D, unsigned int q, int w, int par, StreamLds<NW, CHECK> &sh,
                                               unsigned int *err)
 {
     const int lane = threadIdx.x & 63;
@@ -331,10 +332,12 @@ __device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, CSeg s
         z0 = __builtin_nan("");
         z1 = __builtin_nan("");
     }
-    sh.z[par][w][0][lane] = z0;
-    sh.z[par][w][1][lane] = z1;
-    lds_post(&sh.zflag[par][w], q + 1);
-    if (b >= D) {
+    if constexpr (CHECK) {
+        sh.z[par][w][0][lane] = z0;
+        sh.z[par][w][1][lane] = z1;
+        lds_post(&sh.zflag[par][w], q + 1);
+    }
+    if (CHECK && b >= D) {
         // what block b - D left out, P z, against the state it took
         const int ww = w >= D ? w - D : w - D + NW, pp = w >= D ? par : par ^ 1;
         const CTrunc P = trunc + 4 * (int64_t)(b - D);

@@ -58,6 +58,88 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
         }
 }
 
+// r = f - A x over a block (v: f on entry, r on exit; x the block's rows, h
+// the two rows above it and the two below), compensated (dot2_row); rows k >=
+// L zero.  The five diagonals come as the records do, one row per lane.
+template <int K>
+__device__ __forceinline__ void stream_residual(double (&v)[K], const double (&x)[K], const double (&h)[4],
+                                                const double *__restrict__ diag, int64_t n, int64_t r0, int L)
+{
+    double cl[5];
+    const int64_t row = r0 + (threadIdx.x & (K - 1));
+#pragma unroll
+    for (int d = 0; d < 5; d++) cl[d] = diag[d * n + (row < n ? row : n - 1)];  // rows past the matrix: dropped
+    unroll<K>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        if constexpr (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        const double cf[5] = {lane_get(cl[0], k), lane_get(cl[1], k), lane_get(cl[2], k), lane_get(cl[3], k),
+                              lane_get(cl[4], k)};
+        const double xv[5] = {k >= 2 ? x[k >= 2 ? k - 2 : 0] : h[k < 2 ? k : 0],
+                              k >= 1 ? x[k >= 1 ? k - 1 : 0] : h[1], x[k],
+                              k + 1 < K ? x[k + 1 < K ? k + 1 : 0] : h[2],
+                              k + 2 < K ? x[k + 2 < K ? k + 2 : 0] : h[k + 2 - K >= 0 ? 2 + k + 2 - K : 2]};
+        const double r = dot2_row(v[k], cf, xv);
+        v[k] = k < L ? r : 0.0;
+    });
+}
+
+// One refinement correction, x += A^{-1}(f - A x) in place, as a stream: each
+// block keeps its x beside the residual it turns into the correction, so x is
+// read once and written once (20 bytes per unknown with FP32 f; the look-back
+// form, k_onepass_fix, holds one array and reads x again: 28).  A block's halo
+// rows are read before its neighbours can have stored theirs: block b + 1
+// links its forward state after block b has swept its own rows, and block b -
+// 1 waits for block b's backward state.  The correction is itself of the size
+// of the error it takes away, so its backward chain stops where it would
+// change that by kTruncFix, and nothing is checked (a system with a value that
+// is not finite has none left after its first solve).  The chain's depth sets
+// the time: of 12 waves D wait (N = 8192 x 16384 FP32, sigma = 100: D = 7,
+// for kTruncTarget, 910 us; D = 4, for kTruncFix, 673; the look-back form 1099).
+template <int K, int NW, int EU, bool NT, typename TI>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU))) void k_stream_fix(
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *diag, int D, int64_t n, int nblk,
+    const TI *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, int ntiles, unsigned int *err)
+{
+    __shared__ StreamLds<NW, false> sh;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    const int lane = threadIdx.x & 63;
+    stream_init(sh);
+    const Tiles mine = my_tiles(ntiles);
+    int t = mine.t0, b = w;
+    auto skip = [&]() {
+        while (b >= nblk) {
+            b -= nblk;
+            t += mine.step;
+        }
+    };
+    skip();
+    for (unsigned int q = w; t < mine.end; q += NW) {
+        const bool act = lane < cw && (int64_t)t * cw + lane < batch;
+        const unsigned int lo = act ? lane : 0;  // idle lanes repeat the tile's first column
+        const int64_t r0 = (int64_t)b * K;
+        const int L = (int)(n - r0 < K ? n - r0 : K);
+        double *xt = X + (int64_t)t * cw;
+        double v[K], x[K], h[4];
+        // halo rows outside the matrix meet a zero diagonal entry
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int64_t r = i < 2 ? r0 - 2 + i : r0 + K + i - 2;
+            h[i] = xt[(r < 0 ? 0 : r >= n ? n - 1 : r) * ldx + lo];
+        }
+        load_block<K, false, double>(x, xt + r0 * ldx, lo, ldx, L);
+        load_block<K, NT, TI>(v, F + (int64_t)t * cw + r0 * ldf, lo, ldf, L);
+        stream_residual<K>(v, x, h, diag, n, r0, L);
+        __builtin_amdgcn_sched_barrier(0);
+        Rec<K> rc = load_rec<K>(fwd, bwd, r0);
+        stream_phases<K, NW, false>(v, rc, (CSeg)seg, nullptr, b, nblk, D, q, w, 0, sh, err);
+#pragma unroll
+        for (int k = 0; k < K; k++) v[k] = x[k] + v[k];
+        if (act) store_block<K, NT>(v, xt + r0 * ldx, lane, ldx, L);
+        b += NW;
+        skip();
+    }
+}
+
 // The truncation depth of one segment table and its products P_b: D is the
 // smallest depth at which every P_b with a state left to neglect (b + D <
 // nseg - 1) has all entries below kTruncTarget, 0 if that takes more than
@@ -110,13 +192,17 @@ __global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, i
         mx[threadIdx.x / 64][i] = top[i];
     }
     __syncthreads();
-    int D = 0;
+    int D = 0, Df = 0;
 #pragma unroll
     for (int i = M; i >= 1; i--) {
         const double v = nan_max(nan_max(mx[0][i - 1], mx[1][i - 1]), nan_max(mx[2][i - 1], mx[3][i - 1]));
         if (i <= dmax && v <= kTruncTarget) D = i;
+        if (i <= kStreamDepthFix && v <= kTruncFix) Df = i;
     }
-    if (threadIdx.x == 0) depth[blockIdx.x] = D;
+    if (threadIdx.x == 0) {
+        depth[blockIdx.x] = D;
+        if (blockIdx.x == 0) depth[2] = Df;
+    }
     if (D == 0) return;
     for (int b = threadIdx.x; b < nseg; b += 256)
         products(b, [&](int i, const double(&m)[4]) {
@@ -125,6 +211,9 @@ __global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, i
                 for (int k = 0; k < 4; k++) out[4 * (int64_t)b + k] = b + D < nseg - 1 ? m[k] : 0.0;
         });
 }
+
+// Whole rows on 128-byte lines.
+inline bool on_lines(const void *p, int64_t pitch) { return (uintptr_t)p % 128 == 0 && pitch % 128 == 0; }
 
 template <int K, int NW, int EU, bool NT, typename TI>
 hipError_t launch_k(const StreamPlan &p, int64_t n, const void *F, int64_t ldf, int64_t tsf, double *X, int64_t ldx,
@@ -165,12 +254,30 @@ int stream_tile_width(int64_t batch, int cus)
     return best;
 }
 
+hipError_t launch_stream_fix(const StreamPlan &p, int depth, int64_t n, const double *diag, const void *F, bool f32,
+                             int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
+{
+    constexpr int K = 32, NW = 12, EU = 3;
+    const int64_t ntiles = (batch + cw - 1) / cw, nblk = (n + K - 1) / K;
+    const dim3 grid((unsigned)((ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8)), block(64 * NW);
+    const size_t ef = f32 ? sizeof(float) : sizeof(double);
+    const bool nt = on_lines(F, ldf * ef) && on_lines(X, ldx * 8);
+#define PENT_FIX_GO(NT, T)                                                                                              \
+    hipLaunchKernelGGL((k_stream_fix<K, NW, EU, NT, T>), grid, block, 0, s, p.fwd, p.bwd, p.seg, diag, depth, n,          \
+                       (int)nblk, (const T *)F, ldf, X, ldx, batch, cw, (int)ntiles, err)
+    if (f32 && nt) PENT_FIX_GO(true, float);
+    else if (f32) PENT_FIX_GO(false, float);
+    else if (nt) PENT_FIX_GO(true, double);
+    else PENT_FIX_GO(false, double);
+#undef PENT_FIX_GO
+    return hipGetLastError();
+}
+
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
                          int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
 {
     const size_t ef = f32 ? sizeof(float) : sizeof(double);
-    const bool nt = (uintptr_t)F % 128 == 0 && (uintptr_t)X % 128 == 0 && ldf * ef % 128 == 0 && ldx * 8 % 128 == 0 &&
-                    tsf * ef % 64 == 0 && tsx * 8 % 128 == 0;
+    const bool nt = on_lines(F, ldf * ef) && on_lines(X, ldx * 8) && tsf * ef % 64 == 0 && tsx * 8 % 128 == 0;
 #define PENT_STREAM_GO(K, NW, EU)                                                                                       \
     return f32 ? (nt ? launch_k<K, NW, EU, true, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s)                \
                      : launch_k<K, NW, EU, false, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s))              \

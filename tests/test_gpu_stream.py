@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_1807_07382_amd import pentbatch as pb
-from tests._gpu import colerr, d4_tol, print_case, torch_dev
+from tests._gpu import U, colerr, d4_tol, print_case, torch_dev
 from tests.test_oracle_pins import random_dd
 
 pytestmark = pytest.mark.gpu
@@ -145,3 +145,29 @@ def test_stream_tiled_layout_same_bits(torch):
         V = T[t, :64 * n].view(n, 64)
         assert torch.equal(V[:, :w], X[:, 64 * t:64 * t + w])
         assert bool((V[:, w:] == 3.0).all()) and bool((T[t, 64 * n:] == 3.0).all())
+
+
+# n: partial and whole last blocks, fewer blocks than the correction's 12
+# waves and more; sigma: correction depths from 1 to 8 blocks and past it
+@pytest.mark.parametrize("n,m,pad,sigma", [(33, 2600, 0, 0.1), (1000, 5003, 3, 1.0), (1024, 9000, 0, 100.0),
+                                           (2081, 5120, 16, 2000.0), (4100, 5125, 0, 1e4)])
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("steps", [1, 2])
+def test_stream_corrections(torch, n, m, pad, sigma, f32, steps):
+    """Refined solves: within the solve's tolerance of the oracle, the
+    compensated backward error at rounding level (each correction leaves at
+    most one rounding of x per entry, |dx| <= u |x|, so eta <= u; 2 u covers
+    the evaluation), padding untouched."""
+    print_case(test="stream_fix", n=n, m=m, sigma=sigma, f32=f32, steps=steps)
+    B = rand(torch, (n, m + pad), n)
+    B = B.float() if f32 else B
+    X = torch.full((n, m + pad), 7.0, dtype=torch.float64, device="cuda")
+    eta = torch.empty(m, dtype=torch.float64, device="cuda")
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_mixed(B[:, :m], X[:, :m], steps, eta)
+        p.check()
+    assert bool((X[:, m:] == 7.0).all())
+    assert eta.max().item() <= 2 * U
+    c = probes(m, 64)
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(B[:, c].double().cpu().numpy()))
+    assert np.max(colerr(X[:, c].cpu().numpy(), ref)) <= d4_tol(sigma)
