@@ -382,7 +382,9 @@ int pent_cyclic_destroy(pent_cyclic c);
  *   of one 64-system tile fits on the device at once), kind 1 the E-solve
  *   followed by the update kernels (and, for the step, a separate stencil
  *   kernel), kind 2 single pass with seg_rows in {32, 64} (still falls back
- *   to kind 1 when the blocks would not fit).
+ *   to kind 1 when the blocks would not fit).  With 64 rows and at least 8192
+ *   systems the single pass runs as streaming sweeps where the matrix allows
+ *   it (see pent_set_schedule, kind 4).
  * pent_cyclic_query_schedule: the form a solve (cn = 0) or step (cn = 1) of
  *   `batch` systems runs: kind 1 or 2, seg_rows 0 unless kind 2.
  * pent_cyclic_check: blocking; PENT_TIMEOUT if a single-pass wait on this

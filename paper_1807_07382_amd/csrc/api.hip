@@ -405,6 +405,22 @@ void io_schedule(const pent_plan *p, int64_t batch, bool inplace64, int *kind, i
     }
 }
 
+// The streaming form of h's matrix on `rows`-row blocks; false when its
+// backward chain is too deep for that.
+bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
+{
+    const int i = rows == 32 ? 0 : 1;
+    if (h->strm_depth[i] <= 0) return false;
+    p->fwd = h->d_fwd;
+    p->bwd = h->d_bwd;
+    p->seg = h->seg[seg_slot(rows)].d_seg;
+    p->trunc = h->d_trunc + (i == 0 ? 0 : 4 * h->seg[seg_slot(32)].nseg);
+    p->rows = rows;
+    p->depth = h->strm_depth[i];
+    p->cus = h->cus;
+    return true;
+}
+
 // Whether a solve that io_schedule gave (kind, seg_rows) runs as the
 // streaming sweeps instead, which need no scratch: 32-row blocks where their
 // depth allows, else 64-row ones.  They put a tile on one compute unit and
@@ -422,19 +438,10 @@ bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, Str
 {
     const bool single = kind == 4 && seg_rows == 64;
     if ((!single && h->sched_kind != 0) || onepass_waves_override()) return false;
-    const int i = h->strm_depth[0] > 0 ? 0 : h->strm_depth[1] > 0 ? 1 : -1;
-    if (i < 0 || (batch + 31) / 32 > INT32_MAX) return false;
+    if ((batch + 31) / 32 > INT32_MAX) return false;
     const int64_t nblk = (h->n + 31) / 32;
     if (batch < (kind == 3 ? std::min<int64_t>(80 * nblk, 2560) : 5120)) return false;
-    const SegCache &c = h->seg[seg_slot(i == 0 ? 32 : 64)];
-    p->fwd = h->d_fwd;
-    p->bwd = h->d_bwd;
-    p->seg = c.d_seg;
-    p->trunc = h->d_trunc + (i == 0 ? 0 : 4 * h->seg[seg_slot(32)].nseg);
-    p->rows = i == 0 ? 32 : 64;
-    p->depth = h->strm_depth[i];
-    p->cus = h->cus;
-    return true;
+    return stream_plan(h, 32, p) || stream_plan(h, 64, p);
 }
 
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
@@ -594,6 +601,7 @@ struct pent_cyclic_s {
     int cap[2][2] = {{0, 0}, {0, 0}};  // co-resident single-pass units [seg 32/64][solve/CN]
     bool uni = false;           // each diagonal is the same in every row (bit for bit) ...
     double uc[5] = {0, 0, 0, 0, 0};  // ... with these values, a..e
+    int ends = 0;               // blocks at either end in which h^T E^{-1} counts, 0: no streaming
 };
 
 namespace {
@@ -690,6 +698,7 @@ pent_cyclic finish_cyclic(pent_cyclic c)
         }
     }
     CycAux aux;
+    if (st == PENT_OK) st = hip_status(launch_cyc_reach(c->d_W, n - 2, c->d_aux, 0));
     if (st == PENT_OK)
         st = hip_status(hipMemcpy(&aux, c->d_aux, sizeof(CycAux), hipMemcpyDeviceToHost));
     if (st != PENT_OK) {
@@ -703,6 +712,7 @@ pent_cyclic finish_cyclic(pent_cyclic c)
         ret(PENT_ZERO_PIVOT);
         return nullptr;
     }
+    c->ends = cyc_stream_ends(aux, n);
     // row-invariant diagonals (the constant-coefficient operators of the
     // paper's periodic problems): the CN step then reads them from its
     // arguments instead of five per-row loads
@@ -740,10 +750,28 @@ bool cyc_single_pass(pent_cyclic c, int64_t batch, bool cn)
            cyc_onepass_units(c->n, sr, batch) <= (int64_t)UINT32_MAX / 2;
 }
 
+// Systems from which the periodic single pass runs as streaming sweeps (us,
+// streaming / look-back, solve and step: N = 4096 x 5003 135 / 135 and 171 /
+// 139, x 8192 170 / 173 and 179 / 179, x 16384 212 / 322 and 219 / 329; N =
+// 1537 x 5003 62 / 61 and 67 / 63, x 16384 91 / 137 and 85 / 142).
+constexpr int64_t kCycStreamBatch = 8192;
+
 int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
                    int64_t batch, hipStream_t s)
 {
     int st;
+    StreamPlan sp;
+    if (c->seg_rows == 64 && batch >= kCycStreamBatch && c->ends > 0 && !onepass_waves_override() &&
+        stream_plan(c->E, 32, &sp)) {
+        const int cw = stream_tile_width(batch, c->E->cus);
+        void *dx = nullptr;
+        hipError_t e = scratch_alloc(&dx, cyc_stream_scratch_bytes(batch, cw), s);
+        if (e != hipSuccess) return hip_status(e);
+        e = launch_cyc_stream(sp, c->d_cd, c->d_Z, c->d_W, c->d_aux, c->ends, c->n, cn, F, ldf, X, ldx, batch, cw, dx,
+                              c->E->d_err, s, c->uni ? c->uc : nullptr);
+        const hipError_t e2 = hipFreeAsync(dx, s);
+        return hip_status(e != hipSuccess ? e : e2);
+    }
     const SegRec *seg = seg_cache(c->E, c->seg_rows, &st);
     if (!seg) return st;
     void *xbuf = nullptr;

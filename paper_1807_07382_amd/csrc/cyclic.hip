@@ -15,7 +15,9 @@
 //
 // Cyclic row-indexed diagonals: row i holds a[i] at column (i-2) mod n,
 // b[i] at (i-1) mod n, c[i] at i, d[i] at (i+1) mod n, e[i] at (i+2) mod n.
-#include "lookback.h"
+#include <algorithm>
+
+#include "stream.h"
 
 namespace pent {
 namespace {
@@ -550,6 +552,303 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     }
 }
 
+// ---- the same solve and step as streaming sweeps (stream.h): one workgroup
+// walks down whole tiles.  x_tail needs W^T f = h^T E^{-1} f^ before the first
+// block can be finished, and W = (h^T E^{-1})^T has values that count at both
+// ends of the rows only.  So a tile starts with its T bottom blocks read for
+// their part of W^T f alone (T / nblk more to read), then streams from the
+// top; with block T - 1 x_tail is known, before the first block's backward
+// state is.  The middle blocks' part is summed as they pass, and where it is
+// not negligible against what x_tail was formed from, the difference goes to
+// scratch (dx) and is applied after the workgroup's last block, as for the
+// truncated backward chain.  N = 4096 x 65536: solve 830 us, step 890, against
+// 1040 and 1090 by look-back (which waits 18 us of a unit's 49); a step costs
+// more than a plain solve (800) by its halo rows (25 us, through the L2), the
+// border products (18) and the values spilled for them.
+constexpr int kCsK = 32, kCsNW = 16, kCsEU = 4;
+
+struct CycLds {
+    double p[kCsNW][2][64];  // W^T f so far, beside the forward state in its slot
+    double xt[2][2][64];     // x_tail, by the tile's turn
+    double ft[2][64];        // f_{n-2}, f_{n-1}
+    unsigned int xflag;      // turns whose x_tail is there
+};
+
+// A two-column table (Z or W) of the block's rows as coefficients.
+__device__ __forceinline__ void load_pair(const double *tab, int64_t r0, st::Coef<kCsK> &a, st::Coef<kCsK> &b)
+{
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+        const st::Dbl2 u = ((const st::Dbl2 *)tab)[r0 + st::coef_row<kCsK>(s)];
+        a.c[s] = u.x;
+        b.c[s] = u.y;
+    }
+}
+
+struct CycExtra {
+    static constexpr bool late = true;  // with them the first sweep would not fit its registers
+    CycLds &c;
+    const double *Z;
+    st::Coef<kCsK> z0, z1;  // Z of the block's rows
+    double p0, p1;          // the block's part of W^T f
+    int item, b, T, nblk, w;
+    unsigned int turn;
+    bool act;
+    const CycAux *aux;
+    double *xm;             // X at row n-2 of the lane's system
+    int64_t ldx;
+    double *dx;             // the tile's two rows of scratch
+    st::StreamLds<kCsNW> &sh;
+    unsigned int *err;
+    double c0, c1;
+    __device__ __forceinline__ void fetch() { load_pair(Z, (int64_t)b * kCsK, z0, z1); }
+    __device__ __forceinline__ void ordered(int lane)
+    {
+        const int pw = w == 0 ? kCsNW - 1 : w - 1;
+        double s0 = 0.0, s1 = 0.0;
+        if (item != 0 && b != T) {  // the ends' sum starts with the tile, the middle's with block T
+            s0 = c.p[pw][0][lane];
+            s1 = c.p[pw][1][lane];
+        }
+        if (b < nblk - T) {  // (the bottom blocks came first)
+            s0 += p0;
+            s1 += p1;
+        }
+        c.p[w][0][lane] = s0;
+        c.p[w][1][lane] = s1;
+        if (b != T - 1 && b != nblk - 1) return;
+        const double m0 = aux->minv[0], m1 = aux->minv[1], m2 = aux->minv[2], m3 = aux->minv[3];
+        double(*xt)[64] = c.xt[turn & 1];
+        if (b == T - 1) {
+            const double r0 = c.ft[0][lane] - s0, r1 = c.ft[1][lane] - s1;
+            const double x0 = fma(m1, r1, m0 * r0), x1 = fma(m3, r1, m2 * r0);
+            xt[0][lane] = x0;
+            xt[1][lane] = x1;
+            st::lds_post(&c.xflag, turn + 1);
+            if (act) {
+                xm[lane] = x0;
+                xm[ldx + lane] = x1;
+            }
+        } else {
+            double d0 = -fma(m1, s1, m0 * s0), d1 = -fma(m3, s1, m2 * s0);
+            const bool fine = fmax(fabs(d0), fabs(d1)) <= st::kNegligible * fmax(fabs(xt[0][lane]), fabs(xt[1][lane])) &&
+                              d0 == d0 && d1 == d1;
+            if (fine) d0 = d1 = 0.0;
+            dx[lane] = d0;
+            dx[64 + lane] = d1;
+            if (__ballot(!fine) != 0 && lane == 0) atomicMax(&sh.last[turn % 32], 0);
+        }
+    }
+    __device__ __forceinline__ void ready()
+    {
+        const int lane = threadIdx.x & 63;
+        const bool ok = st::lds_wait(&c.xflag, turn + 1);
+        c0 = c.xt[turn & 1][0][lane];
+        c1 = c.xt[turn & 1][1][lane];
+        if (!ok) {
+            if (lane == 0) atomicOr(err, 1u);
+            c0 = c1 = __builtin_nan("");
+        }
+    }
+    template <int k>
+    __device__ __forceinline__ double out(double x) const
+    {
+        return fma(-z1.template get<k>(), c1, fma(-z0.template get<k>(), c0, x));
+    }
+    __device__ __forceinline__ void hold()
+    {
+        z0.hold();
+        z1.hold();
+    }
+};
+
+template <bool CN, bool UNI, bool NT>
+__global__ __launch_bounds__(64 * kCsNW) __attribute__((amdgpu_waves_per_eu(kCsEU, kCsEU))) void k_cyc_stream(
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, const double *__restrict__ cd,
+    const double *Z, const double *Wt, const CycAux *__restrict__ aux, int T, int64_t n, int nblk, const double *F,
+    int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, int ntiles, double *dx, unsigned int *err, CycUni uc)
+{
+    using namespace st;
+    constexpr int K = kCsK, NW = kCsNW;
+    __shared__ StreamLds<NW> sh;
+    __shared__ CycLds cl;
+    const int64_t m = n - 2;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) cl.xflag = 0;
+    stream_init(sh);
+    const Tiles mine = my_tiles(ntiles);
+    const int nit = T + nblk;  // items of a tile: the bottom blocks' products, then the blocks
+    int t = mine.t0, item = w, par = 0;
+    unsigned int turn = 0;
+    auto skip = [&]() {
+        while (item >= nit) {
+            item -= nit;
+            t += mine.step;
+            turn++;
+        }
+    };
+    skip();
+    for (unsigned int q = w; t < mine.end; q += NW, par ^= 1) {
+        const bool act = lane < cw && (int64_t)t * cw + lane < batch;
+        const unsigned int lo = act ? lane : 0;  // idle lanes repeat the tile's first column
+        const bool pre = item < T;
+        const int b = pre ? nblk - T + item : item - T;
+        const int64_t r0 = (int64_t)b * K;
+        const int L = (int)(m - r0 < K ? m - r0 : K);  // E rows of the block
+        const double *ft = F + (int64_t)t * cw;
+        double *xt = X + (int64_t)t * cw;
+        double v[K];
+        if constexpr (CN) {
+            // C rows r0-2 .. r0+K+1, periodic (only the top block wraps: past
+            // the last E row stand rows n-2 and n-1), and f over them
+            double h[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int64_t r = i < 2 ? r0 - 2 + i : r0 + K + i - 2;
+                h[i] = ft[(r < 0 ? r + n : r >= n ? n - 1 : r) * ldf + lo];
+            }
+            load_block<K, false, double>(v, ft + r0 * ldf, lo, ldf, (int)(n - r0 < K ? n - r0 : K));
+            double g[5];
+            if constexpr (!UNI) {
+#pragma unroll
+                for (int d = 0; d < 5; d++) g[d] = cd[d * cyc_ld(n) + r0 + (lane & (K - 1))];
+            }
+            double c2 = h[0], c1 = h[1];
+            unroll<K>([&](auto kk) {
+                constexpr int k = decltype(kk)::value;
+                if constexpr (!UNI && k % 8 == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int d = 0; d < 5; d++) pin(g[d]);
+                }
+                const double ck = v[k];
+                const double n1 = k + 1 < K ? v[k + 1 < K ? k + 1 : 0] : h[2];
+                const double n2 = k + 2 < K ? v[k + 2 < K ? k + 2 : 0] : (k + 2 == K ? h[2] : h[3]);
+                CycUni u = uc;
+                if constexpr (!UNI) u = CycUni{{lane_get(g[0], k), lane_get(g[1], k), lane_get(g[2], k),
+                                                lane_get(g[3], k), lane_get(g[4], k)}};
+                const double f = cn_row_u(u, c2, c1, ck, n1, n2);
+                v[k] = k < L ? f : 0.0;
+                c2 = c1;
+                c1 = ck;
+            });
+        } else {
+            load_block<K, NT, double>(v, ft + r0 * ldf, lo, ldf, L);
+        }
+        CycExtra ex{cl, Z, {}, {}, 0.0, 0.0, item, pre ? -1 : b, T, nblk, w, turn, act, aux, xt + m * ldx, ldx,
+                    dx + (int64_t)t * 128, sh, err, 0.0, 0.0};
+        {
+            Coef<K> w0, w1;
+            load_pair(Wt, r0, w0, w1);
+            unroll<K>([&](auto kk) {
+                constexpr int k = decltype(kk)::value;
+                if constexpr (k % 8 == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    w0.hold();
+                    w1.hold();
+                }
+                ex.p0 = fma(w0.template get<k>(), v[k], ex.p0);
+                ex.p1 = fma(w1.template get<k>(), v[k], ex.p1);
+            });
+            pin(ex.p0);
+            pin(ex.p1);
+        }
+        if (pre) {
+            if (item == T - 1) {  // the right-hand side's last two entries
+                if constexpr (CN) {
+                    const double c0 = ft[(m - 2) * ldf + lo], c1 = ft[(m - 1) * ldf + lo], c2 = ft[m * ldf + lo],
+                                 c3 = ft[(m + 1) * ldf + lo], c4 = ft[lo], c5 = ft[ldf + lo];
+                    CycUni u = uc, u1 = uc;
+                    if constexpr (!UNI)
+                        for (int d = 0; d < 5; d++) {
+                            u.c[d] = cd[d * cyc_ld(n) + m];
+                            u1.c[d] = cd[d * cyc_ld(n) + m + 1];
+                        }
+                    cl.ft[0][lane] = cn_row_u(u, c0, c1, c2, c3, c4);
+                    cl.ft[1][lane] = cn_row_u(u1, c1, c2, c3, c4, c5);
+                } else {
+                    cl.ft[0][lane] = ft[m * ldf + lo];
+                    cl.ft[1][lane] = ft[(m + 1) * ldf + lo];
+                }
+            }
+            if (!lds_wait(&sh.fdone, q) && lane == 0) atomicOr(err, 1u);
+            ex.ordered(lane);
+            lds_post(&sh.fdone, q + 1);
+        } else {
+            Rec<K> rc;
+            load_forward<K>(rc, fwd, r0);
+            stream_phases<K, NW, true, CycExtra &>(v, rc, bwd, (CSeg)seg, (CTrunc)trunc, b, nblk, D, q, w, par, turn, sh, err, ex);
+            if (act) store_block<K, NT>(v, xt + r0 * ldx, lane, ldx, L);
+        }
+        item += NW;
+        skip();
+    }
+    store_fence();  // every wave's x is in memory before the repair reads it
+    __syncthreads();
+    const CDbl Zc = (CDbl)Z;
+    turn = 0;
+    for (t = mine.t0; t < mine.end; t += mine.step, turn++) {
+        if (sh.last[turn % 32] < 0) continue;
+        const bool act = lane < cw && (int64_t)t * cw + lane < batch;
+        double *x = X + (int64_t)t * cw + (act ? lane : 0);
+        const double c0 = xload(x + m * ldx), c1 = xload(x + (m + 1) * ldx);
+        stream_repair<K, NW>(x, ldx, act, m, nblk, D, (CSeg)seg, (CBwd)bwd, (CTrunc)trunc, sh, w, turn % 32,
+                             [&](int64_t i) { return fma(Zc[2 * i + 1], c1, Zc[2 * i] * c0); });
+        // x -= Z (the tail's difference), in the blocks where it counts
+        // against the rows at their ends
+        const double d0 = xload(dx + (int64_t)t * 128 + lane), d1 = xload(dx + (int64_t)t * 128 + 64 + lane);
+        const bool add = act && !(d0 == 0.0 && d1 == 0.0);
+        if (__ballot(add) == 0) continue;
+        for (int b = w; b < nblk; b += NW) {  // (every wave sees the repaired tile: stream_repair ends in a barrier)
+            const int64_t r0 = (int64_t)b * K;
+            const int L = (int)(m - r0 < K ? m - r0 : K);
+            auto change = [&](int64_t i) { return fma(Zc[2 * i + 1], d1, Zc[2 * i] * d0); };
+            auto counts = [&](int64_t i) {  // at rows i, i + 1
+                const int64_t j = i + 1 < m ? i + 1 : i;
+                const double e0 = change(i), e1 = change(j);
+                return !(fmax(fabs(e0), fabs(e1)) <= kRepair * fmax(fabs(xload(x + i * ldx)), fabs(xload(x + j * ldx)))) ||
+                       e0 != e0 || e1 != e1;
+            };
+            const bool here = add && (counts(r0) || counts(r0 + (L >= 2 ? L - 2 : 0)));
+            if (__ballot(here) == 0) continue;
+            for (int k = 0; k < L; k++)
+                if (here) xstore(x + (r0 + k) * ldx, xload(x + (r0 + k) * ldx) - change(r0 + k));
+        }
+        if (w == 0 && add) {
+            xstore(x + m * ldx, c0 + d0);
+            xstore(x + (m + 1) * ldx, c1 + d1);
+        }
+    }
+}
+
+// Rows from either end of W beyond which every entry is below kTruncTarget of
+// its largest.
+__global__ __launch_bounds__(256) void k_cyc_reach(const double *__restrict__ Wt, int64_t m, CycAux *aux)
+{
+    __shared__ double top[256];
+    __shared__ unsigned long long r[2];
+    double big = 0.0;
+    for (int64_t i = threadIdx.x; i < 2 * m; i += 256) big = nan_max(big, fabs(Wt[i]));
+    top[threadIdx.x] = big;
+    if (threadIdx.x < 2) r[threadIdx.x] = 0ull;
+    __syncthreads();
+    for (int i = 0; i < 256; i++) big = nan_max(big, top[i]);
+    unsigned long long rt = 0, rb = 0;
+    for (int64_t i = threadIdx.x; i < m; i += 256)
+        if (!(fmax(fabs(Wt[2 * i]), fabs(Wt[2 * i + 1])) <= kTruncTarget * big)) {
+            if (i < m / 2) rt = (unsigned long long)(i + 1) > rt ? i + 1 : rt;
+            else rb = (unsigned long long)(m - i) > rb ? m - i : rb;
+        }
+    atomicMax(&r[0], rt);
+    atomicMax(&r[1], rb);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        aux->reach[0] = (int64_t)r[0];
+        aux->reach[1] = (int64_t)r[1];
+    }
+}
+
 __global__ void k_cyc_zero(unsigned int *p, int64_t count)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -656,6 +955,47 @@ hipError_t launch_cyc_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec
                     (void *)&err, (void *)&uc};
     return hipLaunchKernel(cyc_fn_kw(seg_rows, W, cn, uni != nullptr), dim3((unsigned)units),
                            dim3(64 * W), args, 0, s);
+}
+
+hipError_t launch_cyc_reach(const double *Wt, int64_t m, CycAux *aux, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_cyc_reach, dim3(1), dim3(256), 0, s, Wt, m, aux);
+    return hipGetLastError();
+}
+
+int cyc_stream_ends(const CycAux &aux, int64_t n)
+{
+    const int64_t m = n - 2, nblk = (m + kCsK - 1) / kCsK;
+    const int64_t t = (aux.reach[0] + kCsK - 1) / kCsK, b = nblk - (m - aux.reach[1]) / kCsK;
+    const int64_t T = std::max<int64_t>(std::max(t, b), 1);
+    // enough blocks that the ends do not meet and a tile's next-but-one turn
+    // comes after its waves have finished
+    return nblk >= 3 * T && nblk >= kCsNW ? (int)T : 0;
+}
+
+size_t cyc_stream_scratch_bytes(int64_t batch, int cw) { return (size_t)((batch + cw - 1) / cw) * 128 * sizeof(double); }
+
+hipError_t launch_cyc_stream(const StreamPlan &p, const double *cd, const double *Z, const double *Wt, const CycAux *aux,
+                             int T, int64_t n, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
+                             int64_t batch, int cw, void *scratch, unsigned int *err, hipStream_t s, const double *uni)
+{
+    const int64_t ntiles = (batch + cw - 1) / cw;
+    const int nblk = (int)((n - 2 + kCsK - 1) / kCsK), nt = (int)ntiles, D = p.depth;
+    const int64_t grid = (ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8;
+    const bool lines = (uintptr_t)F % 128 == 0 && (uintptr_t)X % 128 == 0 && ldf % 16 == 0 && ldx % 16 == 0;
+    CycUni uc = {{0.0, 0.0, 0.0, 0.0, 0.0}};
+    if (uni)
+        for (int k = 0; k < 5; k++) uc.c[k] = uni[k];
+    const void *fn;
+    if (!cn) fn = lines ? (const void *)k_cyc_stream<false, false, true> : (const void *)k_cyc_stream<false, false, false>;
+    else if (uni) fn = lines ? (const void *)k_cyc_stream<true, true, true> : (const void *)k_cyc_stream<true, true, false>;
+    else fn = lines ? (const void *)k_cyc_stream<true, false, true> : (const void *)k_cyc_stream<true, false, false>;
+    double *dx = (double *)scratch;
+    void *args[] = {(void *)&p.fwd, (void *)&p.bwd, (void *)&p.seg, (void *)&p.trunc, (void *)&D,    (void *)&cd,
+                    (void *)&Z,     (void *)&Wt,    (void *)&aux,   (void *)&T,       (void *)&n,    (void *)&nblk,
+                    (void *)&F,     (void *)&ldf,   (void *)&X,     (void *)&ldx,     (void *)&batch, (void *)&cw,
+                    (void *)&nt,    (void *)&dx,    (void *)&err,   (void *)&uc};
+    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64 * kCsNW), args, 0, s);
 }
 
 hipError_t launch_cyc_assemble_d4(double *cd, int64_t n, double sigma, hipStream_t s)

@@ -144,6 +144,7 @@ struct CycAux {
     int64_t hcol[10];
     double hv[10];
     double minv[4];
+    int64_t reach[2];  // rows at the top and at the bottom in which (h^T E^{-1})^T counts (k_cyc_reach)
 };
 
 // One unit of the single-pass group solve: rows [g*rows, (g+1)*rows) of
@@ -186,9 +187,12 @@ struct GrpCache {
 
 // Streaming sweeps (stream.hip): a block waits for the next `depth` blocks
 // below it and neglects the state beyond, which the matrix carries up to it
-// by less than kTruncTarget.  Below that a neglected state vanishes against
-// the one it is left out of as long as the two are within 2^18 of each
-// other; where they are not, the kernel adds it.
+// by less than kTruncTarget.  A neglected state then vanishes against the one
+// it is left out of as long as the two are within 2^18 of each other; where
+// they are not, the kernel adds it.  (For 2^-96 a Gaussian of width N / 20
+// needs nothing added, N = 4096 x 65536 854 instead of 888 us, but every
+// solve waits for more blocks: FP32 8192 x 32768 690 instead of 621, the
+// periodic step 962 instead of 892.)
 constexpr double kTruncTarget = 0x1p-72;
 // Depths up to which the streams run: of the 16 waves that hold a tile's
 // 32-row blocks (12 of 64 rows) enough must be left to load.  N = 4096,
@@ -475,6 +479,15 @@ hipError_t launch_cyc_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec
                               int seg_rows, bool cn, const double *Fin, int64_t ldf, double *X,
                               int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
                               hipStream_t s, const double *uni = nullptr);
+// The same as streaming sweeps (stream.h): p of 32-row segments of E, T =
+// cyc_stream_ends (0: too few rows for it).
+hipError_t launch_cyc_reach(const double *Wt, int64_t m, CycAux *aux, hipStream_t s);
+int cyc_stream_ends(const CycAux &aux, int64_t n);
+size_t cyc_stream_scratch_bytes(int64_t batch, int cw);
+hipError_t launch_cyc_stream(const StreamPlan &p, const double *cd, const double *Z, const double *Wt, const CycAux *aux,
+                             int T, int64_t n, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
+                             int64_t batch, int cw, void *scratch, unsigned int *err, hipStream_t s,
+                             const double *uni = nullptr);
 hipError_t launch_cyc_finish(const double *cd, int64_t n, const double *Z, CycAux *aux,
                              hipStream_t s);
 // etd: 5(n-2) diagonals of E^T; H: zrows x 2, ld 2, H[i][q] = A[n-2+q][i]

@@ -20,6 +20,8 @@
 // decides only how often the repair runs.
 #pragma once
 
+#include <climits>
+#include <type_traits>
 #include <utility>
 
 #include "lookback.h"
@@ -94,23 +96,37 @@ struct Rec {
     Coef<K> ra, ap, bp, gm, dl;
 };
 
+// Row of the block that this lane's register s holds.
 template <int K>
-__device__ __forceinline__ Rec<K> load_rec(const FwdRec *f, const BwdRec *b, int64_t r0)
+__device__ __forceinline__ int coef_row(int s)
 {
-    typedef double D2 __attribute__((ext_vector_type(2)));
-    Rec<K> r;
+    return K == 32 ? 16 * s + (int)(threadIdx.x & 15) : (int)(threadIdx.x & 63);
+}
+
+typedef double Dbl2 __attribute__((ext_vector_type(2)));
+
+template <int K>
+__device__ __forceinline__ void load_forward(Rec<K> &r, const FwdRec *f, int64_t r0)
+{
 #pragma unroll
     for (int s = 0; s < Coef<K>::S; s++) {
-        const int l = K == 32 ? 16 * s + (threadIdx.x & 15) : threadIdx.x & 63;
-        const D2 *p = (const D2 *)(f + r0 + l);
-        const D2 u = p[0], v = p[1], q = *(const D2 *)(b + r0 + l);
+        const Dbl2 *p = (const Dbl2 *)(f + r0 + coef_row<K>(s));
+        const Dbl2 u = p[0];
         r.ra.c[s] = u.x;
         r.ap.c[s] = u.y;
-        r.bp.c[s] = v.x;
+        r.bp.c[s] = p[1].x;
+    }
+}
+
+template <int K>
+__device__ __forceinline__ void load_backward(Rec<K> &r, const BwdRec *b, int64_t r0)
+{
+#pragma unroll
+    for (int s = 0; s < Coef<K>::S; s++) {
+        const Dbl2 q = *(const Dbl2 *)(b + r0 + coef_row<K>(s));
         r.gm.c[s] = q.x;
         r.dl.c[s] = q.y;
     }
-    return r;
 }
 
 // Rows p, p + ld, ... at lane offset lo into v; rows k >= L give zero (the
@@ -198,10 +214,24 @@ __device__ __forceinline__ void sweep_forward(double (&v)[K], Rec<K> &r, double 
     });
 }
 
+// What a plain solve adds to the phases: nothing.
+struct Plain {
+    static constexpr bool late = false;              // whether the backward records wait for the second sweep
+    __device__ __forceinline__ void fetch() {}       // with the backward records, ahead of the second sweep
+    __device__ __forceinline__ void ordered(int) {}  // in the tile's order, with the forward state
+    __device__ __forceinline__ void ready() {}       // before the last sweep
+    template <int k>
+    __device__ __forceinline__ double out(double x) const  // what is stored for row k
+    {
+        return x;
+    }
+    __device__ __forceinline__ void hold() {}
+};
+
 // Back substitution over the block from (q1, q2) = (x_{r0+K}, x_{r0+K+1}); on
-// exit (q1, q2) = (x_{r0}, x_{r0+1}).  STORE writes x over v.
-template <int K, bool STORE>
-__device__ __forceinline__ void sweep_backward(double (&v)[K], Rec<K> &r, double &q1, double &q2)
+// exit (q1, q2) = (x_{r0}, x_{r0+1}).  STORE writes x (ex.out of it) over v.
+template <int K, bool STORE, typename Extra>
+__device__ __forceinline__ void sweep_backward(double (&v)[K], Rec<K> &r, double &q1, double &q2, Extra &ex)
 {
     unroll<K>([&](auto kk) {
         constexpr int k = K - 1 - decltype(kk)::value;
@@ -209,9 +239,10 @@ __device__ __forceinline__ void sweep_backward(double (&v)[K], Rec<K> &r, double
             __builtin_amdgcn_sched_barrier(0);
             r.gm.hold();
             r.dl.hold();
+            if (STORE) ex.hold();
         }
         const double x = fma(-r.gm.template get<k>(), q1, fma(-r.dl.template get<k>(), q2, v[k]));
-        if (STORE) v[k] = x;
+        if (STORE) v[k] = ex.template out<k>(x);
         q2 = q1;
         q1 = x;
     });
@@ -232,7 +263,7 @@ struct StreamLds {
     double z[CHECK ? 2 : 1][CHECK ? NW : 1][2][64];  // state taken to enter the block from below
     unsigned int fdone;                  // blocks swept forward
     unsigned int aflag[NW], zflag[2][NW];
-    unsigned int repair;                 // some neglected state was not negligible
+    int last[32], first[32];             // by turn % 32: the tile's blocks that left out something not negligible
 };
 
 template <int NW, bool CHECK>
@@ -243,10 +274,11 @@ __device__ __forceinline__ void stream_init(StreamLds<NW, CHECK> &sh)
         sh.zflag[0][threadIdx.x] = 0;
         sh.zflag[1][threadIdx.x] = 0;
     }
-    if (threadIdx.x == 0) {
-        sh.fdone = 0;
-        sh.repair = 0;
+    if (threadIdx.x < 32) {
+        sh.last[threadIdx.x] = -1;
+        sh.first[threadIdx.x] = INT_MAX;
     }
+    if (threadIdx.x == 0) sh.fdone = 0;
     __syncthreads();
 }
 
@@ -281,10 +313,11 @@ typedef __attribute__((address_space(4))) const double *CTrunc;  // P_b, four do
 // Both sweeps of block q of the workgroup (block b of nblk of its tile, wave
 // w's par-th round): v holds the right-hand side on entry and x on exit.
 // CHECK false: what is left out is known not to matter (the caller says why).
-template <int K, int NW, bool CHECK = true>
-__device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, CSeg seg, CTrunc trunc, int b, int nblk,
-                                              int D, unsigned int q, int w, int par, StreamLds<NW, CHECK> &sh,
-                                              unsigned int *err)
+template <int K, int NW, bool CHECK, typename Extra>
+__device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, const BwdRec *bwd, CSeg seg, CTrunc trunc, int b, int nblk,
+                                              int D, unsigned int q, int w, int par, unsigned int turn,
+                                              StreamLds<NW, CHECK> &sh,
+                                              unsigned int *err, Extra ex)
 {
     const int lane = threadIdx.x & 63;
     // forward: the block's outgoing state for a zero incoming one, while the
@@ -308,11 +341,18 @@ __device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, CSeg s
     link(e0, e1, t0, t1, t2, t3, n0, n1);
     sh.y[w][0][lane] = n0;
     sh.y[w][1][lane] = n1;
+    ex.ordered(lane);
     lds_post(&sh.fdone, q + 1);
     __builtin_amdgcn_s_setprio(0);
+    if constexpr (std::remove_reference_t<Extra>::late) {
+        load_backward<K>(rc, bwd, (int64_t)b * K);
+        ex.fetch();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     sweep_forward<K, true>(v, rc, y0, y1);
     double a0 = 0.0, a1 = 0.0;
-    sweep_backward<K, false>(v, rc, a0, a1);
+    sweep_backward<K, false>(v, rc, a0, a1, ex);
     pin(a0);
     pin(a1);
     sh.a[w][0][lane] = a0;
@@ -346,47 +386,116 @@ __device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, CSeg s
         const double c0 = fma(p2, z1, p0 * z0), c1 = fma(p3, z1, p1 * z0);
         const double o0 = sh.z[pp][ww][0][lane], o1 = sh.z[pp][ww][1][lane];
         const bool fine = fmax(fabs(c0), fabs(c1)) <= kNegligible * fmax(fabs(o0), fabs(o1)) && c0 == c0 && c1 == c1;
-        if (__ballot(!fine) != 0) sh.repair = 1u;
+        if (__ballot(!fine) != 0 && lane == 0) {
+            atomicMax(&sh.last[turn % 32], b - D);
+            atomicMin(&sh.first[turn % 32], b - D);
+        }
     }
-    sweep_backward<K, true>(v, rc, z0, z1);
+    ex.ready();
+    sweep_backward<K, true>(v, rc, z0, z1, ex);
     // x is complete here: keep the sweep from sinking into the stores
 #pragma unroll
     for (int k = 0; k < K; k++) pin(v[k]);
 }
 
-// Adds to a finished tile what its blocks left out (see above), from the
-// bottom block up, one wave per tile: element (i, this lane's system) of x at
-// x[i * rs].  Every value is read past the caches of the compute unit, in
-// which lines loaded earlier may still stand.
-template <int K>
-__device__ __forceinline__ void stream_repair(double *x, int64_t rs, bool act, int64_t n, int nblk, int D,
-                                              CBwd bwd, CTrunc trunc)
+// f(k, row r + k of this lane) for 16 rows, one pointer moved along.
+template <typename F>
+__device__ __forceinline__ void repair_rows(double *x, int64_t rs, int64_t r, F f)
 {
-    for (int b = nblk - 2 - D; b >= 0; b--) {
-        const int64_t re = (int64_t)(b + D + 1) * K, ro = (int64_t)(b + 1) * K;  // rows below the states
-        const double e0 = xload(x + re * rs), e1 = re + 1 < n ? xload(x + (re + 1) * rs) : 0.0;
-        const double o0 = xload(x + ro * rs), o1 = ro + 1 < n ? xload(x + (ro + 1) * rs) : 0.0;
-        const CTrunc P = trunc + 4 * (int64_t)b;
-        double d1 = fma(P[2], e1, P[0] * e0), d2 = fma(P[3], e1, P[1] * e0);
-        const bool fine = fmax(fabs(d1), fabs(d2)) <= kRepair * fmax(fabs(o0), fabs(o1)) && d1 == d1 && d2 == d2;
-        const bool add = act && !fine;
-        if (__ballot(add) == 0) continue;
-        if (!add) d1 = d2 = 0.0;
-        for (int k0 = K - 8; k0 >= 0; k0 -= 8) {
-            const int64_t r = (int64_t)b * K + k0;
-            double o[8];
+    double *p = x + r * rs;
 #pragma unroll
-            for (int k = 0; k < 8; k++) o[k] = xload(x + (r + k) * rs);
-#pragma unroll
-            for (int k = 7; k >= 0; k--) {
-                const double d = fma(-bwd[r + k].gm, d1, -bwd[r + k].dl * d2);
-                d2 = d1;
-                d1 = d;
-                if (add) xstore(x + (r + k) * rs, o[k] + d);
+    for (int k = 0; k < 16; k++) {
+        f(k, p);
+        p += rs;
+        asm volatile("" : "+v"(p));
+    }
+}
+
+// Adds to a finished tile what its blocks left out (see above), by the whole
+// workgroup: element (i, this lane's system) of x at x[i * rs]; off(i) is what
+// the stored value lacks to the recurrence's.  From the bottom, sixteen
+// blocks at a time: every wave brings one block's incoming state from memory,
+// wave 0 carries the states of the chain through them,
+//     z_b = (top of block b+1 as stored) + Tb_{b+1} delta_{b+1},
+//     delta_b = P_b z_{b+D} (where it counts),
+// and every wave adds its block's response to delta.
+// Values are read past the caches of the compute unit, in which lines loaded
+// earlier may still stand.  A tile of 128 blocks takes some 70 us; in it, as
+// much again is read and written as there are blocks with something to add.
+template <int K, int NW, typename Off>
+__device__ __forceinline__ void stream_repair(double *x, int64_t rs, bool act, int64_t n, int nblk, int D,
+                                              CSeg seg, CBwd bwd, CTrunc trunc, StreamLds<NW> &sh, int w, int slot, Off off)
+{
+    static_assert(NW >= kStreamMaxDepth + 1, "a.slots hold the last D + 1 states");
+    const int lane = threadIdx.x & 63;
+    double(*zs)[2][64] = sh.z[0], (*dl)[2][64] = sh.z[1], (*ring)[2][64] = sh.a, (*mat)[2][64] = sh.y;
+    // nothing is to be added below the last block that noted something, nor
+    // once past the first of them no block of a chunk has anything
+    const int top = sh.first[slot], low = sh.last[slot] + D;
+    bool any = true;
+    for (int b1 = low < nblk - 2 ? low : nblk - 2; b1 >= 0 && (any || b1 >= top); b1 -= NW) {
+        const int b = b1 - w;
+        __syncthreads();
+        if (b >= 0) {
+            const int64_t r = (int64_t)(b + 1) * K;
+            zs[w][0][lane] = xload(x + r * rs) + off(r);
+            zs[w][1][lane] = r + 1 < n ? xload(x + (r + 1) * rs) + off(r + 1) : 0.0;
+            // Tb_{b+1} and P_b beside it
+            if (lane < 8) mat[w][0][lane] = lane < 4 ? seg[b + 1].tb[lane & 3] : trunc[4 * (int64_t)b + (lane & 3)];
+        }
+        __syncthreads();
+        if (w == 0) {
+            double d0 = 0.0, d1 = 0.0;  // delta of the block below (its own response is in memory across chunks)
+            for (int i = 0; i < NW && b1 - i >= 0; i++) {
+                const int bb = b1 - i;
+                double z0 = zs[i][0][lane], z1 = zs[i][1][lane];
+                const double *M = mat[i][0];
+                link(z0, z1, M[0], M[1], M[2], M[3], d0, d1);
+                z0 = d0;
+                z1 = d1;
+                d0 = d1 = 0.0;
+                if (bb + D <= low && bb + D <= nblk - 2) {
+                    const double e0 = ring[(bb + D) % NW][0][lane], e1 = ring[(bb + D) % NW][1][lane];
+                    const double c0 = fma(M[6], e1, M[4] * e0), c1 = fma(M[7], e1, M[5] * e0);
+                    const bool fine = fmax(fabs(c0), fabs(c1)) <= kRepair * fmax(fabs(z0), fabs(z1)) && c0 == c0 && c1 == c1;
+                    if (act && !fine) {
+                        d0 = c0;
+                        d1 = c1;
+                    }
+                }
+                ring[bb % NW][0][lane] = z0;
+                ring[bb % NW][1][lane] = z1;
+                dl[i][0][lane] = d0;
+                dl[i][1][lane] = d1;
             }
         }
-        store_fence();
+        __syncthreads();
+        any = false;
+        for (int i = 0; i < NW && b1 - i >= 0; i++)
+            any = any || __ballot(!(dl[i][0][lane] == 0.0 && dl[i][1][lane] == 0.0)) != 0;
+        if (b >= 0) {
+            double d1 = dl[w][0][lane], d2 = dl[w][1][lane];
+            const bool add = !(d1 == 0.0 && d2 == 0.0);
+            if (__ballot(add) != 0) {
+                for (int64_t r = (int64_t)(b + 1) * K - 16; r >= (int64_t)b * K; r -= 16) {
+                    double o[16];
+                    repair_rows(x, rs, r, [&](int k, const double *p) { o[k] = xload(p); });
+#pragma unroll
+                    for (int k = 15; k >= 0; k--) {
+                        const double d = fma(-bwd[r + k].gm, d1, -bwd[r + k].dl * d2);
+                        d2 = d1;
+                        d1 = d;
+                        o[k] += d;
+                    }
+                    repair_rows(x, rs, r, [&](int k, double *p) {
+                        if (add) xstore(p, o[k]);
+                    });
+                }
+            }
+        }
+        store_fence();  // in memory before the next chunk's states are read
     }
+    __syncthreads();
 }
 
 }  // namespace st

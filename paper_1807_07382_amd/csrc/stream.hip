@@ -27,10 +27,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
     stream_init(sh);
     const Tiles mine = my_tiles(ntiles);
     int t = mine.t0, b = w, par = 0;
+    unsigned int turn = 0;
     auto skip = [&]() {  // block index into tile and block
         while (b >= nblk) {
             b -= nblk;
             t += mine.step;
+            turn++;
         }
     };
     skip();
@@ -39,22 +41,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
         const int64_t r0 = (int64_t)b * K;
         const int L = (int)(n - r0 < K ? n - r0 : K);
         double v[K];
-        Rec<K> rc = load_rec<K>(fwd, bwd, r0);
+        Rec<K> rc;
+        load_forward<K>(rc, fwd, r0);
+        load_backward<K>(rc, bwd, r0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_sched_barrier(0);  // the records first: the first sweep needs them with its first row
         // idle lanes repeat the tile's first column
         load_block<K, NT, TI>(v, F + (int64_t)t * tsf + r0 * ldf, act ? lane : 0, ldf, L);
-        stream_phases<K, NW>(v, rc, (CSeg)seg, (CTrunc)trunc, b, nblk, D, q, w, par, sh, err);
+        stream_phases<K, NW, true, Plain>(v, rc, bwd, (CSeg)seg, (CTrunc)trunc, b, nblk, D, q, w, par, turn, sh, err, Plain());
         if (act) store_block<K, NT>(v, X + (int64_t)t * tsx + r0 * ldx, lane, ldx, L);
         b += NW;
         skip();
     }
     store_fence();  // every wave's x is in memory before the repair reads it
     __syncthreads();
-    if (sh.repair)
-        for (t = mine.t0 + w * mine.step; t < mine.end; t += NW * mine.step) {
+    turn = 0;
+    for (t = mine.t0; t < mine.end; t += mine.step, turn++)
+        if (sh.last[turn % 32] >= 0) {
             const bool act = lane < cw && (int64_t)t * cw + lane < batch;
-            stream_repair<K>(X + (int64_t)t * tsx + (act ? lane : 0), ldx, act, n, nblk, D, (CBwd)bwd, (CTrunc)trunc);
+            stream_repair<K, NW>(X + (int64_t)t * tsx + (act ? lane : 0), ldx, act, n, nblk, D, (CSeg)seg, (CBwd)bwd,
+                                 (CTrunc)trunc, sh, w, turn % 32, [](int64_t) { return 0.0; });
         }
 }
 
@@ -130,8 +136,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
         load_block<K, NT, TI>(v, F + (int64_t)t * cw + r0 * ldf, lo, ldf, L);
         stream_residual<K>(v, x, h, diag, n, r0, L);
         __builtin_amdgcn_sched_barrier(0);
-        Rec<K> rc = load_rec<K>(fwd, bwd, r0);
-        stream_phases<K, NW, false>(v, rc, (CSeg)seg, nullptr, b, nblk, D, q, w, 0, sh, err);
+        Rec<K> rc;
+        load_forward<K>(rc, fwd, r0);
+        load_backward<K>(rc, bwd, r0);
+        stream_phases<K, NW, false, Plain>(v, rc, bwd, (CSeg)seg, nullptr, b, nblk, D, q, w, 0, 0, sh, err, Plain());
 #pragma unroll
         for (int k = 0; k < K; k++) v[k] = x[k] + v[k];
         if (act) store_block<K, NT>(v, xt + r0 * ldx, lane, ldx, L);

@@ -171,3 +171,109 @@ def test_stream_corrections(torch, n, m, pad, sigma, f32, steps):
     c = probes(m, 64)
     ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(B[:, c].double().cpu().numpy()))
     assert np.max(colerr(X[:, c].cpu().numpy(), ref)) <= d4_tol(sigma)
+
+
+def cyc_lu(n, sigma):
+    """Sparse LU of the periodic I + sigma*D4 (scipy, with pivoting)."""
+    import scipy.sparse as sp
+    import scipy.sparse.linalg as sl
+    rows = np.arange(n)
+    A = sp.lil_matrix((n, n))
+    for o, v in ((-2, sigma), (-1, -4 * sigma), (0, 1 + 6 * sigma), (1, -4 * sigma), (2, sigma)):
+        for r in rows:
+            A[r, (r + o) % n] += v
+    return sl.splu(A.tocsc()), A.tocsr()
+
+
+# n: E rows on and off block edges, with one to 32 rows in the last block;
+# sigma: few and many end blocks (and, at 1e4, the look-back form)
+@pytest.mark.parametrize("n,m,pad,sigma", [(514, 8192, 0, 0.1), (515, 8200, 3, 1.0), (1026, 8192, 16, 50.0),
+                                           (1057, 9001, 0, 50.0), (2047, 8192, 0, 300.0), (1537, 8192, 0, 1e4)])
+def test_stream_periodic(torch, n, m, pad, sigma):
+    """Periodic solves and Crank-Nicolson steps of large batches against an
+    independent sparse LU (kappa_2 <= 1 + 16 sigma, as for d4_tol; the step's
+    right-hand side adds at most (2 + 16 sigma) of max|C|, see the stencil's
+    bound in the periodic tests)."""
+    print_case(test="stream_cyc", n=n, m=m, pad=pad, sigma=sigma)
+    B = rand(torch, (n, m + pad), n + 1)
+    X = torch.full((n, m + pad), 7.0, dtype=torch.float64, device="cuda")
+    F = B.clone()
+    c = probes(m, 48)
+    Bc = B[:, c].cpu().numpy()
+    lu, A = cyc_lu(n, sigma)
+    with pb.Cyclic.factor_d4(n, sigma) as cy:
+        cy.solve_(F[:, :m])
+        cy.cn_step(B[:, :m], X[:, :m])
+        cy.check()
+    assert torch.equal(F[:, m:], B[:, m:]) and bool((X[:, m:] == 7.0).all())
+    assert np.max(colerr(F[:, c].cpu().numpy(), lu.solve(Bc))) <= d4_tol(sigma)
+    ref = lu.solve(2 * Bc - A @ Bc)
+    err = np.max(np.abs(X[:, c].cpu().numpy() - ref), axis=0)
+    assert np.all(err <= d4_tol(sigma) * (np.max(np.abs(ref), axis=0) + (2 + 16 * sigma) * np.max(np.abs(Bc), axis=0)))
+
+
+def test_stream_periodic_varying_rows(torch):
+    """Diagonals that differ from row to row (the step reads them per row)."""
+    n, m = 700, 8192
+    print_case(test="stream_cyc_rows", n=n, m=m)
+    g = np.random.Generator(np.random.PCG64(2))
+    dg = [g.uniform(-1, 1, n) for _ in range(5)]
+    dg[2] = 5.0 + g.uniform(0, 1, n)
+    A = np.zeros((n, n))
+    for o in range(-2, 3):
+        for r in range(n):
+            A[r, (r + o) % n] += dg[o + 2][r]
+    C = rand(torch, (n, m), 6)
+    X = torch.empty_like(C)
+    c = probes(m, 64)
+    Cc = C[:, c].cpu().numpy()
+    with pb.Cyclic.factor(*dg) as cy:
+        cy.cn_step(C, X)
+        F = cy.solve_(C.clone())
+        cy.check()
+    kappa = np.linalg.cond(A, np.inf)
+    assert np.max(colerr(F[:, c].cpu().numpy(), np.linalg.solve(A, Cc))) <= 64 * U * kappa
+    ref = np.linalg.solve(A, 2 * Cc - A @ Cc)
+    assert np.max(np.abs(X[:, c].cpu().numpy() - ref)) <= 64 * U * kappa * 12 * np.max(np.abs(Cc))
+
+
+@pytest.mark.parametrize("row", [0, 600, 1199])
+def test_stream_periodic_far_tails_and_non_finite(torch, row):
+    """A right-hand side that is zero but for one row, far tails in each
+    stretch of rows (the tail unknowns are formed from the ends of the rows
+    only); a system with a NaN has no finite value and spoils no other."""
+    n, m, sigma = 1200, 8192, 20.0
+    print_case(test="stream_cyc_tail", row=row)
+    F = rand(torch, (n, m), 9)
+    c = np.array([0, 17, 63, 64, m - 1])
+    F[:, c] = 0.0
+    F[row, c] = 1.0
+    lu, A = cyc_lu(n, sigma)
+    # the exact tail decays both ways round: its values by the real-space
+    # Green's function of the infinite row, wrapped (the LU's own tails are
+    # only normwise accurate)
+    z = np.roots([sigma, -4 * sigma, 1 + 6 * sigma, -4 * sigma, sigma])
+    z = z[np.abs(z) < 1]
+    d = np.arange(n + 1)
+    G = np.zeros(n + 1, dtype=complex)
+    for r in z:  # residues of z^{d+1} / (sigma (z - r1)(z - r2)(z - 1/r1)(z - 1/r2)) inside the circle
+        others = [q for q in list(z) + [1 / q for q in z] if q is not r and abs(q - r) > 1e-12]
+        G += r ** (d + 1) / (sigma * np.prod([r - q for q in others]))
+    G = G.real
+    k = (np.arange(n) - row) % n
+    ref = G[k] + G[n - k]
+    assert np.max(np.abs(ref - lu.solve(F[:, :1].cpu().numpy())[:, 0])) <= 1e-12
+    keep = F[:, 1].clone()
+    with pb.Cyclic.factor_d4(n, sigma) as cy:
+        X = cy.solve_(F.clone())
+        F[n // 2, 70] = float("nan")
+        Y = cy.solve_(F)
+        cy.check()
+    X = X[:, c].cpu().numpy()
+    for r in range(0, n, 100):
+        big = np.max(np.abs(ref[r:r + 100]))
+        err = np.max(np.abs(X[r:r + 100] - ref[r:r + 100, None]))
+        assert err <= n * d4_tol(sigma) * big
+    assert not bool(torch.isfinite(Y[:, 70]).any())
+    assert bool(torch.isfinite(Y[:, [69, 71]]).all())
+    assert np.max(np.abs(A @ Y[:, 1].cpu().numpy() - keep.cpu().numpy())) <= 1e-11
