@@ -444,6 +444,21 @@ bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, Str
     return stream_plan(h, 32, p) || stream_plan(h, 64, p);
 }
 
+// Whether a system-major solve of `batch` systems runs as streaming sweeps
+// (us, streaming / before: n = 64 x 500 8 / 25; n = 1024 x 2048 24 / 32, x
+// 32768 117 / 130; n = 2000 x 5200 62 / 54, x 10000 76 / 94; n = 4096 x 9000
+// 161 / 152, x 16384 230 / 261).  The x sweeps of a 2-D step go by the same
+// rule, so that they give the bits of the separate passes; theirs is the
+// exception for large grids and deep chains (the explicit term is formed in
+// the waves that are not waiting for the chain, 7 of 16 at sigma = 200: the
+// step on 1024 x 1024 x 32 280 us streaming, 257 by look-back in x; 512 x 512 x
+// 32 64 / 72; 1000 x 1000 x 8 95 / 92).
+bool t_stream_route(const pent_plan *h, int64_t batch, StreamPlan *p)
+{
+    if (!((h->n <= 1024 || batch >= 10000) && (batch + 31) / 32 <= INT32_MAX && stream_plan(h, 32, p))) return false;
+    return p->depth <= 6 || h->n * batch < (int64_t)8 << 20;
+}
+
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
 // summ_bytes() for the chosen schedule.
 int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int64_t ldx,
@@ -1663,8 +1678,11 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
     // x sweeps, system (y, k) being nx contiguous values: the single pass
     // forms the explicit right-hand side from C itself where a tile of it
     // fits on the device; else the stencil pass writes it to R first
+    StreamPlan xsp;
     if (hx->tst_cap == 0) hx->tst_cap = onepass_t_capacity(true);
-    if (hx->tst_cap > 0 && onepass_t_groups(nx) <= hx->tst_cap / 4 &&
+    if (t_stream_route(hx, batch, &xsp)) {
+        st = hip_status(launch_stream_ch2d(xsp, nx, C, R, ny, ninst, dt, h, hx->d_err, s));
+    } else if (hx->tst_cap > 0 && onepass_t_groups(nx) <= hx->tst_cap / 4 &&
         (batch + 63) / 64 * onepass_t_groups(nx) <= (int64_t)UINT32_MAX / 2) {
         const SegRec *seg64 = seg_cache(hx, 64, &st);
         if (seg64) {
@@ -1868,6 +1886,8 @@ int pent_solve_strided(pent_handle h, double *F, int64_t batch, int64_t ld, void
     if (batch == 0) return ret(PENT_OK);
     if (!F) return ret(PENT_INVALID_VALUE);
     hipStream_t s = (hipStream_t)stream;
+    StreamPlan sp;
+    if (t_stream_route(h, batch, &sp)) return ret(hip_status(launch_stream_t(sp, h->n, F, ld, batch, h->d_err, s)));
     // the single pass (blocks transposed through LDS) where a tile of it
     // fits on the device; else one lane per system
     if (h->t_cap == 0) h->t_cap = onepass_t_capacity();

@@ -726,8 +726,8 @@ __global__ __launch_bounds__(64 * kCsNW) __attribute__((amdgpu_waves_per_eu(kCsE
                 const double n1 = k + 1 < K ? v[k + 1 < K ? k + 1 : 0] : h[2];
                 const double n2 = k + 2 < K ? v[k + 2 < K ? k + 2 : 0] : (k + 2 == K ? h[2] : h[3]);
                 CycUni u = uc;
-                if constexpr (!UNI) u = CycUni{{lane_get(g[0], k), lane_get(g[1], k), lane_get(g[2], k),
-                                                lane_get(g[3], k), lane_get(g[4], k)}};
+                if constexpr (!UNI) u = CycUni{{lane_double(g[0], k), lane_double(g[1], k), lane_double(g[2], k),
+                                                lane_double(g[3], k), lane_double(g[4], k)}};
                 const double f = cn_row_u(u, c2, c1, ck, n1, n2);
                 v[k] = k < L ? f : 0.0;
                 c2 = c1;

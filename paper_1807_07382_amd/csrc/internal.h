@@ -432,6 +432,13 @@ int stream_tile_width(int64_t batch, int cus);
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
                          int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
 
+// System-major right-hand sides, system s at F + s * ld (p of 32-row
+// segments); and the x sweeps of a 2-D Cahn-Hilliard step from C into R, both
+// [y][k][x], the explicit term formed on the fly.
+hipError_t launch_stream_t(const StreamPlan &p, int64_t n, double *F, int64_t ld, int64_t batch, unsigned int *err,
+                           hipStream_t s);
+hipError_t launch_stream_ch2d(const StreamPlan &p, int64_t n, const double *C, double *R, int64_t ny, int64_t ninst,
+                              const double *dt, double h, unsigned int *err, hipStream_t s);
 // One refinement correction by 32-row blocks (p of 32-row segments).
 hipError_t launch_stream_fix(const StreamPlan &p, int depth, int64_t n, const double *diag, const void *F, bool f32,
                              int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, unsigned int *err, hipStream_t s);

@@ -30,6 +30,28 @@ typedef __attribute__((address_space(4))) const SegRec *CSeg;
 
 constexpr int kSpin = 1 << 20;  // polls per wait before giving up
 
+// The double in lane l (a wave-uniform constant index) of v.
+__device__ __forceinline__ double lane_double(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// The double of lane l - 1 (UP) or l + 1 of the wave, by a DPP wave shift;
+// the lane with no such neighbour (0, resp. 63) gets edge.  Every lane of
+// the wave must be active.
+template <bool UP>
+__device__ __forceinline__ double lane_shift(double x, double edge)
+{
+    constexpr int ctrl = UP ? 0x138 : 0x130;  // wave_shr:1 / wave_shl:1
+    const long long xi = __double_as_longlong(x), ei = __double_as_longlong(edge);
+    const int lo = __builtin_amdgcn_update_dpp((int)ei, (int)xi, ctrl, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(ei >> 32), (int)(xi >> 32), ctrl, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // Units are numbered through kTicketLines counters, one per 128-byte line,
 // counter c serving the blocks with blockIdx % kTicketLines == c: ticket k
 // of counter c is unit k * kTicketLines + c, so the grid (one block per

@@ -35,15 +35,6 @@ constexpr double kNegligible = 0x1p-54;  // a neglected state against the state 
 constexpr double kRepair = 0x1p-53;      // ... and from where the repair adds it: a system that
                                          // passed above is never touched for a neighbour's sake
 
-// The double in lane l (a wave-uniform constant index) of v.
-__device__ __forceinline__ double lane_get(double v, int l)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, l);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 // Lane L of every row of 16 lanes, to the whole row (one 64-bit DPP move).
 template <int L>
 __device__ __forceinline__ double row_get(double v)
@@ -82,7 +73,7 @@ struct Coef {
     __device__ __forceinline__ double get() const
     {
         if constexpr (K == 32) return row_get<k % 16>(c[k / 16]);
-        else return lane_get(c[0], k);
+        else return lane_double(c[0], k);
     }
     __device__ __forceinline__ void hold()
     {
@@ -226,6 +217,10 @@ struct Plain {
         return x;
     }
     __device__ __forceinline__ void hold() {}
+};
+
+struct PlainLate : Plain {
+    static constexpr bool late = true;
 };
 
 // Back substitution over the block from (q1, q2) = (x_{r0+K}, x_{r0+K+1}); on

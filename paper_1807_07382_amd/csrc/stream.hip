@@ -78,8 +78,8 @@ __device__ __forceinline__ void stream_residual(double (&v)[K], const double (&x
     unroll<K>([&](auto kk) {
         constexpr int k = decltype(kk)::value;
         if constexpr (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-        const double cf[5] = {lane_get(cl[0], k), lane_get(cl[1], k), lane_get(cl[2], k), lane_get(cl[3], k),
-                              lane_get(cl[4], k)};
+        const double cf[5] = {lane_double(cl[0], k), lane_double(cl[1], k), lane_double(cl[2], k), lane_double(cl[3], k),
+                              lane_double(cl[4], k)};
         const double xv[5] = {k >= 2 ? x[k >= 2 ? k - 2 : 0] : h[k < 2 ? k : 0],
                               k >= 1 ? x[k >= 1 ? k - 1 : 0] : h[1], x[k],
                               k + 1 < K ? x[k + 1 < K ? k + 1 : 0] : h[2],
@@ -244,19 +244,23 @@ hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, con
     return hipGetLastError();
 }
 
-// Systems per tile: the width with the fewest systems in a compute unit's
-// turns (tiles are dealt whole; the rate of a compute unit, not of the
-// memory, bounds one that has a tile more than the others).  Multiples of 16
-// keep tiles on 128-byte lines of an aligned row.
+// Systems per tile: the width with the least work in a compute unit's turns
+// (tiles are dealt whole; the rate of a compute unit, not of the memory,
+// bounds one that has a tile more than the others).  Narrow tiles use lanes
+// and lines less well, a tenth for every 16 systems given up (n = 4096 x
+// 20000: 266 us at 48, 302 at 64, 316 at 32; x 8192 110 at 32, 133 at 64;
+// system-major 300 x 40000 43 at 64, 50 at 32).  Multiples of 16 keep tiles on
+// 128-byte lines of an aligned row.
 int stream_tile_width(int64_t batch, int cus)
 {
     int best = 64;
     int64_t cost = 0;
     for (int cw = 64; cw >= 32; cw -= 16) {
         const int64_t tiles = (batch + cw - 1) / cw, turns = (tiles + cus - 1) / cus;
-        if (cw == 64 || turns * cw < cost) {
+        const int64_t c = turns * cw * (160 + 64 - cw);
+        if (cw == 64 || c < cost) {
             best = cw;
-            cost = turns * cw;
+            cost = c;
         }
     }
     return best;

@@ -277,3 +277,43 @@ def test_stream_periodic_far_tails_and_non_finite(torch, row):
     assert not bool(torch.isfinite(Y[:, 70]).any())
     assert bool(torch.isfinite(Y[:, [69, 71]]).all())
     assert np.max(np.abs(A @ Y[:, 1].cpu().numpy() - keep.cpu().numpy())) <= 1e-11
+
+
+# n: one block to many, partial last blocks of 1 to 32 rows; ld: runs on lines
+# of their own, at any double, and with a gap; m: partial last tiles and slices
+@pytest.mark.parametrize("n,m,ld,sigma", [(1, 3, 1, 50.0), (2, 70, 2, 0.1), (31, 64, 33, 1.0), (33, 1000, 48, 50.0),
+                                          (64, 513, 64, 0.1), (257, 2100, 257, 300.0), (1021, 20011, 1021, 20.0),
+                                          (1024, 999, 1040, 50.0), (2049, 10007, 2051, 50.0), (500, 333, 500, 1e4)])
+def test_stream_system_major(torch, n, m, ld, sigma):
+    print_case(test="stream_t", n=n, m=m, ld=ld, sigma=sigma)
+    B = rand(torch, (m, ld), n + ld)
+    F = B.clone()
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_strided_(F[:, :n])
+        p.check()
+    assert torch.equal(F[:, n:], B[:, n:])
+    c = probes(m, 48)
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(B[c, :n].T.cpu().numpy()))
+    assert np.max(colerr(F[c, :n].T.cpu().numpy(), ref)) <= d4_tol(sigma)
+
+
+def test_stream_system_major_offset_and_far_tails(torch):
+    """Storage that starts at an odd double; systems that are zero but for
+    their last row keep their tails; one with a NaN spoils no other."""
+    n, m, sigma = 900, 301, 5.0
+    print_case(test="stream_t_tail", n=n, m=m)
+    buf = rand(torch, (m * n + 1,), 3)
+    F = buf[1:].view(m, n)
+    F[::7] = 0.0
+    F[::7, n - 1] = 1.0
+    F[3, n // 2] = float("nan")
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(F[[0, 1, 294, 300]].T.cpu().numpy()))
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_strided_(F)
+        p.check()
+    X = F[[0, 1, 294, 300]].T.cpu().numpy()
+    assert np.max(colerr(X, ref)) <= d4_tol(sigma)
+    for r in range(0, n, 60):
+        big = np.max(np.abs(ref[r:r + 60]), axis=0)
+        assert np.all(np.max(np.abs(X[r:r + 60] - ref[r:r + 60]), axis=0) <= n * d4_tol(sigma) * big + 1e-290)
+    assert not bool(torch.isfinite(F[3]).any()) and bool(torch.isfinite(F[[2, 4]]).all())
