@@ -66,9 +66,10 @@ typedef enum pent_status {
  * Factor A = L R once (Sec. 2.4, factorisation steps; Sec. 2.6 splits the
  * factorisation from the solve so a constant matrix is factored only once).
  * a..e: HOST arrays of n doubles (row-indexed, see above); copied, the caller
- * keeps ownership.  The factorisation runs on the current device and the call
- * blocks until it has finished (one synchronisation, to read the pivot
- * check).  Returns a handle, or NULL with pent_last_status() set to
+ * keeps ownership.  The recurrence, one serial chain, runs on the host (IEEE
+ * double, one operation at a time); the tables of the solves are built on the
+ * current device, and the call blocks until they are there (one
+ * synchronisation).  Returns a handle, or NULL with pent_last_status() set to
  * PENT_INVALID_VALUE, PENT_ZERO_PIVOT (see pent_last_pivot_row()),
  * PENT_OUT_OF_MEMORY or PENT_HIP_ERROR.  Limits: 1 <= n <= 2^31 - 1. */
 pent_handle pent_factor(int64_t n, const double *a, const double *b, const double *c,
@@ -77,7 +78,7 @@ pent_handle pent_factor(int64_t n, const double *a, const double *b, const doubl
 /* Same, for the matrix of the implicit hyperdiffusion step I + sigma*D4
  * (Sec. 2.3, coefficient list a = e = sigma, b = d = -4 sigma,
  * c = 1 + 6 sigma), non-periodic: the row stencil is truncated at both ends.
- * The diagonals are assembled on the device. */
+ * The diagonals are assembled and factored on the device (to the same bits). */
 pent_handle pent_factor_d4(int64_t n, double sigma);
 
 /* Free a handle.  NULL is a no-op.  The caller must have synchronised every

@@ -1,6 +1,7 @@
 // api.hip -- the C ABI of libpentbatch (declared in include/pentbatch.h):
 // argument checks, handle lifetime, schedule choice and kernel launches.
 #include <algorithm>
+#include <cfenv>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -91,24 +92,18 @@ hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s)
 void free_plan(pent_plan *p)
 {
     if (!p) return;
-    if (p->d_diag) (void)hipFree(p->d_diag);
-    if (p->d_fac) (void)hipFree(p->d_fac);
-    if (p->d_anorm) (void)hipFree(p->d_anorm);
-    if (p->d_fwd) (void)hipFree(p->d_fwd);
-    if (p->d_bwd) (void)hipFree(p->d_bwd);
     for (auto &c : p->seg)
-        if (c.d_seg) (void)hipFree(c.d_seg);
+        if (c.d_seg && c.own) (void)hipFree(c.d_seg);
     for (auto &c : p->grp)
         if (c.d_grp) (void)hipFree(c.d_grp);
-    if (p->d_scan) (void)hipFree(p->d_scan);
-    if (p->d_trec) (void)hipFree(p->d_trec);
-    if (p->d_trunc) (void)hipFree(p->d_trunc);
-    if (p->d_err) (void)hipFree(p->d_err);
+    if (p->d_pool) (void)hipFree(p->d_pool);
     p->magic = 0;
     delete p;
 }
 
-// Allocate a plan whose diagonals (5n doubles, device) the caller fills.
+// Allocate a plan whose diagonals (5n doubles, device) the caller fills.  One
+// allocation holds everything the automatic schedules need (an allocation of
+// its own for each of fourteen arrays cost 100 us and more per handle).
 pent_plan *new_plan(int64_t n, int *st)
 {
     pent_plan *p = new (std::nothrow) pent_plan();
@@ -121,39 +116,65 @@ pent_plan *new_plan(int64_t n, int *st)
     // past n, room for one more group of the many-matrix single pass (it
     // reads whole groups of 4 x kGroupSegRows records)
     p->npad = (n + 256 + kRecPad - 1) / kRecPad * kRecPad;
-    p->d_diag = nullptr;
-    p->d_fac = nullptr;
-    p->d_anorm = nullptr;
-    p->d_fwd = nullptr;
-    p->d_bwd = nullptr;
     p->sched_kind = 0;
     p->sched_seg = 0;
     p->refine_tol = 0.0;
     p->d_scan = nullptr;
     p->d_trec = nullptr;
-    p->scan_rows = 0;
     p->d_trunc = nullptr;
     p->strm_depth[0] = p->strm_depth[1] = p->strm_depth[2] = 0;
     p->cus = 0;
-    p->d_err = nullptr;
     p->onepass_cap[0] = p->onepass_cap[1] = 0;
     p->fix_cap = 0;
     p->t_cap = 0;
     p->tst_cap = 0;
+    p->d_pool = nullptr;
+    const int rows = tile_rows_for(n);
+    const int64_t nseg = (n + 31) / 32 + (n + 63) / 64;
+    size_t at = 0;
+    auto room = [&](size_t bytes) {
+        const size_t o = at;
+        at += (bytes + 255) / 256 * 256;
+        return o;
+    };
+    const size_t o_diag = room(sizeof(double) * 9 * n), o_anorm = room(sizeof(double)), o_err = room(sizeof(unsigned int)),
+                 o_bad = room(4 * sizeof(int64_t)),
+                 o_fwd = room(sizeof(FwdRec) * p->npad), o_bwd = room(sizeof(BwdRec) * p->npad),
+                 o_s64 = room(sizeof(SegRec) * seg_padded(n, 64)), o_s32 = room(sizeof(SegRec) * seg_padded(n, 32)),
+                 o_s16 = room(rows == 16 ? sizeof(SegRec) * seg_padded(n, 16) : 0),
+                 o_trunc = room(n <= kStreamMaxRows ? sizeof(double) * 4 * nseg : 0),
+                 o_scan = room(rows ? sizeof(ScanRec) * 64 : 0),
+                 o_trec = room(rows ? sizeof(double) * tile_recs_doubles(rows) : 0);
     hipError_t e = hipGetDevice(&p->device);
     if (e == hipSuccess)
         e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
-    if (e == hipSuccess) e = hipMalloc(&p->d_diag, sizeof(double) * 5 * n);
-    if (e == hipSuccess) e = hipMalloc(&p->d_fac, sizeof(double) * 4 * n);
-    if (e == hipSuccess) e = hipMalloc(&p->d_anorm, sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&p->d_fwd, sizeof(FwdRec) * p->npad);
-    if (e == hipSuccess) e = hipMalloc(&p->d_bwd, sizeof(BwdRec) * p->npad);
-    if (e == hipSuccess) e = hipMalloc(&p->d_err, sizeof(unsigned int));
-    if (e == hipSuccess) e = hipMemset(p->d_err, 0, sizeof(unsigned int));
+    if (e == hipSuccess) e = hipMalloc(&p->d_pool, at);
     if (e != hipSuccess) {
         free_plan(p);
         *st = hip_status(e);
         return nullptr;
+    }
+    char *d = p->d_pool;
+    p->d_diag = (double *)(d + o_diag);
+    p->d_fac = p->d_diag + 5 * n;
+    p->d_anorm = (double *)(d + o_anorm);
+    p->d_err = (unsigned int *)(d + o_err);
+    p->d_bad = (int64_t *)(d + o_bad);
+    p->d_fwd = (FwdRec *)(d + o_fwd);
+    p->d_bwd = (BwdRec *)(d + o_bwd);
+    auto table = [&](int seg_rows, size_t o) {
+        SegCache &c = p->seg[seg_slot(seg_rows)];
+        c.seg_rows = seg_rows;
+        c.nseg = (n + seg_rows - 1) / seg_rows;
+        c.d_seg = (SegRec *)(d + o);
+    };
+    table(64, o_s64);
+    table(32, o_s32);
+    if (rows == 16) table(16, o_s16);
+    if (n <= kStreamMaxRows) p->d_trunc = (double *)(d + o_trunc);
+    if (rows) {
+        p->d_scan = (ScanRec *)(d + o_scan);
+        p->d_trec = (double *)(d + o_trec);
     }
     *st = PENT_OK;
     return p;
@@ -166,48 +187,86 @@ void query_onepass_cap(pent_plan *p, int seg_rows)
     if (cap == 0) cap = onepass_capacity(seg_rows);
 }
 
-const SegRec *seg_cache_locked(pent_plan *p, int seg_rows, int *st, bool sync);
-const GrpRec *grp_cache_locked(pent_plan *p, int seg_rows, int waves, int *st, bool sync);
-bool tile_cache(pent_plan *p, int rows, const ScanRec **scan, const double **trec, int *st,
-                bool sync);
-
-// Factor the diagonals already in p->d_diag and build the per-schedule
-// tables of the automatic schedule (segment constants for 64- and 32-row
-// segments, and the resident tile's tables where n allows it), all on the
-// null stream, then synchronise once to read the pivot check.  Later solves
-// with the automatic schedule then allocate nothing for these tables.
-// Consumes p on error.
-pent_handle finish_factor(pent_plan *p)
+// A = L R (Sec. 2.4) of diagonals in host memory: dg holds the 5n zero-padded
+// diagonals, fac receives alpha, beta, gamma, delta.  Returns the first row
+// with a zero or non-finite pivot, or -1.  The recurrence is one serial chain
+// (a product, two differences and a division per row) whose latency is all it
+// costs: about 9 ns a row here, 145 ns on one lane of the device (n = 4096:
+// about 40 us against 610), so diagonals that arrive in host memory are factored
+// on their way.  The operations are those of the device kernel
+// (k_factor_serial), rounded one by one in the same order, so the factors are
+// the same bits.
+__attribute__((noinline)) int64_t factor_host(int64_t n, const double *dg, double *fac)
 {
-    int64_t *d_bad = nullptr;
+    const double *a = dg, *b = dg + n, *c = dg + 2 * n, *d = dg + 3 * n, *e = dg + 4 * n;
+    double *alpha = fac, *beta = fac + n, *gamma = fac + 2 * n, *delta = fac + 3 * n;
+    double gam2 = 0.0, del2 = 0.0, gam1 = 0.0, del1 = 0.0;
+    for (int64_t i = 0; i < n; i++) {
+        const double be = b[i] - a[i] * gam2;
+        const double al = c[i] - a[i] * del2 - be * gam1;
+        if (!(al != 0.0) || !std::isfinite(al)) return i;
+        const double ga = (d[i] - be * del1) / al;
+        const double de = e[i] / al;
+        alpha[i] = al;
+        beta[i] = be;
+        gamma[i] = ga;
+        delta[i] = de;
+        gam2 = gam1;
+        del2 = del1;
+        gam1 = ga;
+        del1 = de;
+    }
+    return -1;
+}
+
+// factor_host in the default floating-point environment (round to nearest,
+// subnormal numbers kept), whatever the caller has set for its thread.
+int64_t factor_host_ieee(int64_t n, const double *dg, double *fac)
+{
+    fenv_t env;
+    (void)fegetenv(&env);
+    (void)fesetenv(FE_DFL_ENV);
+    const int64_t bad = factor_host(n, dg, fac);
+    (void)fesetenv(&env);
+    return bad;
+}
+
+// Factor the diagonals already in p->d_diag (factored: the factors are there
+// too) and build the tables of the automatic schedules: segment constants for
+// 64- and 32-row segments, the truncation of the streaming sweeps, and the
+// resident tile's tables where n allows it, all on the null stream, then
+// synchronise once to read the pivot check.  Later solves with the automatic
+// schedule then allocate nothing for these tables.  Consumes p on error.
+pent_handle finish_factor(pent_plan *p, bool factored = false)
+{
+    int64_t *const d_bad = p->d_bad;
     int64_t bad[4] = {-1, 0, 0, 0};  // the pivot check, then the streaming sweeps' depths
-    int st = PENT_OK;
-    hipError_t e = hipMalloc(&d_bad, sizeof(bad));
-    if (e == hipSuccess) e = launch_factor(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, d_bad, 0);
-    if (e == hipSuccess) e = launch_anorm(p->d_diag, p->n, p->d_anorm, 0);
+    const int rows = tile_rows_for(p->n);
+    SegRec *s64 = p->seg[seg_slot(64)].d_seg, *s32 = p->seg[seg_slot(32)].d_seg,
+           *s16 = rows == 16 ? p->seg[seg_slot(16)].d_seg : nullptr;
+    const int64_t n32 = (p->n + 31) / 32, n64 = (p->n + 63) / 64;
+    const bool strm = p->d_trunc != nullptr;
+    hipError_t e = hipSuccess;
+    if (!factored) e = launch_factor(p->d_diag, p->n, p->d_fac, d_bad, 0);
+    if (e == hipSuccess) e = launch_records(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, 0);
+    if (e == hipSuccess) e = launch_anorm(p->d_diag, p->n, p->d_anorm, p->d_err, 0);
+    if (e == hipSuccess) e = launch_seg_prep_all(p->d_fwd, p->d_bwd, p->n, s64, s32, s16, 0);
+    if (e == hipSuccess && strm)
+        e = launch_stream_prep(s32, n32, p->d_trunc, s64, n64, p->d_trunc + 4 * n32, d_bad + 1, 0);
+    if (e == hipSuccess && rows > 0) {
+        const SegRec *seg = p->seg[seg_slot(rows)].d_seg;
+        e = launch_scan_prep(seg, (p->n + rows - 1) / rows, p->d_scan, 0);
+        if (e == hipSuccess) e = launch_tile_recs(p->d_fwd, p->d_bwd, rows, p->d_trec, 0);
+    }
     if (e == hipSuccess) {
-        std::lock_guard<std::mutex> lk(p->mu);
-        if (!seg_cache_locked(p, 64, &st, false) || !seg_cache_locked(p, 32, &st, false))
-            e = hipErrorUnknown;
+        // (a copy waits for the null stream's work; without one, wait for it)
+        const size_t first = factored ? 1 : 0, count = strm ? 4 : 1;
+        e = first < count ? hipMemcpy(bad + first, d_bad + first, sizeof(int64_t) * (count - first), hipMemcpyDeviceToHost)
+                          : hipStreamSynchronize(0);
     }
-    const bool strm = p->n <= kStreamMaxRows;
-    if (e == hipSuccess && strm) {
-        const SegCache &s32 = p->seg[seg_slot(32)], &s64 = p->seg[seg_slot(64)];
-        e = hipMalloc(&p->d_trunc, sizeof(double) * 4 * (s32.nseg + s64.nseg));
-        if (e == hipSuccess)
-            e = launch_stream_prep(s32.d_seg, s32.nseg, p->d_trunc, s64.d_seg, s64.nseg, p->d_trunc + 4 * s32.nseg,
-                                   d_bad + 1, 0);
-    }
-    if (e == hipSuccess && tile_rows_for(p->n) > 0) {
-        const ScanRec *sc;
-        const double *tr;
-        if (!tile_cache(p, tile_rows_for(p->n), &sc, &tr, &st, false)) e = hipErrorUnknown;
-    }
-    if (e == hipSuccess) e = hipMemcpy(bad, d_bad, strm ? sizeof(bad) : sizeof(bad[0]), hipMemcpyDeviceToHost);
-    if (d_bad) (void)hipFree(d_bad);
     if (e != hipSuccess) {
         free_plan(p);
-        ret(st != PENT_OK ? st : hip_status(e));
+        ret(hip_status(e));
         return nullptr;
     }
     if (bad[0] >= 0) {
@@ -239,10 +298,8 @@ const SegRec *seg_cache_locked(pent_plan *p, int seg_rows, int *st, bool sync = 
     const int64_t nseg = (p->n + seg_rows - 1) / seg_rows;
     // padded with all-zero records to a multiple of kSegPad segments, so
     // kernels that take segments in groups read no past-the-end record
-    const int64_t nalloc = (nseg + kSegPad - 1) / kSegPad * kSegPad;
     SegRec *d = nullptr;
-    hipError_t e = hipMalloc(&d, sizeof(SegRec) * nalloc);
-    if (e == hipSuccess) e = hipMemset(d, 0, sizeof(SegRec) * nalloc);
+    hipError_t e = hipMalloc(&d, sizeof(SegRec) * seg_padded(p->n, seg_rows));
     if (e == hipSuccess) e = launch_seg_prep(p->d_fwd, p->d_bwd, p->n, seg_rows, d, 0);
     if (e == hipSuccess && sync) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
@@ -253,6 +310,7 @@ const SegRec *seg_cache_locked(pent_plan *p, int seg_rows, int *st, bool sync = 
     c.seg_rows = seg_rows;
     c.nseg = nseg;
     c.d_seg = d;
+    c.own = true;
     *st = PENT_OK;
     return d;
 }
@@ -304,40 +362,6 @@ const GrpRec *grp_cache(pent_plan *p, int seg_rows, int waves, int *st)
 {
     std::lock_guard<std::mutex> lk(p->mu);
     return grp_cache_locked(p, seg_rows, waves, st);
-}
-
-// Interface-scan constants and record image of the resident-tile schedule
-// (built once per handle).
-bool tile_cache(pent_plan *p, int rows, const ScanRec **scan, const double **trec, int *st,
-                bool sync = true)
-{
-    std::lock_guard<std::mutex> lk(p->mu);
-    if (!(p->d_scan && p->scan_rows == rows)) {
-        const SegRec *seg = seg_cache_locked(p, rows, st, sync);
-        if (!seg) return false;
-        ScanRec *d = nullptr;
-        double *t = nullptr;
-        hipError_t e = hipMalloc(&d, sizeof(ScanRec) * 64);
-        if (e == hipSuccess) e = hipMalloc(&t, sizeof(double) * tile_recs_doubles(rows));
-        if (e == hipSuccess) e = launch_scan_prep(seg, (p->n + rows - 1) / rows, d, 0);
-        if (e == hipSuccess) e = launch_tile_recs(p->d_fwd, p->d_bwd, rows, t, 0);
-        if (e == hipSuccess && sync) e = hipDeviceSynchronize();
-        if (e != hipSuccess) {
-            if (d) (void)hipFree(d);
-            if (t) (void)hipFree(t);
-            *st = hip_status(e);
-            return false;
-        }
-        if (p->d_scan) (void)hipFree(p->d_scan);
-        if (p->d_trec) (void)hipFree(p->d_trec);
-        p->d_scan = d;
-        p->d_trec = t;
-        p->scan_rows = rows;
-    }
-    *scan = p->d_scan;
-    *trec = p->d_trec;
-    *st = PENT_OK;
-    return true;
 }
 
 // Automatic schedule (chosen from measured sweeps over sizes on MI355X): the
@@ -475,11 +499,7 @@ int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int6
     if (kind == 1)
         return hip_status(launch_lane_sweep(h->d_fwd, h->d_bwd, h->n, x, batch, ldx, seg_rows, s));
     if (kind == 3) {
-        const int rows = tile_rows_for(h->n);
-        const ScanRec *scan;
-        const double *trec;
-        if (!tile_cache(h, rows, &scan, &trec, &st)) return st;
-        return hip_status(launch_tile_sweep_io(trec, scan, h->n, rows, f, f32, ldf, x, ldx, batch, s));
+        return hip_status(launch_tile_sweep_io(h->d_trec, h->d_scan, h->n, tile_rows_for(h->n), f, f32, ldf, x, ldx, batch, s));
     }
     const SegRec *seg = seg_cache(h, seg_rows, &st);
     if (!seg) return st;
@@ -882,11 +902,6 @@ int group_bind(pent_group g, double *const *F, const int64_t *batch, const int64
         int kind, seg_rows;
         io_schedule(p, batch[k], true, &kind, &seg_rows);
         if ((kind == 2 || kind == 4) && !seg_cache(p, seg_rows, &st)) return st;
-        if (kind == 3) {
-            const ScanRec *sc;
-            const double *tr;
-            if (!tile_cache(p, tile_rows_for(p->n), &sc, &tr, &st)) return st;
-        }
         mats[k] = GroupMat{p->d_fwd, p->d_bwd, seg64, F[k], p->n, p->npad, ld[k], batch[k],
                            segp, grpp};
     }
@@ -1113,7 +1128,7 @@ bool tables_ready(pent_plan *p, int kind, int seg_rows)
     if (kind == 1) return true;
     if (kind == 3) {
         const int rows = tile_rows_for(p->n);
-        return p->d_scan != nullptr && p->scan_rows == rows;
+        return p->d_scan != nullptr && rows > 0;
     }
     return p->seg[seg_slot(seg_rows)].d_seg != nullptr;
 }
@@ -1136,8 +1151,8 @@ pent_handle pent_factor(int64_t n, const double *a, const double *b, const doubl
         ret(st);
         return nullptr;
     }
-    // zero-pad the entries that fall outside the matrix, then copy
-    double *h = new (std::nothrow) double[5 * n];
+    // zero-pad the entries that fall outside the matrix, factor, then copy
+    double *h = new (std::nothrow) double[9 * n];
     if (!h) {
         free_plan(p);
         ret(PENT_OUT_OF_MEMORY);
@@ -1150,14 +1165,17 @@ pent_handle pent_factor(int64_t n, const double *a, const double *b, const doubl
         h[3 * n + i] = (i + 1 < n) ? d[i] : 0.0;
         h[4 * n + i] = (i + 2 < n) ? e[i] : 0.0;
     }
-    hipError_t err = hipMemcpy(p->d_diag, h, sizeof(double) * 5 * n, hipMemcpyHostToDevice);
+    const int64_t bad = factor_host_ieee(n, h, h + 5 * n);
+    hipError_t err = hipSuccess;
+    if (bad < 0) err = hipMemcpy(p->d_diag, h, sizeof(double) * 9 * n, hipMemcpyHostToDevice);
     delete[] h;
-    if (err != hipSuccess) {
+    if (bad >= 0 || err != hipSuccess) {
         free_plan(p);
-        ret(hip_status(err));
+        if (bad >= 0) g_pivot_row = bad;
+        ret(bad >= 0 ? PENT_ZERO_PIVOT : hip_status(err));
         return nullptr;
     }
-    return finish_factor(p);
+    return finish_factor(p, true);
 }
 
 pent_handle pent_factor_d4(int64_t n, double sigma)

@@ -254,67 +254,77 @@ __global__ void k_records(const double *__restrict__ diag, const double *__restr
 //   cg    = outgoing backward state of the zero-incoming back substitution of u, v;
 //   tb    = outgoing backward state of the back substitution of g = 0 from the
 //           incoming states (1,0) and (0,1).
-// The recurrences are the same prescaled ones the sweeps use.
+// The recurrences are the same prescaled ones the sweeps use.  Four lanes per
+// segment, one per unit state: lanes 0 and 1 sweep u and v forward and then
+// back from zero, lanes 2 and 3 (whose forward values are zero) back from the
+// unit states.  Every record of the segment is loaded (the table is padded)
+// and only used where its row exists: latency-bound, a load under a condition
+// would be waited for row by row.  N = 4096, 64- and 32-row tables: 7.6 us (one
+// lane per segment and a launch each 42).  Segments nseg .. nalloc - 1 are zero.
 template <int K>
-__global__ __launch_bounds__(64) void k_seg_prep(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd,
-                           int64_t n, int64_t nseg, SegRec *__restrict__ seg)
+__device__ __forceinline__ void seg_tables(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd, int64_t n,
+                                           int64_t nseg, int64_t nalloc, SegRec *__restrict__ seg, int64_t block)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nseg) return;
+    const int64_t s = block * 16 + threadIdx.x / 4;
+    const int role = threadIdx.x & 3;
+    if (s >= nalloc) return;
+    double *out = (double *)(seg + s);
+    if (s >= nseg) {
+        for (int k = 0; k < 4; k++) out[4 * role + k] = 0.0;
+        return;
+    }
     const int64_t r0 = s * K;
     const int L = (int)((n - r0) < K ? (n - r0) : K);
-    double u[K], v[K];
-    SegRec out;
-    // Every record of the segment is loaded (the table is padded), and only
-    // used where its row exists: latency-bound, one load a row under a
-    // condition was waited for row by row (30 us for 64 rows at N = 4096, now 21).
-    // forward responses
-    {
-        double up2 = 1.0, up1 = 0.0, vp2 = 0.0, vp1 = 1.0;
+    double u[K];
+    double p2 = role == 0 ? 1.0 : 0.0, p1 = role == 1 ? 1.0 : 0.0;
 #pragma unroll
-        for (int k = 0; k < K; k++) {
-            const FwdRec r = fwd[r0 + k];
-            if (k < L) {
-                const double gu = fma(-r.bp, up1, -r.ap * up2);
-                const double gv = fma(-r.bp, vp1, -r.ap * vp2);
-                u[k] = gu; v[k] = gv;
-                up2 = up1; up1 = gu;
-                vp2 = vp1; vp1 = gv;
-            } else {
-                u[k] = 0.0; v[k] = 0.0;
-            }
-        }
-        out.tf[0] = up2; out.tf[1] = up1;
-        out.tf[2] = vp2; out.tf[3] = vp1;
+    for (int k = 0; k < K; k++) {
+        const FwdRec r = fwd[r0 + k];
+        const double g = fma(-r.bp, p1, -r.ap * p2);
+        u[k] = k < L ? g : 0.0;
+        p2 = k < L ? p1 : p2;
+        p1 = k < L ? g : p1;
     }
-    // backward: zero-incoming over u, v; and g = 0 from unit incoming states
-    {
-        double uq1 = 0.0, uq2 = 0.0, vq1 = 0.0, vq2 = 0.0;
-        double aq1 = 1.0, aq2 = 0.0, bq1 = 0.0, bq2 = 1.0;
+    double q1 = role == 2 ? 1.0 : 0.0, q2 = role == 3 ? 1.0 : 0.0;
 #pragma unroll
-        for (int k = K - 1; k >= 0; k--) {
-            const BwdRec q = bwd[r0 + k];
-            if (k < L) {
-                const double xu = fma(-q.gm, uq1, fma(-q.dl, uq2, u[k]));
-                const double xv = fma(-q.gm, vq1, fma(-q.dl, vq2, v[k]));
-                const double xa = fma(-q.gm, aq1, -q.dl * aq2);
-                const double xb = fma(-q.gm, bq1, -q.dl * bq2);
-                uq2 = uq1; uq1 = xu;
-                vq2 = vq1; vq1 = xv;
-                aq2 = aq1; aq1 = xa;
-                bq2 = bq1; bq1 = xb;
-            }
-        }
-        out.cg[0] = uq1; out.cg[1] = uq2;
-        out.cg[2] = vq1; out.cg[3] = vq2;
-        out.tb[0] = aq1; out.tb[1] = aq2;
-        out.tb[2] = bq1; out.tb[3] = bq2;
+    for (int k = K - 1; k >= 0; k--) {
+        const BwdRec q = bwd[r0 + k];
+        const double x = fma(-q.gm, q1, fma(-q.dl, q2, u[k]));
+        q2 = k < L ? q1 : q2;
+        q1 = k < L ? x : q1;
     }
-    out.pad[0] = out.pad[1] = out.pad[2] = out.pad[3] = 0.0;
-    seg[s] = out;
+    if (role < 2) {
+        out[2 * role] = p2;
+        out[2 * role + 1] = p1;
+        out[4 + 2 * role] = q1;
+        out[4 + 2 * role + 1] = q2;
+        out[12 + 2 * role] = 0.0;
+        out[12 + 2 * role + 1] = 0.0;
+    } else {
+        out[8 + 2 * (role - 2)] = q1;
+        out[8 + 2 * (role - 2) + 1] = q2;
+    }
 }
 
-// C = A B for column-major 2x2 matrices, explicit fused multiply-adds.
+template <int K>
+__global__ __launch_bounds__(64) void k_seg_prep(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd,
+                                                 int64_t n, int64_t nseg, int64_t nalloc, SegRec *__restrict__ seg)
+{
+    seg_tables<K>(fwd, bwd, n, nseg, nalloc, seg, blockIdx.x);
+}
+
+// The 64-, 32- and (b16 > 0 blocks) 16-row tables in one launch, side by side.
+__global__ __launch_bounds__(64) void k_seg_prep_all(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd,
+                                                     int64_t n, SegRec *__restrict__ s64, int64_t b64,
+                                                     SegRec *__restrict__ s32, int64_t b32, SegRec *__restrict__ s16)
+{
+    const int64_t b = blockIdx.x;
+    if (b < b64) seg_tables<64>(fwd, bwd, n, (n + 63) / 64, seg_padded(n, 64), s64, b);
+    else if (b < b64 + b32) seg_tables<32>(fwd, bwd, n, (n + 31) / 32, seg_padded(n, 32), s32, b - b64);
+    else seg_tables<16>(fwd, bwd, n, (n + 15) / 16, seg_padded(n, 16), s16, b - b64 - b32);
+}
+
+// C = A B for 2x2 column-major matrices (C may be A or B).
 __device__ __forceinline__ void mat2_mul(const double *a, const double *b, double *c)
 {
     const double c0 = fma(a[2], b[1], a[0] * b[0]), c1 = fma(a[3], b[1], a[1] * b[0]);
@@ -381,12 +391,15 @@ hipError_t launch_assemble_d4(double *d_diag, int64_t n, double sigma, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_factor(const double *d_diag, int64_t n, int64_t npad, double *d_fac,
-                         FwdRec *d_fwd, BwdRec *d_bwd, int64_t *d_bad, hipStream_t s)
+hipError_t launch_factor(const double *d_diag, int64_t n, double *d_fac, int64_t *d_bad, hipStream_t s)
 {
     hipLaunchKernelGGL(k_factor_serial, dim3(1), dim3(256), 0, s, d_diag, n, d_fac, d_bad);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
+    return hipGetLastError();
+}
+
+hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const double *d_fac, FwdRec *d_fwd,
+                          BwdRec *d_bwd, hipStream_t s)
+{
     const int bs = 256;
     const int64_t grid = (npad + bs - 1) / bs;
     hipLaunchKernelGGL(k_records, dim3((unsigned)grid), dim3(bs), 0, s, d_diag, d_fac, n, npad,
@@ -394,18 +407,28 @@ hipError_t launch_factor(const double *d_diag, int64_t n, int64_t npad, double *
     return hipGetLastError();
 }
 
+hipError_t launch_seg_prep_all(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, SegRec *s64, SegRec *s32,
+                               SegRec *s16, hipStream_t s)
+{
+    auto blocks = [&](int rows) { return (seg_padded(n, rows) + 15) / 16; };
+    const int64_t b64 = blocks(64), b32 = blocks(32), b16 = s16 ? blocks(16) : 0;
+    hipLaunchKernelGGL(k_seg_prep_all, dim3((unsigned)(b64 + b32 + b16)), dim3(64), 0, s, d_fwd, d_bwd, n, s64, b64,
+                       s32, b32, s16);
+    return hipGetLastError();
+}
+
 hipError_t launch_seg_prep(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, int seg_rows,
                            SegRec *d_seg, hipStream_t s)
 {
-    const int64_t nseg = (n + seg_rows - 1) / seg_rows;
+    const int64_t nseg = (n + seg_rows - 1) / seg_rows, nalloc = seg_padded(n, seg_rows);
     const int bs = 64;
-    const dim3 grid((unsigned)((nseg + bs - 1) / bs));
+    const dim3 grid((unsigned)((nalloc + 15) / 16));
     switch (seg_rows) {
-    case 16: hipLaunchKernelGGL(k_seg_prep<16>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, d_seg); break;
-    case 32: hipLaunchKernelGGL(k_seg_prep<32>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, d_seg); break;
-    case 64: hipLaunchKernelGGL(k_seg_prep<64>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, d_seg); break;
+    case 16: hipLaunchKernelGGL(k_seg_prep<16>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, nalloc, d_seg); break;
+    case 32: hipLaunchKernelGGL(k_seg_prep<32>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, nalloc, d_seg); break;
+    case 64: hipLaunchKernelGGL(k_seg_prep<64>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, nalloc, d_seg); break;
     case kGroupSegRows:
-        hipLaunchKernelGGL(k_seg_prep<kGroupSegRows>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, d_seg);
+        hipLaunchKernelGGL(k_seg_prep<kGroupSegRows>, grid, dim3(bs), 0, s, d_fwd, d_bwd, n, nseg, nalloc, d_seg);
         break;
     default: return hipErrorInvalidValue;
     }

@@ -170,10 +170,17 @@ inline int seg_slot(int seg_rows)
 }
 constexpr int kSegPad = 16;       // segment records are padded to a multiple of this
 
+// records of the table of seg_rows-row segments, padding (all zero) included
+__host__ __device__ inline int64_t seg_padded(int64_t n, int64_t seg_rows)
+{
+    return ((n + seg_rows - 1) / seg_rows + kSegPad - 1) / kSegPad * kSegPad;
+}
+
 struct SegCache {
     int seg_rows = 0;
     int64_t nseg = 0;
     SegRec *d_seg = nullptr;
+    bool own = false;  // an allocation of its own (else part of the plan's)
 };
 
 // Group constants of the single pass for (seg_rows, waves per group).
@@ -218,9 +225,11 @@ struct pent_plan {
     uint64_t magic;
     int64_t n;
     int device;
+    char *d_pool;            // the one allocation the pointers below point into
     double *d_diag;          // 5n: a, b, c, d, e (zero-padded outside the matrix)
-    double *d_fac;           // 4n: alpha, beta, gamma, delta
+    double *d_fac;           // 4n: alpha, beta, gamma, delta (right behind the diagonals)
     double *d_anorm;         // 1: ||A||_inf
+    int64_t *d_bad;          // 4: pivot check and streaming depths, read back once by the factorisation
     int64_t npad;            // record rows: n + 256 rounded up to kRecPad, rows >= n all zero
     pent::FwdRec *d_fwd;     // npad
     pent::BwdRec *d_bwd;     // npad
@@ -236,12 +245,11 @@ struct pent_plan {
     std::mutex mu;           // guards seg caches (lazy build)
     pent::SegCache seg[pent::kMaxSegCaches];
     pent::GrpCache grp[pent::kMaxGrpCaches];  // lazily built, guarded by mu
-    pent::ScanRec *d_scan;   // resident-tile scan constants (64 records), lazily built
+    pent::ScanRec *d_scan;   // resident-tile scan constants (64 records), where n allows the tile
     double *d_trunc;         // truncation products of the streaming sweeps: 32-row segments, then 64-row
     int strm_depth[3];       // their depths (32, 64 rows; corrections, 32), 0: too deep to stream
     int cus;                 // compute units of the device
     double *d_trec;          // resident-tile record image (5 x 64 x rows doubles)
-    int scan_rows;           // rows per lane they were built for
 };
 
 namespace pent {
@@ -317,8 +325,12 @@ constexpr uint64_t kMagic = 0x70656e7462617463ull;  // "pentbatc"
 
 // ---- launchers (each returns a hipError_t from the launch) ----
 hipError_t launch_assemble_d4(double *d_diag, int64_t n, double sigma, hipStream_t s);
-hipError_t launch_factor(const double *d_diag, int64_t n, int64_t npad, double *d_fac,
-                         FwdRec *d_fwd, BwdRec *d_bwd, int64_t *d_bad, hipStream_t s);
+hipError_t launch_factor(const double *d_diag, int64_t n, double *d_fac, int64_t *d_bad, hipStream_t s);
+hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const double *d_fac, FwdRec *d_fwd,
+                          BwdRec *d_bwd, hipStream_t s);
+// The segment tables (seg_padded records each) of 64, 32 and, unless null, 16 rows.
+hipError_t launch_seg_prep_all(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, SegRec *s64, SegRec *s32,
+                               SegRec *s16, hipStream_t s);
 hipError_t launch_seg_prep(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, int seg_rows,
                            SegRec *d_seg, hipStream_t s);
 // Group constants for groups of `waves` segments from the segment table
@@ -363,7 +375,8 @@ hipError_t launch_eta(const double *d_diag, const double *d_anorm, int64_t n, co
                       bool f32, int64_t ldf, const double *x, int64_t ldx, int64_t batch,
                       unsigned long long *acc, double *eta, double tol, unsigned int *err,
                       hipStream_t s);
-hipError_t launch_anorm(const double *d_diag, int64_t n, double *d_anorm, hipStream_t s);
+// ||A||_inf, and *d_err = 0
+hipError_t launch_anorm(const double *d_diag, int64_t n, double *d_anorm, unsigned int *d_err, hipStream_t s);
 
 // ---- 2-D Cahn-Hilliard explicit term (ch2d.hip, and fused into k_onepass_t) ----
 // R = C + dt_k * Lap_h(C^3 - C) at one point, from the point's C and the

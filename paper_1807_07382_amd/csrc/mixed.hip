@@ -188,8 +188,9 @@ __global__ void k_eta_final(const unsigned long long *__restrict__ acc,
 
 // ||A||_inf = max_i sum_k |A_ik| over the (zero-padded) diagonals.
 __global__ __launch_bounds__(256) void k_anorm(const double *__restrict__ diag, int64_t n,
-                                               double *__restrict__ out)
+                                               double *__restrict__ out, unsigned int *__restrict__ err)
 {
+    if (threadIdx.x == 0) *err = 0u;  // the new handle's status word
     __shared__ double red[256];
     double m = 0.0;
     for (int64_t i = threadIdx.x; i < n; i += 256) {
@@ -254,9 +255,9 @@ hipError_t launch_eta(const double *d_diag, const double *d_anorm, int64_t n, co
     return hipGetLastError();
 }
 
-hipError_t launch_anorm(const double *d_diag, int64_t n, double *d_anorm, hipStream_t s)
+hipError_t launch_anorm(const double *d_diag, int64_t n, double *d_anorm, unsigned int *d_err, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_anorm, dim3(1), dim3(256), 0, s, d_diag, n, d_anorm);
+    hipLaunchKernelGGL(k_anorm, dim3(1), dim3(256), 0, s, d_diag, n, d_anorm, d_err);
     return hipGetLastError();
 }
 

@@ -258,25 +258,30 @@ __device__ __forceinline__ void mul2(const double *A, const double *B, double *C
     C[0] = c0; C[1] = c1; C[2] = c2; C[3] = c3;
 }
 
-__global__ void k_scan_prep(const SegRec *__restrict__ seg, int64_t nseg, ScanRec *__restrict__ out)
+__global__ __launch_bounds__(kTileSeg) void k_scan_prep(const SegRec *__restrict__ seg, int64_t nseg, ScanRec *__restrict__ out)
 {
     const int s = threadIdx.x;
     if (s >= kTileSeg) return;
+    // the segments' matrices in LDS first: the products below are a chain of
+    // up to 32 of them per lane (from memory 22 us at 64 segments, so 10)
+    __shared__ double tf[kTileSeg][4], tb[kTileSeg][4];
+    for (int k = 0; k < 4; k++) {
+        const double one = k % 3 == 0 ? 1.0 : 0.0;  // past the matrix: the identity
+        tf[s][k] = s < nseg ? seg[s].tf[k] : one;
+        tb[s][k] = s < nseg ? seg[s].tb[k] : one;
+    }
+    __syncthreads();
     ScanRec r;
     for (int l = 0; l < 6; l++) {
         const int len = 1 << l;
         double M[4] = {1.0, 0.0, 0.0, 1.0};
         for (int t = s; t >= 0 && t > s - len; t--) {  // M = M * Tf_t, t descending
-            double T[4] = {1.0, 0.0, 0.0, 1.0};
-            if (t < nseg) { T[0] = seg[t].tf[0]; T[1] = seg[t].tf[1]; T[2] = seg[t].tf[2]; T[3] = seg[t].tf[3]; }
-            mul2(M, T, M);
+            mul2(M, tf[t], M);
         }
         for (int k = 0; k < 4; k++) r.p[l][k] = M[k];
         double Q[4] = {1.0, 0.0, 0.0, 1.0};
         for (int t = s; t < kTileSeg && t < s + len; t++) {  // Q = Q * Tb_t, t ascending
-            double T[4] = {1.0, 0.0, 0.0, 1.0};
-            if (t < nseg) { T[0] = seg[t].tb[0]; T[1] = seg[t].tb[1]; T[2] = seg[t].tb[2]; T[3] = seg[t].tb[3]; }
-            mul2(Q, T, Q);
+            mul2(Q, tb[t], Q);
         }
         for (int k = 0; k < 4; k++) r.q[l][k] = Q[k];
     }
