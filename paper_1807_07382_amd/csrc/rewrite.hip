@@ -157,7 +157,11 @@ hipError_t launch_rewrite(const double *a, const double *b, const double *c, con
     hipLaunchKernelGGL(k_rewrite_init, dim3(1), dim3(64), 0, s, bad);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int bs = 256;
+    // one wave per workgroup, so that few systems still spread over all compute
+    // units: 16384 of them are 256 workgroups (n = 1024: 425 us; 687 with
+    // workgroups of four waves, which left three units in four idle), 65536 are
+    // bound by memory either way (1141 and 1178 us, 6.1 and 5.9 TB/s)
+    const int bs = 64;
     hipLaunchKernelGGL(k_rewrite<8>, dim3((unsigned)((batch + bs - 1) / bs)), dim3(bs), 0, s, a, b, c,
                        d, e, ldm, (int)n, F, batch, ld, G, H, bad);
     return hipGetLastError();
