@@ -139,3 +139,36 @@ def test_rewrite_workload_full_size_sampled(torch):
         # A^{-1} has norm <= 1 here (SPD, eigenvalues >= 1), so the first
         # step's difference is carried into the second without growth
         assert np.all(err <= (step + 1) * tol), (step, err / tol)
+
+
+@pytest.mark.parametrize("n", [1, 13, 14, 15, 29, 111, 112, 113, 125, 224, 226, 341])
+def test_rewrite_several_tiles_per_workgroup(torch, n):
+    """Rows round the block (14) and the round of all waves (112), and enough
+    systems that a workgroup takes up to three tiles, the last one ragged, of
+    random matrices that repeat every 1000 systems: sampled systems against
+    the oracle, every system against its repetition, and a zero pivot in the
+    last row of a system of the second round."""
+    tiles = 2 * torch.cuda.get_device_properties(0).multi_processor_count + 5
+    m = 64 * tiles - 27
+    print_case(test="rewrite_tiles", n=n, m=m)
+    diags = per_system(n, 1000, seed=n)
+    F = np.random.Generator(np.random.PCG64(n)).uniform(-1, 1, (n, 1000))
+    ref = oracle.rewrite_solve(*diags, F)
+    which = torch.arange(m, device="cuda") % 1000
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda()[:, which].contiguous() for x in diags]
+    Fd = torch.from_numpy(F).cuda()[:, which].contiguous()
+    Fd2 = Fd.clone()
+    pb.solve_rewrite_(*dev, Fd, check=True)
+    X = Fd[:, :1000].cpu().numpy()
+    assert np.all(colerr(X, ref) <= 64 * U * varah_kappa_cols(diags))
+    assert bool(torch.equal(Fd, Fd[:, :1000][:, which]))
+    # the pivot of the last row: c - a delta_{n-3} - beta gamma_{n-2} with a = b = 0
+    bad = 64 * (tiles // 2) + 9
+    for x in (dev[0], dev[1], dev[2]):
+        x[n - 1, bad] = 0.0
+    with pytest.raises(pb.SystemZeroPivotError) as ei:
+        pb.solve_rewrite_(*dev, Fd2, check=True)
+    assert (ei.value.system, ei.value.row) == (bad, n - 1)
+    assert not bool(torch.isfinite(Fd2[n - 1, bad]))
+    Fd2[:, bad] = Fd[:, bad]
+    assert bool(torch.equal(Fd2, Fd))
