@@ -342,6 +342,9 @@ int pent_rewrite_check(const void *work, int64_t n, int64_t *system, int64_t *ro
  * decoupled look-back, the last two unknowns formed by the first block of
  * every 64-system tile, the update applied before the one store) or the
  * E-solve followed by two light kernels; both take stream-ordered scratch.
+ * Under the automatic schedule, n <= 2050 and a batch that fits the device in
+ * one turn, it is one kernel that holds whole systems in a workgroup and takes
+ * no scratch.
  *
  * pent_cyclic_factor: a..e HOST FP64 arrays of length n, row-indexed and
  *   wrapped: row i holds a[i] at column (i-2) mod n, b[i] at (i-1) mod n,
@@ -418,7 +421,10 @@ int64_t pent_size(pent_handle h); /* n, or -1 for a bad handle */
  *           segments (seg_rows in {16, 32, 64});
  *   kind 3: resident tile: 8 systems per workgroup held whole in registers
  *           (n <= 4096), one read of f and one write of x; seg_rows ignored.
- *           For larger n a solve falls back to kind 2.
+ *           For larger n a solve falls back to kind 2.  For n <= 2048 and
+ *           most batches that fit the device in one turn the workgroup holds
+ *           16 or 32 systems instead (a form of this kind; the automatic
+ *           schedule takes it there whatever n * batch is).
  *   kind 4: single pass: the partitioned sweep of kind 2 in one kernel, each
  *           (64-system, seg_rows-row) block held in registers from load to
  *           store, the segment interface states exchanged between blocks

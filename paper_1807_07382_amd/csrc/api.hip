@@ -453,9 +453,9 @@ bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
 // form where that stands in for it below n = 1024) they win from about 5000
 // systems at every n (us, streaming / before: n = 2048 58 / 56 at 5003, 57 /
 // 81 at 8192; n = 4096 110 / 112 and 110 / 159; n = 8192 230 / 224 and 214 /
-// 290).  In the resident tile's place, from a batch that grows with n (n = 64
-// 8 / 22 at 5003; n = 256 10.5 / 16.5 at 2500; n = 1000 25 / 25 at 2500, 27 /
-// 57 at 5003; n = 4096 not at all within its sizes: 90 / 42 at 1024).  A
+// 290).  In the place of the tiles of eight systems (n above 2048, where the
+// wider resident tiles end) from half as many, which that schedule's own limit
+// on n * batch leaves little of (n = 4096 x 1024 90 / 42).  A
 // schedule forced to 64-row single pass streams by the same rule; any other
 // forced schedule is run as asked.
 bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, StreamPlan *p)
@@ -463,8 +463,7 @@ bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, Str
     const bool single = kind == 4 && seg_rows == 64;
     if ((!single && h->sched_kind != 0) || onepass_waves_override()) return false;
     if ((batch + 31) / 32 > INT32_MAX) return false;
-    const int64_t nblk = (h->n + 31) / 32;
-    if (batch < (kind == 3 ? std::min<int64_t>(80 * nblk, 2560) : 5120)) return false;
+    if (batch < (kind == 3 ? 2560 : 5120)) return false;
     return stream_plan(h, 32, p) || stream_plan(h, 64, p);
 }
 
@@ -483,6 +482,32 @@ bool t_stream_route(const pent_plan *h, int64_t batch, StreamPlan *p)
     return p->depth <= 6 || h->n * batch < (int64_t)8 << 20;
 }
 
+// Tile width of the resident form for n rows and this many systems, or 0.
+// Tiles of 16 systems spread over the most compute units; from 5000 systems
+// there are enough of 32, whose rows share fewer lines where they are not
+// aligned (us, 16 / 32: 256 x 5003 11.3 / 9.9, 1000 x 5003 27.9 / 25.6, but
+// 1000 x 2500 17.1 / 22.5).  Past one turn of the device (of a workgroup per
+// compute unit above 1024 rows, two of half the waves below) walking tiles
+// are better (us, resident / before: 1000 x 6000 27 / 32, x 10000 42 / 37;
+// 1537 x 4096 30 / 45, x 5008 48 / 46; 2048 x 4096 35 / 58, x 5008 60 / 49).
+int resident_width(int64_t n, int64_t batch, int cus)
+{
+    if (n > 2048 || batch > (n > 1024 ? 16 : 24) * (int64_t)cus) return 0;
+    return n <= 1024 && batch >= 5000 ? 32 : 16;
+}
+
+// Tile width of the resident form for a solve with h under the automatic
+// schedule or the resident-tile one (kind 3), or 0.  The tiles of eight systems
+// (tile.hip) spread further still, and keep the long systems of small batches (us, resident / eight: 1000 x 500 11.2 /
+// 13.4, x 1000 14.2 / 13.3, x 1500 15.7 / 17.3; 2048 x 500 23 / 20, x 1000 24 /
+// 20, x 1500 27 / 31; 256 x 256 7.5 / 8.7).
+int resident_route(const pent_plan *h, int64_t ldf, int64_t ldx, int64_t batch)
+{
+    if ((h->sched_kind != 0 && h->sched_kind != 3) || onepass_waves_override() || ldf > kResidentLd || ldx > kResidentLd) return 0;
+    if (h->n > 768 && batch <= 1100 && (h->n > 1024 || batch > 640)) return 0;
+    return resident_width(h->n, batch, h->cus);
+}
+
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
 // summ_bytes() for the chosen schedule.
 int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int64_t ldx,
@@ -492,6 +517,9 @@ int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int6
     int kind, seg_rows, st;
     io_schedule(h, batch, inplace64, &kind, &seg_rows);
     StreamPlan sp;
+    if (const int width = resident_route(h, ldf, ldx, batch))
+        return hip_status(launch_resident(h->d_fwd, h->d_bwd, h->seg[seg_slot(32)].d_seg, h->seg[seg_slot(64)].d_seg, h->n,
+                                          width, f, f32, ldf, x, ldx, batch, s));
     if (stream_route(h, kind, seg_rows, batch, &sp)) {
         const int cw = stream_tile_width(batch, h->cus);
         return hip_status(launch_stream(sp, h->n, f, f32, ldf, cw, x, ldx, cw, batch, cw, h->d_err, s));
@@ -518,7 +546,8 @@ int solve_io_scratch(pent_plan *h, const double *f, int64_t ldf, double *x, int6
     int kind, seg_rows;
     io_schedule(h, batch, (const void *)f == (const void *)x && ldf == ldx, &kind, &seg_rows);
     StreamPlan sp;
-    const size_t bytes = stream_route(h, kind, seg_rows, batch, &sp) ? 0 : summ_bytes(h, kind, seg_rows, batch);
+    const bool scratch = !resident_route(h, ldf, ldx, batch) && !stream_route(h, kind, seg_rows, batch, &sp);
+    const size_t bytes = scratch ? summ_bytes(h, kind, seg_rows, batch) : 0;
     void *summ = nullptr;
     if (bytes) {
         hipError_t e = scratch_alloc(&summ, bytes, s);
@@ -791,11 +820,28 @@ bool cyc_single_pass(pent_cyclic c, int64_t batch, bool cn)
 // 1537 x 5003 62 / 61 and 67 / 63, x 16384 91 / 137 and 85 / 142).
 constexpr int64_t kCycStreamBatch = 8192;
 
+// Tile width of the resident form for a periodic solve or step under the
+// automatic schedule, or 0 (us, solve and step, resident / look-back: N = 256 x 256 7.6 /
+// 26 and 8.8 / 28; N = 1000 x 2500 20 / 35 and 20 / 37, x 6000 29 / 45 and 30 /
+// 47; N = 1537 x 3001 29 / 48 and 31 / 50; N = 2050 x 4096 40 / 54 and 38 / 55,
+// x 6000 66 / 63).
+int cyc_resident_width(const pent_cyclic_s *c, int64_t ldf, int64_t ldx, int64_t batch)
+{
+    if (c->kind != 0 || onepass_waves_override() || ldf > kResidentLd || ldx > kResidentLd) return 0;
+    return resident_width(c->E->n, batch, c->E->cus);
+}
+
 int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
                    int64_t batch, hipStream_t s)
 {
     int st;
     StreamPlan sp;
+    if (const int width = cyc_resident_width(c, ldf, ldx, batch)) {
+        const pent_plan *E = c->E;
+        return hip_status(launch_resident_cyclic(E->d_fwd, E->d_bwd, E->seg[seg_slot(32)].d_seg, E->seg[seg_slot(64)].d_seg,
+                                                 c->d_cd, c->d_Z, c->d_aux, E->n, width, cn, F, ldf, X, ldx, batch, s,
+                                                 c->uni ? c->uc : nullptr));
+    }
     if (c->seg_rows == 64 && batch >= kCycStreamBatch && c->ends > 0 && !onepass_waves_override() &&
         stream_plan(c->E, 32, &sp)) {
         const int cw = stream_tile_width(batch, c->E->cus);
@@ -1684,7 +1730,8 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
     int ykind, yseg;
     io_schedule(hy, ybatch, false, &ykind, &yseg);
     StreamPlan ysp;
-    const bool ystream = stream_route(hy, ykind, yseg, ybatch, &ysp);  // needs no scratch
+    const bool ystream = resident_route(hy, ybatch, ybatch, ybatch) ||
+                         stream_route(hy, ykind, yseg, ybatch, &ysp);  // one of the forms without scratch
     const size_t ybytes = ystream ? 0 : summ_bytes(hy, ykind, yseg, ybatch);
     void *ybuf = nullptr;
     if (ybytes) {

@@ -244,23 +244,6 @@ __device__ __forceinline__ int64_t wrap(int64_t r, int64_t n)
     return r;
 }
 
-// f_i = 2 C_i - (A C)_i with row-invariant diagonals u (same operations in
-// the same order as cn_row).
-struct CycUni {
-    double c[5];
-};
-__device__ __forceinline__ double cn_row_u(const CycUni &u, double c0, double c1, double c2,
-                                           double c3, double c4)
-{
-    double acc = 2.0 * c2;
-    acc = fma(-u.c[0], c0, acc);
-    acc = fma(-u.c[1], c1, acc);
-    acc = fma(-u.c[2], c2, acc);
-    acc = fma(-u.c[3], c3, acc);
-    acc = fma(-u.c[4], c4, acc);
-    return acc;
-}
-
 // Waits until *p >= want; false (and *err raised) if the wait ran out.
 __device__ __forceinline__ bool wait_nonzero(unsigned int *p, unsigned int want, unsigned int *err)
 {

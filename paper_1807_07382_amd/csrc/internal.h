@@ -147,6 +147,23 @@ struct CycAux {
     int64_t reach[2];  // rows at the top and at the bottom in which (h^T E^{-1})^T counts (k_cyc_reach)
 };
 
+// f_i = 2 C_i - (A C)_i with row-invariant diagonals u (in the order
+// of the stencil from the left).
+struct CycUni {
+    double c[5];
+};
+__device__ __forceinline__ double cn_row_u(const CycUni &u, double c0, double c1, double c2,
+                                           double c3, double c4)
+{
+    double acc = 2.0 * c2;
+    acc = fma(-u.c[0], c0, acc);
+    acc = fma(-u.c[1], c1, acc);
+    acc = fma(-u.c[2], c2, acc);
+    acc = fma(-u.c[3], c3, acc);
+    acc = fma(-u.c[4], c4, acc);
+    return acc;
+}
+
 // One unit of the single-pass group solve: rows [g*rows, (g+1)*rows) of
 // the 64 systems of matrix `mat` that start at col0; u0 = index of the
 // first unit of that tile (its units are consecutive).
@@ -444,6 +461,17 @@ int stream_tile_width(int64_t batch, int cus);
 // Tile t of cw <= 64 systems starts at F + t * tsf and X + t * tsx.
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
                          int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
+
+// Whole tiles of `width` (16 or 32) systems, n <= 32768 / width rows, by one
+// workgroup each (resident.hip); ldf, ldx <= kResidentLd.  The periodic form:
+// n = the rows of E, cn: the Crank-Nicolson step.
+constexpr int64_t kResidentLd = (int64_t)1 << 22;
+hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
+                           const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s);
+hipError_t launch_resident_cyclic(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64,
+                                  const double *cd, const double *Z, const CycAux *aux, int64_t n, int width, bool cn,
+                                  const double *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s,
+                                  const double *uni = nullptr);
 
 // System-major right-hand sides, system s at F + s * ld (p of 32-row
 // segments); and the x sweeps of a 2-D Cahn-Hilliard step from C into R, both

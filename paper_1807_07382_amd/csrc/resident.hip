@@ -1,0 +1,442 @@
+// resident.hip -- whole systems resident in one workgroup, for matrices of up
+// to 2048 rows and batches too small to fill the device with walking tiles.
+//
+// A workgroup holds all rows of a tile of S systems (S = 16 or 32): lane
+// l of wave w has rows [32 b, 32 b + 32) of system l % S in registers, b = w *
+// 64/S + l / S.  Each row is read once and written once in pieces of S
+// consecutive systems.  The sweeps are those of the streaming form (stream.h:
+// zero-start sweep of every block at once, then the true one), but the
+// states between the blocks come from a scan over all of them: within a wave
+// lane to lane, between waves through LDS after one barrier per direction.
+// Nothing is truncated, nothing goes through memory, and no wave waits for
+// another workgroup: the latency of a solve is that of one load, four sweeps
+// of 32 rows, two barriers and one store (us, before / now: N = 256 x 256, tiles
+// of eight systems, 8.5 / 7.4, of which a launch is 7; N = 1000 x 5003 as
+// walking tiles 26.7 / 20.5, 3.9 TB/s; N = 1537 x 2500 by partitions 47 / 25).
+// Full tiles of 16 waves are bound by the four sweeps, 32 rows x 4 waves x 9
+// operations of a SIMD each.
+//
+// The periodic solve and Crank-Nicolson step (cyclic.hip) end with
+// x_tail = Minv ((f_{n-2}, f_{n-1}) - h^T y) from y = E^{-1} f^, whose four
+// rows next to the border pass through LDS, and y - Z x_tail in registers (N =
+// 1537 x 3001: look-back 38.6 us and 5 to clear its flags, 49.5 with the gaps;
+// now 24.5).
+#include "stream.h"
+
+namespace pent {
+namespace {
+
+using namespace st;
+
+constexpr int kResK = 32;      // rows of a block
+constexpr int kResWaves = 16;  // most waves of a workgroup
+
+// What is between the waves of a tile of S systems.
+template <int S>
+struct ResLds {
+    double e[kResWaves][2][S];  // state leaving a wave's rows downward, from zero
+    double a[kResWaves][2][S];  // ... and upward
+    double ft[2][S], xe[4][S];  // periodic: f_{n-2}, f_{n-1}; y at rows 0, 1, m-2, m-1
+};
+
+// (x0, x1) of the lane d before (d > 0) or after (d < 0) this one.
+__device__ __forceinline__ void from_lane(int d, double x0, double x1, double &r0, double &r1)
+{
+    const int l = (int)(threadIdx.x & 63) - d;
+    r0 = __shfl(x0, l, 64);
+    r1 = __shfl(x1, l, 64);
+}
+
+// The state through all rows of wave u: y = e + T y, the wave's T from the
+// table of 64-row segments (one for S = 32, two for S = 16).
+template <int S, bool FWD>
+__device__ __forceinline__ void through_wave(CSeg seg, int u, double e0, double e1, double &y0, double &y1)
+{
+    if constexpr (S == 16) {
+        const int first = FWD ? 2 * u : 2 * u + 1, then = FWD ? 2 * u + 1 : 2 * u;
+        if constexpr (FWD) {
+            link(0.0, 0.0, seg[first].tf[0], seg[first].tf[1], seg[first].tf[2], seg[first].tf[3], y0, y1);
+            link(e0, e1, seg[then].tf[0], seg[then].tf[1], seg[then].tf[2], seg[then].tf[3], y0, y1);
+        } else {
+            link(0.0, 0.0, seg[first].tb[0], seg[first].tb[1], seg[first].tb[2], seg[first].tb[3], y0, y1);
+            link(e0, e1, seg[then].tb[0], seg[then].tb[1], seg[then].tb[2], seg[then].tb[3], y0, y1);
+        }
+    } else {
+        if constexpr (FWD) link(e0, e1, seg[u].tf[0], seg[u].tf[1], seg[u].tf[2], seg[u].tf[3], y0, y1);
+        else link(e0, e1, seg[u].tb[0], seg[u].tb[1], seg[u].tb[2], seg[u].tb[3], y0, y1);
+    }
+}
+
+// The forward recurrence of every block, with the state that enters it.
+template <int S>
+__device__ __forceinline__ void res_forward(double (&v)[kResK], Rec<kResK> &rc, const SegRec *seg32, CSeg segw, int w, int sub,
+                                            int64_t blk, ResLds<S> &sh)
+{
+    constexpr int G = 64 / S;
+    const int s = threadIdx.x & (S - 1);
+    const double t0 = seg32[blk].tf[0], t1 = seg32[blk].tf[1], t2 = seg32[blk].tf[2], t3 = seg32[blk].tf[3];
+    double e0 = 0.0, e1 = 0.0;
+    sweep_forward<kResK, false>(v, rc, e0, e1);
+    pin(e0);
+    pin(e1);
+    double c0 = e0, c1 = e1;
+#pragma unroll
+    for (int j = 1; j < G; j++) {
+        double p0, p1;
+        from_lane(S, c0, c1, p0, p1);
+        double n0 = p0, n1 = p1;
+        link(e0, e1, t0, t1, t2, t3, n0, n1);
+        c0 = sub == j ? n0 : c0;
+        c1 = sub == j ? n1 : c1;
+    }
+    if (sub == G - 1) {
+        sh.e[w][0][s] = c0;
+        sh.e[w][1][s] = c1;
+    }
+    __syncthreads();
+    double y0 = 0.0, y1 = 0.0;
+    for (int u = 0; u < w; u++) through_wave<S, true>(segw, u, sh.e[u][0][s], sh.e[u][1][s], y0, y1);
+#pragma unroll
+    for (int j = 1; j < G; j++) {
+        double n0 = y0, n1 = y1, p0, p1;
+        link(e0, e1, t0, t1, t2, t3, n0, n1);
+        from_lane(S, n0, n1, p0, p1);
+        y0 = sub == j ? p0 : y0;
+        y1 = sub == j ? p1 : y1;
+    }
+    sweep_forward<kResK, true>(v, rc, y0, y1);
+}
+
+// Back substitution of every block, with the state that enters it from below.
+template <int S, typename Extra>
+__device__ __forceinline__ void res_backward(double (&v)[kResK], Rec<kResK> &rc, const SegRec *seg32, CSeg segw, int w, int waves,
+                                             int sub, int64_t blk, bool rows, ResLds<S> &sh, Extra ex)
+{
+    constexpr int G = 64 / S;
+    const int s = threadIdx.x & (S - 1);
+    const double t0 = seg32[blk].tb[0], t1 = seg32[blk].tb[1], t2 = seg32[blk].tb[2], t3 = seg32[blk].tb[3];
+    double a0 = 0.0, a1 = 0.0;
+    sweep_backward<kResK, false>(v, rc, a0, a1, ex);
+    a0 = rows ? a0 : 0.0;  // blocks past the last row
+    a1 = rows ? a1 : 0.0;
+    pin(a0);
+    pin(a1);
+    double c0 = a0, c1 = a1;
+#pragma unroll
+    for (int j = G - 2; j >= 0; j--) {
+        double p0, p1;
+        from_lane(-S, c0, c1, p0, p1);
+        double n0 = p0, n1 = p1;
+        link(a0, a1, t0, t1, t2, t3, n0, n1);
+        c0 = sub == j ? n0 : c0;
+        c1 = sub == j ? n1 : c1;
+    }
+    if (sub == 0) {
+        sh.a[w][0][s] = c0;
+        sh.a[w][1][s] = c1;
+    }
+    __syncthreads();
+    double z0 = 0.0, z1 = 0.0;
+    for (int u = waves - 1; u > w; u--) through_wave<S, false>(segw, u, sh.a[u][0][s], sh.a[u][1][s], z0, z1);
+#pragma unroll
+    for (int j = G - 2; j >= 0; j--) {
+        double n0 = z0, n1 = z1, p0, p1;
+        link(a0, a1, t0, t1, t2, t3, n0, n1);
+        from_lane(-S, n0, n1, p0, p1);
+        z0 = sub == j ? p0 : z0;
+        z1 = sub == j ? p1 : z1;
+    }
+    sweep_backward<kResK, true>(v, rc, z0, z1, ex);
+#pragma unroll
+    for (int k = 0; k < kResK; k++) pin(v[k]);
+}
+
+typedef __attribute__((address_space(1))) const char *GBytes;
+typedef __attribute__((address_space(1))) char *GBytesOut;
+typedef __attribute__((address_space(1))) double *GDblOut;
+
+// Where a lane's rows are: 32 from row r0 of its column, `off` bytes past the
+// uniform address of the wave's first row.
+struct Place {
+    int64_t rw, r0;  // first row of the wave, of the lane
+    int sub, s;      // the lane's block in the wave, its system in the tile
+};
+
+// The lane's rows from column p of the tile; rows from n on give zero.
+template <typename TI>
+__device__ __forceinline__ void res_load(double (&v)[kResK], const TI *F, int64_t ld, int64_t s, const Place &at, int64_t n,
+                                         bool full)
+{
+    typedef __attribute__((address_space(1))) const TI *G;
+    if (full) {
+        const unsigned int off = (unsigned int)(sizeof(TI) * (at.sub * kResK * ld + s));
+        GBytes q = (GBytes)(F + at.rw * ld);
+#pragma unroll
+        for (int k = 0; k < kResK; k++) {
+            v[k] = (double)*(G)(q + off);
+            q = fresh(q + sizeof(TI) * ld);
+        }
+    } else {
+        const int L = n - at.r0 < kResK ? (int)(n - at.r0) : kResK;
+        G q = (G)F + (L > 0 ? at.r0 : n - 1) * ld + s;
+#pragma unroll
+        for (int k = 0; k < kResK; k++) {
+            v[k] = (double)*q;
+            q += k + 1 < L ? ld : 0;
+            asm volatile("" : "+v"(q));
+        }
+#pragma unroll
+        for (int k = 0; k < kResK; k++) v[k] = k < L ? v[k] : 0.0;
+    }
+}
+
+__device__ __forceinline__ void res_store(const double (&v)[kResK], double *X, int64_t ld, const Place &at, int64_t n, bool full)
+{
+    if (full) {
+        const unsigned int off = (unsigned int)(8 * (at.sub * kResK * ld + at.s));
+        GBytesOut q = (GBytesOut)(X + at.rw * ld);
+#pragma unroll
+        for (int k = 0; k < kResK; k++) {
+            *(GDblOut)(q + off) = v[k];
+            q = fresh(q + 8 * ld);
+        }
+    } else {
+        const int L = n - at.r0 < kResK ? (int)(n - at.r0) : kResK;
+        GDblOut q = (GDblOut)X + at.r0 * ld + at.s;
+#pragma unroll
+        for (int k = 0; k < kResK; k++) {
+            if (k < L) *q = v[k];
+            q += ld;
+            asm volatile("" : "+v"(q));
+        }
+    }
+}
+
+// Tiles in the order that gives each XCD a contiguous eighth of them; < 0:
+// this workgroup has none.
+__device__ __forceinline__ int64_t res_tile(int64_t ntiles)
+{
+    const int x = blockIdx.x % 8;
+    const int64_t t = ntiles * x / 8 + blockIdx.x / 8;
+    return t < ntiles * (x + 1) / 8 ? t : -1;
+}
+
+template <int S>
+__device__ __forceinline__ Place res_place(int w)
+{
+    const int lane = threadIdx.x & 63;
+    Place at;
+    at.sub = lane / S;
+    at.s = lane & (S - 1);
+    at.rw = (int64_t)w * (64 / S) * kResK;
+    at.r0 = at.rw + at.sub * kResK;
+    return at;
+}
+
+template <int S, typename TI>
+__global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_resident(
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t n, const TI *F, int64_t ldf,
+    double *X, int64_t ldx, int64_t batch, int64_t ntiles)
+{
+    __shared__ ResLds<S> sh;
+    const int64_t tile = res_tile(ntiles);
+    if (tile < 0) return;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
+    const Place at = res_place<S>(w);
+    const int64_t c0 = tile * S, blk = at.r0 / kResK;
+    const bool act = c0 + at.s < batch, full = at.rw + 64 / S * kResK <= n;
+    double v[kResK];
+    Rec<kResK> rc;
+    res_load(v, F + c0, ldf, act ? at.s : batch - 1 - c0, at, n, full);  // idle lanes repeat the last column
+    load_forward<kResK>(rc, fwd, at.r0);
+    load_backward<kResK>(rc, bwd, at.r0);
+    res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
+    res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < n, sh, Plain());
+    if (act) res_store(v, X + c0, ldx, at, n, full);
+}
+
+// As above for E (m rows) and the border of a periodic matrix of m + 2 rows.
+// CN: F holds C, and f_i = 2 C_i - (A C)_i is formed in registers; UNI: with
+// the same five coefficients in every row, else those of cd.
+template <int S, bool CN, bool UNI>
+__global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_resident_cyclic(
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t m, const double *F, int64_t ldf,
+    double *X, int64_t ldx, int64_t batch, int64_t ntiles, const double *cd, const double *Z,
+    const CycAux *__restrict__ aux, CycUni uc)
+{
+    constexpr int K = kResK;
+    __shared__ ResLds<S> sh;
+    const int64_t tile = res_tile(ntiles), n = m + 2, ldc = cyc_ld(n);
+    if (tile < 0) return;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
+    const Place at = res_place<S>(w);
+    const int64_t c0 = tile * S, blk = at.r0 / K;
+    const bool act = c0 + at.s < batch, full = at.rw + 64 / S * K <= m;
+    const int64_t sc = act ? at.s : batch - 1 - c0;
+    const double *col = F + c0 + sc;
+    const int L = m - at.r0 < K ? (int)(m - at.r0) : K;
+    double v[K];
+    Rec<K> rc;
+    if (w == 0) {  // the right-hand side's last two entries
+        double f0, f1;
+        if constexpr (CN) {
+            const double g0 = col[(m - 2) * ldf], g1 = col[(m - 1) * ldf], g2 = col[m * ldf], g3 = col[(m + 1) * ldf], g4 = col[0],
+                         g5 = col[ldf];
+            CycUni u0 = uc, u1 = uc;
+            if constexpr (!UNI)
+#pragma unroll
+                for (int d = 0; d < 5; d++) {
+                    u0.c[d] = cd[d * ldc + m];
+                    u1.c[d] = cd[d * ldc + m + 1];
+                }
+            f0 = cn_row_u(u0, g0, g1, g2, g3, g4);
+            f1 = cn_row_u(u1, g1, g2, g3, g4, g5);
+        } else {
+            f0 = col[m * ldf];
+            f1 = col[(m + 1) * ldf];
+        }
+        sh.ft[0][at.s] = f0;
+        sh.ft[1][at.s] = f1;
+    }
+    if constexpr (CN) {
+        // C rows r0-2 .. r0+K+1, periodic (past row n-1 nothing is used)
+        double h[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int64_t r = i < 2 ? at.r0 - 2 + i : at.r0 + K + i - 2;
+            h[i] = col[(r < 0 ? r + n : r >= n ? n - 1 : r) * ldf];
+        }
+        res_load(v, F + c0, ldf, sc, at, n, full);
+        Coef<K> g[5];
+        if constexpr (!UNI) {
+#pragma unroll
+            for (int d = 0; d < 5; d++)
+#pragma unroll
+                for (int i = 0; i < Coef<K>::S; i++) {
+                    const int64_t r = at.r0 + coef_row<K>(i);
+                    g[d].c[i] = cd[d * ldc + (r < n ? r : n - 1)];
+                }
+        }
+        double p2 = h[0], p1 = h[1];
+        unroll<K>([&](auto kk) {
+            constexpr int k = decltype(kk)::value;
+            if constexpr (!UNI && k % 8 == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int d = 0; d < 5; d++) g[d].hold();
+            }
+            const double ck = v[k];
+            const double n1 = k + 1 < K ? v[k + 1 < K ? k + 1 : 0] : h[2];
+            const double n2 = k + 2 < K ? v[k + 2 < K ? k + 2 : 0] : (k + 2 == K ? h[2] : h[3]);
+            CycUni u = uc;
+            if constexpr (!UNI) u = CycUni{{g[0].template get<k>(), g[1].template get<k>(), g[2].template get<k>(),
+                                            g[3].template get<k>(), g[4].template get<k>()}};
+            v[k] = cn_row_u(u, p2, p1, ck, n1, n2);
+            p2 = p1;
+            p1 = ck;
+        });
+        if (!full) {
+#pragma unroll
+            for (int k = 0; k < K; k++) v[k] = k < L ? v[k] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < K; k++) pin(v[k]);
+    } else {
+        res_load(v, F + c0, ldf, sc, at, m, full);
+    }
+    load_forward<K>(rc, fwd, at.r0);
+    load_backward<K>(rc, bwd, at.r0);
+    res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
+    res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < m, sh, Plain());
+    // y at the rows that the border meets, x_tail, and x = y - Z x_tail
+    if (at.r0 == 0) {
+        sh.xe[0][at.s] = v[0];
+        sh.xe[1][at.s] = v[1];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const int64_t r = m - 2 + i;
+        double y = v[0];
+#pragma unroll
+        for (int k = 1; k < K; k++) y = k == (int)(r % K) ? v[k] : y;
+        if (blk == r / K) sh.xe[2 + i][at.s] = y;
+    }
+    Coef<K> z0, z1;
+#pragma unroll
+    for (int i = 0; i < Coef<K>::S; i++) {
+        const Dbl2 u = ((const Dbl2 *)Z)[at.r0 + coef_row<K>(i)];
+        z0.c[i] = u.x;
+        z1.c[i] = u.y;
+    }
+    __syncthreads();
+    double t0 = sh.ft[0][at.s], t1 = sh.ft[1][at.s];
+    const int nh = aux->nh;
+    for (int k = 0; k < nh; k++) {
+        const int64_t c = aux->hcol[k];
+        const double y = aux->hv[k] * sh.xe[c < 2 ? (int)c : (int)(c - m) + 4][at.s];
+        if (aux->hq[k] == 0) t0 -= y;
+        else t1 -= y;
+    }
+    const double x0 = fma(aux->minv[1], t1, aux->minv[0] * t0), x1 = fma(aux->minv[3], t1, aux->minv[2] * t0);
+    unroll<K>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        if constexpr (k % 8 == 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            z0.hold();
+            z1.hold();
+        }
+        v[k] = fma(-z1.template get<k>(), x1, fma(-z0.template get<k>(), x0, v[k]));
+        pin(v[k]);  // here, not in the stores' branch
+    });
+    if (!act) return;
+    res_store(v, X + c0, ldx, at, m, full);
+    if (at.r0 == 0) {
+        X[c0 + at.s + m * ldx] = x0;
+        X[c0 + at.s + (m + 1) * ldx] = x1;
+    }
+}
+
+struct ResLaunch {
+    dim3 grid, block;
+    int64_t ntiles;
+};
+
+ResLaunch res_launch(int64_t n, int width, int64_t batch)
+{
+    const int64_t ntiles = (batch + width - 1) / width, rows = 64 / width * kResK;
+    return ResLaunch{dim3((unsigned)((ntiles + 7) / 8 * 8)), dim3((unsigned)(64 * ((n + rows - 1) / rows))), ntiles};
+}
+
+}  // namespace
+
+hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
+                           const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s)
+{
+    const ResLaunch g = res_launch(n, width, batch);
+    if (f32) {
+        const auto fn = width == 16 ? k_resident<16, float> : k_resident<32, float>;
+        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const float *)F, ldf, X, ldx, batch, g.ntiles);
+    } else {
+        const auto fn = width == 16 ? k_resident<16, double> : k_resident<32, double>;
+        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const double *)F, ldf, X, ldx, batch, g.ntiles);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_cyclic(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64,
+                                  const double *cd, const double *Z, const CycAux *aux, int64_t n, int width, bool cn,
+                                  const double *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s,
+                                  const double *uni)
+{
+    CycUni uc = {{0.0, 0.0, 0.0, 0.0, 0.0}};
+    if (uni)
+        for (int k = 0; k < 5; k++) uc.c[k] = uni[k];
+    auto fn = width == 16 ? k_resident_cyclic<16, false, true> : k_resident_cyclic<32, false, true>;
+    if (cn && uni) fn = width == 16 ? k_resident_cyclic<16, true, true> : k_resident_cyclic<32, true, true>;
+    else if (cn) fn = width == 16 ? k_resident_cyclic<16, true, false> : k_resident_cyclic<32, true, false>;
+    const ResLaunch g = res_launch(n, width, batch);
+    hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, F, ldf, X, ldx, batch, g.ntiles, cd, Z, aux, uc);
+    return hipGetLastError();
+}
+
+}  // namespace pent

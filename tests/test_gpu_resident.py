@@ -1,0 +1,129 @@
+"""Whole systems resident in one workgroup (the automatic schedule of matrices
+of up to 2048 rows and batches that do not fill the device): edges of blocks,
+waves and tiles, types and strides, deep chains, non-finite systems, and the
+periodic solve and step."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1807_07382_amd import pentbatch as pb
+from tests._gpu import U, colerr, d4_tol, print_case, torch_dev
+from tests.test_gpu_stream import cyc_lu, probes, rand
+from tests.test_oracle_pins import random_dd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    return torch_dev()
+
+
+# n: one row to a full workgroup; blocks of 32 rows, waves of 64 and 128, on
+# and off their edges; m: tiles of 16 and (from 5000) 32, partial last tiles
+SIZES = [(1, 3, 0), (2, 16, 1), (31, 17, 0), (32, 5000, 0), (33, 15, 2), (64, 5003, 1), (65, 6001, 0), (127, 100, 0),
+         (128, 33, 7), (129, 33, 0), (512, 700, 0), (513, 5100, 3), (768, 1000, 0), (1000, 5003, 5), (1023, 6000, 0),
+         (1024, 500, 16), (1025, 1101, 0), (1537, 2500, 1), (1920, 1200, 0), (1921, 1200, 0), (2047, 4096, 0),
+         (2048, 1500, 3)]
+
+
+@pytest.mark.parametrize("n,m,pad", SIZES)
+@pytest.mark.parametrize("sigma", [0.1, 1e5])
+def test_resident_matches_oracle(torch, n, m, pad, sigma):
+    """In place from FP64 and out of place from FP32; nothing is written
+    beside the batch."""
+    print_case(test="resident", n=n, m=m, pad=pad, sigma=sigma)
+    B = rand(torch, (n, m + pad), n + m).float().double()
+    c = probes(m, 16)
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(B[:, c].cpu().numpy()))
+    F = B.clone()
+    X = torch.full((n, m + 2 * pad), 7.0, dtype=torch.float64, device="cuda")
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_(F[:, :m])
+        p.solve_mixed(B.float()[:, :m], X[:, :m])
+        p.check()
+    assert torch.equal(F[:, m:], B[:, m:]) and bool((X[:, m:] == 7.0).all())
+    assert np.max(colerr(F[:, c].cpu().numpy(), ref)) <= d4_tol(sigma)
+    assert torch.equal(F[:, :m], X[:, :m])
+
+
+@pytest.mark.parametrize("n,m", [(300, 1000), (1000, 5003), (1700, 2000)])
+def test_resident_against_forced_schedule(torch, n, m):
+    """A matrix of differing rows: every system against the partitioned
+    schedule (both within 64 u kappa of the solution, per column), and
+    non-finite right-hand sides, which leave no finite value in their system
+    and the others alone."""
+    print_case(test="resident_forced", n=n, m=m)
+    dg = random_dd(n, seed=n)
+    B = rand(torch, (n, m), n)
+    with pb.Plan.factor(*(getattr(dg, k) for k in "abcde")) as p:
+        X = p.solve_(B.clone())
+        F = B.clone()
+        bad = {3: (n - 1, np.nan), 16: (n // 2, np.inf), 17: (0, np.nan), m - 1: (n - 1, -np.inf)}
+        for col, (row, val) in bad.items():
+            F[row, col] = val
+        Y = p.solve_(F)
+        p.set_schedule(2, 64)
+        ref = p.solve_(B.clone())
+        p.check()
+    kappa = np.linalg.cond(oracle.dense(dg), np.inf)
+    err = (X - ref).abs().amax(0) / ref.abs().amax(0)
+    assert float(err.max()) <= 128 * U * kappa
+    assert not bool(torch.isfinite(Y[:, list(bad)]).any())
+    keep = [j for j in range(m) if j not in bad]
+    assert torch.equal(Y[:, keep], X[:, keep])
+
+
+@pytest.mark.parametrize("n,m,pad,sigma", [(5, 7, 0, 1.0), (6, 40, 1, 0.1), (33, 16, 0, 10.0), (34, 100, 0, 10.0),
+                                           (35, 100, 3, 1e4), (66, 6000, 0, 10.0), (130, 33, 0, 100.0),
+                                           (131, 5003, 5, 1.0), (1026, 5100, 0, 50.0), (1027, 300, 0, 1.0),
+                                           (1537, 3001, 0, 10.0), (1922, 64, 16, 1e4), (2050, 4096, 0, 3.0)])
+def test_resident_periodic(torch, n, m, pad, sigma):
+    """Solves and Crank-Nicolson steps, uniform diagonals (bounds as for the
+    streaming form)."""
+    print_case(test="resident_cyc", n=n, m=m, pad=pad, sigma=sigma)
+    B = rand(torch, (n, m + pad), n + 1)
+    X = torch.full((n, m + pad), 7.0, dtype=torch.float64, device="cuda")
+    F = B.clone()
+    c = probes(m, 16)
+    Bc = B[:, c].cpu().numpy()
+    lu, A = cyc_lu(n, sigma)
+    with pb.Cyclic.factor_d4(n, sigma) as cy:
+        cy.solve_(F[:, :m])
+        cy.cn_step(B[:, :m], X[:, :m])
+        cy.check()
+    assert torch.equal(F[:, m:], B[:, m:]) and bool((X[:, m:] == 7.0).all())
+    assert np.max(colerr(F[:, c].cpu().numpy(), lu.solve(Bc))) <= d4_tol(sigma)
+    ref = lu.solve(2 * Bc - A @ Bc)
+    err = np.max(np.abs(X[:, c].cpu().numpy() - ref), axis=0)
+    assert np.all(err <= d4_tol(sigma) * (np.max(np.abs(ref), axis=0) + (2 + 16 * sigma) * np.max(np.abs(Bc), axis=0)))
+
+
+@pytest.mark.parametrize("n,m", [(5, 20), (34, 100), (300, 5001), (1500, 1200)])
+def test_resident_periodic_varying_rows(torch, n, m):
+    """Diagonals that differ from row to row (the step reads them per row)."""
+    print_case(test="resident_cyc_rows", n=n, m=m)
+    g = np.random.Generator(np.random.PCG64(n))
+    dg = [g.uniform(-1, 1, n) for _ in range(5)]
+    dg[2] = 5.0 + g.uniform(0, 1, n)
+    A = np.zeros((n, n))
+    for o in range(-2, 3):
+        for r in range(n):
+            A[r, (r + o) % n] += dg[o + 2][r]
+    C = rand(torch, (n, m), 6)
+    X = torch.empty_like(C)
+    c = probes(m, 16)
+    Cc = C[:, c].cpu().numpy()
+    with pb.Cyclic.factor(*dg) as cy:
+        cy.cn_step(C, X)
+        F = cy.solve_(C.clone())
+        C[n // 2, 4] = float("nan")
+        Y = cy.solve_(C.clone())
+        cy.check()
+    kappa = np.linalg.cond(A, np.inf)
+    assert np.max(colerr(F[:, c].cpu().numpy(), np.linalg.solve(A, Cc))) <= 64 * U * kappa
+    ref = np.linalg.solve(A, 2 * Cc - A @ Cc)
+    assert np.max(np.abs(X[:, c].cpu().numpy() - ref)) <= 64 * U * kappa * 12 * np.max(np.abs(Cc))
+    assert not bool(torch.isfinite(Y[:, 4]).any())
+    keep = [j for j in range(m) if j != 4]
+    assert torch.equal(Y[:, keep], F[:, keep])
