@@ -467,19 +467,32 @@ bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, Str
     return stream_plan(h, 32, p) || stream_plan(h, 64, p);
 }
 
-// Whether a system-major solve of `batch` systems runs as streaming sweeps
-// (us, streaming / before: n = 64 x 500 8 / 25; n = 1024 x 2048 24 / 32, x
-// 32768 117 / 130; n = 2000 x 5200 62 / 54, x 10000 76 / 94; n = 4096 x 9000
-// 161 / 152, x 16384 230 / 261).  The x sweeps of a 2-D step go by the same
-// rule, so that they give the bits of the separate passes; theirs is the
-// exception for large grids and deep chains (the explicit term is formed in
-// the waves that are not waiting for the chain, 7 of 16 at sigma = 200: the
-// step on 1024 x 1024 x 32 280 us streaming, 257 by look-back in x; 512 x 512 x
-// 32 64 / 72; 1000 x 1000 x 8 95 / 92).
+// Whether a system-major solve of `batch` systems runs as streaming sweeps,
+// where it does not run in resident tiles (us, streaming / look-back: n = 4096
+// x 9000 161 / 152, x 16384 230 / 261).  The x sweeps of a 2-D step go by the
+// same two rules, so that they give the bits of the separate passes; it is
+// theirs that deep chains are left to look-back (the explicit term is formed
+// in the waves that are not waiting for the chain, 7 of 16 at sigma = 200).
 bool t_stream_route(const pent_plan *h, int64_t batch, StreamPlan *p)
 {
-    if (!((h->n <= 1024 || batch >= 10000) && (batch + 31) / 32 <= INT32_MAX && stream_plan(h, 32, p))) return false;
-    return p->depth <= 6 || h->n * batch < (int64_t)8 << 20;
+    return batch >= 10000 && (batch + 31) / 32 <= INT32_MAX && stream_plan(h, 32, p) && p->depth <= 6;
+}
+
+// Whether it runs in resident tiles of 16 systems.  Up to 1024 rows two or more
+// workgroups share a compute unit, one loading while the other sweeps (us,
+// resident / streaming, at sigma = 1: n = 256 x 117187 87 / 95, n = 512 x 58593 88 /
+// 102, n = 1021 x 20011 81 / 88, n = 1024 x 32768 100 / 115, at sigma = 200 100 / 139;
+// the 2-D step on 1024 x 1024 x 32 221, 256 by look-back in x); but matrices of
+// less than a wave's 128 rows (n = 64 x 100000 32 / 22), and of five waves, which
+// leave the sixteenth idle (n = 640 x 46875 100 / 95), stream when there are many
+// turns, and so do longer ones, alone on their compute unit (n = 1537 x 19518
+// 133 / 123, x 4000 32 / 61; at sigma = 200 x 20000 140, look-back 195).
+bool t_resident_route(const pent_plan *h, int64_t batch)
+{
+    StreamPlan sp;
+    if (h->n > 2048 || (batch + 15) / 16 > INT32_MAX / 2) return false;
+    if (!t_stream_route(h, batch, &sp)) return true;
+    return h->n > 96 && h->n <= 1024 && (h->n <= 512 || h->n > 640);
 }
 
 // Tile width of the resident form for n rows and this many systems, or 0.
@@ -1745,7 +1758,10 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
     // fits on the device; else the stencil pass writes it to R first
     StreamPlan xsp;
     if (hx->tst_cap == 0) hx->tst_cap = onepass_t_capacity(true);
-    if (t_stream_route(hx, batch, &xsp)) {
+    if (t_resident_route(hx, batch)) {
+        st = hip_status(launch_resident_ch2d(hx->d_fwd, hx->d_bwd, hx->seg[seg_slot(32)].d_seg, hx->seg[seg_slot(64)].d_seg,
+                                             nx, C, R, ny, ninst, dt, h, s));
+    } else if (t_stream_route(hx, batch, &xsp)) {
         st = hip_status(launch_stream_ch2d(xsp, nx, C, R, ny, ninst, dt, h, hx->d_err, s));
     } else if (hx->tst_cap > 0 && onepass_t_groups(nx) <= hx->tst_cap / 4 &&
         (batch + 63) / 64 * onepass_t_groups(nx) <= (int64_t)UINT32_MAX / 2) {
@@ -1952,6 +1968,9 @@ int pent_solve_strided(pent_handle h, double *F, int64_t batch, int64_t ld, void
     if (!F) return ret(PENT_INVALID_VALUE);
     hipStream_t s = (hipStream_t)stream;
     StreamPlan sp;
+    if (t_resident_route(h, batch))
+        return ret(hip_status(launch_resident_t(h->d_fwd, h->d_bwd, h->seg[seg_slot(32)].d_seg, h->seg[seg_slot(64)].d_seg,
+                                                h->n, F, ld, batch, s)));
     if (t_stream_route(h, batch, &sp)) return ret(hip_status(launch_stream_t(sp, h->n, F, ld, batch, h->d_err, s)));
     // the single pass (blocks transposed through LDS) where a tile of it
     // fits on the device; else one lane per system

@@ -468,6 +468,11 @@ hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32
 constexpr int64_t kResidentLd = (int64_t)1 << 22;
 hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
                            const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s);
+// System-major solves and 2-D x sweeps, as launch_stream_t and _ch2d.
+hipError_t launch_resident_t(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n,
+                             double *F, int64_t ld, int64_t batch, hipStream_t s);
+hipError_t launch_resident_ch2d(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n,
+                                const double *C, double *R, int64_t ny, int64_t ninst, const double *dt, double h, hipStream_t s);
 hipError_t launch_resident_cyclic(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64,
                                   const double *cd, const double *Z, const CycAux *aux, int64_t n, int width, bool cn,
                                   const double *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s,

@@ -32,10 +32,10 @@ constexpr int kResK = 32;      // rows of a block
 constexpr int kResWaves = 16;  // most waves of a workgroup
 
 // What is between the waves of a tile of S systems.
-template <int S>
+template <int S, int NW>
 struct ResLds {
-    double e[kResWaves][2][S];  // state leaving a wave's rows downward, from zero
-    double a[kResWaves][2][S];  // ... and upward
+    double e[NW][2][S];  // state leaving a wave's rows downward, from zero
+    double a[NW][2][S];  // ... and upward
     double ft[2][S], xe[4][S];  // periodic: f_{n-2}, f_{n-1}; y at rows 0, 1, m-2, m-1
 };
 
@@ -68,9 +68,9 @@ __device__ __forceinline__ void through_wave(CSeg seg, int u, double e0, double 
 }
 
 // The forward recurrence of every block, with the state that enters it.
-template <int S>
+template <int S, typename Lds>
 __device__ __forceinline__ void res_forward(double (&v)[kResK], Rec<kResK> &rc, const SegRec *seg32, CSeg segw, int w, int sub,
-                                            int64_t blk, ResLds<S> &sh)
+                                            int64_t blk, Lds &sh)
 {
     constexpr int G = 64 / S;
     const int s = threadIdx.x & (S - 1);
@@ -108,9 +108,9 @@ __device__ __forceinline__ void res_forward(double (&v)[kResK], Rec<kResK> &rc, 
 }
 
 // Back substitution of every block, with the state that enters it from below.
-template <int S, typename Extra>
+template <int S, typename Lds, typename Extra>
 __device__ __forceinline__ void res_backward(double (&v)[kResK], Rec<kResK> &rc, const SegRec *seg32, CSeg segw, int w, int waves,
-                                             int sub, int64_t blk, bool rows, ResLds<S> &sh, Extra ex)
+                                             int sub, int64_t blk, bool rows, Lds &sh, Extra ex)
 {
     constexpr int G = 64 / S;
     const int s = threadIdx.x & (S - 1);
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t n, const TI *F, int64_t ldf,
     double *X, int64_t ldx, int64_t batch, int64_t ntiles)
 {
-    __shared__ ResLds<S> sh;
+    __shared__ ResLds<S, kResWaves> sh;
     const int64_t tile = res_tile(ntiles);
     if (tile < 0) return;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     const CycAux *__restrict__ aux, CycUni uc)
 {
     constexpr int K = kResK;
-    __shared__ ResLds<S> sh;
+    __shared__ ResLds<S, kResWaves> sh;
     const int64_t tile = res_tile(ntiles), n = m + 2, ldc = cyc_ld(n);
     if (tile < 0) return;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
@@ -396,6 +396,174 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
+// System-major storage (system i = 0 .. per - 1 of group g at src + g * kst + i *
+// sst, n values each; a tile is up to S systems of one group), as k_stream_t
+// (stream_t.hip) has it: runs of 16 rows are loaded as pairs and turned in
+// place through LDS, 64 (system, block) combinations to the wave.
+//
+// ST: C comes in at src and R = C + dt_g Lap_h(C^3 - C) is formed over it.  The y
+// neighbours' terms are the next lanes' own, and at the tile's ends those of
+// two more systems, from LDS; the rows above and below a block are read from
+// memory.
+//
+// A workgroup of 16 systems has as many waves as the rows take, and as many
+// workgroups share a compute unit as its 16 waves allow, each in a phase of
+// its own: HBM-bound (n = 1024 x 32768 100 us, 5.4 TB/s, from 118 streaming; with
+// 32 systems, one workgroup to the unit, 126).
+template <int S, int NW, bool ST, bool NT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_resident_t(
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t n, const double *src, double *F,
+    int64_t per, int64_t sst, int64_t kst, int64_t tpk, int64_t ntiles, const double *dt, double inv_h2)
+{
+    constexpr int K = kResK, G = 64 / S;
+    __shared__ ResLds<S, NW> sh;
+    __shared__ double tb[NW][8][66];
+    const int64_t tile = res_tile(ntiles);
+    if (tile < 0) return;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
+    const Place at = res_place<S>(w);
+    const int lane = threadIdx.x & 63, pair = lane & 7, grp = lane >> 3;
+    const int64_t g = ST ? tile / tpk : 0, s0 = (tile - g * tpk) * S, base = g * kst + s0 * sst, blk = at.r0 / K;
+    const int cnt = (int)(per - s0 < S ? per - s0 : S);
+    const bool full = at.rw + G * K <= n;
+    const int L = n - at.r0 < K ? (int)(n - at.r0) : K;
+    double(*tw)[66] = tb[w];
+    typedef Dbl2 Dbl2u __attribute__((aligned(8)));  // 16 bytes at any double
+    typedef __attribute__((address_space(1))) const Dbl2u *G2;
+    typedef __attribute__((address_space(1))) Dbl2u *W2;
+    typedef __attribute__((address_space(1))) const double *G1;
+    double v[K], up = 0.0, low = 0.0, hv[G] = {};
+    if constexpr (ST) {
+        // the rows around the block, and the tile's neighbour systems: rows rw + 64 i +
+        // lane of the system above in hv[i], of the one below in hv[G / 2 + i]
+        const double *c = src + base + (int64_t)(at.s < cnt ? at.s : cnt - 1) * sst;
+        const int64_t ru = at.r0 - 1, rl = at.r0 + K;
+        up = c[ru < 0 ? 0 : ru < n ? ru : n - 1];
+        low = c[rl < n ? rl : n - 1];
+        up = ru >= 0 ? up : 0.0;
+        low = rl < n ? low : 0.0;
+#pragma unroll
+        for (int i = 0; i < G; i++) {
+            const bool below = i >= G / 2, in = below ? s0 + cnt < per : s0 > 0;
+            const int64_t row = at.rw + 64 * (i % (G / 2)) + lane, y = below ? (in ? cnt : cnt - 1) : in ? -1 : 0;
+            hv[i] = src[base + y * sst + (row < n ? row : n - 1)];
+            hv[i] = in && row < n ? hv[i] : 0.0;
+        }
+    }
+    // rows 16 c + 2 pair + e of combination 8 q + grp into v[16 c + 2 q + e];
+    // systems past the tile repeat its last one.  Rows past the last one are
+    // read all the same, and cleared, where a further system lies behind the
+    // tile's (so that they are inside the array: at most 127 of them).
+    const bool whole = full || (s0 + S < per && sst >= 128);
+#pragma unroll
+    for (int j = 0; j < S / 8; j++) {
+        const int sj = 8 * j + grp;
+        const double *p = src + base + (int64_t)(sj < cnt ? sj : cnt - 1) * sst;
+        if (whole) {
+            p += at.rw + 2 * pair;
+#pragma unroll
+            for (int b = 0; b < G; b++)
+#pragma unroll
+                for (int c = 0; c < K / 16; c++) {
+                    const G2 a = (G2)(p + K * b + 16 * c);
+                    const Dbl2u u = NT ? __builtin_nontemporal_load(a) : *a;
+                    v[16 * c + 2 * (b * (S / 8) + j)] = u.x;
+                    v[16 * c + 2 * (b * (S / 8) + j) + 1] = u.y;
+                }
+        } else {
+#pragma unroll
+            for (int b = 0; b < G; b++)
+#pragma unroll
+                for (int c = 0; c < K / 16; c++)
+#pragma unroll
+                    for (int e = 0; e < 2; e++) {
+                        const int64_t row = at.rw + K * b + 16 * c + 2 * pair + e;
+                        v[16 * c + 2 * (b * (S / 8) + j) + e] = ((G1)p)[row < n ? row : n - 1];
+                    }
+        }
+    }
+    // turned: v[k] = row r0 + k of the lane's system
+#pragma unroll
+    for (int c = 0; c < K / 16; c++)
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) tw[pair][8 * i + grp] = v[16 * c + 2 * i + e];
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[16 * c + 2 * i + e] = tw[i][lane];
+        }
+    if (!full) {
+#pragma unroll
+        for (int k = 0; k < K; k++) v[k] = k < L ? v[k] : 0.0;
+    }
+    Rec<K> rc;
+    if constexpr (ST) {
+        if (cnt < S) {
+#pragma unroll
+            for (int k = 0; k < K; k++) v[k] = at.s < cnt ? v[k] : 0.0;
+        }
+        double *nb = tw[0];  // terms of the neighbour systems, above then below
+#pragma unroll
+        for (int i = 0; i < G; i++) nb[64 * i + lane] = ch_wterm(hv[i]);
+        const bool first = at.s == 0, last = at.s == S - 1;
+        const double *mine = nb + (first ? 0 : 32 * G) + 32 * at.sub;
+        const double dtk = dt[g];
+        double wprev = at.r0 > 0 ? ch_wterm(up) : 0.0, wcur = ch_wterm(v[0]);
+        unroll<K>([&](auto kk) {
+            constexpr int row = decltype(kk)::value;
+            if constexpr (row % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+            const double e = mine[row];
+            const double a = lane_shift<true>(wcur, e), b = lane_shift<false>(wcur, e);
+            const double ws = first ? e : a, wn = last ? e : b;
+            const double wnext = ch_wterm(row + 1 < K ? v[row + 1 < K ? row + 1 : 0] : low);
+            v[row] = ch_point(v[row], wcur, wnext, wprev, wn, ws, dtk, inv_h2);
+            wprev = wcur;
+            wcur = wnext;
+        });
+        if (!full) {
+#pragma unroll
+            for (int k = 0; k < K; k++) v[k] = k < L ? v[k] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < K; k++) pin(v[k]);
+    }
+    load_forward<K>(rc, fwd, at.r0);
+    load_backward<K>(rc, bwd, at.r0);
+    res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
+    res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < n, sh, Plain());
+    // turned back and stored as runs
+#pragma unroll
+    for (int c = 0; c < K / 16; c++)
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) tw[i][lane] = v[16 * c + 2 * i + e];
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[16 * c + 2 * i + e] = tw[pair][8 * i + grp];
+        }
+#pragma unroll
+    for (int j = 0; j < S / 8; j++) {
+        const int sj = 8 * j + grp;
+        if (sj >= cnt) continue;
+        double *p = F + base + (int64_t)sj * sst + at.rw + 2 * pair;
+        const int left = (int)(n - at.rw < G * K ? n - at.rw : G * K) - 2 * pair;
+#pragma unroll
+        for (int b = 0; b < G; b++)
+#pragma unroll
+            for (int c = 0; c < K / 16; c++) {
+                const int i = b * (S / 8) + j;
+                const Dbl2u u = {v[16 * c + 2 * i], v[16 * c + 2 * i + 1]};
+                if (full) {
+                    if (NT) __builtin_nontemporal_store(u, (W2)(p + K * b + 16 * c));
+                    else *(W2)(p + K * b + 16 * c) = u;
+                } else {
+                    if (K * b + 16 * c + 1 < left) *(W2)(p + K * b + 16 * c) = u;
+                    else if (K * b + 16 * c < left) p[K * b + 16 * c] = u.x;
+                }
+            }
+    }
+}
+
 struct ResLaunch {
     dim3 grid, block;
     int64_t ntiles;
@@ -407,7 +575,37 @@ ResLaunch res_launch(int64_t n, int width, int64_t batch)
     return ResLaunch{dim3((unsigned)((ntiles + 7) / 8 * 8)), dim3((unsigned)(64 * ((n + rows - 1) / rows))), ntiles};
 }
 
+template <bool ST>
+hipError_t launch_t(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n,
+                    const double *src, double *F, int64_t per, int64_t sst, int64_t kst, int64_t groups, const double *dt,
+                    double inv_h2, hipStream_t s)
+{
+    const int64_t tpk = (per + 15) / 16, ntiles = tpk * groups;
+    const ResLaunch g = res_launch(n, 16, ntiles * 16);
+    const bool lines = (uintptr_t)src % 128 == 0 && (uintptr_t)F % 128 == 0 && sst % 16 == 0 && kst % 16 == 0;
+    // (LDS for the waves there are, so that it does not limit the workgroups)
+    auto fn = lines ? k_resident_t<16, 16, ST, true> : k_resident_t<16, 16, ST, false>;
+    if (g.block.x <= 64) fn = lines ? k_resident_t<16, 1, ST, true> : k_resident_t<16, 1, ST, false>;
+    else if (g.block.x <= 128) fn = lines ? k_resident_t<16, 2, ST, true> : k_resident_t<16, 2, ST, false>;
+    else if (g.block.x <= 256) fn = lines ? k_resident_t<16, 4, ST, true> : k_resident_t<16, 4, ST, false>;
+    else if (g.block.x <= 512) fn = lines ? k_resident_t<16, 8, ST, true> : k_resident_t<16, 8, ST, false>;
+    hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, src, F, per, sst, kst, tpk, ntiles, dt, inv_h2);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_resident_t(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n,
+                             double *F, int64_t ld, int64_t batch, hipStream_t s)
+{
+    return launch_t<false>(fwd, bwd, seg32, seg64, n, F, F, batch, ld, 0, 1, nullptr, 0.0, s);
+}
+
+hipError_t launch_resident_ch2d(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n,
+                                const double *C, double *R, int64_t ny, int64_t ninst, const double *dt, double h, hipStream_t s)
+{
+    return launch_t<true>(fwd, bwd, seg32, seg64, n, C, R, ny, ninst * n, n, ninst, dt, 1.0 / (h * h), s);
+}
 
 hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
                            const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s)

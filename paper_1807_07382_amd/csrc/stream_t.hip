@@ -28,9 +28,9 @@ typedef double Dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // 16 byt
 // selects (with them it kept 32 row masks and spilled 71 registers, and the
 // sweep took 230 us).
 //
-// HBM-bound: n = 1024 x 32768 117 us, 4.6 TB/s (133 by look-back, which read
-// the same runs); n = 1021 x 20011 with no run on a line of its own 66 us
-// (108: it fetched such runs a double at a time).
+// HBM-bound: n = 2048 x 32768 217 us, 4.9 TB/s; n = 1537 x 20000, with no run on
+// a line of its own, 130 us (195 by look-back, which fetched such runs a double
+// at a time).
 template <bool ST, bool NT>
 __global__ __launch_bounds__(64 * kTNW) __attribute__((amdgpu_waves_per_eu(kTEU, kTEU))) void k_stream_t(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, int64_t n, int nblk,

@@ -127,3 +127,47 @@ def test_resident_periodic_varying_rows(torch, n, m):
     assert not bool(torch.isfinite(Y[:, 4]).any())
     keep = [j for j in range(m) if j != 4]
     assert torch.equal(Y[:, keep], F[:, keep])
+
+
+# n: waves of 128 rows, one to sixteen, full, short by one row and by nearly all
+# of it; ld: runs on lines of their own, at any double, with a gap; m: partial
+# last tiles of 16 systems, the last of which ends the array
+@pytest.mark.parametrize("n,m,ld,sigma", [(1, 3, 1, 50.0), (2, 20, 2, 0.1), (31, 64, 33, 1.0), (97, 16, 97, 1e5),
+                                          (127, 17, 127, 1.0), (128, 48, 128, 1e4), (129, 1000, 129, 50.0),
+                                          (255, 33, 300, 1.0), (257, 31, 257, 1e4), (513, 5, 520, 20.0),
+                                          (640, 12000, 640, 200.0), (1000, 333, 1001, 1e4), (1024, 100, 1024, 200.0),
+                                          (1025, 40, 1025, 1.0), (1921, 90, 1921, 1e4), (2048, 64, 2064, 1.0)])
+def test_resident_system_major(torch, n, m, ld, sigma):
+    """In an array that ends with the last system's last value; nothing is
+    written between the systems."""
+    print_case(test="resident_t", n=n, m=m, ld=ld, sigma=sigma)
+    buf = rand(torch, ((m - 1) * ld + n,), n + m)
+    keep = buf.clone()
+    F = buf.as_strided((m, n), (ld, 1))
+    c = probes(m, 16)
+    ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(F.cpu().numpy()[c].T))
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_strided_(F)
+        p.check()
+    assert np.max(colerr(np.ascontiguousarray(F.cpu().numpy()[c].T), ref)) <= d4_tol(sigma)
+    if ld > n and m > 1:
+        gap = (m - 1, ld - n)
+        assert torch.equal(buf.as_strided(gap, (ld, 1), n), keep.as_strided(gap, (ld, 1), n))
+
+
+@pytest.mark.parametrize("ny,nx,k", [(1, 5, 2), (16, 128, 3), (17, 127, 2), (33, 130, 1), (15, 260, 5), (40, 1000, 2),
+                                     (50, 1024, 1), (18, 1500, 2)])
+def test_resident_2d_x_sweep(torch, ny, nx, k):
+    """The 2-D step, its explicit term formed in the x sweeps, against the
+    separate passes: the same bits."""
+    print_case(test="resident_ch2d", ny=ny, nx=nx, k=k)
+    C = rand(torch, (ny, k, nx), ny + nx) * 0.1
+    R, C2 = torch.empty_like(C), C.clone()
+    h = 1.0 / nx
+    dt = torch.full((k,), 200.0 * h ** 4 / 0.01, dtype=torch.float64, device="cuda")
+    with pb.Plan.factor_d4(nx, 200.0) as px, pb.Plan.factor_d4(ny, 200.0) as py:
+        pb.ch2d_rhs(C2, R, dt, h)
+        px.solve_strided_(R.view(ny * k, nx))
+        py.solve_(R.view(ny, k * nx))
+        pb.ch2d_step(px, py, C, torch.empty_like(C), dt, h)
+    assert bool(torch.isfinite(C).all()) and torch.equal(C, R)
