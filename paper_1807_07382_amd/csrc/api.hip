@@ -495,30 +495,39 @@ bool t_resident_route(const pent_plan *h, int64_t batch)
     return h->n > 96 && h->n <= 1024 && (h->n <= 512 || h->n > 640);
 }
 
-// Tile width of the resident form for n rows and this many systems, or 0.
-// Tiles of 16 systems spread over the most compute units; from 5000 systems
-// there are enough of 32, whose rows share fewer lines where they are not
-// aligned (us, 16 / 32: 256 x 5003 11.3 / 9.9, 1000 x 5003 27.9 / 25.6, but
-// 1000 x 2500 17.1 / 22.5).  Past one turn of the device (of a workgroup per
-// compute unit above 1024 rows, two of half the waves below) walking tiles
-// are better (us, resident / before: 1000 x 6000 27 / 32, x 10000 42 / 37;
-// 1537 x 4096 30 / 45, x 5008 48 / 46; 2048 x 4096 35 / 58, x 5008 60 / 49).
-int resident_width(int64_t n, int64_t batch, int cus)
+// Tile width of the resident form for n <= 2048 rows and this many systems.
+// Tiles of 16 systems spread over the most compute units, and more of them run
+// apart in their phases; in between, from 5000 systems, there are enough of 32,
+// whose rows share fewer lines where they are not aligned (us, 16 / 32: 256 x 5003
+// 11.3 / 9.9, 1000 x 5003 27.9 / 25.6, but 1000 x 2500 17.1 / 22.5, 1000 x 65536
+// 240 / 258).  A single wave has its 32 systems at any batch (periodic, 130 x
+// 65536 40 / 37).
+int resident_width(int64_t n, int64_t batch)
 {
-    if (n > 2048 || batch > (n > 1024 ? 16 : 24) * (int64_t)cus) return 0;
-    return n <= 1024 && batch >= 5000 ? 32 : 16;
+    return n <= 1024 && batch >= 5000 && (batch <= 16384 || n <= 128) ? 32 : 16;
 }
 
 // Tile width of the resident form for a solve with h under the automatic
-// schedule or the resident-tile one (kind 3), or 0.  The tiles of eight systems
-// (tile.hip) spread further still, and keep the long systems of small batches (us, resident / eight: 1000 x 500 11.2 /
-// 13.4, x 1000 14.2 / 13.3, x 1500 15.7 / 17.3; 2048 x 500 23 / 20, x 1000 24 /
-// 20, x 1500 27 / 31; 256 x 256 7.5 / 8.7).
+// schedule or the resident-tile one (kind 3), or 0.  Past one turn of the device
+// (of a workgroup per compute unit above 1024 rows, two of half the waves below)
+// walking tiles are better (us, resident / before: 1000 x 6000 27 / 32, x 10000 42 /
+// 37, x 131072 453 / 411; 1537 x 4096 30 / 45, x 5008 48 / 46; 2048 x 4096 35 / 58, x
+// 5008 60 / 49), but not what stands in for them where the chain is too deep
+// below 1024 rows (partitions; sigma = 3000: 1000 x 10000 42 / 77, x 131072 453 /
+// 637).  The tiles of eight systems (tile.hip) spread further still, and keep the
+// long systems of small batches (1000 x 500 11.2 / 13.4, x 1000 14.2 / 13.3, x
+// 1500 15.7 / 17.3; 2048 x 500 23 / 20, x 1000 24 / 20, x 1500 27 / 31; 256 x 256 7.5 /
+// 8.7).
 int resident_route(const pent_plan *h, int64_t ldf, int64_t ldx, int64_t batch)
 {
-    if ((h->sched_kind != 0 && h->sched_kind != 3) || onepass_waves_override() || ldf > kResidentLd || ldx > kResidentLd) return 0;
+    if (h->n > 2048 || (h->sched_kind != 0 && h->sched_kind != 3) || onepass_waves_override()) return 0;
+    if (ldf > kResidentLd || ldx > kResidentLd || (batch + 15) / 16 > INT32_MAX / 2) return 0;
     if (h->n > 768 && batch <= 1100 && (h->n > 1024 || batch > 640)) return 0;
-    return resident_width(h->n, batch, h->cus);
+    StreamPlan sp;
+    if (batch > (h->n > 1024 ? 16 : 24) * (int64_t)h->cus &&
+        !(h->sched_kind == 0 && h->n < 1024 && !stream_plan(h, 32, &sp) && !stream_plan(h, 64, &sp)))
+        return 0;
+    return resident_width(h->n, batch);
 }
 
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
@@ -834,14 +843,25 @@ bool cyc_single_pass(pent_cyclic c, int64_t batch, bool cn)
 constexpr int64_t kCycStreamBatch = 8192;
 
 // Tile width of the resident form for a periodic solve or step under the
-// automatic schedule, or 0 (us, solve and step, resident / look-back: N = 256 x 256 7.6 /
-// 26 and 8.8 / 28; N = 1000 x 2500 20 / 35 and 20 / 37, x 6000 29 / 45 and 30 /
-// 47; N = 1537 x 3001 29 / 48 and 31 / 50; N = 2050 x 4096 40 / 54 and 38 / 55,
-// x 6000 66 / 63).
+// automatic schedule, or 0 (us, solve and step, resident / look-back: N = 256 x 256
+// 7.6 / 26 and 8.8 / 28; N = 1000 x 2500 20 / 35 and 20 / 37; N = 1026 x 8192 40 / 49
+// and 39 / 56; N = 1537 x 3001 29 / 48 and 31 / 50; N = 2050 x 4096 40 / 54 and 38 /
+// 55, x 6000 66 / 63).  More than one turn (of 32 systems to the compute unit up to
+// 1024 rows) it also takes where E fits one wave (130 x 131072 64 / 79 and 66 / 81)
+// and where the walking tiles' chain is deep (sigma = 100: 500 x 16384 40 / 51 and
+// 37 / 53; 573 x 131072 305 / 330 and 337 / 347; 1026 x 65536 258 / 266 and 265 / 289,
+// but x 16384 79 / 73; at sigma = 1 x 65536 258 / 227).
 int cyc_resident_width(const pent_cyclic_s *c, int64_t ldf, int64_t ldx, int64_t batch)
 {
-    if (c->kind != 0 || onepass_waves_override() || ldf > kResidentLd || ldx > kResidentLd) return 0;
-    return resident_width(c->E->n, batch, c->E->cus);
+    const pent_plan *E = c->E;
+    if (E->n > 2048 || c->kind != 0 || onepass_waves_override()) return 0;
+    if (ldf > kResidentLd || ldx > kResidentLd || (batch + 15) / 16 > INT32_MAX / 2) return 0;
+    if (batch > (E->n > 1024 ? 16 : 32) * (int64_t)E->cus && E->n > 128) {
+        StreamPlan sp;
+        const bool deep = !stream_plan(E, 32, &sp) || sp.depth > 6;
+        if (!deep || E->n > 1024 || (E->n > 640 && batch < 32768)) return 0;
+    }
+    return resident_width(E->n, batch);
 }
 
 int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,

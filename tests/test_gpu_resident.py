@@ -24,7 +24,7 @@ def torch():
 SIZES = [(1, 3, 0), (2, 16, 1), (31, 17, 0), (32, 5000, 0), (33, 15, 2), (64, 5003, 1), (65, 6001, 0), (127, 100, 0),
          (128, 33, 7), (129, 33, 0), (512, 700, 0), (513, 5100, 3), (768, 1000, 0), (1000, 5003, 5), (1023, 6000, 0),
          (1024, 500, 16), (1025, 1101, 0), (1537, 2500, 1), (1920, 1200, 0), (1921, 1200, 0), (2047, 4096, 0),
-         (2048, 1500, 3)]
+         (2048, 1500, 3), (700, 7000, 0)]
 
 
 @pytest.mark.parametrize("n,m,pad", SIZES)
@@ -77,7 +77,8 @@ def test_resident_against_forced_schedule(torch, n, m):
 @pytest.mark.parametrize("n,m,pad,sigma", [(5, 7, 0, 1.0), (6, 40, 1, 0.1), (33, 16, 0, 10.0), (34, 100, 0, 10.0),
                                            (35, 100, 3, 1e4), (66, 6000, 0, 10.0), (130, 33, 0, 100.0),
                                            (131, 5003, 5, 1.0), (1026, 5100, 0, 50.0), (1027, 300, 0, 1.0),
-                                           (1537, 3001, 0, 10.0), (1922, 64, 16, 1e4), (2050, 4096, 0, 3.0)])
+                                           (1537, 3001, 0, 10.0), (1922, 64, 16, 1e4),
+                                           (100, 20000, 0, 1.0), (500, 17000, 1, 300.0), (800, 33000, 0, 300.0), (2050, 4096, 0, 3.0)])
 def test_resident_periodic(torch, n, m, pad, sigma):
     """Solves and Crank-Nicolson steps, uniform diagonals (bounds as for the
     streaming form)."""
