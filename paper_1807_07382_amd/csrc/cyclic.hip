@@ -544,17 +544,19 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 // state is.  The middle blocks' part is summed as they pass, and where it is
 // not negligible against what x_tail was formed from, the difference goes to
 // scratch (dx) and is applied after the workgroup's last block, as for the
-// truncated backward chain.  N = 4096 x 65536: solve 830 us, step 890, against
+// truncated backward chain.  N = 4096 x 65536: solve 830 us, step 880, against
 // 1040 and 1090 by look-back (which waits 18 us of a unit's 49); a step costs
-// more than a plain solve (800) by its halo rows (25 us, through the L2), the
-// border products (18) and the values spilled for them.
+// more than a plain solve (800) by the bottom blocks read twice, the border
+// products (18 us) and the values spilled for them.
 constexpr int kCsK = 32, kCsNW = 16, kCsEU = 4;
 
 struct CycLds {
     double p[kCsNW][2][64];  // W^T f so far, beside the forward state in its slot
     double xt[2][2][64];     // x_tail, by the tile's turn
     double ft[2][64];        // f_{n-2}, f_{n-1}
+    double h[kCsNW][4][64];  // CN: the last four rows of C that a wave has loaded, for the next
     unsigned int xflag;      // turns whose x_tail is there
+    unsigned int hflag[kCsNW];
 };
 
 // A two-column table (Z or W) of the block's rows as coefficients.
@@ -659,6 +661,7 @@ __global__ __launch_bounds__(64 * kCsNW) __attribute__((amdgpu_waves_per_eu(kCsE
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int lane = threadIdx.x & 63;
     if (threadIdx.x == 0) cl.xflag = 0;
+    if (threadIdx.x < NW) cl.hflag[threadIdx.x] = 0;
     stream_init(sh);
     const Tiles mine = my_tiles(ntiles);
     const int nit = T + nblk;  // items of a tile: the bottom blocks' products, then the blocks
@@ -684,20 +687,33 @@ __global__ __launch_bounds__(64 * kCsNW) __attribute__((amdgpu_waves_per_eu(kCsE
         double v[K];
         if constexpr (CN) {
             // C rows r0-2 .. r0+K+1, periodic (only the top block wraps: past
-            // the last E row stand rows n-2 and n-1), and f over them
+            // the last E row stand rows n-2 and n-1), and f over them.  Loaded
+            // are rows r0+2 on; the four before are the last of the item before,
+            // which leaves them in LDS (a first block reads them itself), so that
+            // no row is read twice: the 12% more of a halo loaded with each block
+            // were reads from HBM (906 us with it, 880 so).  A slot is free when
+            // the item after its last one has been swept forward.
+            load_block<K, NT, double>(v, ft + (r0 + 2) * ldf, lo, ldf, L);
             double h[4];
+            if (q >= NW && !lds_wait(&sh.fdone, q - NW + 2) && lane == 0) atomicOr(err, 1u);
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int64_t r = i < 2 ? r0 - 2 + i : r0 + K + i - 2;
-                h[i] = ft[(r < 0 ? r + n : r >= n ? n - 1 : r) * ldf + lo];
+            for (int i = 0; i < 4; i++) cl.h[w][i][lane] = v[K - 4 + i];
+            lds_post(&cl.hflag[w], q + 1);
+            if (item == 0 || b == 0) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) h[i] = ft[(r0 + i < 2 ? r0 + i - 2 + n : r0 + i - 2) * ldf + lo];
+            } else {
+                const int pw = w == 0 ? NW - 1 : w - 1;
+                if (!lds_wait(&cl.hflag[pw], q) && lane == 0) atomicOr(err, 1u);
+#pragma unroll
+                for (int i = 0; i < 4; i++) h[i] = cl.h[pw][i][lane];
             }
-            load_block<K, false, double>(v, ft + r0 * ldf, lo, ldf, (int)(n - r0 < K ? n - r0 : K));
             double g[5];
             if constexpr (!UNI) {
 #pragma unroll
                 for (int d = 0; d < 5; d++) g[d] = cd[d * cyc_ld(n) + r0 + (lane & (K - 1))];
             }
-            double c2 = h[0], c1 = h[1];
+            double c0 = h[0], c1 = h[1], c2 = h[2], c3 = h[3];
             unroll<K>([&](auto kk) {
                 constexpr int k = decltype(kk)::value;
                 if constexpr (!UNI && k % 8 == 0) {
@@ -705,16 +721,15 @@ __global__ __launch_bounds__(64 * kCsNW) __attribute__((amdgpu_waves_per_eu(kCsE
 #pragma unroll
                     for (int d = 0; d < 5; d++) pin(g[d]);
                 }
-                const double ck = v[k];
-                const double n1 = k + 1 < K ? v[k + 1 < K ? k + 1 : 0] : h[2];
-                const double n2 = k + 2 < K ? v[k + 2 < K ? k + 2 : 0] : (k + 2 == K ? h[2] : h[3]);
                 CycUni u = uc;
                 if constexpr (!UNI) u = CycUni{{lane_double(g[0], k), lane_double(g[1], k), lane_double(g[2], k),
                                                 lane_double(g[3], k), lane_double(g[4], k)}};
-                const double f = cn_row_u(u, c2, c1, ck, n1, n2);
+                const double c4 = v[k], f = cn_row_u(u, c0, c1, c2, c3, c4);
                 v[k] = k < L ? f : 0.0;
-                c2 = c1;
-                c1 = ck;
+                c0 = c1;
+                c1 = c2;
+                c2 = c3;
+                c3 = c4;
             });
         } else {
             load_block<K, NT, double>(v, ft + r0 * ldf, lo, ldf, L);
