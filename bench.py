@@ -48,9 +48,11 @@ BYTES_PER_UNKNOWN_FP64 = 16  # read f once, write x once
 SCHEDULE_NAMES = {1: "lane", 2: "partitioned", 3: "tile", 4: "onepass"}
 
 
-# kernel source file of each schedule (the counters go stale when it changes)
-SCHEDULE_SOURCES = {"lane": ("sweep.hip",), "partitioned": ("sweep.hip",), "tile": ("tile.hip",),
-                    "onepass": ("onepass.hip", "lookback.h")}
+# kernel source files of each schedule (the counters go stale when one changes);
+# the single pass also runs as streaming sweeps
+STREAM_SOURCES = ("stream.hip", "stream.h", "lookback.h")
+SCHEDULE_SOURCES = {"lane": ("sweep.hip",), "partitioned": ("sweep.hip",), "tile": ("tile.hip", "resident.hip", "stream.h"),
+                    "onepass": ("onepass.hip",) + STREAM_SOURCES}
 
 
 def kernel_source_hash(names) -> str:
@@ -214,7 +216,7 @@ def all_configs(args, torch):
     # HBM bytes of one FP32-stream solve (k = 0) at N = 8192 x 131072 from the
     # committed counters, against its 12 B per unknown
     prec["fp32_stream_refine0_traffic"] = traffic_for("onepass64_f32", "precision",
-                                                      ("onepass.hip", "lookback.h"))
+                                                      SCHEDULE_SOURCES["onepass"])
     prec["note"] = ("FP32 is the storage precision of the right-hand-side stream; the factors, "
                     "every operation and x are FP64, so the k=0 solve already has FP64 accuracy "
                     "(same eta as the FP64 solve) and is the form that beats FP64 (12 instead of "
@@ -510,7 +512,7 @@ def run_cahn2d(args, torch):
                 roofline=dict(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s",
                               frac=gbs / PEAK_HBM_GBS,
                               traffic=traffic_for("ch2d", "cahn2d",
-                                                  ("onepass.hip", "lookback.h", "ch2d.hip"))),
+                                                  ("resident.hip", "ch2d.hip") + STREAM_SOURCES)),
                 parity=dict(instance=0, max_rel_err_vs_oracle=err))
 
 
@@ -667,7 +669,7 @@ def run_periodic(args, torch):
                 roofline=dict(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s",
                               frac=gbs / PEAK_HBM_GBS,
                               traffic=traffic_for("cyc_onepass64", "periodic",
-                                                  ("cyclic.hip", "lookback.h"))
+                                                  ("cyclic.hip", "stream.h", "lookback.h"))
                               if form == (2, 64) else None),
                 parity=dict(probe_systems=len(probe), max_rel_err_vs_oracle=err,
                             oracle_steps=args.warmup + steps))
@@ -778,7 +780,7 @@ def run_rewrite(args, torch):
                             matrices="one per system, refactored every call"),
                 roofline=dict(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s",
                               frac=gbs / PEAK_HBM_GBS, bytes_per_unknown=56,
-                              traffic=traffic_for("rewrite_lane", "rewrite", ("rewrite.hip",))),
+                              traffic=traffic_for("rewrite_lane", "rewrite", ("rewrite.hip", "stream.h"))),
                 kernel_plan_roofline=dict(bytes_per_unknown=104, achieved=gbs104,
                                           frac=gbs104 / PEAK_HBM_GBS),
                 parity=dict(probe_systems=len(cols), max_rel_err_vs_oracle=err),
