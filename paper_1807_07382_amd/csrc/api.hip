@@ -248,16 +248,12 @@ pent_handle finish_factor(pent_plan *p, bool factored = false)
     const bool strm = p->d_trunc != nullptr;
     hipError_t e = hipSuccess;
     if (!factored) e = launch_factor(p->d_diag, p->n, p->d_fac, d_bad, 0);
-    if (e == hipSuccess) e = launch_records(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, 0);
-    if (e == hipSuccess) e = launch_anorm(p->d_diag, p->n, p->d_anorm, p->d_err, 0);
+    if (e == hipSuccess)
+        e = launch_records(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, rows, p->d_trec, p->d_anorm, p->d_err, 0);
     if (e == hipSuccess) e = launch_seg_prep_all(p->d_fwd, p->d_bwd, p->n, s64, s32, s16, 0);
-    if (e == hipSuccess && strm)
-        e = launch_stream_prep(s32, n32, p->d_trunc, s64, n64, p->d_trunc + 4 * n32, d_bad + 1, 0);
-    if (e == hipSuccess && rows > 0) {
-        const SegRec *seg = p->seg[seg_slot(rows)].d_seg;
-        e = launch_scan_prep(seg, (p->n + rows - 1) / rows, p->d_scan, 0);
-        if (e == hipSuccess) e = launch_tile_recs(p->d_fwd, p->d_bwd, rows, p->d_trec, 0);
-    }
+    if (e == hipSuccess)
+        e = launch_seg_use(s32, n32, s64, n64, p->d_trunc, d_bad + 1, rows ? p->seg[seg_slot(rows)].d_seg : nullptr,
+                           rows ? (p->n + rows - 1) / rows : 0, p->d_scan, 0);
     if (e == hipSuccess) {
         // (a copy waits for the null stream's work; without one, wait for it)
         const size_t first = factored ? 1 : 0, count = strm ? 4 : 1;

@@ -219,32 +219,69 @@ __global__ __launch_bounds__(256) void k_factor_serial(const double *__restrict_
     if (tid == 0) *bad = b0;
 }
 
-// Sweep records from the factors (row-parallel).
-__global__ void k_records(const double *__restrict__ diag, const double *__restrict__ fac,
-                          int64_t n, int64_t npad, FwdRec *__restrict__ fwd,
-                          BwdRec *__restrict__ bwd)
+// ||A||_inf = max_i sum_k |A_ik| over the (zero-padded) diagonals.
+__device__ __forceinline__ void anorm_max(const double *__restrict__ diag, int64_t n, double *__restrict__ out)
+{
+    __shared__ double red[256];
+    double m = 0.0;
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < n; i += 256) {
+        const double sum = fabs(diag[i]) + fabs(diag[n + i]) + fabs(diag[2 * n + i]) +
+                           fabs(diag[3 * n + i]) + fabs(diag[4 * n + i]);
+        m = fmax(m, sum);
+    }
+    red[threadIdx.x] = m;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[0] = red[0];
+}
+
+// Sweep records from the factors (row-parallel), and where tile_rows > 0 the
+// image of those of the resident tile's LDS, tile[comp][k][s] = component comp
+// (ra, ap, bp, gm, dl) of row s * tile_rows + k.  Block 0 takes the norm, and
+// zeroes the new handle's status word.  Latency-bound like all that a handle is
+// made from, so what can stand side by side shares a launch: three (7, 7 and 11
+// us at n = 4096) where six of 7 to 10 us took their turns (pent_factor 109 us,
+// now 81; with one solve of 64 systems 173 and 127).
+__global__ __launch_bounds__(256) void k_records(const double *__restrict__ diag, const double *__restrict__ fac,
+                                                 int64_t n, int64_t npad, FwdRec *__restrict__ fwd,
+                                                 BwdRec *__restrict__ bwd, int tile_rows, double *__restrict__ tile,
+                                                 double *__restrict__ anorm, unsigned int *__restrict__ err)
 {
 #pragma clang fp contract(off)
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= npad) return;
-    if (i >= n) {  // padding rows: all zero
-        fwd[i] = FwdRec{0.0, 0.0, 0.0, 0.0};
-        bwd[i] = BwdRec{0.0, 0.0};
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) *err = 0u;
+        anorm_max(diag, n, anorm);
         return;
     }
-    const double al = fac[i];
-    const double be = (i >= 1) ? fac[n + i] : 0.0;
-    const double ai = (i >= 2) ? diag[i] : 0.0;
-    FwdRec r;
-    r.ra = 1.0 / al;
-    r.ap = ai / al;
-    r.bp = be / al;
-    r.pad = 0.0;
+    const int64_t i = (int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
+    if (i >= npad) return;
+    FwdRec r = {0.0, 0.0, 0.0, 0.0};  // padding rows: all zero
+    BwdRec q = {0.0, 0.0};
+    if (i < n) {
+        const double al = fac[i];
+        const double be = (i >= 1) ? fac[n + i] : 0.0;
+        const double ai = (i >= 2) ? diag[i] : 0.0;
+        r.ra = 1.0 / al;
+        r.ap = ai / al;
+        r.bp = be / al;
+        q.gm = (i + 1 < n) ? fac[2 * n + i] : 0.0;
+        q.dl = (i + 2 < n) ? fac[3 * n + i] : 0.0;
+    }
     fwd[i] = r;
-    BwdRec q;
-    q.gm = (i + 1 < n) ? fac[2 * n + i] : 0.0;
-    q.dl = (i + 2 < n) ? fac[3 * n + i] : 0.0;
     bwd[i] = q;
+    if (tile_rows > 0 && i < (int64_t)kTileSeg * tile_rows) {
+        const int c = kTileSeg * tile_rows;
+        double *t = tile + i % tile_rows * kTileSeg + i / tile_rows;
+        t[0] = r.ra;
+        t[c] = r.ap;
+        t[2 * c] = r.bp;
+        t[3 * c] = q.gm;
+        t[4 * c] = q.dl;
+    }
 }
 
 // Per-segment transfer matrices of the partitioned sweep.  For segment s
@@ -324,6 +361,141 @@ __global__ __launch_bounds__(64) void k_seg_prep_all(const FwdRec *__restrict__ 
     else seg_tables<16>(fwd, bwd, n, (n + 15) / 16, seg_padded(n, 16), s16, b - b64 - b32);
 }
 
+// The truncation depth of one segment table and its products P_b: D is the
+// smallest depth at which every P_b with a state left to neglect (b + D <
+// nseg - 1) has all entries below kTruncTarget, 0 if that takes more than
+// dmax segments.  One workgroup per table, a thread per segment: latency-
+// bound, so all of a product's factors are fetched before the first is used
+// and the maxima stay in registers until the end (8 us at N = 4096; 100 us
+// with the loads in the loop and a shared maximum per product).
+__device__ __forceinline__ void trunc_tables(const SegRec *seg, int nseg, int dmax, double *out, int64_t *depth, int64_t *fix)
+{
+    constexpr int M = kStreamMaxDepth;
+    __shared__ double mx[4][M];
+    typedef double D2 __attribute__((ext_vector_type(2)));
+    // f(i, m) for i = 1 .. M: m the product of the i segments after b
+    auto products = [&](int b, auto f) {
+        D2 t[M][2];
+#pragma unroll
+        for (int i = 0; i < M; i++) {
+            const D2 *p = (const D2 *)seg[b + 1 + i < nseg ? b + 1 + i : nseg - 1].tb;
+            t[i][0] = p[0];
+            t[i][1] = p[1];
+        }
+        double m[4] = {1.0, 0.0, 0.0, 1.0};
+#pragma unroll
+        for (int i = 0; i < M; i++) {
+            const double n0 = fma(m[2], t[i][0].y, m[0] * t[i][0].x), n1 = fma(m[3], t[i][0].y, m[1] * t[i][0].x);
+            const double n2 = fma(m[2], t[i][1].y, m[0] * t[i][1].x), n3 = fma(m[3], t[i][1].y, m[1] * t[i][1].x);
+            m[0] = n0;
+            m[1] = n1;
+            m[2] = n2;
+            m[3] = n3;
+            f(i + 1, m);
+        }
+    };
+    double top[M];
+#pragma unroll
+    for (int i = 0; i < M; i++) top[i] = 0.0;
+    for (int b = threadIdx.x; b < nseg - 1; b += 256)
+        products(b, [&](int i, const double(&m)[4]) {
+            if (b + i < nseg - 1)
+#pragma unroll
+                for (int k = 0; k < 4; k++) top[i - 1] = nan_max(top[i - 1], fabs(m[k]));
+        });
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        for (int d = 32; d > 0; d >>= 1) top[i] = nan_max(top[i], __shfl_xor(top[i], d, 64));
+        mx[threadIdx.x / 64][i] = top[i];
+    }
+    __syncthreads();
+    int D = 0, Df = 0;
+#pragma unroll
+    for (int i = M; i >= 1; i--) {
+        const double v = nan_max(nan_max(mx[0][i - 1], mx[1][i - 1]), nan_max(mx[2][i - 1], mx[3][i - 1]));
+        if (i <= dmax && v <= kTruncTarget) D = i;
+        if (i <= kStreamDepthFix && v <= kTruncFix) Df = i;
+    }
+    if (threadIdx.x == 0) {
+        *depth = D;
+        if (fix) *fix = Df;
+    }
+    if (D == 0) return;
+    for (int b = threadIdx.x; b < nseg; b += 256)
+        products(b, [&](int i, const double(&m)[4]) {
+            if (i == D)
+#pragma unroll
+                for (int k = 0; k < 4; k++) out[4 * (int64_t)b + k] = b + D < nseg - 1 ? m[k] : 0.0;
+        });
+}
+
+// Scan matrices from the per-segment transfer matrices (one lane per
+// segment, 64 segments).  p[l] = Tf_s Tf_{s-1} ... Tf_{max(0, s-2^l+1)},
+// q[l] = Tb_s Tb_{s+1} ... Tb_{min(63, s+2^l-1)}; matrices column-major.
+__device__ __forceinline__ void mul2(const double *A, const double *B, double *C)
+{
+    // C = A * B, column-major 2x2
+    const double c0 = A[0] * B[0] + A[2] * B[1];
+    const double c1 = A[1] * B[0] + A[3] * B[1];
+    const double c2 = A[0] * B[2] + A[2] * B[3];
+    const double c3 = A[1] * B[2] + A[3] * B[3];
+    C[0] = c0; C[1] = c1; C[2] = c2; C[3] = c3;
+}
+
+__device__ __forceinline__ void scan_tables(const SegRec *__restrict__ seg, int64_t nseg, ScanRec *__restrict__ out)
+{
+    const int s = threadIdx.x;
+    if (s >= kTileSeg) return;
+    // the segments' matrices in LDS first: the products below are a chain of
+    // up to 32 of them per lane (from memory 22 us at 64 segments, so 10)
+    __shared__ double tf[kTileSeg][4], tb[kTileSeg][4];
+    for (int k = 0; k < 4; k++) {
+        const double one = k % 3 == 0 ? 1.0 : 0.0;  // past the matrix: the identity
+        tf[s][k] = s < nseg ? seg[s].tf[k] : one;
+        tb[s][k] = s < nseg ? seg[s].tb[k] : one;
+    }
+    __syncthreads();
+    ScanRec r;
+    for (int l = 0; l < 6; l++) {
+        const int len = 1 << l;
+        double M[4] = {1.0, 0.0, 0.0, 1.0};
+        for (int t = s; t >= 0 && t > s - len; t--) {  // M = M * Tf_t, t descending
+            mul2(M, tf[t], M);
+        }
+        for (int k = 0; k < 4; k++) r.p[l][k] = M[k];
+        double Q[4] = {1.0, 0.0, 0.0, 1.0};
+        for (int t = s; t < kTileSeg && t < s + len; t++) {  // Q = Q * Tb_t, t ascending
+            mul2(Q, tb[t], Q);
+        }
+        for (int k = 0; k < 4; k++) r.q[l][k] = Q[k];
+    }
+    for (int k = 0; k < 4; k++) r.cg[k] = (s < nseg) ? seg[s].cg[k] : 0.0;
+    for (int k = 0; k < 4; k++) r.pad[k] = 0.0;
+    out[s] = r;
+}
+
+// What follows from the segment tables, side by side: the truncation of the
+// 32- and 64-row streaming sweeps (trunc), the resident tile's scan (scan).
+struct SegUse {
+    const SegRec *s32, *s64;
+    int n32, n64;
+    double *trunc32, *trunc64;  // null: not streamed
+    int64_t *depth;             // of 32 rows, of 64, of a correction
+    const SegRec *tile;         // null: no resident tile
+    int64_t ntile;
+    ScanRec *scan;
+};
+__global__ __launch_bounds__(256) void k_seg_use(SegUse u)
+{
+    if (blockIdx.x == 2) {
+        if (u.tile) scan_tables(u.tile, u.ntile, u.scan);
+    } else if (u.trunc32) {
+        const bool b = blockIdx.x == 1;
+        trunc_tables(b ? u.s64 : u.s32, b ? u.n64 : u.n32, b ? kStreamDepth64 : kStreamDepth32, b ? u.trunc64 : u.trunc32,
+                     u.depth + blockIdx.x, b ? nullptr : u.depth + 2);
+    }
+}
+
 // C = A B for 2x2 column-major matrices (C may be A or B).
 __device__ __forceinline__ void mat2_mul(const double *a, const double *b, double *c)
 {
@@ -398,12 +570,21 @@ hipError_t launch_factor(const double *d_diag, int64_t n, double *d_fac, int64_t
 }
 
 hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const double *d_fac, FwdRec *d_fwd,
-                          BwdRec *d_bwd, hipStream_t s)
+                          BwdRec *d_bwd, int tile_rows, double *d_tile, double *d_anorm, unsigned int *d_err, hipStream_t s)
 {
     const int bs = 256;
-    const int64_t grid = (npad + bs - 1) / bs;
-    hipLaunchKernelGGL(k_records, dim3((unsigned)grid), dim3(bs), 0, s, d_diag, d_fac, n, npad,
-                       d_fwd, d_bwd);
+    const int64_t grid = (npad + bs - 1) / bs + 1;
+    hipLaunchKernelGGL(k_records, dim3((unsigned)grid), dim3(bs), 0, s, d_diag, d_fac, n, npad, d_fwd, d_bwd, tile_rows,
+                       d_tile, d_anorm, d_err);
+    return hipGetLastError();
+}
+
+hipError_t launch_seg_use(const SegRec *s32, int64_t n32, const SegRec *s64, int64_t n64, double *trunc, int64_t *depth,
+                          const SegRec *tile, int64_t ntile, ScanRec *scan, hipStream_t s)
+{
+    if (!trunc && !tile) return hipSuccess;
+    const SegUse u = {s32, s64, (int)n32, (int)n64, trunc, trunc ? trunc + 4 * n32 : nullptr, depth, tile, ntile, scan};
+    hipLaunchKernelGGL(k_seg_use, dim3(3), dim3(256), 0, s, u);
     return hipGetLastError();
 }
 

@@ -99,6 +99,8 @@ struct alignas(128) GrpRec {
     double q[4];
 };
 
+constexpr int kTileSeg = 64;  // segments per system of the resident tile (= lanes of its scan wave)
+
 // Interface-scan constants of the resident-tile schedule, one record per
 // segment (64 segments): p[l] and q[l] are the products of 2^l consecutive
 // forward / backward transfer matrices ending (p) or starting (q) at the
@@ -343,11 +345,19 @@ constexpr uint64_t kMagic = 0x70656e7462617463ull;  // "pentbatc"
 // ---- launchers (each returns a hipError_t from the launch) ----
 hipError_t launch_assemble_d4(double *d_diag, int64_t n, double sigma, hipStream_t s);
 hipError_t launch_factor(const double *d_diag, int64_t n, double *d_fac, int64_t *d_bad, hipStream_t s);
+// The sweep records, the resident tile's image of them (tile_rows > 0), ||A||_inf,
+// and *d_err = 0.
 hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const double *d_fac, FwdRec *d_fwd,
-                          BwdRec *d_bwd, hipStream_t s);
+                          BwdRec *d_bwd, int tile_rows, double *d_tile, double *d_anorm, unsigned int *d_err, hipStream_t s);
 // The segment tables (seg_padded records each) of 64, 32 and, unless null, 16 rows.
 hipError_t launch_seg_prep_all(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, SegRec *s64, SegRec *s32,
                                SegRec *s16, hipStream_t s);
+// What the schedules take from the segment tables: unless trunc is null the
+// products P_b of the streaming sweeps (4 doubles per segment, 32-row ones
+// first) and depth[0..2] (device: of 32-row blocks, of 64-row ones, of a
+// correction's); unless tile is null the resident tile's scan matrices.
+hipError_t launch_seg_use(const SegRec *s32, int64_t n32, const SegRec *s64, int64_t n64, double *trunc, int64_t *depth,
+                          const SegRec *tile, int64_t ntile, ScanRec *scan, hipStream_t s);
 hipError_t launch_seg_prep(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, int seg_rows,
                            SegRec *d_seg, hipStream_t s);
 // Group constants for groups of `waves` segments from the segment table
@@ -366,10 +376,7 @@ hipError_t launch_part_sweep_io(const FwdRec *fwd, const BwdRec *bwd, const SegR
                                 int64_t ldf, double *X, int64_t ldx, int64_t batch, double *summ,
                                 int64_t summ_ld, hipStream_t s);
 int tile_rows_for(int64_t n);  // rows per lane of the resident tile, 0 if n is too large
-hipError_t launch_scan_prep(const SegRec *seg, int64_t nseg, ScanRec *out, hipStream_t s);
 size_t tile_recs_doubles(int rows);
-hipError_t launch_tile_recs(const FwdRec *fwd, const BwdRec *bwd, int rows, double *out,
-                            hipStream_t s);
 hipError_t launch_tile_sweep(const double *trec, const ScanRec *scan, int64_t n, int rows,
                              double *F, int64_t batch, int64_t ld, hipStream_t s);
 hipError_t launch_tile_sweep_io(const double *trec, const ScanRec *scan, int64_t n, int rows,
@@ -392,8 +399,6 @@ hipError_t launch_eta(const double *d_diag, const double *d_anorm, int64_t n, co
                       bool f32, int64_t ldf, const double *x, int64_t ldx, int64_t batch,
                       unsigned long long *acc, double *eta, double tol, unsigned int *err,
                       hipStream_t s);
-// ||A||_inf, and *d_err = 0
-hipError_t launch_anorm(const double *d_diag, int64_t n, double *d_anorm, unsigned int *d_err, hipStream_t s);
 
 // ---- 2-D Cahn-Hilliard explicit term (ch2d.hip, and fused into k_onepass_t) ----
 // R = C + dt_k * Lap_h(C^3 - C) at one point, from the point's C and the
@@ -453,10 +458,6 @@ hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *se
                           bool words_clear = false);  // words_clear: the status words are zero already
 
 // ---- streaming sweeps (stream.hip) ----
-// p32, p64: 4 doubles per segment; depth[0..2] (device): the two depths and
-// the corrections' (32-row segments).
-hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
-                              double *p64, int64_t *depth, hipStream_t s);
 int stream_tile_width(int64_t batch, int cus);
 // Tile t of cw <= 64 systems starts at F + t * tsf and X + t * tsx.
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,

@@ -186,27 +186,6 @@ __global__ void k_eta_final(const unsigned long long *__restrict__ acc,
     if (tol > 0.0 && !(e <= tol)) atomicOr(err, 2u);
 }
 
-// ||A||_inf = max_i sum_k |A_ik| over the (zero-padded) diagonals.
-__global__ __launch_bounds__(256) void k_anorm(const double *__restrict__ diag, int64_t n,
-                                               double *__restrict__ out, unsigned int *__restrict__ err)
-{
-    if (threadIdx.x == 0) *err = 0u;  // the new handle's status word
-    __shared__ double red[256];
-    double m = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) {
-        const double sum = fabs(diag[i]) + fabs(diag[n + i]) + fabs(diag[2 * n + i]) +
-                           fabs(diag[3 * n + i]) + fabs(diag[4 * n + i]);
-        m = fmax(m, sum);
-    }
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = red[0];
-}
-
 }  // namespace
 
 hipError_t launch_residual(const double *d_diag, int64_t n, const void *f, bool f32, int64_t ldf,
@@ -252,12 +231,6 @@ hipError_t launch_eta(const double *d_diag, const double *d_anorm, int64_t n, co
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_eta_final, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, s, acc,
                        d_anorm, batch, eta, tol, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_anorm(const double *d_diag, int64_t n, double *d_anorm, unsigned int *d_err, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_anorm, dim3(1), dim3(256), 0, s, d_diag, n, d_anorm, d_err);
     return hipGetLastError();
 }
 

@@ -148,78 +148,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
     }
 }
 
-// The truncation depth of one segment table and its products P_b: D is the
-// smallest depth at which every P_b with a state left to neglect (b + D <
-// nseg - 1) has all entries below kTruncTarget, 0 if that takes more than
-// dmax segments.  One workgroup per table, a thread per segment: latency-
-// bound, so all of a product's factors are fetched before the first is used
-// and the maxima stay in registers until the end (8 us at N = 4096; 100 us
-// with the loads in the loop and a shared maximum per product).
-__global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, int da, double *pa, const SegRec *sb,
-                                                     int nb, int db, double *pb, int64_t *depth)
-{
-    constexpr int M = kStreamMaxDepth;
-    const SegRec *seg = blockIdx.x == 0 ? sa : sb;
-    const int nseg = blockIdx.x == 0 ? na : nb, dmax = blockIdx.x == 0 ? da : db;
-    double *out = blockIdx.x == 0 ? pa : pb;
-    __shared__ double mx[4][M];
-    typedef double D2 __attribute__((ext_vector_type(2)));
-    // f(i, m) for i = 1 .. M: m the product of the i segments after b
-    auto products = [&](int b, auto f) {
-        D2 t[M][2];
-#pragma unroll
-        for (int i = 0; i < M; i++) {
-            const D2 *p = (const D2 *)seg[b + 1 + i < nseg ? b + 1 + i : nseg - 1].tb;
-            t[i][0] = p[0];
-            t[i][1] = p[1];
-        }
-        double m[4] = {1.0, 0.0, 0.0, 1.0};
-#pragma unroll
-        for (int i = 0; i < M; i++) {
-            const double n0 = fma(m[2], t[i][0].y, m[0] * t[i][0].x), n1 = fma(m[3], t[i][0].y, m[1] * t[i][0].x);
-            const double n2 = fma(m[2], t[i][1].y, m[0] * t[i][1].x), n3 = fma(m[3], t[i][1].y, m[1] * t[i][1].x);
-            m[0] = n0;
-            m[1] = n1;
-            m[2] = n2;
-            m[3] = n3;
-            f(i + 1, m);
-        }
-    };
-    double top[M];
-#pragma unroll
-    for (int i = 0; i < M; i++) top[i] = 0.0;
-    for (int b = threadIdx.x; b < nseg - 1; b += 256)
-        products(b, [&](int i, const double(&m)[4]) {
-            if (b + i < nseg - 1)
-#pragma unroll
-                for (int k = 0; k < 4; k++) top[i - 1] = nan_max(top[i - 1], fabs(m[k]));
-        });
-#pragma unroll
-    for (int i = 0; i < M; i++) {
-        for (int d = 32; d > 0; d >>= 1) top[i] = nan_max(top[i], __shfl_xor(top[i], d, 64));
-        mx[threadIdx.x / 64][i] = top[i];
-    }
-    __syncthreads();
-    int D = 0, Df = 0;
-#pragma unroll
-    for (int i = M; i >= 1; i--) {
-        const double v = nan_max(nan_max(mx[0][i - 1], mx[1][i - 1]), nan_max(mx[2][i - 1], mx[3][i - 1]));
-        if (i <= dmax && v <= kTruncTarget) D = i;
-        if (i <= kStreamDepthFix && v <= kTruncFix) Df = i;
-    }
-    if (threadIdx.x == 0) {
-        depth[blockIdx.x] = D;
-        if (blockIdx.x == 0) depth[2] = Df;
-    }
-    if (D == 0) return;
-    for (int b = threadIdx.x; b < nseg; b += 256)
-        products(b, [&](int i, const double(&m)[4]) {
-            if (i == D)
-#pragma unroll
-                for (int k = 0; k < 4; k++) out[4 * (int64_t)b + k] = b + D < nseg - 1 ? m[k] : 0.0;
-        });
-}
-
 // Whole rows on 128-byte lines.
 inline bool on_lines(const void *p, int64_t pitch) { return (uintptr_t)p % 128 == 0 && pitch % 128 == 0; }
 
@@ -235,14 +163,6 @@ hipError_t launch_k(const StreamPlan &p, int64_t n, const void *F, int64_t ldf, 
 }
 
 }  // namespace
-
-hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
-                              double *p64, int64_t *depth, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_stream_prep, dim3(2), dim3(256), 0, s, seg32, (int)n32, kStreamDepth32, p32, seg64, (int)n64,
-                       kStreamDepth64, p64, depth);
-    return hipGetLastError();
-}
 
 // Systems per tile: the width with the least work in a compute unit's turns
 // (tiles are dealt whole; the rate of a compute unit, not of the memory,

@@ -25,7 +25,6 @@
 namespace pent {
 namespace {
 
-constexpr int kTileSeg = 64;  // segments per system (= lanes of the scan wave)
 constexpr int kTileW = 8;     // systems per workgroup
 constexpr int kTileThreads = kTileSeg * kTileW;
 constexpr int kFence = 8;     // rows between scheduling fences (bounds record lookahead)
@@ -223,73 +222,6 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(const double *__restrict_
     }
 }
 
-// Records in the LDS image layout: out[comp][k][s] = component comp of row
-// s*K + k (comp: ra, ap, bp, gm, dl).
-template <int K>
-__global__ void k_tile_recs(const FwdRec *__restrict__ fwd, const BwdRec *__restrict__ bwd,
-                            double *__restrict__ out)
-{
-    constexpr int C = kTileSeg * K;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 5 * C) return;
-    const int comp = i / C, rem = i % C, k = rem / kTileSeg, sg = rem % kTileSeg;
-    const int row = sg * K + k;
-    double v;
-    switch (comp) {
-    case 0: v = fwd[row].ra; break;
-    case 1: v = fwd[row].ap; break;
-    case 2: v = fwd[row].bp; break;
-    case 3: v = bwd[row].gm; break;
-    default: v = bwd[row].dl; break;
-    }
-    out[i] = v;
-}
-
-// Scan matrices from the per-segment transfer matrices (one lane per
-// segment, 64 segments).  p[l] = Tf_s Tf_{s-1} ... Tf_{max(0, s-2^l+1)},
-// q[l] = Tb_s Tb_{s+1} ... Tb_{min(63, s+2^l-1)}; matrices column-major.
-__device__ __forceinline__ void mul2(const double *A, const double *B, double *C)
-{
-    // C = A * B, column-major 2x2
-    const double c0 = A[0] * B[0] + A[2] * B[1];
-    const double c1 = A[1] * B[0] + A[3] * B[1];
-    const double c2 = A[0] * B[2] + A[2] * B[3];
-    const double c3 = A[1] * B[2] + A[3] * B[3];
-    C[0] = c0; C[1] = c1; C[2] = c2; C[3] = c3;
-}
-
-__global__ __launch_bounds__(kTileSeg) void k_scan_prep(const SegRec *__restrict__ seg, int64_t nseg, ScanRec *__restrict__ out)
-{
-    const int s = threadIdx.x;
-    if (s >= kTileSeg) return;
-    // the segments' matrices in LDS first: the products below are a chain of
-    // up to 32 of them per lane (from memory 22 us at 64 segments, so 10)
-    __shared__ double tf[kTileSeg][4], tb[kTileSeg][4];
-    for (int k = 0; k < 4; k++) {
-        const double one = k % 3 == 0 ? 1.0 : 0.0;  // past the matrix: the identity
-        tf[s][k] = s < nseg ? seg[s].tf[k] : one;
-        tb[s][k] = s < nseg ? seg[s].tb[k] : one;
-    }
-    __syncthreads();
-    ScanRec r;
-    for (int l = 0; l < 6; l++) {
-        const int len = 1 << l;
-        double M[4] = {1.0, 0.0, 0.0, 1.0};
-        for (int t = s; t >= 0 && t > s - len; t--) {  // M = M * Tf_t, t descending
-            mul2(M, tf[t], M);
-        }
-        for (int k = 0; k < 4; k++) r.p[l][k] = M[k];
-        double Q[4] = {1.0, 0.0, 0.0, 1.0};
-        for (int t = s; t < kTileSeg && t < s + len; t++) {  // Q = Q * Tb_t, t ascending
-            mul2(Q, tb[t], Q);
-        }
-        for (int k = 0; k < 4; k++) r.q[l][k] = Q[k];
-    }
-    for (int k = 0; k < 4; k++) r.cg[k] = (s < nseg) ? seg[s].cg[k] : 0.0;
-    for (int k = 0; k < 4; k++) r.pad[k] = 0.0;
-    out[s] = r;
-}
-
 }  // namespace
 
 int tile_rows_for(int64_t n)
@@ -300,27 +232,7 @@ int tile_rows_for(int64_t n)
     return 0;
 }
 
-hipError_t launch_scan_prep(const SegRec *seg, int64_t nseg, ScanRec *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_scan_prep, dim3(1), dim3(kTileSeg), 0, s, seg, nseg, out);
-    return hipGetLastError();
-}
-
 size_t tile_recs_doubles(int rows) { return (size_t)5 * kTileSeg * rows; }
-
-hipError_t launch_tile_recs(const FwdRec *fwd, const BwdRec *bwd, int rows, double *out,
-                            hipStream_t s)
-{
-    const int total = 5 * kTileSeg * rows;
-    const dim3 grid((total + 255) / 256), block(256);
-    switch (rows) {
-    case 16: hipLaunchKernelGGL(k_tile_recs<16>, grid, block, 0, s, fwd, bwd, out); break;
-    case 32: hipLaunchKernelGGL(k_tile_recs<32>, grid, block, 0, s, fwd, bwd, out); break;
-    case 64: hipLaunchKernelGGL(k_tile_recs<64>, grid, block, 0, s, fwd, bwd, out); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
 
 namespace {
 template <int K, typename TI>
