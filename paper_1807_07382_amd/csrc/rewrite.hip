@@ -15,7 +15,8 @@
 // outstanding, less than a row's latency needs.  gamma, delta and g go to
 // memory (gamma and delta to the workspace, g over f) and come back to the
 // same wave, except those of each wave's last block, which stay in its
-// registers: 104 B of HBM per unknown, 48 less for the last 112 rows.
+// registers, and gamma and delta of the one before, which stay in LDS: 104 B of
+// HBM per unknown, 48 less for the last 112 rows and 32 less for the 112 above.
 #include "stream.h"
 
 namespace pent {
@@ -23,8 +24,8 @@ namespace {
 
 // 14 rows of six values fit the 256 registers of two waves per SIMD; with 16
 // a few spill, and 12 waves of 8 rows spend more on the handovers
-// (n = 1024, us, 14 x 8 / 16 x 8 / 8 x 12: 500 systems 136 / 140 / 138,
-// 16384 245 / 249 / 252, 65536 1134 / 1128 / 1154; n = 8192 x 2000
+// (before the blocks in LDS, n = 1024, us, 14 x 8 / 16 x 8 / 8 x 12: 500 systems
+// 136 / 140 / 138, 16384 245 / 249 / 252, 65536 1134 / 1128 / 1154; n = 8192 x 2000
 // 1069 / 1143 / 1079).
 constexpr int kRows = 14;  // rows of a block
 constexpr int kWaves = 8;  // waves of a workgroup
@@ -116,6 +117,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 {
     __shared__ double carries[2][6][64];  // the carried values of the last finished block
     __shared__ unsigned int dones[2];     // blocks finished
+    __shared__ double held[kWaves][kRows][2][64];  // gamma and delta of a wave's last block but one
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t tiles = (batch + 63) / 64;
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
         GIn A = A_ + j0, B = B_ + j0, C = C_ + j0, D = D_ + j0, E = E_ + j0;
         GOut F = F_ + j0;
         // gamma and delta of a tile lie together, a row of each in turn (rows
-        // as far apart as F's: 131072 systems 2341 us; so 2280)
+        // as far apart as F's cost 131072 systems 3%)
         const int64_t lw = batch - j0 < 64 ? batch - j0 : 64;
         GOut W = W_ + 2 * (int64_t)n * j0;
         double(&carry)[6][64] = carries[turn & 1];
@@ -187,18 +189,31 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
             carry[4][lane] = s.g2;
             carry[5][lane] = s.g1;
             st::lds_post(&done, base + (unsigned int)b + 1);
-            if (t < mine) {  // the last block stays in the registers
-                if (active) {
-                    const unsigned int lo = local(off);
-                    GOut pw = W + (int64_t)i0 * 2 * lw, pf = F + (int64_t)i0 * ld;
+            if (t < mine) {  // the last block stays in the registers, the one before in LDS
+                if (t == mine - 1) {
 #pragma unroll
                     for (int k = 0; k < kRows; k++) {
-                        __builtin_nontemporal_store(q.a[k], at(pw, lo));
-                        pw = fresh(pw + lw);
-                        __builtin_nontemporal_store(q.b[k], at(pw, lo));
-                        pw = fresh(pw + lw);
+                        held[w][k][0][lane] = q.a[k];
+                        held[w][k][1][lane] = q.b[k];
+                    }
+                }
+                if (active) {
+                    const unsigned int lo = local(off);
+                    GOut pf = F + (int64_t)i0 * ld;
+#pragma unroll
+                    for (int k = 0; k < kRows; k++) {
                         *at(pf, lo) = q.f[k];
                         pf = fresh(pf + ld);
+                    }
+                    if (t < mine - 1) {
+                        GOut pw = W + (int64_t)i0 * 2 * lw;
+#pragma unroll
+                        for (int k = 0; k < kRows; k++) {
+                            __builtin_nontemporal_store(q.a[k], at(pw, lo));
+                            pw = fresh(pw + lw);
+                            __builtin_nontemporal_store(q.b[k], at(pw, lo));
+                            pw = fresh(pw + lw);
+                        }
                     }
                 }
             } else if (last < kRows - 1) {  // rows past the end
@@ -214,15 +229,27 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
             const int b = first + t * kWaves, i0 = b * kRows, last = n - 1 - i0, after = nblk - 1 - b;
             if (t < mine) {
                 const unsigned int lo = local(off);
-                GIn pw = W + (int64_t)i0 * 2 * lw, pf = F + (int64_t)i0 * ld;
+                GIn pf = F + (int64_t)i0 * ld;
 #pragma unroll
                 for (int k = 0; k < kRows; k++) {
-                    q.a[k] = __builtin_nontemporal_load(at(pw, lo));
-                    pw = fresh(pw + lw);
-                    q.b[k] = __builtin_nontemporal_load(at(pw, lo));
-                    pw = fresh(pw + lw);
                     q.f[k] = *at(pf, lo);
                     pf = fresh(pf + ld);
+                }
+                if (t < mine - 1) {
+                    GIn pw = W + (int64_t)i0 * 2 * lw;
+#pragma unroll
+                    for (int k = 0; k < kRows; k++) {
+                        q.a[k] = __builtin_nontemporal_load(at(pw, lo));
+                        pw = fresh(pw + lw);
+                        q.b[k] = __builtin_nontemporal_load(at(pw, lo));
+                        pw = fresh(pw + lw);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kRows; k++) {
+                        q.a[k] = held[w][k][0][lane];
+                        q.b[k] = held[w][k][1][lane];
+                    }
                 }
             }
             const unsigned int up = base + (unsigned int)(nblk + after);
@@ -277,10 +304,11 @@ hipError_t launch_rewrite(const double *a, const double *b, const double *c, con
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     // one workgroup per compute unit: its waves take all the registers
-    // (n = 1024, us, one lane per system in workgroups of four waves / now:
-    // 500 systems 604 / 136, 16384 687 / 245, 65536 1178 / 1134, 131072
-    // 2659 / 2280, 6.0 TB/s; n = 8192 x 2000 4671 / 1069, n = 64 x 100000
-    // 115 / 77)
+    // (n = 1024, us, one lane per system in workgroups of four waves / this
+    // without the blocks in LDS / now: 500 systems 604 / 136 / 132, 16384 687 / 245 /
+    // 237, 65536 1178 / 1132 / 1096, 131072 2659 / 2277 / 2180, 5.9 TB/s; n = 8192 x
+    // 2000 4671 / 1072 / 1062, n = 203 x 131072 450 / 338 / 290, n = 64 x 100000 115 / 77 /
+    // 77)
     int dev = 0, cus = 0;
     if ((err = hipGetDevice(&dev)) != hipSuccess) return err;
     if ((err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return err;
