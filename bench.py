@@ -51,7 +51,7 @@ SCHEDULE_NAMES = {1: "lane", 2: "partitioned", 3: "tile", 4: "onepass"}
 # kernel source files of each schedule (the counters go stale when one changes);
 # the single pass also runs as streaming sweeps
 STREAM_SOURCES = ("stream.hip", "stream.h", "lookback.h")
-SCHEDULE_SOURCES = {"lane": ("sweep.hip",), "partitioned": ("sweep.hip",), "tile": ("tile.hip", "resident.hip", "stream.h"),
+SCHEDULE_SOURCES = {"lane": ("sweep.hip",), "partitioned": ("sweep.hip",), "tile": ("resident.hip", "stream.h"),
                     "onepass": ("onepass.hip",) + STREAM_SOURCES}
 
 

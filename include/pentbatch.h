@@ -420,12 +420,12 @@ int64_t pent_size(pent_handle h); /* n, or -1 for a bad handle */
  *   kind 2: partitioned: seg_rows consecutive rows per lane, several lanes
  *           per system, with a reduced interface recurrence between the
  *           segments (seg_rows in {16, 32, 64});
- *   kind 3: resident tile: 8 systems per workgroup held whole in registers
- *           (n <= 4096), one read of f and one write of x; seg_rows ignored.
- *           For larger n a solve falls back to kind 2.  For n <= 2048 and
- *           most batches that fit the device in one turn the workgroup holds
- *           16 or 32 systems instead (a form of this kind; the automatic
- *           schedule takes it there whatever n * batch is).
+ *   kind 3: resident tile: whole systems held in the registers of one
+ *           workgroup, 4, 16 or 32 of them by n and batch (n <= 4096), one
+ *           read of f and one write of x; seg_rows ignored.  For larger n a
+ *           solve falls back to kind 2.  (The automatic schedule also takes
+ *           this form beyond n * batch = 8M while the batch fits the device in
+ *           one turn, and for a few hundred systems up to n = 6656.)
  *   kind 4: single pass: the partitioned sweep of kind 2 in one kernel, each
  *           (64-system, seg_rows-row) block held in registers from load to
  *           store, the segment interface states exchanged between blocks

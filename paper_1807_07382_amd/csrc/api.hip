@@ -119,8 +119,6 @@ pent_plan *new_plan(int64_t n, int *st)
     p->sched_kind = 0;
     p->sched_seg = 0;
     p->refine_tol = 0.0;
-    p->d_scan = nullptr;
-    p->d_trec = nullptr;
     p->d_trunc = nullptr;
     p->strm_depth[0] = p->strm_depth[1] = p->strm_depth[2] = 0;
     p->cus = 0;
@@ -129,7 +127,6 @@ pent_plan *new_plan(int64_t n, int *st)
     p->t_cap = 0;
     p->tst_cap = 0;
     p->d_pool = nullptr;
-    const int rows = tile_rows_for(n);
     const int64_t nseg = (n + 31) / 32 + (n + 63) / 64;
     size_t at = 0;
     auto room = [&](size_t bytes) {
@@ -141,10 +138,8 @@ pent_plan *new_plan(int64_t n, int *st)
                  o_bad = room(4 * sizeof(int64_t)),
                  o_fwd = room(sizeof(FwdRec) * p->npad), o_bwd = room(sizeof(BwdRec) * p->npad),
                  o_s64 = room(sizeof(SegRec) * seg_padded(n, 64)), o_s32 = room(sizeof(SegRec) * seg_padded(n, 32)),
-                 o_s16 = room(rows == 16 ? sizeof(SegRec) * seg_padded(n, 16) : 0),
-                 o_trunc = room(n <= kStreamMaxRows ? sizeof(double) * 4 * nseg : 0),
-                 o_scan = room(rows ? sizeof(ScanRec) * 64 : 0),
-                 o_trec = room(rows ? sizeof(double) * tile_recs_doubles(rows) : 0);
+                 o_s16 = room(n <= 1024 ? sizeof(SegRec) * seg_padded(n, 16) : 0),
+                 o_trunc = room(n <= kStreamMaxRows ? sizeof(double) * 4 * nseg : 0);
     hipError_t e = hipGetDevice(&p->device);
     if (e == hipSuccess)
         e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
@@ -170,12 +165,8 @@ pent_plan *new_plan(int64_t n, int *st)
     };
     table(64, o_s64);
     table(32, o_s32);
-    if (rows == 16) table(16, o_s16);
+    if (n <= 1024) table(16, o_s16);
     if (n <= kStreamMaxRows) p->d_trunc = (double *)(d + o_trunc);
-    if (rows) {
-        p->d_scan = (ScanRec *)(d + o_scan);
-        p->d_trec = (double *)(d + o_trec);
-    }
     *st = PENT_OK;
     return p;
 }
@@ -233,27 +224,25 @@ int64_t factor_host_ieee(int64_t n, const double *dg, double *fac)
 
 // Factor the diagonals already in p->d_diag (factored: the factors are there
 // too) and build the tables of the automatic schedules: segment constants for
-// 64- and 32-row segments, the truncation of the streaming sweeps, and the
-// resident tile's tables where n allows it, all on the null stream, then
-// synchronise once to read the pivot check.  Later solves with the automatic
-// schedule then allocate nothing for these tables.  Consumes p on error.
+// 64- and 32-row (up to 1024 rows also 16-row) segments and the truncation of
+// the streaming sweeps, all on the null stream, then synchronise once to read
+// the pivot check.  Later solves with the automatic schedule then allocate
+// nothing for these tables.  Consumes p on error.
 pent_handle finish_factor(pent_plan *p, bool factored = false)
 {
     int64_t *const d_bad = p->d_bad;
     int64_t bad[4] = {-1, 0, 0, 0};  // the pivot check, then the streaming sweeps' depths
-    const int rows = tile_rows_for(p->n);
     SegRec *s64 = p->seg[seg_slot(64)].d_seg, *s32 = p->seg[seg_slot(32)].d_seg,
-           *s16 = rows == 16 ? p->seg[seg_slot(16)].d_seg : nullptr;
+           *s16 = p->n <= 1024 ? p->seg[seg_slot(16)].d_seg : nullptr;
     const int64_t n32 = (p->n + 31) / 32, n64 = (p->n + 63) / 64;
     const bool strm = p->d_trunc != nullptr;
     hipError_t e = hipSuccess;
     if (!factored) e = launch_factor(p->d_diag, p->n, p->d_fac, d_bad, 0);
     if (e == hipSuccess)
-        e = launch_records(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, rows, p->d_trec, p->d_anorm, p->d_err, 0);
+        e = launch_records(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, p->d_anorm, p->d_err, 0);
     if (e == hipSuccess) e = launch_seg_prep_all(p->d_fwd, p->d_bwd, p->n, s64, s32, s16, 0);
-    if (e == hipSuccess)
-        e = launch_seg_use(s32, n32, s64, n64, p->d_trunc, d_bad + 1, rows ? p->seg[seg_slot(rows)].d_seg : nullptr,
-                           rows ? (p->n + rows - 1) / rows : 0, p->d_scan, 0);
+    if (e == hipSuccess && strm)
+        e = launch_stream_prep(s32, n32, p->d_trunc, s64, n64, p->d_trunc + 4 * n32, d_bad + 1, 0);
     if (e == hipSuccess) {
         // (a copy waits for the null stream's work; without one, wait for it)
         const size_t first = factored ? 1 : 0, count = strm ? 4 : 1;
@@ -371,7 +360,7 @@ void choose_schedule(const pent_plan *p, int64_t batch, int *kind, int *seg_rows
     if (p->sched_kind != 0) {
         *kind = p->sched_kind;
         *seg_rows = p->sched_seg;
-    } else if (tile_rows_for(p->n) > 0 && p->n * batch <= (int64_t)8 << 20) {
+    } else if (p->n <= kResidentRows && p->n * batch <= (int64_t)8 << 20) {
         *kind = 3;
         *seg_rows = 0;
     } else if (p->onepass_cap[1] > 0 && p->n >= 1024) {
@@ -381,7 +370,7 @@ void choose_schedule(const pent_plan *p, int64_t batch, int *kind, int *seg_rows
         *kind = 2;
         *seg_rows = p->n <= 2048 ? 32 : 64;
     }
-    if (*kind == 3 && tile_rows_for(p->n) == 0) {
+    if (*kind == 3 && p->n > kResidentRows) {
         *kind = 2;
         *seg_rows = 64;
     }
@@ -449,9 +438,8 @@ bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
 // form where that stands in for it below n = 1024) they win from about 5000
 // systems at every n (us, streaming / before: n = 2048 58 / 56 at 5003, 57 /
 // 81 at 8192; n = 4096 110 / 112 and 110 / 159; n = 8192 230 / 224 and 214 /
-// 290).  In the place of the tiles of eight systems (n above 2048, where the
-// wider resident tiles end) from half as many, which that schedule's own limit
-// on n * batch leaves little of (n = 4096 x 1024 90 / 42).  A
+// 290).  In the place of the resident tiles (n above 2048, past a turn of theirs)
+// from half as many (n = 2500 x 4000 54 / 72, n = 4096 x 2560 52 / 75).  A
 // schedule forced to 64-row single pass streams by the same rule; any other
 // forced schedule is run as asked.
 bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, StreamPlan *p)
@@ -491,39 +479,38 @@ bool t_resident_route(const pent_plan *h, int64_t batch)
     return h->n > 96 && h->n <= 1024 && (h->n <= 512 || h->n > 640);
 }
 
-// Tile width of the resident form for n <= 2048 rows and this many systems.
-// Tiles of 16 systems spread over the most compute units, and more of them run
-// apart in their phases; in between, from 5000 systems, there are enough of 32,
-// whose rows share fewer lines where they are not aligned (us, 16 / 32: 256 x 5003
-// 11.3 / 9.9, 1000 x 5003 27.9 / 25.6, but 1000 x 2500 17.1 / 22.5, 1000 x 65536
-// 240 / 258).  A single wave has its 32 systems at any batch (periodic, 130 x
-// 65536 40 / 37).
-int resident_width(int64_t n, int64_t batch)
+// Tile width of the resident form for n rows and this many systems.  Tiles of
+// four systems spread over the most compute units, and their waves, at most
+// two to a SIMD, have the shortest sweeps: up to about four tiles a compute unit
+// (us, 4 / 16 systems: 1000 x 400 8.9 / 10.5, x 1024 10.2 / 11.3, x 2000 16.8 /
+// 15.4; 2048 x 400 12.2 / 18.3, x 1800 24 / 27, x 3000 - / 30), and they are all
+// that holds more than 2048 rows.  In between, from 5000 systems, there are
+// enough tiles of 32, whose rows share fewer lines where they are not aligned
+// (16 / 32: 256 x 5003 11.3 / 9.9, 1000 x 5003 27.9 / 25.6, but 1000 x 2500 17.1 /
+// 22.5, 1000 x 65536 240 / 258).  A single wave has its 32 systems at any batch
+// (periodic, 130 x 65536 40 / 37).
+int resident_width(int64_t n, int64_t batch, int cus)
 {
+    if (n > 2048 || (n > 512 && batch <= (n > 1024 ? 7 : 4) * (int64_t)cus)) return 4;
     return n <= 1024 && batch >= 5000 && (batch <= 16384 || n <= 128) ? 32 : 16;
 }
 
-// Tile width of the resident form for a solve with h under the automatic
-// schedule or the resident-tile one (kind 3), or 0.  Past one turn of the device
-// (of a workgroup per compute unit above 1024 rows, two of half the waves below)
-// walking tiles are better (us, resident / before: 1000 x 6000 27 / 32, x 10000 42 /
-// 37, x 131072 453 / 411; 1537 x 4096 30 / 45, x 5008 48 / 46; 2048 x 4096 35 / 58, x
-// 5008 60 / 49), but not what stands in for them where the chain is too deep
-// below 1024 rows (partitions; sigma = 3000: 1000 x 10000 42 / 77, x 131072 453 /
-// 637).  The tiles of eight systems (tile.hip) spread further still, and keep the
-// long systems of small batches (1000 x 500 11.2 / 13.4, x 1000 14.2 / 13.3, x
-// 1500 15.7 / 17.3; 2048 x 500 23 / 20, x 1000 24 / 20, x 1500 27 / 31; 256 x 256 7.5 /
-// 8.7).
-int resident_route(const pent_plan *h, int64_t ldf, int64_t ldx, int64_t batch)
+// Whether a solve with h that io_schedule gave `kind` runs in resident tiles
+// ahead of the other schedules: always where it is a turn or so of the device
+// (us, resident / before: 1000 x 6000 27 / 32, x 10000 42 / 37, x 131072 453 / 411;
+// 1537 x 4096 30 / 45, x 5008 48 / 46; 2048 x 4096 35 / 58, x 5008 60 / 49; 3384 x 154
+// 16 / 37, x 2000 45 / 55; 4096 x 64 18 / 37, x 2300 70 / 58; 5000 x 200 28 / 36, x
+// 300 34 / 36; 6000 x 200 35 / 36), and under 1024 rows also where the chain is too
+// deep for walking tiles (sigma = 3000: 1000 x 10000 42 / 77, x 131072 453 / 637, by
+// partitions).
+bool resident_route(const pent_plan *h, int kind, int64_t batch)
 {
-    if (h->n > 2048 || (h->sched_kind != 0 && h->sched_kind != 3) || onepass_waves_override()) return 0;
-    if (ldf > kResidentLd || ldx > kResidentLd || (batch + 15) / 16 > INT32_MAX / 2) return 0;
-    if (h->n > 768 && batch <= 1100 && (h->n > 1024 || batch > 640)) return 0;
+    if ((h->sched_kind != 0 && (h->sched_kind != 3 || kind != 3)) || onepass_waves_override()) return false;
+    if (h->n > kResidentRows) return h->n <= 6656 && h->n * batch <= 1200000;
+    if (batch <= (h->n <= 1024 ? 24 : h->n <= 2048 ? 16 : 8) * (int64_t)h->cus) return true;
     StreamPlan sp;
-    if (batch > (h->n > 1024 ? 16 : 24) * (int64_t)h->cus &&
-        !(h->sched_kind == 0 && h->n < 1024 && !stream_plan(h, 32, &sp) && !stream_plan(h, 64, &sp)))
-        return 0;
-    return resident_width(h->n, batch);
+    return h->sched_kind == 0 && h->n < 1024 && (batch + 15) / 16 <= INT32_MAX / 2 && !stream_plan(h, 32, &sp) &&
+           !stream_plan(h, 64, &sp);
 }
 
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
@@ -535,18 +522,16 @@ int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int6
     int kind, seg_rows, st;
     io_schedule(h, batch, inplace64, &kind, &seg_rows);
     StreamPlan sp;
-    if (const int width = resident_route(h, ldf, ldx, batch))
-        return hip_status(launch_resident(h->d_fwd, h->d_bwd, h->seg[seg_slot(32)].d_seg, h->seg[seg_slot(64)].d_seg, h->n,
-                                          width, f, f32, ldf, x, ldx, batch, s));
-    if (stream_route(h, kind, seg_rows, batch, &sp)) {
+    const bool resident = resident_route(h, kind, batch);
+    if (!resident && stream_route(h, kind, seg_rows, batch, &sp)) {
         const int cw = stream_tile_width(batch, h->cus);
         return hip_status(launch_stream(sp, h->n, f, f32, ldf, cw, x, ldx, cw, batch, cw, h->d_err, s));
     }
     if (kind == 1)
         return hip_status(launch_lane_sweep(h->d_fwd, h->d_bwd, h->n, x, batch, ldx, seg_rows, s));
-    if (kind == 3) {
-        return hip_status(launch_tile_sweep_io(h->d_trec, h->d_scan, h->n, tile_rows_for(h->n), f, f32, ldf, x, ldx, batch, s));
-    }
+    if (resident || kind == 3)
+        return hip_status(launch_resident(h->d_fwd, h->d_bwd, h->seg[seg_slot(32)].d_seg, h->seg[seg_slot(64)].d_seg, h->n,
+                                          resident_width(h->n, batch, h->cus), f, f32, ldf, x, ldx, batch, s));
     const SegRec *seg = seg_cache(h, seg_rows, &st);
     if (!seg) return st;
     if (kind == 4)
@@ -564,7 +549,7 @@ int solve_io_scratch(pent_plan *h, const double *f, int64_t ldf, double *x, int6
     int kind, seg_rows;
     io_schedule(h, batch, (const void *)f == (const void *)x && ldf == ldx, &kind, &seg_rows);
     StreamPlan sp;
-    const bool scratch = !resident_route(h, ldf, ldx, batch) && !stream_route(h, kind, seg_rows, batch, &sp);
+    const bool scratch = !resident_route(h, kind, batch) && !stream_route(h, kind, seg_rows, batch, &sp);
     const size_t bytes = scratch ? summ_bytes(h, kind, seg_rows, batch) : 0;
     void *summ = nullptr;
     if (bytes) {
@@ -847,17 +832,17 @@ constexpr int64_t kCycStreamBatch = 8192;
 // and where the walking tiles' chain is deep (sigma = 100: 500 x 16384 40 / 51 and
 // 37 / 53; 573 x 131072 305 / 330 and 337 / 347; 1026 x 65536 258 / 266 and 265 / 289,
 // but x 16384 79 / 73; at sigma = 1 x 65536 258 / 227).
-int cyc_resident_width(const pent_cyclic_s *c, int64_t ldf, int64_t ldx, int64_t batch)
+int cyc_resident_width(const pent_cyclic_s *c, int64_t batch)
 {
     const pent_plan *E = c->E;
     if (E->n > 2048 || c->kind != 0 || onepass_waves_override()) return 0;
-    if (ldf > kResidentLd || ldx > kResidentLd || (batch + 15) / 16 > INT32_MAX / 2) return 0;
+    if ((batch + 15) / 16 > INT32_MAX / 2) return 0;
     if (batch > (E->n > 1024 ? 16 : 32) * (int64_t)E->cus && E->n > 128) {
         StreamPlan sp;
         const bool deep = !stream_plan(E, 32, &sp) || sp.depth > 6;
         if (!deep || E->n > 1024 || (E->n > 640 && batch < 32768)) return 0;
     }
-    return resident_width(E->n, batch);
+    return E->n <= 1024 && batch >= 5000 && (batch <= 16384 || E->n <= 128) ? 32 : 16;  // as resident_width
 }
 
 int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
@@ -865,7 +850,7 @@ int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double 
 {
     int st;
     StreamPlan sp;
-    if (const int width = cyc_resident_width(c, ldf, ldx, batch)) {
+    if (const int width = cyc_resident_width(c, batch)) {
         const pent_plan *E = c->E;
         return hip_status(launch_resident_cyclic(E->d_fwd, E->d_bwd, E->seg[seg_slot(32)].d_seg, E->seg[seg_slot(64)].d_seg,
                                                  c->d_cd, c->d_Z, c->d_aux, E->n, width, cn, F, ldf, X, ldx, batch, s,
@@ -1200,11 +1185,7 @@ int noalloc_scratch(void **out)
 bool tables_ready(pent_plan *p, int kind, int seg_rows)
 {
     std::lock_guard<std::mutex> lk(p->mu);
-    if (kind == 1) return true;
-    if (kind == 3) {
-        const int rows = tile_rows_for(p->n);
-        return p->d_scan != nullptr && rows > 0;
-    }
+    if (kind == 1 || kind == 3) return true;
     return p->seg[seg_slot(seg_rows)].d_seg != nullptr;
 }
 
@@ -1539,7 +1520,7 @@ int pent_autotune(pent_handle h, int64_t batch, int *kind_out, int *seg_rows_out
     double best = 1e300;
     for (const auto &c : cands) {
         if (st != PENT_OK) break;
-        if (c[0] == 3 && tile_rows_for(h->n) == 0) continue;
+        if (c[0] == 3 && h->n > kResidentRows) continue;
         if (c[0] == 2 && (h->n + c[1] - 1) / c[1] > 65535) continue;
         h->sched_kind = c[0];
         h->sched_seg = c[1];
@@ -1759,7 +1740,7 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
     int ykind, yseg;
     io_schedule(hy, ybatch, false, &ykind, &yseg);
     StreamPlan ysp;
-    const bool ystream = resident_route(hy, ybatch, ybatch, ybatch) ||
+    const bool ystream = resident_route(hy, ykind, ybatch) ||
                          stream_route(hy, ykind, yseg, ybatch, &ysp);  // one of the forms without scratch
     const size_t ybytes = ystream ? 0 : summ_bytes(hy, ykind, yseg, ybatch);
     void *ybuf = nullptr;

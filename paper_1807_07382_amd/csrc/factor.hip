@@ -239,17 +239,15 @@ __device__ __forceinline__ void anorm_max(const double *__restrict__ diag, int64
     if (threadIdx.x == 0) out[0] = red[0];
 }
 
-// Sweep records from the factors (row-parallel), and where tile_rows > 0 the
-// image of those of the resident tile's LDS, tile[comp][k][s] = component comp
-// (ra, ap, bp, gm, dl) of row s * tile_rows + k.  Block 0 takes the norm, and
-// zeroes the new handle's status word.  Latency-bound like all that a handle is
-// made from, so what can stand side by side shares a launch: three (7, 7 and 11
-// us at n = 4096) where six of 7 to 10 us took their turns (pent_factor 109 us,
-// now 81; with one solve of 64 systems 173 and 127).
+// Sweep records from the factors (row-parallel).  Block 0 takes the norm, and
+// zeroes the new handle's status word.  All that a handle is made from is
+// latency, so what can stand side by side shares a launch (a solve's handle at
+// n = 4096 takes three launches of 7 us; six took their turns at first:
+// pent_factor 109 us, now 82).
 __global__ __launch_bounds__(256) void k_records(const double *__restrict__ diag, const double *__restrict__ fac,
                                                  int64_t n, int64_t npad, FwdRec *__restrict__ fwd,
-                                                 BwdRec *__restrict__ bwd, int tile_rows, double *__restrict__ tile,
-                                                 double *__restrict__ anorm, unsigned int *__restrict__ err)
+                                                 BwdRec *__restrict__ bwd, double *__restrict__ anorm,
+                                                 unsigned int *__restrict__ err)
 {
 #pragma clang fp contract(off)
     if (blockIdx.x == 0) {
@@ -273,15 +271,6 @@ __global__ __launch_bounds__(256) void k_records(const double *__restrict__ diag
     }
     fwd[i] = r;
     bwd[i] = q;
-    if (tile_rows > 0 && i < (int64_t)kTileSeg * tile_rows) {
-        const int c = kTileSeg * tile_rows;
-        double *t = tile + i % tile_rows * kTileSeg + i / tile_rows;
-        t[0] = r.ra;
-        t[c] = r.ap;
-        t[2 * c] = r.bp;
-        t[3 * c] = q.gm;
-        t[4 * c] = q.dl;
-    }
 }
 
 // Per-segment transfer matrices of the partitioned sweep.  For segment s
@@ -368,9 +357,13 @@ __global__ __launch_bounds__(64) void k_seg_prep_all(const FwdRec *__restrict__ 
 // bound, so all of a product's factors are fetched before the first is used
 // and the maxima stay in registers until the end (8 us at N = 4096; 100 us
 // with the loads in the loop and a shared maximum per product).
-__device__ __forceinline__ void trunc_tables(const SegRec *seg, int nseg, int dmax, double *out, int64_t *depth, int64_t *fix)
+__global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, int da, double *pa, const SegRec *sb,
+                                                     int nb, int db, double *pb, int64_t *depth)
 {
     constexpr int M = kStreamMaxDepth;
+    const SegRec *seg = blockIdx.x == 0 ? sa : sb;
+    const int nseg = blockIdx.x == 0 ? na : nb, dmax = blockIdx.x == 0 ? da : db;
+    double *out = blockIdx.x == 0 ? pa : pb;
     __shared__ double mx[4][M];
     typedef double D2 __attribute__((ext_vector_type(2)));
     // f(i, m) for i = 1 .. M: m the product of the i segments after b
@@ -417,8 +410,8 @@ __device__ __forceinline__ void trunc_tables(const SegRec *seg, int nseg, int dm
         if (i <= kStreamDepthFix && v <= kTruncFix) Df = i;
     }
     if (threadIdx.x == 0) {
-        *depth = D;
-        if (fix) *fix = Df;
+        depth[blockIdx.x] = D;
+        if (blockIdx.x == 0) depth[2] = Df;
     }
     if (D == 0) return;
     for (int b = threadIdx.x; b < nseg; b += 256)
@@ -427,73 +420,6 @@ __device__ __forceinline__ void trunc_tables(const SegRec *seg, int nseg, int dm
 #pragma unroll
                 for (int k = 0; k < 4; k++) out[4 * (int64_t)b + k] = b + D < nseg - 1 ? m[k] : 0.0;
         });
-}
-
-// Scan matrices from the per-segment transfer matrices (one lane per
-// segment, 64 segments).  p[l] = Tf_s Tf_{s-1} ... Tf_{max(0, s-2^l+1)},
-// q[l] = Tb_s Tb_{s+1} ... Tb_{min(63, s+2^l-1)}; matrices column-major.
-__device__ __forceinline__ void mul2(const double *A, const double *B, double *C)
-{
-    // C = A * B, column-major 2x2
-    const double c0 = A[0] * B[0] + A[2] * B[1];
-    const double c1 = A[1] * B[0] + A[3] * B[1];
-    const double c2 = A[0] * B[2] + A[2] * B[3];
-    const double c3 = A[1] * B[2] + A[3] * B[3];
-    C[0] = c0; C[1] = c1; C[2] = c2; C[3] = c3;
-}
-
-__device__ __forceinline__ void scan_tables(const SegRec *__restrict__ seg, int64_t nseg, ScanRec *__restrict__ out)
-{
-    const int s = threadIdx.x;
-    if (s >= kTileSeg) return;
-    // the segments' matrices in LDS first: the products below are a chain of
-    // up to 32 of them per lane (from memory 22 us at 64 segments, so 10)
-    __shared__ double tf[kTileSeg][4], tb[kTileSeg][4];
-    for (int k = 0; k < 4; k++) {
-        const double one = k % 3 == 0 ? 1.0 : 0.0;  // past the matrix: the identity
-        tf[s][k] = s < nseg ? seg[s].tf[k] : one;
-        tb[s][k] = s < nseg ? seg[s].tb[k] : one;
-    }
-    __syncthreads();
-    ScanRec r;
-    for (int l = 0; l < 6; l++) {
-        const int len = 1 << l;
-        double M[4] = {1.0, 0.0, 0.0, 1.0};
-        for (int t = s; t >= 0 && t > s - len; t--) {  // M = M * Tf_t, t descending
-            mul2(M, tf[t], M);
-        }
-        for (int k = 0; k < 4; k++) r.p[l][k] = M[k];
-        double Q[4] = {1.0, 0.0, 0.0, 1.0};
-        for (int t = s; t < kTileSeg && t < s + len; t++) {  // Q = Q * Tb_t, t ascending
-            mul2(Q, tb[t], Q);
-        }
-        for (int k = 0; k < 4; k++) r.q[l][k] = Q[k];
-    }
-    for (int k = 0; k < 4; k++) r.cg[k] = (s < nseg) ? seg[s].cg[k] : 0.0;
-    for (int k = 0; k < 4; k++) r.pad[k] = 0.0;
-    out[s] = r;
-}
-
-// What follows from the segment tables, side by side: the truncation of the
-// 32- and 64-row streaming sweeps (trunc), the resident tile's scan (scan).
-struct SegUse {
-    const SegRec *s32, *s64;
-    int n32, n64;
-    double *trunc32, *trunc64;  // null: not streamed
-    int64_t *depth;             // of 32 rows, of 64, of a correction
-    const SegRec *tile;         // null: no resident tile
-    int64_t ntile;
-    ScanRec *scan;
-};
-__global__ __launch_bounds__(256) void k_seg_use(SegUse u)
-{
-    if (blockIdx.x == 2) {
-        if (u.tile) scan_tables(u.tile, u.ntile, u.scan);
-    } else if (u.trunc32) {
-        const bool b = blockIdx.x == 1;
-        trunc_tables(b ? u.s64 : u.s32, b ? u.n64 : u.n32, b ? kStreamDepth64 : kStreamDepth32, b ? u.trunc64 : u.trunc32,
-                     u.depth + blockIdx.x, b ? nullptr : u.depth + 2);
-    }
 }
 
 // C = A B for 2x2 column-major matrices (C may be A or B).
@@ -570,21 +496,20 @@ hipError_t launch_factor(const double *d_diag, int64_t n, double *d_fac, int64_t
 }
 
 hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const double *d_fac, FwdRec *d_fwd,
-                          BwdRec *d_bwd, int tile_rows, double *d_tile, double *d_anorm, unsigned int *d_err, hipStream_t s)
+                          BwdRec *d_bwd, double *d_anorm, unsigned int *d_err, hipStream_t s)
 {
     const int bs = 256;
     const int64_t grid = (npad + bs - 1) / bs + 1;
-    hipLaunchKernelGGL(k_records, dim3((unsigned)grid), dim3(bs), 0, s, d_diag, d_fac, n, npad, d_fwd, d_bwd, tile_rows,
-                       d_tile, d_anorm, d_err);
+    hipLaunchKernelGGL(k_records, dim3((unsigned)grid), dim3(bs), 0, s, d_diag, d_fac, n, npad, d_fwd, d_bwd, d_anorm,
+                       d_err);
     return hipGetLastError();
 }
 
-hipError_t launch_seg_use(const SegRec *s32, int64_t n32, const SegRec *s64, int64_t n64, double *trunc, int64_t *depth,
-                          const SegRec *tile, int64_t ntile, ScanRec *scan, hipStream_t s)
+hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
+                              double *p64, int64_t *depth, hipStream_t s)
 {
-    if (!trunc && !tile) return hipSuccess;
-    const SegUse u = {s32, s64, (int)n32, (int)n64, trunc, trunc ? trunc + 4 * n32 : nullptr, depth, tile, ntile, scan};
-    hipLaunchKernelGGL(k_seg_use, dim3(3), dim3(256), 0, s, u);
+    hipLaunchKernelGGL(k_stream_prep, dim3(2), dim3(256), 0, s, seg32, (int)n32, kStreamDepth32, p32, seg64, (int)n64,
+                       kStreamDepth64, p64, depth);
     return hipGetLastError();
 }
 

@@ -99,19 +99,6 @@ struct alignas(128) GrpRec {
     double q[4];
 };
 
-constexpr int kTileSeg = 64;  // segments per system of the resident tile (= lanes of its scan wave)
-
-// Interface-scan constants of the resident-tile schedule, one record per
-// segment (64 segments): p[l] and q[l] are the products of 2^l consecutive
-// forward / backward transfer matrices ending (p) or starting (q) at the
-// segment, cg the segment's forward-in -> backward-out matrix.
-struct alignas(64) ScanRec {
-    double p[6][4];
-    double q[6][4];
-    double cg[4];
-    double pad[4];
-};
-
 // Factor records are stored for n rounded up to this many rows; the rows
 // past n are all-zero records, which map a zero right-hand side to zero and
 // let fixed-height kernels run without per-row guards.
@@ -264,11 +251,9 @@ struct pent_plan {
     std::mutex mu;           // guards seg caches (lazy build)
     pent::SegCache seg[pent::kMaxSegCaches];
     pent::GrpCache grp[pent::kMaxGrpCaches];  // lazily built, guarded by mu
-    pent::ScanRec *d_scan;   // resident-tile scan constants (64 records), where n allows the tile
     double *d_trunc;         // truncation products of the streaming sweeps: 32-row segments, then 64-row
     int strm_depth[3];       // their depths (32, 64 rows; corrections, 32), 0: too deep to stream
     int cus;                 // compute units of the device
-    double *d_trec;          // resident-tile record image (5 x 64 x rows doubles)
 };
 
 namespace pent {
@@ -345,19 +330,16 @@ constexpr uint64_t kMagic = 0x70656e7462617463ull;  // "pentbatc"
 // ---- launchers (each returns a hipError_t from the launch) ----
 hipError_t launch_assemble_d4(double *d_diag, int64_t n, double sigma, hipStream_t s);
 hipError_t launch_factor(const double *d_diag, int64_t n, double *d_fac, int64_t *d_bad, hipStream_t s);
-// The sweep records, the resident tile's image of them (tile_rows > 0), ||A||_inf,
-// and *d_err = 0.
+// The sweep records, ||A||_inf, and *d_err = 0.
 hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const double *d_fac, FwdRec *d_fwd,
-                          BwdRec *d_bwd, int tile_rows, double *d_tile, double *d_anorm, unsigned int *d_err, hipStream_t s);
+                          BwdRec *d_bwd, double *d_anorm, unsigned int *d_err, hipStream_t s);
 // The segment tables (seg_padded records each) of 64, 32 and, unless null, 16 rows.
 hipError_t launch_seg_prep_all(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, SegRec *s64, SegRec *s32,
                                SegRec *s16, hipStream_t s);
-// What the schedules take from the segment tables: unless trunc is null the
-// products P_b of the streaming sweeps (4 doubles per segment, 32-row ones
-// first) and depth[0..2] (device: of 32-row blocks, of 64-row ones, of a
-// correction's); unless tile is null the resident tile's scan matrices.
-hipError_t launch_seg_use(const SegRec *s32, int64_t n32, const SegRec *s64, int64_t n64, double *trunc, int64_t *depth,
-                          const SegRec *tile, int64_t ntile, ScanRec *scan, hipStream_t s);
+// The truncation of the streaming sweeps.  p32, p64: 4 doubles per segment;
+// depth[0..2] (device): the two depths and the corrections' (32-row segments).
+hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
+                              double *p64, int64_t *depth, hipStream_t s);
 hipError_t launch_seg_prep(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, int seg_rows,
                            SegRec *d_seg, hipStream_t s);
 // Group constants for groups of `waves` segments from the segment table
@@ -375,13 +357,6 @@ hipError_t launch_part_sweep_io(const FwdRec *fwd, const BwdRec *bwd, const SegR
                                 int64_t n, int64_t npad, int seg_rows, const void *Fin, bool f32,
                                 int64_t ldf, double *X, int64_t ldx, int64_t batch, double *summ,
                                 int64_t summ_ld, hipStream_t s);
-int tile_rows_for(int64_t n);  // rows per lane of the resident tile, 0 if n is too large
-size_t tile_recs_doubles(int rows);
-hipError_t launch_tile_sweep(const double *trec, const ScanRec *scan, int64_t n, int rows,
-                             double *F, int64_t batch, int64_t ld, hipStream_t s);
-hipError_t launch_tile_sweep_io(const double *trec, const ScanRec *scan, int64_t n, int rows,
-                                const void *Fin, bool f32, int64_t ldf, double *X, int64_t ldx,
-                                int64_t batch, hipStream_t s);
 
 // ---- precision extension (mixed.hip) ----
 // r = f - A x in compensated FP64 (f of type float or double); r may not alias f or x.
@@ -463,10 +438,10 @@ int stream_tile_width(int64_t batch, int cus);
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
                          int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
 
-// Whole tiles of `width` (16 or 32) systems, n <= 32768 / width rows, by one
-// workgroup each (resident.hip); ldf, ldx <= kResidentLd.  The periodic form:
-// n = the rows of E, cn: the Crank-Nicolson step.
-constexpr int64_t kResidentLd = (int64_t)1 << 22;
+// Whole tiles of `width` (4, 16 or 32) systems, n <= 32768 / width rows, by one
+// workgroup each (resident.hip).  The periodic form: n = the rows of E, cn: the
+// Crank-Nicolson step.
+constexpr int64_t kResidentRows = 4096;  // the resident-tile schedule's (kind 3) most rows
 hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
                            const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s);
 // System-major solves and 2-D x sweeps, as launch_stream_t and _ch2d.

@@ -1,7 +1,9 @@
-// resident.hip -- whole systems resident in one workgroup, for matrices of up
-// to 2048 rows and batches too small to fill the device with walking tiles.
+// resident.hip -- whole systems resident in one workgroup, for batches too small
+// to fill the device with walking tiles and up to 2048 rows (32 or 16 systems to
+// the workgroup), 4096 (four systems, as the resident-tile schedule at any batch)
+// or, for a few hundred systems, 6656.
 //
-// A workgroup holds all rows of a tile of S systems (S = 16 or 32): lane
+// A workgroup holds all rows of a tile of S systems (S = 4, 16 or 32): lane
 // l of wave w has rows [32 b, 32 b + 32) of system l % S in registers, b = w *
 // 64/S + l / S.  Each row is read once and written once in pieces of S
 // consecutive systems.  The sweeps are those of the streaming form (stream.h:
@@ -11,8 +13,9 @@
 // Nothing is truncated, nothing goes through memory, and no wave waits for
 // another workgroup: the latency of a solve is that of one load, four sweeps
 // of 32 rows, two barriers and one store (us, before / now: N = 256 x 256, tiles
-// of eight systems, 8.5 / 7.4, of which a launch is 7; N = 1000 x 5003 as
-// walking tiles 26.7 / 20.5, 3.9 TB/s; N = 1537 x 2500 by partitions 47 / 25).
+// of eight systems with their records in LDS, 8.5 / 7.4, of which a launch is 7;
+// N = 3384 x 154, the same, 37 / 16; N = 1000 x 5003 as walking tiles 26.7 / 20.5,
+// 3.9 TB/s; N = 1537 x 2500 by partitions 47 / 25; N = 4313 x 67 by look-back 33 / 24).
 // Full tiles of 16 waves are bound by the four sweeps, 32 rows x 4 waves x 9
 // operations of a SIMD each.
 //
@@ -36,6 +39,7 @@ template <int S, int NW>
 struct ResLds {
     double e[NW][2][S];  // state leaving a wave's rows downward, from zero
     double a[NW][2][S];  // ... and upward
+    double te[S < 16 ? NW : 1][4], ta[S < 16 ? NW : 1][4];  // narrow tiles: the waves' transfer matrices
     double ft[2][S], xe[4][S];  // periodic: f_{n-2}, f_{n-1}; y at rows 0, 1, m-2, m-1
 };
 
@@ -151,6 +155,136 @@ __device__ __forceinline__ void res_backward(double (&v)[kResK], Rec<kResK> &rc,
     for (int k = 0; k < kResK; k++) pin(v[k]);
 }
 
+// Coefficients of tiles of four systems, where a row of 16 lanes holds
+// more than one block: rows 4 i + l of the block in lane l of every four,
+// broadcast within them.
+struct QuadCoef {
+    double c[kResK / 4];
+    template <int k>
+    __device__ __forceinline__ double get() const
+    {
+        constexpr int ctrl = k % 4 * 0x55;  // quad_perm: the same lane four times
+        const long long x = __double_as_longlong(c[k / 4]);
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), ctrl, 0xF, 0xF, true);
+        return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    }
+    __device__ __forceinline__ void hold()
+    {
+#pragma unroll
+        for (int i = 0; i < kResK / 4; i++) pin(c[i]);
+    }
+};
+struct QuadRec {
+    QuadCoef ra, ap, bp, gm, dl;
+};
+
+__device__ __forceinline__ void load_quads_forward(QuadRec &r, const FwdRec *f, int64_t r0)
+{
+#pragma unroll
+    for (int i = 0; i < kResK / 4; i++) {
+        const Dbl2 *p = (const Dbl2 *)(f + r0 + 4 * i + (threadIdx.x & 3));
+        const Dbl2 u = p[0];
+        r.ra.c[i] = u.x;
+        r.ap.c[i] = u.y;
+        r.bp.c[i] = p[1].x;
+    }
+}
+
+__device__ __forceinline__ void load_quads_backward(QuadRec &r, const BwdRec *b, int64_t r0)
+{
+#pragma unroll
+    for (int i = 0; i < kResK / 4; i++) {
+        const Dbl2 q = *(const Dbl2 *)(b + r0 + 4 * i + (threadIdx.x & 3));
+        r.gm.c[i] = q.x;
+        r.dl.c[i] = q.y;
+    }
+}
+
+// The affine map y -> c + m y (m column-major) of the G blocks of a wave up to
+// and including each (FWD: from the first, else from the last), by doubling;
+// the wave's goes to LDS, and (c, m) become those of the blocks before.
+template <int S, bool FWD>
+__device__ __forceinline__ void scan_maps(double (&c)[2], double (&m)[4], int sub, double (*wc)[S], double *wm)
+{
+    constexpr int G = 64 / S;
+    const int at = FWD ? sub : G - 1 - sub;
+#pragma unroll
+    for (int d = 1; d < G; d *= 2) {
+        double p0, p1, q0, q1, q2, q3;
+        from_lane(FWD ? S * d : -S * d, c[0], c[1], p0, p1);
+        from_lane(FWD ? S * d : -S * d, m[0], m[1], q0, q1);
+        from_lane(FWD ? S * d : -S * d, m[2], m[3], q2, q3);
+        link(c[0], c[1], m[0], m[1], m[2], m[3], p0, p1);
+        const double n0 = fma(m[2], q1, m[0] * q0), n1 = fma(m[3], q1, m[1] * q0), n2 = fma(m[2], q3, m[0] * q2),
+                     n3 = fma(m[3], q3, m[1] * q2);
+        if (at >= d) {
+            c[0] = p0;
+            c[1] = p1;
+            m[0] = n0;
+            m[1] = n1;
+            m[2] = n2;
+            m[3] = n3;
+        }
+    }
+    if (at == G - 1) {
+        const int s = threadIdx.x & (S - 1);
+        wc[0][s] = c[0];
+        wc[1][s] = c[1];
+        if (s < 4) wm[s] = s == 0 ? m[0] : s == 1 ? m[1] : s == 2 ? m[2] : m[3];
+    }
+    from_lane(FWD ? S : -S, c[0], c[1], c[0], c[1]);
+    from_lane(FWD ? S : -S, m[0], m[1], m[0], m[1]);
+    from_lane(FWD ? S : -S, m[2], m[3], m[2], m[3]);
+    if (at == 0) {
+        c[0] = c[1] = m[1] = m[2] = 0.0;
+        m[0] = m[3] = 1.0;
+    }
+}
+
+// Both sweeps of tiles of four systems: as above, with the states between the 16
+// blocks of a wave by doubling.
+template <int S, typename Lds>
+__device__ __forceinline__ void narrow_sweeps(double (&v)[kResK], const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, int w,
+                                              int waves, int sub, int64_t blk, bool rows, Lds &sh)
+{
+    const int s = threadIdx.x & (S - 1);
+    Plain ex;
+    QuadRec rc;
+    load_quads_forward(rc, fwd, blk * kResK);
+    double c[2] = {0.0, 0.0}, m[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) m[k] = seg32[blk].tf[k];
+    sweep_forward<kResK, false>(v, rc, c[0], c[1]);
+    pin(c[0]);
+    pin(c[1]);
+    scan_maps<S, true>(c, m, sub, sh.e[w], sh.te[w]);
+    __syncthreads();
+    double y0 = 0.0, y1 = 0.0;
+    for (int u = 0; u < w; u++)
+        link(sh.e[u][0][s], sh.e[u][1][s], sh.te[u][0], sh.te[u][1], sh.te[u][2], sh.te[u][3], y0, y1);
+    link(c[0], c[1], m[0], m[1], m[2], m[3], y0, y1);
+    sweep_forward<kResK, true>(v, rc, y0, y1);
+    load_quads_backward(rc, bwd, blk * kResK);
+#pragma unroll
+    for (int k = 0; k < 4; k++) m[k] = seg32[blk].tb[k];
+    c[0] = c[1] = 0.0;
+    sweep_backward<kResK, false>(v, rc, c[0], c[1], ex);
+    c[0] = rows ? c[0] : 0.0;  // blocks past the last row
+    c[1] = rows ? c[1] : 0.0;
+    pin(c[0]);
+    pin(c[1]);
+    scan_maps<S, false>(c, m, sub, sh.a[w], sh.ta[w]);
+    __syncthreads();
+    double z0 = 0.0, z1 = 0.0;
+    for (int u = waves - 1; u > w; u--)
+        link(sh.a[u][0][s], sh.a[u][1][s], sh.ta[u][0], sh.ta[u][1], sh.ta[u][2], sh.ta[u][3], z0, z1);
+    link(c[0], c[1], m[0], m[1], m[2], m[3], z0, z1);
+    sweep_backward<kResK, true>(v, rc, z0, z1, ex);
+#pragma unroll
+    for (int k = 0; k < kResK; k++) pin(v[k]);
+}
+
 typedef __attribute__((address_space(1))) const char *GBytes;
 typedef __attribute__((address_space(1))) char *GBytesOut;
 typedef __attribute__((address_space(1))) double *GDblOut;
@@ -162,7 +296,12 @@ struct Place {
     int sub, s;      // the lane's block in the wave, its system in the tile
 };
 
-// The lane's rows from column p of the tile; rows from n on give zero.
+// Pitches up to which a lane's rows are within 32 bits of the wave's first.
+template <int S>
+constexpr int64_t kFullLd = ((int64_t)1 << 24) / (64 / S);
+
+// The lane's rows from column s of the tile F; rows from n on give zero.  full:
+// no lane of the wave has such rows, and the pitch is at most kFullLd.
 template <typename TI>
 __device__ __forceinline__ void res_load(double (&v)[kResK], const TI *F, int64_t ld, int64_t s, const Place &at, int64_t n,
                                          bool full)
@@ -233,8 +372,8 @@ __device__ __forceinline__ Place res_place(int w)
     return at;
 }
 
-template <int S, typename TI>
-__global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_resident(
+template <int S, int NW, typename TI>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_resident(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t n, const TI *F, int64_t ldf,
     double *X, int64_t ldx, int64_t batch, int64_t ntiles)
 {
@@ -244,14 +383,18 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
     const Place at = res_place<S>(w);
     const int64_t c0 = tile * S, blk = at.r0 / kResK;
-    const bool act = c0 + at.s < batch, full = at.rw + 64 / S * kResK <= n;
+    const bool act = c0 + at.s < batch, full = at.rw + 64 / S * kResK <= n && ldf <= kFullLd<S> && ldx <= kFullLd<S>;
     double v[kResK];
-    Rec<kResK> rc;
     res_load(v, F + c0, ldf, act ? at.s : batch - 1 - c0, at, n, full);  // idle lanes repeat the last column
-    load_forward<kResK>(rc, fwd, at.r0);
-    load_backward<kResK>(rc, bwd, at.r0);
-    res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
-    res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < n, sh, Plain());
+    if constexpr (S < 16) {
+        narrow_sweeps<S>(v, fwd, bwd, seg32, w, waves, at.sub, blk, at.r0 < n, sh);
+    } else {
+        Rec<kResK> rc;
+        load_forward<kResK>(rc, fwd, at.r0);
+        load_backward<kResK>(rc, bwd, at.r0);
+        res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
+        res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < n, sh, Plain());
+    }
     if (act) res_store(v, X + c0, ldx, at, n, full);
 }
 
@@ -271,7 +414,7 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), waves = (int)(blockDim.x / 64);
     const Place at = res_place<S>(w);
     const int64_t c0 = tile * S, blk = at.r0 / K;
-    const bool act = c0 + at.s < batch, full = at.rw + 64 / S * K <= m;
+    const bool act = c0 + at.s < batch, full = at.rw + 64 / S * K <= m && ldf <= kFullLd<S> && ldx <= kFullLd<S>;
     const int64_t sc = act ? at.s : batch - 1 - c0;
     const double *col = F + c0 + sc;
     const int L = m - at.r0 < K ? (int)(m - at.r0) : K;
@@ -617,14 +760,16 @@ hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *s
                            const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s)
 {
     const ResLaunch g = res_launch(n, width, batch);
-    if (f32) {
-        const auto fn = width == 16 ? k_resident<16, float> : k_resident<32, float>;
-        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const float *)F, ldf, X, ldx, batch, g.ntiles);
-    } else {
-        const auto fn = width == 16 ? k_resident<16, double> : k_resident<32, double>;
-        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const double *)F, ldf, X, ldx, batch, g.ntiles);
-    }
-    return hipGetLastError();
+    auto go = [&](auto f) {
+        typedef decltype(f) TI;
+        auto fn = width == 32 ? k_resident<32, 16, TI> : k_resident<16, 16, TI>;
+        // (eight waves of four systems have 256 registers each; sixteen spill
+        // 59 of theirs: 4096 x 154 23 us, with eight 18)
+        if (width == 4) fn = g.block.x <= 512 ? k_resident<4, 8, TI> : k_resident<4, 16, TI>;
+        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const TI *)F, ldf, X, ldx, batch, g.ntiles);
+        return hipGetLastError();
+    };
+    return f32 ? go(float()) : go(double());
 }
 
 hipError_t launch_resident_cyclic(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64,

@@ -187,8 +187,8 @@ __device__ __forceinline__ Tiles my_tiles(int ntiles)
 }
 
 // Forward recurrence over the block from (p2, p1).  STORE writes g over v.
-template <int K, bool STORE>
-__device__ __forceinline__ void sweep_forward(double (&v)[K], Rec<K> &r, double &p2, double &p1)
+template <int K, bool STORE, typename R>
+__device__ __forceinline__ void sweep_forward(double (&v)[K], R &r, double &p2, double &p1)
 {
     unroll<K>([&](auto kk) {
         constexpr int k = decltype(kk)::value;
@@ -225,8 +225,8 @@ struct PlainLate : Plain {
 
 // Back substitution over the block from (q1, q2) = (x_{r0+K}, x_{r0+K+1}); on
 // exit (q1, q2) = (x_{r0}, x_{r0+1}).  STORE writes x (ex.out of it) over v.
-template <int K, bool STORE, typename Extra>
-__device__ __forceinline__ void sweep_backward(double (&v)[K], Rec<K> &r, double &q1, double &q2, Extra &ex)
+template <int K, bool STORE, typename R, typename Extra>
+__device__ __forceinline__ void sweep_backward(double (&v)[K], R &r, double &q1, double &q2, Extra &ex)
 {
     unroll<K>([&](auto kk) {
         constexpr int k = K - 1 - decltype(kk)::value;

@@ -25,6 +25,9 @@ SIZES = [(1, 3, 0), (2, 16, 1), (31, 17, 0), (32, 5000, 0), (33, 15, 2), (64, 50
          (128, 33, 7), (129, 33, 0), (512, 700, 0), (513, 5100, 3), (768, 1000, 0), (1000, 5003, 5), (1023, 6000, 0),
          (1024, 500, 16), (1025, 1101, 0), (1537, 2500, 1), (1920, 1200, 0), (1921, 1200, 0), (2047, 4096, 0),
          (2048, 1500, 3), (700, 7000, 0)]
+# tiles of four systems: blocks of 32 rows, waves of 512, eight and sixteen waves
+SIZES += [(513, 1024, 0), (1025, 1, 0), (1536, 4, 0), (1537, 5, 3), (2049, 100, 0), (2500, 390, 1), (3583, 7, 0),
+          (3585, 2048, 0), (4095, 66, 2), (4096, 130, 0), (4097, 50, 0), (5000, 201, 1), (6656, 33, 0)]
 
 
 @pytest.mark.parametrize("n,m,pad", SIZES)
@@ -47,7 +50,7 @@ def test_resident_matches_oracle(torch, n, m, pad, sigma):
     assert torch.equal(F[:, :m], X[:, :m])
 
 
-@pytest.mark.parametrize("n,m", [(300, 1000), (1000, 5003), (1700, 2000)])
+@pytest.mark.parametrize("n,m", [(300, 1000), (1000, 5003), (1700, 2000), (900, 600), (3000, 300), (5000, 200)])
 def test_resident_against_forced_schedule(torch, n, m):
     """A matrix of differing rows: every system against the partitioned
     schedule (both within 64 u kappa of the solution, per column), and
@@ -172,3 +175,17 @@ def test_resident_2d_x_sweep(torch, ny, nx, k):
         py.solve_(R.view(ny, k * nx))
         pb.ch2d_step(px, py, C, torch.empty_like(C), dt, h)
     assert bool(torch.isfinite(C).all()) and torch.equal(C, R)
+
+
+@pytest.mark.parametrize("n,m", [(100, 7000), (1000, 9000), (3000, 3001)])
+def test_resident_tile_schedule_any_batch(torch, n, m):
+    """Forced (kind 3), past the batches that take it by themselves."""
+    print_case(test="resident_kind3", n=n, m=m)
+    B = rand(torch, (n, m), 3)
+    c = probes(m, 16)
+    ref = oracle.solve(oracle.assemble_d4(n, 10.0), np.ascontiguousarray(B[:, c].cpu().numpy()))
+    with pb.Plan.factor_d4(n, 10.0) as p:
+        p.set_schedule(3, 0)
+        p.solve_(B)
+        p.check()
+    assert np.max(colerr(B[:, c].cpu().numpy(), ref)) <= d4_tol(10.0)
