@@ -827,22 +827,23 @@ constexpr int64_t kCycStreamBatch = 8192;
 // automatic schedule, or 0 (us, solve and step, resident / look-back: N = 256 x 256
 // 7.6 / 26 and 8.8 / 28; N = 1000 x 2500 20 / 35 and 20 / 37; N = 1026 x 8192 40 / 49
 // and 39 / 56; N = 1537 x 3001 29 / 48 and 31 / 50; N = 2050 x 4096 40 / 54 and 38 /
-// 55, x 6000 66 / 63).  More than one turn (of 32 systems to the compute unit up to
-// 1024 rows) it also takes where E fits one wave (130 x 131072 64 / 79 and 66 / 81)
-// and where the walking tiles' chain is deep (sigma = 100: 500 x 16384 40 / 51 and
-// 37 / 53; 573 x 131072 305 / 330 and 337 / 347; 1026 x 65536 258 / 266 and 265 / 289,
-// but x 16384 79 / 73; at sigma = 1 x 65536 258 / 227).
+// 55, x 6000 66 / 63; N = 2500 x 200 16 / 34 and 16 / 36; N = 4098 x 67 21 / 35 and 20 /
+// 37, x 1000 30 / 41, x 1500 54 / 52).  More than one turn (of 32 systems to the
+// compute unit up to 1024 rows, 16 up to 2048) it also takes where E fits one wave
+// (130 x 131072 64 / 79 and 66 / 81) and where the walking tiles' chain is deep (sigma
+// = 100: 500 x 16384 40 / 51 and 37 / 53; 573 x 131072 305 / 330 and 337 / 347; 1026 x
+// 65536 258 / 266 and 265 / 289, but x 16384 79 / 73; at sigma = 1 x 65536 258 / 227).
 int cyc_resident_width(const pent_cyclic_s *c, int64_t batch)
 {
     const pent_plan *E = c->E;
-    if (E->n > 2048 || c->kind != 0 || onepass_waves_override()) return 0;
-    if ((batch + 15) / 16 > INT32_MAX / 2) return 0;
-    if (batch > (E->n > 1024 ? 16 : 32) * (int64_t)E->cus && E->n > 128) {
+    const int64_t turn = (E->n <= 1024 ? 32 : E->n <= 2048 ? 16 : 5) * (int64_t)E->cus;
+    if (E->n > kResidentRows || c->kind != 0 || onepass_waves_override() || (batch + 15) / 16 > INT32_MAX / 2) return 0;
+    if (batch > turn && E->n > 128) {
         StreamPlan sp;
         const bool deep = !stream_plan(E, 32, &sp) || sp.depth > 6;
         if (!deep || E->n > 1024 || (E->n > 640 && batch < 32768)) return 0;
     }
-    return E->n <= 1024 && batch >= 5000 && (batch <= 16384 || E->n <= 128) ? 32 : 16;  // as resident_width
+    return resident_width(E->n, batch, E->cus);
 }
 
 int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,

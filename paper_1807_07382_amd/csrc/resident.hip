@@ -401,8 +401,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // As above for E (m rows) and the border of a periodic matrix of m + 2 rows.
 // CN: F holds C, and f_i = 2 C_i - (A C)_i is formed in registers; UNI: with
 // the same five coefficients in every row, else those of cd.
-template <int S, bool CN, bool UNI>
-__global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_resident_cyclic(
+template <int S, int NW, bool CN, bool UNI>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_resident_cyclic(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t m, const double *F, int64_t ldf,
     double *X, int64_t ldx, int64_t batch, int64_t ntiles, const double *cd, const double *Z,
     const CycAux *__restrict__ aux, CycUni uc)
@@ -418,8 +418,10 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     const int64_t sc = act ? at.s : batch - 1 - c0;
     const double *col = F + c0 + sc;
     const int L = m - at.r0 < K ? (int)(m - at.r0) : K;
+    typedef std::conditional_t<(S < 16), QuadCoef, Coef<K>> C;
+    constexpr int CR = sizeof(C) / sizeof(double);
+    auto crow = [&](int i) { return at.r0 + (S < 16 ? 4 * i + (int)(threadIdx.x & 3) : coef_row<K>(i)); };
     double v[K];
-    Rec<K> rc;
     if (w == 0) {  // the right-hand side's last two entries
         double f0, f1;
         if constexpr (CN) {
@@ -450,15 +452,12 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
             h[i] = col[(r < 0 ? r + n : r >= n ? n - 1 : r) * ldf];
         }
         res_load(v, F + c0, ldf, sc, at, n, full);
-        Coef<K> g[5];
+        C g[5];
         if constexpr (!UNI) {
 #pragma unroll
             for (int d = 0; d < 5; d++)
 #pragma unroll
-                for (int i = 0; i < Coef<K>::S; i++) {
-                    const int64_t r = at.r0 + coef_row<K>(i);
-                    g[d].c[i] = cd[d * ldc + (r < n ? r : n - 1)];
-                }
+                for (int i = 0; i < CR; i++) g[d].c[i] = cd[d * ldc + (crow(i) < n ? crow(i) : n - 1)];
         }
         double p2 = h[0], p1 = h[1];
         unroll<K>([&](auto kk) {
@@ -487,10 +486,15 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
     } else {
         res_load(v, F + c0, ldf, sc, at, m, full);
     }
-    load_forward<K>(rc, fwd, at.r0);
-    load_backward<K>(rc, bwd, at.r0);
-    res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
-    res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < m, sh, Plain());
+    if constexpr (S < 16) {
+        narrow_sweeps<S>(v, fwd, bwd, seg32, w, waves, at.sub, blk, at.r0 < m, sh);
+    } else {
+        Rec<K> rc;
+        load_forward<K>(rc, fwd, at.r0);
+        load_backward<K>(rc, bwd, at.r0);
+        res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
+        res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < m, sh, Plain());
+    }
     // y at the rows that the border meets, x_tail, and x = y - Z x_tail
     if (at.r0 == 0) {
         sh.xe[0][at.s] = v[0];
@@ -504,10 +508,10 @@ __global__ __launch_bounds__(64 * kResWaves) __attribute__((amdgpu_waves_per_eu(
         for (int k = 1; k < K; k++) y = k == (int)(r % K) ? v[k] : y;
         if (blk == r / K) sh.xe[2 + i][at.s] = y;
     }
-    Coef<K> z0, z1;
+    C z0, z1;
 #pragma unroll
-    for (int i = 0; i < Coef<K>::S; i++) {
-        const Dbl2 u = ((const Dbl2 *)Z)[at.r0 + coef_row<K>(i)];
+    for (int i = 0; i < CR; i++) {
+        const Dbl2 u = ((const Dbl2 *)Z)[crow(i)];
         z0.c[i] = u.x;
         z1.c[i] = u.y;
     }
@@ -780,9 +784,13 @@ hipError_t launch_resident_cyclic(const FwdRec *fwd, const BwdRec *bwd, const Se
     CycUni uc = {{0.0, 0.0, 0.0, 0.0, 0.0}};
     if (uni)
         for (int k = 0; k < 5; k++) uc.c[k] = uni[k];
-    auto fn = width == 16 ? k_resident_cyclic<16, false, true> : k_resident_cyclic<32, false, true>;
-    if (cn && uni) fn = width == 16 ? k_resident_cyclic<16, true, true> : k_resident_cyclic<32, true, true>;
-    else if (cn) fn = width == 16 ? k_resident_cyclic<16, true, false> : k_resident_cyclic<32, true, false>;
+    auto pick = [&](auto cn_, auto uni_) {
+        constexpr bool C = decltype(cn_)::value, U = decltype(uni_)::value;
+        return width == 4 ? k_resident_cyclic<4, 8, C, U> : width == 16 ? k_resident_cyclic<16, 16, C, U> : k_resident_cyclic<32, 16, C, U>;
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    const auto fn = !cn ? pick(no, yes) : uni ? pick(yes, yes) : pick(yes, no);
     const ResLaunch g = res_launch(n, width, batch);
     hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, F, ldf, X, ldx, batch, g.ntiles, cd, Z, aux, uc);
     return hipGetLastError();

@@ -81,7 +81,9 @@ def test_resident_against_forced_schedule(torch, n, m):
                                            (35, 100, 3, 1e4), (66, 6000, 0, 10.0), (130, 33, 0, 100.0),
                                            (131, 5003, 5, 1.0), (1026, 5100, 0, 50.0), (1027, 300, 0, 1.0),
                                            (1537, 3001, 0, 10.0), (1922, 64, 16, 1e4),
-                                           (100, 20000, 0, 1.0), (500, 17000, 1, 300.0), (800, 33000, 0, 300.0), (2050, 4096, 0, 3.0)])
+                                           (100, 20000, 0, 1.0), (500, 17000, 1, 300.0), (800, 33000, 0, 300.0),
+                                           (515, 1024, 0, 1.0), (1538, 5, 1, 10.0), (2051, 1280, 0, 1.0),
+                                           (3587, 90, 0, 1e4), (4098, 66, 3, 10.0), (2050, 4096, 0, 3.0)])
 def test_resident_periodic(torch, n, m, pad, sigma):
     """Solves and Crank-Nicolson steps, uniform diagonals (bounds as for the
     streaming form)."""
@@ -103,7 +105,7 @@ def test_resident_periodic(torch, n, m, pad, sigma):
     assert np.all(err <= d4_tol(sigma) * (np.max(np.abs(ref), axis=0) + (2 + 16 * sigma) * np.max(np.abs(Bc), axis=0)))
 
 
-@pytest.mark.parametrize("n,m", [(5, 20), (34, 100), (300, 5001), (1500, 1200)])
+@pytest.mark.parametrize("n,m", [(5, 20), (34, 100), (300, 5001), (1500, 2000), (700, 300), (2300, 70)])
 def test_resident_periodic_varying_rows(torch, n, m):
     """Diagonals that differ from row to row (the step reads them per row)."""
     print_case(test="resident_cyc_rows", n=n, m=m)
