@@ -237,7 +237,7 @@ def all_configs(args, torch):
     r = run_rewrite(_sub(args, steps=20, warmup=2), torch)
     g = r["rocsparse_gpsv"] or {}
     res["rewrite"] = dict(ms_per_step=r["ms_per_step"], solves_per_s=r["value"],
-                          roofline_56B=_roof(r), roofline_104B=r["kernel_plan_roofline"],
+                          roofline_56B=_roof(r), roofline_kernel_plan=r["kernel_plan_roofline"],
                           parity=r["parity"],
                           rocsparse_gpsv_ms_with_restore=g.get("ms_per_step_with_restore"),
                           rocsparse_gpsv_ms_solve_only=g.get("ms_solve_only"),
@@ -352,10 +352,11 @@ def precision_compare(torch, sigma, reps=10, seed=4):
         # partitioned sweep twice; x is written once (FP64)
         one = plan.schedule_for(m)[0] == 4
         solve64, solve32 = (16, 12) if one else (24, 16)
-        # one correction: fused on the single pass (f and x in, x read again
-        # and written: 4 + 8 + 8 + 8), else residual (f, x in; r out: 20) +
-        # correction solve + x += d (24)
-        refine1 = solve32 + (28 if one else 20 + solve64 + 24)
+        # one correction: fused on the single pass (f and x in, x out: 4 + 8
+        # + 8; by look-back, where the chain is too deep to stream, x is read
+        # twice: 8 more), else residual (f, x in; r out: 20) + correction
+        # solve + x += d (24)
+        refine1 = solve32 + (20 if one else 20 + solve64 + 24)
         out["schedule"] = "single pass" if one else "partitioned"
         nbytes = plan.mixed_workspace_size(m, 1, True)
         work = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
@@ -769,10 +770,12 @@ def run_rewrite(args, torch):
         gpsv = dict(error=str(exc))
     # the method's minimum: five diagonals and f read, x written (56 B per
     # unknown); the kernel's own plan also writes gamma, delta and g and reads
-    # them back (104 B)
+    # them back (48 B), but for the last 112 rows, and for g alone in the 112
+    # before them
     alg = 56 * n * batch
     gbs = alg / (ms / 1e3) / 1e9
-    gbs104 = 104 * n * batch / (ms / 1e3) / 1e9
+    plan_bytes = 56 + (48 * max(n - 112, 0) - 32 * min(max(n - 112, 0), 112)) / n
+    gbs_plan = plan_bytes * n * batch / (ms / 1e3) / 1e9
     return dict(metric=METRIC, value=batch / (ms / 1e3), unit="RHS-solves/s", n_gpus=1,
                 steps=args.steps, warmup=args.warmup, ms_per_step=ms, higher_is_better=True,
                 scaling="weak", vs_baseline=None, dtype="f64", data="synthetic",
@@ -781,8 +784,8 @@ def run_rewrite(args, torch):
                 roofline=dict(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s",
                               frac=gbs / PEAK_HBM_GBS, bytes_per_unknown=56,
                               traffic=traffic_for("rewrite_lane", "rewrite", ("rewrite.hip", "stream.h"))),
-                kernel_plan_roofline=dict(bytes_per_unknown=104, achieved=gbs104,
-                                          frac=gbs104 / PEAK_HBM_GBS),
+                kernel_plan_roofline=dict(bytes_per_unknown=plan_bytes, achieved=gbs_plan,
+                                          frac=gbs_plan / PEAK_HBM_GBS),
                 parity=dict(probe_systems=len(cols), max_rel_err_vs_oracle=err),
                 rocsparse_gpsv=gpsv)
 
