@@ -967,8 +967,11 @@ int cyc_stream_ends(const CycAux &aux, int64_t n)
     const int64_t t = (aux.reach[0] + kCsK - 1) / kCsK, b = nblk - (m - aux.reach[1]) / kCsK;
     const int64_t T = std::max<int64_t>(std::max(t, b), 1);
     // enough blocks that the ends do not meet and a tile's next-but-one turn
-    // comes after its waves have finished
-    return nblk >= 3 * T && nblk >= kCsNW ? (int)T : 0;
+    // comes after its waves have finished; and all of the first T blocks in
+    // work at once, for each of them ends with x_tail, which the last of them
+    // forms: the wave of block T - 1 has to have no block of this tile before
+    // it (T = 17 would find it in block 0, waiting for block 16)
+    return T <= kCsNW && nblk >= 3 * T && nblk >= kCsNW ? (int)T : 0;
 }
 
 size_t cyc_stream_scratch_bytes(int64_t batch, int cw) { return (size_t)((batch + cw - 1) / cw) * 128 * sizeof(double); }
