@@ -414,19 +414,25 @@ void io_schedule(const pent_plan *p, int64_t batch, bool inplace64, int *kind, i
     }
 }
 
+// What the streaming sweeps read of h's matrix in `rows`-row blocks.
+void stream_tables(const pent_plan *h, int rows, StreamPlan *p)
+{
+    p->fwd = h->d_fwd;
+    p->bwd = h->d_bwd;
+    p->seg = h->seg[seg_slot(rows)].d_seg;
+    p->rows = rows;
+    p->cus = h->cus;
+}
+
 // The streaming form of h's matrix on `rows`-row blocks; false when its
 // backward chain is too deep for that.
 bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
 {
     const int i = rows == 32 ? 0 : 1;
     if (h->strm_depth[i] <= 0) return false;
-    p->fwd = h->d_fwd;
-    p->bwd = h->d_bwd;
-    p->seg = h->seg[seg_slot(rows)].d_seg;
+    stream_tables(h, rows, p);
     p->trunc = h->d_trunc + (i == 0 ? 0 : 4 * h->seg[seg_slot(32)].nseg);
-    p->rows = rows;
     p->depth = h->strm_depth[i];
-    p->cus = h->cus;
     return true;
 }
 
@@ -451,32 +457,30 @@ bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, Str
     return stream_plan(h, 32, p) || stream_plan(h, 64, p);
 }
 
-// Whether a system-major solve of `batch` systems runs as streaming sweeps,
-// where it does not run in resident tiles (us, streaming / look-back: n = 4096
-// x 9000 161 / 152, x 16384 230 / 261).  The x sweeps of a 2-D step go by the
-// same two rules, so that they give the bits of the separate passes; it is
-// theirs that deep chains are left to look-back (the explicit term is formed
-// in the waves that are not waiting for the chain, 7 of 16 at sigma = 200).
+// Whether a system-major solve of `batch` systems runs as streaming sweeps:
+// matrices of less than a resident wave's 128 rows, in many turns (n = 64 x
+// 100000 22 us, resident 32).  A tile's blocks are then all in work at once,
+// and nothing is left out.  (Streams of longer matrices are the faster form for
+// some data only: 4096 x 16384 242, look-back 272, where the truncation leaves
+// nothing to add, but 500 where it does, and up to 2048 rows no faster than
+// resident tiles, 2048 x 32768 225 and 225, but 700.)  The x sweeps of a 2-D step go by the same two rules, so that they give the bits
+// of the separate passes.
 bool t_stream_route(const pent_plan *h, int64_t batch, StreamPlan *p)
 {
-    return batch >= 10000 && (batch + 31) / 32 <= INT32_MAX && stream_plan(h, 32, p) && p->depth <= 6;
+    if (h->n > kStreamTRows || batch < 10000 || (batch + 31) / 32 > INT32_MAX) return false;
+    stream_tables(h, 32, p);
+    return true;
 }
 
 // Whether it runs in resident tiles of 16 systems.  Up to 1024 rows two or more
 // workgroups share a compute unit, one loading while the other sweeps (us,
-// resident / streaming, at sigma = 1: n = 256 x 117187 87 / 95, n = 512 x 58593 88 /
-// 102, n = 1021 x 20011 81 / 88, n = 1024 x 32768 100 / 115, at sigma = 200 100 / 139;
-// the 2-D step on 1024 x 1024 x 32 221, 256 by look-back in x); but matrices of
-// less than a wave's 128 rows (n = 64 x 100000 32 / 22), and of five waves, which
-// leave the sixteenth idle (n = 640 x 46875 100 / 95), stream when there are many
-// turns, and so do longer ones, alone on their compute unit (n = 1537 x 19518
-// 133 / 123, x 4000 32 / 61; at sigma = 200 x 20000 140, look-back 195).
+// resident / look-back: n = 1021 x 20011 81 / 124, 1024 x 32768 100 / 159; the 2-D
+// step on 1024 x 1024 x 32 215, 256 by look-back in x); longer ones are alone on
+// theirs (n = 1537 x 20000 128 / 199, 2048 x 10000 80 / 108, x 32768 225 / 261).
 bool t_resident_route(const pent_plan *h, int64_t batch)
 {
     StreamPlan sp;
-    if (h->n > 2048 || (batch + 15) / 16 > INT32_MAX / 2) return false;
-    if (!t_stream_route(h, batch, &sp)) return true;
-    return h->n > 96 && h->n <= 1024 && (h->n <= 512 || h->n > 640);
+    return h->n <= 2048 && (batch + 15) / 16 <= INT32_MAX / 2 && !t_stream_route(h, batch, &sp);
 }
 
 // Tile width of the resident form for n rows and this many systems.  Tiles of

@@ -454,9 +454,10 @@ hipError_t launch_resident_cyclic(const FwdRec *fwd, const BwdRec *bwd, const Se
                                   const double *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s,
                                   const double *uni = nullptr);
 
-// System-major right-hand sides, system s at F + s * ld (p of 32-row
-// segments); and the x sweeps of a 2-D Cahn-Hilliard step from C into R, both
+// System-major right-hand sides of n <= kStreamTRows rows, system s at F + s * ld
+// (p of 32-row segments); and the x sweeps of a 2-D Cahn-Hilliard step from C into R, both
 // [y][k][x], the explicit term formed on the fly.
+constexpr int64_t kStreamTRows = 96;
 hipError_t launch_stream_t(const StreamPlan &p, int64_t n, double *F, int64_t ld, int64_t batch, unsigned int *err,
                            hipStream_t s);
 hipError_t launch_stream_ch2d(const StreamPlan &p, int64_t n, const double *C, double *R, int64_t ny, int64_t ninst,

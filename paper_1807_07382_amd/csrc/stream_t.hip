@@ -1,6 +1,6 @@
-// stream_t.hip -- streaming sweeps (stream.h) over system-major storage: the
-// second direction of an alternating-direction step, also with the 2-D
-// Cahn-Hilliard explicit term formed on the way in.
+// stream_t.hip -- streaming sweeps (stream.h) over system-major storage of a few
+// blocks of rows: the second direction of an alternating-direction step, also
+// with the 2-D Cahn-Hilliard explicit term formed on the way in.
 #include "stream.h"
 
 namespace pent {
@@ -28,17 +28,19 @@ typedef double Dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // 16 byt
 // selects (with them it kept 32 row masks and spilled 71 registers, and the
 // sweep took 230 us).
 //
-// HBM-bound: n = 2048 x 32768 217 us, 4.9 TB/s; n = 1537 x 20000, with no run on
-// a line of its own, 130 us (195 by look-back, which fetched such runs a double
-// at a time).
+// D = nblk - 1: a block takes the states of all blocks below it, and nothing is
+// left out.  Where the chain is cut short, what it leaves out has to be added to
+// finished tiles, in runs of 16 rows of 64 systems, and that costs more than
+// the form saves (n = 2048 x 32768 225 us, but 700 with sources in the bottom
+// rows only; 260 by look-back).
 template <bool ST, bool NT>
 __global__ __launch_bounds__(64 * kTNW) __attribute__((amdgpu_waves_per_eu(kTEU, kTEU))) void k_stream_t(
-    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, int64_t n, int nblk,
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, int64_t n, int nblk,
     const double *src, double *F, int64_t per, int64_t sst, int64_t kst, int tpk, int cw, int ntiles, unsigned int *err,
     const double *dt, double inv_h2)
 {
     constexpr int K = kTK, NW = kTNW;
-    __shared__ StreamLds<NW> sh;
+    __shared__ StreamLds<NW, false> sh;
     __shared__ double tb[NW][8][66];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int lane = threadIdx.x & 63;
@@ -50,12 +52,10 @@ __global__ __launch_bounds__(64 * kTNW) __attribute__((amdgpu_waves_per_eu(kTEU,
     stream_init(sh);
     const Tiles mine = my_tiles(ntiles);
     int t = mine.t0, b = w, par = 0;
-    unsigned int turn = 0;
     auto skip = [&]() {
         while (b >= nblk) {
             b -= nblk;
             t += mine.step;
-            turn++;
         }
     };
     skip();
@@ -164,8 +164,7 @@ __global__ __launch_bounds__(64 * kTNW) __attribute__((amdgpu_waves_per_eu(kTEU,
             });
             clear();
         }
-        stream_phases<K, NW, true, PlainLate>(v, rc, bwd, (CSeg)seg, (CTrunc)trunc, b, nblk, D, q, w, par, turn, sh, err,
-                                              PlainLate());
+        stream_phases<K, NW, false, PlainLate>(v, rc, bwd, (CSeg)seg, nullptr, b, nblk, nblk - 1, q, w, 0, 0, sh, err, PlainLate());
         // turned back and stored as runs
 #pragma unroll
         for (int c = 0; c < K / 16; c++)
@@ -197,17 +196,6 @@ __global__ __launch_bounds__(64 * kTNW) __attribute__((amdgpu_waves_per_eu(kTEU,
         b += NW;
         skip();
     }
-    store_fence();  // every wave's x is in memory before the repair reads it
-    __syncthreads();
-    turn = 0;
-    for (t = mine.t0; t < mine.end; t += mine.step, turn++)
-        if (sh.last[turn % 32] >= 0) {
-            const int g = ST ? t / tpk : 0;
-            const int64_t s0 = (int64_t)(t - g * tpk) * cw;
-            const bool act = lane < cw && s0 + lane < per;
-            stream_repair<K, NW>(F + g * kst + (s0 + (act ? lane : 0)) * sst, 1, act, n, nblk, D, (CSeg)seg, (CBwd)bwd,
-                                 (CTrunc)trunc, sh, w, turn % 32, [](int64_t) { return 0.0; });
-        }
 }
 
 template <bool ST>
@@ -215,12 +203,13 @@ hipError_t launch_t(const StreamPlan &p, int64_t n, const double *src, double *F
                     int64_t groups, int cw, unsigned int *err, const double *dt, double inv_h2, hipStream_t s)
 {
     const int64_t tpk = (per + cw - 1) / cw, ntiles = tpk * groups, nblk = (n + kTK - 1) / kTK;
+    if (n > kStreamTRows) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8)), block(64 * kTNW);
     if ((uintptr_t)src % 128 == 0 && (uintptr_t)F % 128 == 0 && sst % 16 == 0 && kst % 16 == 0)
-        hipLaunchKernelGGL((k_stream_t<ST, true>), grid, block, 0, s, p.fwd, p.bwd, p.seg, p.trunc, p.depth, n, (int)nblk,
+        hipLaunchKernelGGL((k_stream_t<ST, true>), grid, block, 0, s, p.fwd, p.bwd, p.seg, n, (int)nblk,
                            src, F, per, sst, kst, (int)tpk, cw, (int)ntiles, err, dt, inv_h2);
     else
-        hipLaunchKernelGGL((k_stream_t<ST, false>), grid, block, 0, s, p.fwd, p.bwd, p.seg, p.trunc, p.depth, n, (int)nblk,
+        hipLaunchKernelGGL((k_stream_t<ST, false>), grid, block, 0, s, p.fwd, p.bwd, p.seg, n, (int)nblk,
                            src, F, per, sst, kst, (int)tpk, cw, (int)ntiles, err, dt, inv_h2);
     return hipGetLastError();
 }
