@@ -127,7 +127,7 @@ pent_plan *new_plan(int64_t n, int *st)
     p->t_cap = 0;
     p->tst_cap = 0;
     p->d_pool = nullptr;
-    const int64_t nseg = (n + 31) / 32 + (n + 63) / 64;
+    const int64_t nseg = 2 * ((n + 31) / 32) + (n + 63) / 64;
     size_t at = 0;
     auto room = [&](size_t bytes) {
         const size_t o = at;
@@ -242,7 +242,8 @@ pent_handle finish_factor(pent_plan *p, bool factored = false)
         e = launch_records(p->d_diag, p->n, p->npad, p->d_fac, p->d_fwd, p->d_bwd, p->d_anorm, p->d_err, 0);
     if (e == hipSuccess) e = launch_seg_prep_all(p->d_fwd, p->d_bwd, p->n, s64, s32, s16, 0);
     if (e == hipSuccess && strm)
-        e = launch_stream_prep(s32, n32, p->d_trunc, s64, n64, p->d_trunc + 4 * n32, d_bad + 1, 0);
+        e = launch_stream_prep(s32, n32, p->d_trunc, s64, n64, p->d_trunc + 4 * n32, p->d_trunc + 4 * (n32 + n64),
+                               d_bad + 1, 0);
     if (e == hipSuccess) {
         // (a copy waits for the null stream's work; without one, wait for it)
         const size_t first = factored ? 1 : 0, count = strm ? 4 : 1;
@@ -579,6 +580,15 @@ struct MixedLayout {
     size_t total() const { return summ + r + acc; }
 };
 
+// Whether the fused look-back correction can run: a tile's units at once, with
+// room to spare.
+bool fix_fits(pent_plan *h, int64_t batch)
+{
+    if (h->fix_cap == 0) h->fix_cap = onepass_fix_capacity();
+    return h->fix_cap > 0 && onepass_fix_groups(h->n) <= h->fix_cap / 4 &&
+           (batch + 63) / 64 * onepass_fix_groups(h->n) <= (int64_t)UINT32_MAX / 2;
+}
+
 MixedLayout mixed_layout(pent_plan *h, int64_t batch, bool inplace64, int refine_steps, bool want_eta)
 {
     MixedLayout L;
@@ -587,14 +597,29 @@ MixedLayout mixed_layout(pent_plan *h, int64_t batch, bool inplace64, int refine
     L.summ = summ_bytes(h, kind, seg_rows, batch);
     if (refine_steps > 0) {
         if (kind == 4) {
-            if (h->fix_cap == 0) h->fix_cap = onepass_fix_capacity();
-            L.fused = h->fix_cap > 0 && onepass_fix_groups(h->n) <= h->fix_cap / 4 &&
-                      onepass_fix_scratch_bytes(h->n, batch) <= L.summ;
+            L.fused = fix_fits(h, batch) && onepass_fix_scratch_bytes(h->n, batch) <= L.summ;
         }
         if (!L.fused) L.r = align256(sizeof(double) * (size_t)h->n * batch);
     }
     if (want_eta || h->refine_tol > 0.0) L.acc = align256(sizeof(unsigned long long) * 3 * (size_t)batch);
     return L;
+}
+
+// Whether the corrections of a solve that io_schedule gave (kind, seg_rows)
+// run as streaming sweeps, which need the scratch of the look-back form beside
+// them (in the solve's and, where that has less, the correction buffer's
+// place).
+bool fix_stream_route(pent_plan *h, const MixedLayout &L, int kind, int seg_rows, int64_t batch, int refine_steps, StreamPlan *sp)
+{
+    const int64_t cw = stream_tile_width(batch, h->cus), wgs = stream_workgroups(batch, (int)cw, h->cus);
+    if (refine_steps == 0 || h->strm_depth[2] <= 0 || resident_route(h, kind, batch) ||
+        !stream_route(h, kind, seg_rows, batch, sp) || !fix_fits(h, batch) ||
+        onepass_fix_scratch_bytes(h->n, batch) > L.summ + L.r || (batch + cw - 1) / cw > kLeftTiles * wgs)
+        return false;
+    stream_tables(h, 32, sp);
+    sp->trunc = h->d_trunc + 4 * (h->seg[seg_slot(32)].nseg + h->seg[seg_slot(64)].nseg);
+    sp->depth = h->strm_depth[2];
+    return true;
 }
 
 }  // namespace
@@ -1363,16 +1388,22 @@ int pent_solve_mixed(pent_handle h, const void *f, int f_dtype, int64_t ld_f, do
     if (st != PENT_OK) return ret(st);
     // Corrections: where the solve ran as a single pass and a tile of the
     // fused correction fits on the device, each correction is one fused pass
-    // too (residual, solve and update of x in one kernel); else residual,
+    // too (residual, solve and update of x in one kernel), a streaming one
+    // followed by the look-back one for the systems it leaves; else residual,
     // solve, x += d.
     StreamPlan sp;
     int kind, seg_rows;
     io_schedule(h, batch, alias, &kind, &seg_rows);
-    if (refine_steps > 0 && h->strm_depth[2] > 0 && stream_route(h, kind, seg_rows, batch, &sp)) {
-        sp.seg = h->seg[seg_slot(32)].d_seg;
+    if (fix_stream_route(h, L, kind, seg_rows, batch, refine_steps, &sp)) {
+        const SegRec *seg64 = h->seg[seg_slot(64)].d_seg;
+        const int cw = stream_tile_width(batch, h->cus), wgs = (int)left_workgroups(batch, cw);
+        const Left left = onepass_fix_left(h->n, batch, w);
         for (int it = 0; it < refine_steps; it++) {
-            hipError_t e = launch_stream_fix(sp, h->strm_depth[2], h->n, h->d_diag, f, f32, ld_f, x, ld_x, batch,
-                                             stream_tile_width(batch, h->cus), h->d_err, s);
+            hipError_t e = launch_stream_fix(sp, h->n, h->d_diag, f, f32, ld_f, x, ld_x, batch, cw, left,
+                                             h->d_err, s);
+            if (e == hipSuccess)
+                e = launch_onepass_fix_left(h->d_fwd, h->d_bwd, seg64, h->d_diag, h->n, f, f32, ld_f, x, ld_x, batch, w,
+                                            h->d_err, wgs, h->fix_cap, s);
             if (e != hipSuccess) return ret(hip_status(e));
         }
     } else if (refine_steps > 0 && L.fused) {

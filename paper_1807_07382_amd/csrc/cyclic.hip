@@ -624,6 +624,7 @@ struct CycExtra {
             if (__ballot(!fine) != 0 && lane == 0) atomicMax(&sh.last[turn % 32], 0);
         }
     }
+    __device__ __forceinline__ void took(double, double) {}
     __device__ __forceinline__ void ready()
     {
         const int lane = threadIdx.x & 63;

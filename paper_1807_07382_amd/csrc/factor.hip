@@ -358,7 +358,7 @@ __global__ __launch_bounds__(64) void k_seg_prep_all(const FwdRec *__restrict__ 
 // and the maxima stay in registers until the end (8 us at N = 4096; 100 us
 // with the loads in the loop and a shared maximum per product).
 __global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, int da, double *pa, const SegRec *sb,
-                                                     int nb, int db, double *pb, int64_t *depth)
+                                                     int nb, int db, double *pb, double *pfix, int64_t *depth)
 {
     constexpr int M = kStreamMaxDepth;
     const SegRec *seg = blockIdx.x == 0 ? sa : sb;
@@ -413,12 +413,16 @@ __global__ __launch_bounds__(256) void k_stream_prep(const SegRec *sa, int na, i
         depth[blockIdx.x] = D;
         if (blockIdx.x == 0) depth[2] = Df;
     }
-    if (D == 0) return;
+    if (blockIdx.x != 0) Df = 0;
+    if (D == 0 && Df == 0) return;
     for (int b = threadIdx.x; b < nseg; b += 256)
         products(b, [&](int i, const double(&m)[4]) {
             if (i == D)
 #pragma unroll
                 for (int k = 0; k < 4; k++) out[4 * (int64_t)b + k] = b + D < nseg - 1 ? m[k] : 0.0;
+            if (i == Df)
+#pragma unroll
+                for (int k = 0; k < 4; k++) pfix[4 * (int64_t)b + k] = b + Df < nseg - 1 ? m[k] : 0.0;
         });
 }
 
@@ -506,10 +510,10 @@ hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const d
 }
 
 hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
-                              double *p64, int64_t *depth, hipStream_t s)
+                              double *p64, double *pfix, int64_t *depth, hipStream_t s)
 {
     hipLaunchKernelGGL(k_stream_prep, dim3(2), dim3(256), 0, s, seg32, (int)n32, kStreamDepth32, p32, seg64, (int)n64,
-                       kStreamDepth64, p64, depth);
+                       kStreamDepth64, p64, pfix, depth);
     return hipGetLastError();
 }
 

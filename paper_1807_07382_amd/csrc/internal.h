@@ -217,6 +217,17 @@ constexpr double kTruncFix = 0x1p-36;
 constexpr int kStreamDepthFix = 8;
 constexpr int64_t kStreamMaxRows = (int64_t)1 << 20;  // past it the depth is not searched for
 
+// What streaming sweeps leave to the look-back form, which is launched next on
+// the stream with the same scratch and takes the systems marked there.
+struct Left {
+    unsigned int *words;  // the form's tickets and status words; null: nothing is left
+    int64_t nwords;
+    double *ex;           // its exchange area, which holds the marks (lookback.h)
+    int groups;                 // its units per 64-system tile
+    int stride;                 // rows from sample to sample (k_find_left)
+};
+constexpr int kLeftTiles = 1024;  // most tiles of a streaming workgroup that can leave some
+
 struct StreamPlan {
     const FwdRec *fwd = nullptr;
     const BwdRec *bwd = nullptr;
@@ -251,7 +262,7 @@ struct pent_plan {
     std::mutex mu;           // guards seg caches (lazy build)
     pent::SegCache seg[pent::kMaxSegCaches];
     pent::GrpCache grp[pent::kMaxGrpCaches];  // lazily built, guarded by mu
-    double *d_trunc;         // truncation products of the streaming sweeps: 32-row segments, then 64-row
+    double *d_trunc;         // truncation products of the streaming sweeps: 32-row segments, 64-row, the corrections'
     int strm_depth[3];       // their depths (32, 64 rows; corrections, 32), 0: too deep to stream
     int cus;                 // compute units of the device
 };
@@ -336,10 +347,10 @@ hipError_t launch_records(const double *d_diag, int64_t n, int64_t npad, const d
 // The segment tables (seg_padded records each) of 64, 32 and, unless null, 16 rows.
 hipError_t launch_seg_prep_all(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, SegRec *s64, SegRec *s32,
                                SegRec *s16, hipStream_t s);
-// The truncation of the streaming sweeps.  p32, p64: 4 doubles per segment;
+// The truncation of the streaming sweeps.  p32, p64, pfix: 4 doubles per segment;
 // depth[0..2] (device): the two depths and the corrections' (32-row segments).
 hipError_t launch_stream_prep(const SegRec *seg32, int64_t n32, double *p32, const SegRec *seg64, int64_t n64,
-                              double *p64, int64_t *depth, hipStream_t s);
+                              double *p64, double *pfix, int64_t *depth, hipStream_t s);
 hipError_t launch_seg_prep(const FwdRec *d_fwd, const BwdRec *d_bwd, int64_t n, int seg_rows,
                            SegRec *d_seg, hipStream_t s);
 // Group constants for groups of `waves` segments from the segment table
@@ -426,6 +437,12 @@ hipError_t launch_onepass_fix(const FwdRec *fwd, const BwdRec *bwd, const SegRec
                               const double *diag, int64_t n, const void *F, bool f32, int64_t ldf,
                               double *X, int64_t ldx, int64_t batch, void *scratch,
                               unsigned int *err, hipStream_t s);
+// As it, but for the systems that the launch_stream_fix before it left (wgs:
+// left_workgroups), in at most `most` workgroups.
+hipError_t launch_onepass_fix_left(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg64, const double *diag, int64_t n,
+                                   const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch,
+                                   void *scratch, unsigned int *err, int wgs, int most, hipStream_t s);
+Left onepass_fix_left(int64_t n, int64_t batch, void *scratch);
 hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, int64_t n,
                           int seg_rows, const void *Fin, bool f32, int64_t ldf, double *X,
                           int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
@@ -462,9 +479,22 @@ hipError_t launch_stream_t(const StreamPlan &p, int64_t n, double *F, int64_t ld
                            hipStream_t s);
 hipError_t launch_stream_ch2d(const StreamPlan &p, int64_t n, const double *C, double *R, int64_t ny, int64_t ninst,
                               const double *dt, double h, unsigned int *err, hipStream_t s);
-// One refinement correction by 32-row blocks (p of 32-row segments).
-hipError_t launch_stream_fix(const StreamPlan &p, int depth, int64_t n, const double *diag, const void *F, bool f32,
-                             int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
+// Workgroups of a streaming launch.
+inline int64_t stream_workgroups(int64_t batch, int cw, int cus)
+{
+    const int64_t tiles = (batch + cw - 1) / cw;
+    return (tiles < cus ? tiles + 7 : cus) / 8 * 8;
+}
+constexpr int kLeftWgs = 1984;  // most workgroups that look for what is left
+inline int64_t left_workgroups(int64_t batch, int cw)
+{
+    const int64_t tiles = (batch + cw - 1) / cw;
+    return tiles < kLeftWgs ? tiles : kLeftWgs;
+}
+// One refinement correction by 32-row blocks (p: the corrections').
+hipError_t launch_stream_fix(const StreamPlan &p, int64_t n, const double *diag, const void *F, bool f32,
+                             int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, const Left &left,
+                             unsigned int *err, hipStream_t s);
 
 // ---- measurement (copy.hip): dst = src through the single pass's blocks ----
 hipError_t launch_block_copy(const double *src, double *dst, int64_t n, int64_t batch, int64_t lds,

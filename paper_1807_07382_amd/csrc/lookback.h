@@ -227,6 +227,28 @@ __device__ __forceinline__ void link(double w0, double w1, double t0, double t1,
 // aggregate a; 6,7 backward inclusive up.
 constexpr int kExRows = 8;
 
+// Systems that streaming sweeps leave to the look-back form after them (Left): a
+// mark per system, in the exchange rows of the inclusive forward state that
+// leaves its tile's last unit, which no one writes; and words, one of them not
+// zero when any system is marked, in the ticket lines behind the counters.
+__device__ __forceinline__ unsigned long long *left_mark(double *ex, int groups, int64_t j)
+{
+    return (unsigned long long *)(ex + ((j / 64 + 1) * groups - 1) * (kExRows * 64) + 2 * 64 + (j & 63));
+}
+static_assert(kLeftWgs == kTicketLines * (kTicketStride - 1), "as many words as there are");
+__device__ __forceinline__ unsigned int *left_word(unsigned int *words, int wg)
+{
+    return words + (wg % kTicketLines) * kTicketStride + 1 + wg / kTicketLines;
+}
+
+// Whether any of the wgs words is set, to the whole workgroup.
+__device__ __forceinline__ bool any_left(unsigned int *words, int wgs)
+{
+    unsigned int any = 0;
+    for (int i = threadIdx.x; i < wgs; i += blockDim.x) any |= *left_word(words, i);
+    return __syncthreads_or(any != 0) != 0;
+}
+
 // One status word per lane: lane l reads word[base + l] when it is in
 // [lo, hi], else reports 0 (not counted as missing).
 __device__ __forceinline__ unsigned int lane_status(unsigned int *word, int64_t idx, bool in)

@@ -17,6 +17,7 @@
 // units fits on the device at once (checked on the host), every wait ends;
 // each wait is also bounded, and a wait that runs out raises the plan's
 // error word and lets the wave finish.
+#include <algorithm>
 #include <cstdlib>
 
 #include "lookback.h"
@@ -395,58 +396,74 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 // carries have passed through both neighbours, which post them only after
 // their loads have completed.  x = A^{-1} f to one more correction.
 // 2 waves per SIMD: the halo and residual terms need more registers.
-template <int K, int W, typename TI>
+// SOME: only the systems that the streaming form left (lookback.h), by at most
+// as many workgroups as run at once, which pass over the tiles that have none.
+// Each ticket line hands out its units in order, and has more workgroups than a
+// tile has units on it (a tile has at most a quarter of the units that run at
+// once): those of the first tile not done yet are all taken, and it gets done.
+template <int K, int W, bool SOME, typename TI>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) void k_onepass_fix(
     const FwdRec *fwd_, const BwdRec *bwd_, const SegRec *seg_, const double *__restrict__ diag,
     int64_t n, int ngroups, const TI *F, int64_t ldf, double *X, int64_t ldx, int64_t batch,
-    unsigned int *ctr, unsigned int *fst, unsigned int *bst, double *ex, unsigned int *err)
+    unsigned int *ctr, unsigned int *fst, unsigned int *bst, double *ex, unsigned int *err, unsigned int units, int wgs)
 {
     PENT_GROUP_LDS(W);
-    __shared__ unsigned int s_unit;
+    __shared__ unsigned int s_unit[2];
     const CFwd fwd = (CFwd)fwd_;
     const CBwd bwd = (CBwd)bwd_;
     const CSeg seg = (CSeg)seg_;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int lane = threadIdx.x & 63;
-    if (w == 0) s_unit = take_unit(ctr);  // every lane of wave 0 stores the same value
-    __syncthreads();
-    const unsigned int u = (unsigned int)__builtin_amdgcn_readfirstlane((int)s_unit);
-    const int t = (int)(u / (unsigned int)ngroups), g = (int)(u % (unsigned int)ngroups);
-    const int64_t j = (int64_t)t * 64 + lane;
-    const bool act = j < batch;
-    const int64_t jj = act ? j : 0;
-    const int64_t r0 = ((int64_t)g * W + w) * K;
-    const int64_t rem = n - r0;
-    const int L = (int)(rem < 0 ? 0 : rem < K ? rem : K);
-    double v[K];
-    // x of the block, and its halo rows (zero outside the matrix)
-    load_rows<K, double>(v, X + jj + (L > 0 ? r0 * ldx : 0), ldx, act ? L : 0);
-    // Every load below is unconditional, from a row clamped into the matrix
-    // (a load whose value is used under a per-lane condition gets sunk into
-    // that branch and waited for there).  No select is needed: a halo row
-    // outside the matrix meets a zero diagonal entry (the stored diagonals
-    // are zero there), rows past L are zeroed after the residual, and lanes
-    // past the batch store nothing.
-    auto xrow = [&](int64_t i) { return X[(i < 0 ? 0 : i >= n ? n - 1 : i) * ldx + jj]; };
-    const double hm2 = xrow(r0 - 2), hm1 = xrow(r0 - 1), hp0 = xrow(r0 + K), hp1 = xrow(r0 + K + 1);
-    // r over x, row by row, the two overwritten x values kept rolling; rows
-    // past the matrix (k >= L) give zero
-    fix_residual<K, TI>(v, diag, n, F + jj + (L > 0 ? r0 * ldf : 0), ldf, r0, L, hm2, hm1, hp0, hp1);
-    group_phases<K, W>(v, fwd, bwd, seg, r0, w, g, ngroups, u - (unsigned int)g, fst, bst, ex, err,
-                       sh, agg, mat);
-    if (!act || L == 0) return;
-    // x += d, 32 rows at a time: every load of a batch is issued before its
-    // stores (one round trip per batch; the compiler cannot tell the rows
-    // apart, so an interleaved read-modify-write would wait per row)
-    double *base = X + jj + r0 * ldx;
+    if (SOME && !any_left(ctr, wgs)) return;
+    for (int turn = 0;; turn ^= 1) {
+        // the multiples of the pitches are not to be kept from unit to unit (they
+        // took more scalar registers than there are: 35% on the whole)
+        if (SOME) asm volatile("" : "+s"(ldf), "+s"(ldx), "+s"(n), "+s"(diag));
+        if (w == 0) s_unit[turn] = take_unit(ctr);  // every lane of wave 0 stores the same value
+        __syncthreads();
+        const unsigned int u = (unsigned int)__builtin_amdgcn_readfirstlane((int)s_unit[turn]);
+        if (SOME && u >= units) return;
+        const int t = (int)(u / (unsigned int)ngroups), g = (int)(u % (unsigned int)ngroups);
+        const int64_t j = (int64_t)t * 64 + lane;
+        const bool act = j < batch;
+        const int64_t jj = act ? j : 0;
+        const bool mine = act && (!SOME || *left_mark(ex, ngroups, jj) != 0);
+        if (SOME && __ballot(mine) == 0) continue;
+        const int64_t r0 = ((int64_t)g * W + w) * K;
+        const int64_t rem = n - r0;
+        const int L = (int)(rem < 0 ? 0 : rem < K ? rem : K);
+        double v[K];
+        // x of the block, and its halo rows (zero outside the matrix)
+        load_rows<K, double>(v, X + jj + (L > 0 ? r0 * ldx : 0), ldx, act ? L : 0);
+        // Every load below is unconditional, from a row clamped into the matrix
+        // (a load whose value is used under a per-lane condition gets sunk into
+        // that branch and waited for there).  No select is needed: a halo row
+        // outside the matrix meets a zero diagonal entry (the stored diagonals
+        // are zero there), rows past L are zeroed after the residual, and lanes
+        // past the batch store nothing.
+        auto xrow = [&](int64_t i) { return X[(i < 0 ? 0 : i >= n ? n - 1 : i) * ldx + jj]; };
+        const double hm2 = xrow(r0 - 2), hm1 = xrow(r0 - 1), hp0 = xrow(r0 + K), hp1 = xrow(r0 + K + 1);
+        // r over x, row by row, the two overwritten x values kept rolling; rows
+        // past the matrix (k >= L) give zero
+        fix_residual<K, TI>(v, diag, n, F + jj + (L > 0 ? r0 * ldf : 0), ldf, r0, L, hm2, hm1, hp0, hp1);
+        group_phases<K, W>(v, fwd, bwd, seg, r0, w, g, ngroups, u - (unsigned int)g, fst, bst, ex, err,
+                           sh, agg, mat);
+        if (mine && L > 0) {
+            // x += d, 32 rows at a time: every load of a batch is issued before its
+            // stores (one round trip per batch; the compiler cannot tell the rows
+            // apart, so an interleaved read-modify-write would wait per row)
+            double *base = X + jj + r0 * ldx;
 #pragma unroll
-    for (int b = 0; b < K; b += 32) {
-        double xo[32];
+            for (int b = 0; b < K; b += 32) {
+                double xo[32];
 #pragma unroll
-        for (int q = 0; q < 32; q++) xo[q] = base[(b + q < L ? b + q : 0) * ldx];
+                for (int q = 0; q < 32; q++) xo[q] = base[(b + q < L ? b + q : 0) * ldx];
 #pragma unroll
-        for (int q = 0; q < 32; q++)
-            if (b + q < L) base[(b + q) * ldx] = xo[q] + v[b + q];
+                for (int q = 0; q < 32; q++)
+                    if (b + q < L) base[(b + q) * ldx] = xo[q] + v[b + q];
+            }
+        }
+        if (!SOME) return;
     }
 }
 
@@ -652,7 +669,7 @@ int onepass_fix_capacity()
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, (const void *)k_onepass_fix<kFixK, kFixW, double>, 64 * kFixW, 0) != hipSuccess)
+            &per_cu, (const void *)k_onepass_fix<kFixK, kFixW, false, double>, 64 * kFixW, 0) != hipSuccess)
         return 0;
     return cus * per_cu;
 }
@@ -667,30 +684,61 @@ size_t onepass_fix_scratch_bytes(int64_t n, int64_t batch)
     return wbytes + (size_t)units * kExRows * 64 * sizeof(double);
 }
 
+namespace {
+
+hipError_t launch_fix(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg64, const double *diag, int64_t n, const void *F,
+                      bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
+                      bool some, int wgs, int64_t most, hipStream_t s)
+{
+    const int64_t ngroups = onepass_fix_groups(n);
+    const int64_t units = (batch + 63) / 64 * ngroups;
+    if (units > (int64_t)UINT32_MAX / 2 || kSegPad % kFixW != 0) return hipErrorInvalidValue;
+    const Left at = onepass_fix_left(n, batch, scratch);
+    unsigned int *ctr = at.words, *fst = at.words + kTicketWords, *bst = fst + units;
+    double *ex = at.ex;
+    if (!some) {
+        hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((at.nwords + 255) / 256)), dim3(256), 0, s, at.words, at.nwords);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const void *fn = some ? (f32 ? (const void *)k_onepass_fix<kFixK, kFixW, true, float>
+                                 : (const void *)k_onepass_fix<kFixK, kFixW, true, double>)
+                          : (f32 ? (const void *)k_onepass_fix<kFixK, kFixW, false, float>
+                                 : (const void *)k_onepass_fix<kFixK, kFixW, false, double>);
+    int ng = (int)ngroups;
+    unsigned int un = (unsigned int)units;
+    void *args[] = {(void *)&fwd, (void *)&bwd, (void *)&seg64, (void *)&diag, (void *)&n,
+                    (void *)&ng, (void *)&F, (void *)&ldf, (void *)&X, (void *)&ldx,
+                    (void *)&batch, (void *)&ctr, (void *)&fst, (void *)&bst, (void *)&ex,
+                    (void *)&err, (void *)&un, (void *)&wgs};
+    return hipLaunchKernel(fn, dim3((unsigned)std::min(units, most)), dim3(64 * kFixW), args, 0, s);
+}
+
+}  // namespace
+
+Left onepass_fix_left(int64_t n, int64_t batch, void *scratch)
+{
+    Left left = {};
+    left.groups = (int)onepass_fix_groups(n);
+    left.nwords = kTicketWords + 2 * ((batch + 63) / 64 * left.groups);
+    left.words = (unsigned int *)scratch;
+    left.ex = (double *)((char *)scratch + ((size_t)left.nwords * sizeof(unsigned int) + 255) / 256 * 256);
+    return left;
+}
+
 hipError_t launch_onepass_fix(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg64,
                               const double *diag, int64_t n, const void *F, bool f32, int64_t ldf,
                               double *X, int64_t ldx, int64_t batch, void *scratch,
                               unsigned int *err, hipStream_t s)
 {
-    const int64_t ngroups = onepass_fix_groups(n);
-    const int64_t units = (batch + 63) / 64 * ngroups;
-    if (units > (int64_t)UINT32_MAX / 2 || kSegPad % kFixW != 0) return hipErrorInvalidValue;
-    const int64_t words = kTicketWords + 2 * units;
-    unsigned int *w = (unsigned int *)scratch;
-    unsigned int *ctr = w, *fst = w + kTicketWords, *bst = w + kTicketWords + units;
-    const size_t wbytes = ((size_t)words * sizeof(unsigned int) + 255) / 256 * 256;
-    double *ex = (double *)((char *)scratch + wbytes);
-    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, w, words);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const void *fn = f32 ? (const void *)k_onepass_fix<kFixK, kFixW, float>
-                         : (const void *)k_onepass_fix<kFixK, kFixW, double>;
-    int ng = (int)ngroups;
-    void *args[] = {(void *)&fwd, (void *)&bwd, (void *)&seg64, (void *)&diag, (void *)&n,
-                    (void *)&ng, (void *)&F, (void *)&ldf, (void *)&X, (void *)&ldx,
-                    (void *)&batch, (void *)&ctr, (void *)&fst, (void *)&bst, (void *)&ex,
-                    (void *)&err};
-    return hipLaunchKernel(fn, dim3((unsigned)units), dim3(64 * kFixW), args, 0, s);
+    return launch_fix(fwd, bwd, seg64, diag, n, F, f32, ldf, X, ldx, batch, scratch, err, false, 0, INT64_MAX, s);
+}
+
+hipError_t launch_onepass_fix_left(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg64, const double *diag, int64_t n,
+                                   const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch,
+                                   void *scratch, unsigned int *err, int wgs, int most, hipStream_t s)
+{
+    return launch_fix(fwd, bwd, seg64, diag, n, F, f32, ldf, X, ldx, batch, scratch, err, true, wgs, most, s);
 }
 
 // ---- group variant 6: kGroupSegRows-row segments, four per workgroup

@@ -186,6 +186,49 @@ __device__ __forceinline__ Tiles my_tiles(int ntiles)
     return t;
 }
 
+// The walk of a workgroup over its tiles.  leave: a bit for each, in their
+// order, of those that it passes by (null: none).
+typedef unsigned long long LeaveBits[kLeftTiles / 64];
+struct Walk {
+    Tiles mine;
+    const unsigned long long *leave;
+    int t, k;           // the tile, and its number among the workgroup's
+    unsigned int turn;  // tiles walked before it
+    __device__ __forceinline__ void settle()
+    {
+        while (leave && t < mine.end && __builtin_amdgcn_readfirstlane((int)(leave[k / 64] >> (k % 64)) & 1)) {
+            t += mine.step;
+            k++;
+        }
+    }
+    __device__ __forceinline__ void start()
+    {
+        t = mine.t0;
+        k = 0;
+        turn = 0;
+        settle();
+    }
+    __device__ __forceinline__ void next()
+    {
+        t += mine.step;
+        k++;
+        turn++;
+        settle();
+    }
+};
+
+// The tiles of this workgroup that k_find_left marked (stream.hip).
+template <int NW>
+__device__ __forceinline__ void read_left(const Left &left, const Tiles &mine, int cw, LeaveBits &leave)
+{
+    for (int k = threadIdx.x; k < kLeftTiles; k += 64 * NW) {
+        const int64_t t = mine.t0 + (int64_t)k * mine.step;
+        const unsigned long long m = __ballot(t < mine.end && *left_mark(left.ex, left.groups, t * cw) != 0);
+        if ((threadIdx.x & 63) == 0) leave[k / 64] = m;
+    }
+    __syncthreads();
+}
+
 // Forward recurrence over the block from (p2, p1).  STORE writes g over v.
 template <int K, bool STORE, typename R>
 __device__ __forceinline__ void sweep_forward(double (&v)[K], R &r, double &p2, double &p1)
@@ -210,6 +253,7 @@ struct Plain {
     static constexpr bool late = false;              // whether the backward records wait for the second sweep
     __device__ __forceinline__ void fetch() {}       // with the backward records, ahead of the second sweep
     __device__ __forceinline__ void ordered(int) {}  // in the tile's order, with the forward state
+    __device__ __forceinline__ void took(double, double) {}  // with the state taken from below
     __device__ __forceinline__ void ready() {}       // before the last sweep
     template <int k>
     __device__ __forceinline__ double out(double x) const  // what is stored for row k
@@ -307,7 +351,7 @@ typedef __attribute__((address_space(4))) const double *CTrunc;  // P_b, four do
 
 // Both sweeps of block q of the workgroup (block b of nblk of its tile, wave
 // w's par-th round): v holds the right-hand side on entry and x on exit.
-// CHECK false: what is left out is known not to matter (the caller says why).
+// CHECK false: nothing is left out, or Extra looks at it (took).
 template <int K, int NW, bool CHECK, typename Extra>
 __device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, const BwdRec *bwd, CSeg seg, CTrunc trunc, int b, int nblk,
                                               int D, unsigned int q, int w, int par, unsigned int turn,
@@ -386,6 +430,7 @@ __device__ __forceinline__ void stream_phases(double (&v)[K], Rec<K> &rc, const 
             atomicMin(&sh.first[turn % 32], b - D);
         }
     }
+    ex.took(z0, z1);
     ex.ready();
     sweep_backward<K, true>(v, rc, z0, z1, ex);
     // x is complete here: keep the sweep from sinking into the stores

@@ -1,6 +1,8 @@
 // stream.hip -- the sweeps of Sec. 2.4 as one stream down the rows of each
 // tile of systems (stream.h): f read once, x written once, nothing exchanged
 // through memory and nothing to clear before the launch.
+#include <algorithm>
+
 #include "stream.h"
 
 namespace pent {
@@ -89,6 +91,88 @@ __device__ __forceinline__ void stream_residual(double (&v)[K], const double (&x
     });
 }
 
+// Growth from two samples to the next that k_find_left looks for.  In a tail it
+// is at least 2^18 (a correction's chain, kTruncFix) or 2^36 (a solve's) from
+// one sample to the next, while of 64 systems of random values one in 2^16 has
+// such a place.
+constexpr double kSteep = 0x1p-14;
+constexpr int kSampleParts = 4, kSamplePart = 17;
+
+// Finds and marks the tiles that streaming sweeps had better leave to the
+// look-back form: those where some system's values grow by more than 1 / kSteep
+// from two samples to the next one below.  A system like that has long tails
+// above its sources, in which the truncated chain leaves out what counts, and
+// making up for that costs as much again as the sweeps, or more.  Up to 66
+// samples of every system: rows left.stride apart and the last one.  This
+// decides about time only.  Also clears the look-back form's words.
+// A workgroup takes every gridDim.x-th tile, its waves a quarter of the samples
+// each.  A launch of its own, 7 us of latency: inside the streaming kernels it
+// takes scalar registers that their sweeps then lack (a correction of 8192 x
+// 16384 took 40 us more).
+template <typename TI>
+__global__ __launch_bounds__(64 * kSampleParts) void k_find_left(const TI *F, int64_t ldf, int64_t tsf, int64_t n, int64_t batch,
+                                                                int cw, int ntiles, Left left)
+{
+    __shared__ int sus[2][kSampleParts];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), lane = threadIdx.x & 63;
+    const int cnt = (int)((n - 2) / left.stride) + 2, per = (cnt + kSampleParts - 1) / kSampleParts, s0 = w * per;
+    unsigned int any = 0;
+    for (int t = blockIdx.x, turn = 0; t < ntiles; t += gridDim.x, turn ^= 1) {
+        const int64_t j = (int64_t)t * cw + lane;
+        const bool act = lane < cw && j < batch;
+        const TI *c = F + (int64_t)t * tsf + (act ? lane : 0);
+        double a[kSamplePart + 2];
+#pragma unroll
+        for (int i = 0; i < kSamplePart + 2; i++)
+            a[i] = fabs((double)c[(s0 + i < cnt - 1 ? (int64_t)(s0 + i) * left.stride : n - 1) * ldf]);
+        bool here = false;
+#pragma unroll
+        for (int i = 0; i < kSamplePart; i++)
+            here = here || (i < per && s0 + i + 2 < cnt && fmax(a[i], a[i + 1]) <= kSteep * a[i + 2] && a[i + 2] > 0.0 && a[i + 2] <= __DBL_MAX__);
+        const bool one = __ballot(here) != 0;
+        if (lane == 0) sus[turn][w] = one;
+        __syncthreads();
+        unsigned int mark = 0;
+        for (int i = 0; i < kSampleParts; i++) mark |= (unsigned int)sus[turn][i];
+        if (w == 0 && act) *left_mark(left.ex, left.groups, j) = mark;
+        any |= mark;
+    }
+    if (threadIdx.x == 0) *left_word(left.words, blockIdx.x) = any;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < left.nwords; i += (int64_t)gridDim.x * blockDim.x)
+        if (i >= kTicketWords || i % kTicketStride == 0) left.words[i] = 0u;
+}
+
+// What a correction's block leaves out, P z, is held against x in the two rows
+// that it would be added to first, as block b - D left them in LDS before its
+// forward state went on.  A slot is filled again three rounds later, by when
+// its readers, fewer than NW blocks below, are done.  Where even twice the
+// largest entry that P may have makes no difference, P is not looked at.
+template <int NW>
+struct FixLds {
+    double x[3][NW][2][64];              // in the two rows below a wave's block, by its round
+    LeaveBits leave;
+    unsigned long long marks[kLeftTiles];  // a tile's systems in which something counts
+    Left left;  // (its values would take scalar registers all through the walk)
+};
+
+template <int NW>
+struct FixExtra : Plain {
+    FixLds<NW> &f;
+    CTrunc trunc;
+    int b, D, w, par, k;
+    __device__ __forceinline__ void took(double z0, double z1)
+    {
+        if (b < D) return;
+        const int lane = threadIdx.x & 63, ww = w >= D ? w - D : w - D + NW, pp = w >= D ? par : par == 0 ? 2 : par - 1;
+        const double most = kNegligible * fmax(fabs(f.x[pp][ww][0][lane]), fabs(f.x[pp][ww][1][lane]));
+        if (__ballot(!(2 * kTruncFix * fmax(fabs(z0), fabs(z1)) <= most) || z0 != z0 || z1 != z1) == 0) return;
+        const CTrunc P = trunc + 4 * (int64_t)(b - D);
+        const double c0 = fma(P[2], z1, P[0] * z0), c1 = fma(P[3], z1, P[1] * z0);
+        const unsigned long long m = __ballot(!(fmax(fabs(c0), fabs(c1)) <= most) || c0 != c0 || c1 != c1);
+        if (m != 0 && lane == 0) atomicOr(&f.marks[k], m);
+    }
+};
+
 // One refinement correction, x += A^{-1}(f - A x) in place, as a stream: each
 // block keeps its x beside the residual it turns into the correction, so x is
 // read once and written once (20 bytes per unknown with FP32 f; the look-back
@@ -97,34 +181,45 @@ __device__ __forceinline__ void stream_residual(double (&v)[K], const double (&x
 // links its forward state after block b has swept its own rows, and block b -
 // 1 waits for block b's backward state.  The correction is itself of the size
 // of the error it takes away, so its backward chain stops where it would
-// change that by kTruncFix, and nothing is checked (a system with a value that
-// is not finite has none left after its first solve).  The chain's depth sets
-// the time: of 12 waves D wait (N = 8192 x 16384 FP32, sigma = 100: D = 7,
-// for kTruncTarget, 910 us; D = 4, for kTruncFix, 673; the look-back form 1099).
+// change that by kTruncFix: what is left out is not seen in x, as long as x
+// does not fall by as much from one block to the one D above.  In the tails
+// above a source it does, and there a correction comes from the blocks far
+// below; so each tile with a system whose x falls is left to the look-back form
+// (k_find_left), and what a block leaves out is looked at against x: a system in which it
+// counts anywhere gets one more correction by that form.
+// The chain's depth sets the time: of 12 waves D wait (N = 8192 x 16384 FP32,
+// sigma = 100: D = 7, for kTruncTarget, 910 us; D = 4, for kTruncFix, 673; the
+// look-back form 1099).
 template <int K, int NW, int EU, bool NT, typename TI>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU))) void k_stream_fix(
-    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *diag, int D, int64_t n, int nblk,
-    const TI *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, int ntiles, unsigned int *err)
+    const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, const double *diag, int D, int64_t n, int nblk,
+    const TI *F, int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, int ntiles, Left left, unsigned int *err)
 {
     __shared__ StreamLds<NW, false> sh;
+    __shared__ FixLds<NW> fl;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int lane = threadIdx.x & 63;
     stream_init(sh);
-    const Tiles mine = my_tiles(ntiles);
-    int t = mine.t0, b = w;
+    Walk walk{my_tiles(ntiles), fl.leave};
+    if (threadIdx.x == 0) fl.left = left;
+    for (int i = threadIdx.x; i < kLeftTiles; i += 64 * NW) fl.marks[i] = 0;
+    read_left<NW>(left, walk.mine, cw, fl.leave);
+    walk.start();
+    int b = w, par = 0;
     auto skip = [&]() {
         while (b >= nblk) {
             b -= nblk;
-            t += mine.step;
+            walk.next();
         }
     };
     skip();
-    for (unsigned int q = w; t < mine.end; q += NW) {
-        const bool act = lane < cw && (int64_t)t * cw + lane < batch;
+    for (unsigned int q = w; walk.t < walk.mine.end; q += NW, par = par == 2 ? 0 : par + 1) {
+        const int64_t c0 = (int64_t)walk.t * cw;
+        const bool act = lane < cw && c0 + lane < batch;
         const unsigned int lo = act ? lane : 0;  // idle lanes repeat the tile's first column
         const int64_t r0 = (int64_t)b * K;
         const int L = (int)(n - r0 < K ? n - r0 : K);
-        double *xt = X + (int64_t)t * cw;
+        double *xt = X + c0;
         double v[K], x[K], h[4];
         // halo rows outside the matrix meet a zero diagonal entry
 #pragma unroll
@@ -133,19 +228,43 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
             h[i] = xt[(r < 0 ? 0 : r >= n ? n - 1 : r) * ldx + lo];
         }
         load_block<K, false, double>(x, xt + r0 * ldx, lo, ldx, L);
-        load_block<K, NT, TI>(v, F + (int64_t)t * cw + r0 * ldf, lo, ldf, L);
+        load_block<K, NT, TI>(v, F + c0 + r0 * ldf, lo, ldf, L);
         stream_residual<K>(v, x, h, diag, n, r0, L);
+        fl.x[par][w][0][lane] = h[2];
+        fl.x[par][w][1][lane] = h[3];
         __builtin_amdgcn_sched_barrier(0);
         Rec<K> rc;
         load_forward<K>(rc, fwd, r0);
         load_backward<K>(rc, bwd, r0);
-        stream_phases<K, NW, false, Plain>(v, rc, bwd, (CSeg)seg, nullptr, b, nblk, D, q, w, 0, 0, sh, err, Plain());
+        const FixExtra<NW> ex{{}, fl, (CTrunc)trunc, b, D, w, par, walk.k};
+        stream_phases<K, NW, false, FixExtra<NW>>(v, rc, bwd, (CSeg)seg, nullptr, b, nblk, D, q, w, 0, 0, sh, err, ex);
 #pragma unroll
         for (int k = 0; k < K; k++) v[k] = x[k] + v[k];
         if (act) store_block<K, NT>(v, xt + r0 * ldx, lane, ldx, L);
         b += NW;
         skip();
     }
+    __syncthreads();
+    for (int k = w; walk.mine.t0 + k * walk.mine.step < walk.mine.end; k += NW) {
+        const int64_t j = (int64_t)(walk.mine.t0 + k * walk.mine.step) * cw + lane;
+        if ((fl.marks[k] >> lane & 1) && lane < cw && j < batch) {
+            *left_mark(fl.left.ex, fl.left.groups, j) = 1;
+            *left_word(fl.left.words, 0) = 1;
+        }
+    }
+}
+
+// Rows between the samples of find_left: two in the rows of a chain, and not
+// more than it has room for.
+int64_t sample_stride(int64_t n, int depth) { return std::max<int64_t>(16 * depth, (n + 63) / 64); }
+
+template <typename TI>
+hipError_t find_left(const TI *F, int64_t ldf, int64_t tsf, int64_t n, int64_t batch, int cw, const Left &left, hipStream_t s)
+{
+    const int64_t ntiles = (batch + cw - 1) / cw;
+    hipLaunchKernelGGL(k_find_left<TI>, dim3((unsigned)std::min<int64_t>(ntiles, kLeftWgs)), dim3(64 * kSampleParts), 0, s, F, ldf,
+                       tsf, n, batch, cw, (int)ntiles, left);
+    return hipGetLastError();
 }
 
 // Whole rows on 128-byte lines.
@@ -156,7 +275,7 @@ hipError_t launch_k(const StreamPlan &p, int64_t n, const void *F, int64_t ldf, 
                     int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
 {
     const int64_t ntiles = (batch + cw - 1) / cw, nblk = (n + K - 1) / K;
-    const int64_t grid = (ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8;
+    const int64_t grid = stream_workgroups(batch, cw, p.cus);
     hipLaunchKernelGGL((k_stream<K, NW, EU, NT, TI>), dim3((unsigned)grid), dim3(64 * NW), 0, s, p.fwd, p.bwd, p.seg,
                        p.trunc, p.depth, n, (int)nblk, (const TI *)F, ldf, tsf, X, ldx, tsx, batch, cw, (int)ntiles, err);
     return hipGetLastError();
@@ -186,17 +305,23 @@ int stream_tile_width(int64_t batch, int cus)
     return best;
 }
 
-hipError_t launch_stream_fix(const StreamPlan &p, int depth, int64_t n, const double *diag, const void *F, bool f32,
-                             int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
+hipError_t launch_stream_fix(const StreamPlan &p, int64_t n, const double *diag, const void *F, bool f32,
+                             int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, const Left &left_,
+                             unsigned int *err, hipStream_t s)
 {
     constexpr int K = 32, NW = 12, EU = 3;
     const int64_t ntiles = (batch + cw - 1) / cw, nblk = (n + K - 1) / K;
-    const dim3 grid((unsigned)((ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8)), block(64 * NW);
+    const dim3 grid((unsigned)stream_workgroups(batch, cw, p.cus)), block(64 * NW);
+    Left left = left_;
+    left.stride = (int)sample_stride(n, p.depth);
+    if (!left.words || ntiles > (int64_t)kLeftTiles * grid.x) return hipErrorInvalidValue;
+    const hipError_t e = find_left<double>(X, ldx, cw, n, batch, cw, left, s);
+    if (e != hipSuccess) return e;
     const size_t ef = f32 ? sizeof(float) : sizeof(double);
     const bool nt = on_lines(F, ldf * ef) && on_lines(X, ldx * 8);
 #define PENT_FIX_GO(NT, T)                                                                                              \
-    hipLaunchKernelGGL((k_stream_fix<K, NW, EU, NT, T>), grid, block, 0, s, p.fwd, p.bwd, p.seg, diag, depth, n,          \
-                       (int)nblk, (const T *)F, ldf, X, ldx, batch, cw, (int)ntiles, err)
+    hipLaunchKernelGGL((k_stream_fix<K, NW, EU, NT, T>), grid, block, 0, s, p.fwd, p.bwd, p.seg, p.trunc, diag, p.depth, n, \
+                       (int)nblk, (const T *)F, ldf, X, ldx, batch, cw, (int)ntiles, left, err)
     if (f32 && nt) PENT_FIX_GO(true, float);
     else if (f32) PENT_FIX_GO(false, float);
     else if (nt) PENT_FIX_GO(true, double);

@@ -141,3 +141,115 @@ def test_grid_step_with_many_rows(torch, ny, ninst, nx, off):
         px.check()
         py.check()
     assert torch.equal(R, R2)
+
+
+def d4_extended(n, sigma, F):
+    """(I + sigma D4)^{-1} F with 50 digits, rounded to the 64-bit mantissa of a
+    long double: the recurrences of the factorisation row by row (no pivoting
+    is needed, the matrix is symmetric positive definite).  The far tails of a
+    solution have n roundings and more in them, so that a long double's own
+    arithmetic would show in a relative error of one rounding of a double."""
+    import decimal
+    D = decimal.Decimal
+    dg = oracle.assemble_d4(n, sigma)
+    with decimal.localcontext() as ctx:
+        ctx.prec = 50
+        a, b, c, d, e = ([D(float(v)) for v in getattr(dg, k)] for k in "abcde")
+        zero = D(0)
+        ga, de, al, be = [zero] * (n + 2), [zero] * (n + 2), [zero] * n, [zero] * n  # ga, de from row -2 on
+        for i in range(n):
+            be[i] = b[i] - a[i] * ga[i]
+            al[i] = 1 / (c[i] - a[i] * de[i] - be[i] * ga[i + 1])
+            ga[i + 2] = (d[i] - be[i] * de[i + 1]) * al[i]
+            de[i + 2] = e[i] * al[i]
+        out = np.empty(F.shape, np.longdouble)
+        for j in range(F.shape[1]):
+            g2, g1, g = zero, zero, []
+            for i in range(n):
+                g2, g1 = g1, (D(float(F[i, j])) - a[i] * g2 - be[i] * g1) * al[i]
+                g.append(g1)
+            x1, x2 = zero, zero
+            for i in range(n - 1, -1, -1):
+                x1, x2 = g[i] - ga[i + 2] * x1 - de[i + 2] * x2, x1
+                hi = float(x1)
+                out[i, j] = np.longdouble(hi) + np.longdouble(float(x1 - D(hi)))
+    return out
+
+
+def refined(torch, p, F, steps, f32=False):
+    X = torch.empty(F.shape, dtype=torch.float64, device="cuda")
+    p.solve_mixed(F.float() if f32 else F, X, steps)
+    p.check()
+    return X
+
+
+@pytest.mark.parametrize("n,m,sigma", [(2048, 5120, 100.0), (2050, 6000, 1.0), (4099, 5123, 30.0), (700, 9000, 0.1)])
+@pytest.mark.parametrize("f32,steps", [(False, 1), (True, 1), (False, 2)])
+def test_corrections_keep_far_tails(torch, n, m, sigma, f32, steps):
+    """A corrected solve is right to rounding in every stretch of rows on its
+    own, also where the solution is the far tail of a source many rows below:
+    with a relative error of n d4_tol in x and in the correction of such a
+    tail, what is left after it is the square of that and one rounding of x."""
+    print_case(test="fix_tails", n=n, m=m, sigma=sigma, f32=f32, steps=steps)
+    F = rand(torch, (n, m), n).float().double()
+    c = np.array([0, 1, 17, 63, 64, m - 1])
+    for col, row in zip(c[[0, 2, 3, 5]], (n - 1, n - 1, n // 2, n - 3)):
+        tail_columns(F, [col], row)
+    ref = d4_extended(n, sigma, F[:, c].cpu().numpy())
+    with pb.Plan.factor_d4(n, sigma) as p:
+        X = refined(torch, p, F, steps, f32)[:, c].cpu().numpy()
+    tol = 2 * U + (n * d4_tol(sigma)) ** 2
+    for r in range(0, n, 256):
+        big = np.max(np.abs(ref[r:r + 256]), axis=0)
+        err = np.max(np.abs(X[r:r + 256] - ref[r:r + 256]), axis=0)
+        assert np.all(err <= tol * big + 1e-290), (r, err / big)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+def test_corrections_beside_small_values(torch, f32):
+    """Systems whose solution is zero in a few rows at the end of a block of
+    32, and of order 1000 elsewhere: there the state that the correction's
+    chain leaves out counts against x, though x falls nowhere over the rows
+    that the kernel samples.  x and f are whole numbers, so the solution is
+    known.  The first solve is within d4_tol, the correction within d4_tol of
+    that and the compensated residual's u^2 sum |a x|, and one rounding of x."""
+    n, m, sigma = 8192, 5120, 4.0
+    print_case(test="fix_small_values", f32=f32)
+    F = rand(torch, (n, m), 7).float().double()
+    c = np.array([0, 3, 70, 71, m - 1])
+    x = np.random.Generator(np.random.PCG64(3)).integers(-1000, 1000, (n, len(c))).astype(float)
+    for k, at in enumerate((32, 32 * 33, 32 * 97, 32 * 130, 32 * 201)):
+        x[at - 2:at + 4, k] = 0.0
+    p = np.pad(x, ((2, 2), (0, 0)))
+    f = 4 * p[:-4] - 16 * p[1:-3] + 25 * p[2:-2] - 16 * p[3:-1] + 4 * p[4:]
+    old = F[:, c].clone()
+    F[:, c] = torch.from_numpy(f).cuda()
+    keep = np.setdiff1d(np.arange(m), c)
+    with pb.Plan.factor_d4(n, sigma) as plan:
+        X = refined(torch, plan, F, 1, f32)
+        F[:, c] = old
+        Y = refined(torch, plan, F, 1, f32)
+    assert torch.equal(X[:, keep], Y[:, keep])  # the neighbours' bits do not depend on it
+    tol = d4_tol(sigma)
+    err = np.abs(X[:, c].cpu().numpy() - x)
+    assert np.all(err <= U * np.abs(x) + 1000 * (tol ** 2 + 5 * 65 * U ** 2))
+
+
+def test_corrections_of_many_tiles(torch):
+    """More tiles to a workgroup than the streaming sweeps have slots for (32),
+    some left to the other form, with partial tiles; all columns by the
+    backward error, some against extended precision."""
+    n, m, sigma = 70, 64 * 256 * 33 + 21, 5.0
+    print_case(test="fix_many")
+    F = rand(torch, (n, m), 3)
+    F[:-1, 100_000:100_010] = 0.0
+    F[:-1, -1] = 0.0
+    eta = torch.empty(m, dtype=torch.float64, device="cuda")
+    X = torch.empty_like(F)
+    c = np.array([0, 99_999, 100_000, 100_009, 100_010, m - 2, m - 1])
+    with pb.Plan.factor_d4(n, sigma) as p:
+        p.solve_mixed(F, X, 1, eta)
+        p.check()
+    assert eta.max().item() <= 2 * U
+    ref = d4_extended(n, sigma, F[:, c].cpu().numpy())
+    assert np.max(colerr(X[:, c].cpu().numpy(), ref.astype(float))) <= 4 * U
