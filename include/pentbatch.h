@@ -134,9 +134,9 @@ int pent_solve_tiled(pent_handle h, double *F, int64_t batch, int64_t ld, int64_
  * layout of the second direction of an alternating-direction (ADI-style)
  * sweep over a 2-D grid (Sec. 4 names ADI as the route to 2-D and 3-D
  * problems).  Systems are transposed through LDS, so that memory moves in
- * contiguous runs of each: n <= 2048 in resident tiles, 10000 systems and
- * more of most matrices as streaming sweeps (neither takes scratch), else as
- * the single pass, allocating stream-ordered scratch on `stream`, when one
+ * contiguous runs of each: n <= 2048 in resident tiles (10000 systems and more
+ * of n <= 96 as streaming sweeps; neither takes scratch), else as the single
+ * pass, allocating stream-ordered scratch on `stream`, when one
  * tile of it fits on the device; else one lane per system.  A single-pass
  * wait that runs out is reported by pent_check, as for pent_solve. */
 int pent_solve_strided(pent_handle h, double *F, int64_t batch, int64_t ld, void *stream);
@@ -159,9 +159,11 @@ int pent_solve_strided(pent_handle h, double *F, int64_t batch, int64_t ld, void
  *             each evaluates r = f - A x in compensated FP64 (every product
  *             and sum carried with its rounding error), solves A d = r and
  *             sets x += d.  Where the solve runs as the single pass (kind 4)
- *             each correction is one fused pass too (the residual formed as
- *             the blocks load, x updated in place as they store); else three
- *             kernels (residual, solve, update).
+ *             or as streaming sweeps each correction is one fused pass too
+ *             (the residual formed as the blocks load, x updated in place as
+ *             they store; a streaming one is followed by the single pass over
+ *             the systems for which its shortened chain does not do); else
+ *             three kernels (residual, solve, update).
  *   eta_out : optional DEVICE array of batch doubles; receives each system's
  *             backward error ||f - A x||_inf / (||A||_inf ||x||_inf +
  *             ||f||_inf) with the residual evaluated compensated (NaN or Inf
@@ -343,9 +345,9 @@ int pent_rewrite_check(const void *work, int64_t n, int64_t *system, int64_t *ro
  * decoupled look-back, the last two unknowns formed by the first block of
  * every 64-system tile, the update applied before the one store) or the
  * E-solve followed by two light kernels; both take stream-ordered scratch.
- * Under the automatic schedule, n <= 2050 and a batch that fits the device in
- * one turn, it is one kernel that holds whole systems in a workgroup and takes
- * no scratch.
+ * Under the automatic schedule, n <= 4098 and a batch that fits the device in
+ * one turn or so (n <= 130, and long chains up to n = 1026, beyond that too), it
+ * is one kernel that holds whole systems in a workgroup and takes no scratch.
  *
  * pent_cyclic_factor: a..e HOST FP64 arrays of length n, row-indexed and
  *   wrapped: row i holds a[i] at column (i-2) mod n, b[i] at (i-1) mod n,
@@ -387,17 +389,21 @@ int pent_cyclic_destroy(pent_cyclic c);
  *   of one 64-system tile fits on the device at once), kind 1 the E-solve
  *   followed by the update kernels (and, for the step, a separate stencil
  *   kernel), kind 2 single pass with seg_rows in {32, 64} (still falls back
- *   to kind 1 when the blocks would not fit).  With 64 rows and at least 8192
- *   systems the single pass runs as streaming sweeps where the matrix allows
- *   it (see pent_set_schedule, kind 4).
- * pent_cyclic_query_schedule: the form a solve (cn = 0) or step (cn = 1) of
- *   `batch` systems runs: kind 1 or 2, seg_rows 0 unless kind 2.
+ *   to kind 1 when the blocks would not fit).  Under kind 0 the single pass
+ *   runs in resident tiles or, from 10000 systems, as streaming sweeps where
+ *   the matrix allows it (see pent_set_schedule, also for the data for which
+ *   kind 2 is to be forced).
+ * pent_cyclic_query_schedule: the schedule of a solve (cn = 0) or step (cn =
+ *   1) of `batch` systems: kind 1 or 2, seg_rows 0 unless kind 2.
+ * pent_cyclic_query_form: the form in which it runs, PENT_FORM_SCHEDULE (the
+ *   kernels of that kind), _RESIDENT or _STREAM.
  * pent_cyclic_check: blocking; PENT_TIMEOUT if a single-pass wait on this
  *   handle ran out since the last check (values of that call are wrong). */
 int pent_cyclic_cn_step(pent_cyclic c, const double *C, int64_t ldc, double *X, int64_t ldx,
                         int64_t batch, void *stream);
 int pent_cyclic_set_schedule(pent_cyclic c, int kind, int seg_rows);
 int pent_cyclic_query_schedule(pent_cyclic c, int64_t batch, int cn, int *kind, int *seg_rows);
+int pent_cyclic_query_form(pent_cyclic c, int64_t batch, int cn, int *form);
 int pent_cyclic_check(pent_cyclic c);
 
 /* ----------------------------------------------------------- inspection --
@@ -434,17 +440,21 @@ int64_t pent_size(pent_handle h); /* n, or -1 for a bad handle */
  *           the blocks of one 64-system tile could not all be resident at
  *           once.  Its waits are bounded; a wait that runs out (only possible
  *           when other work holds most of the device) leaves wrong values in
- *           that solve and is reported by pent_check.  With 64-row
- *           segments and at least 5120 systems, and where the matrix carries
- *           a back substitution's state less than 2^-72 of itself over some
- *           512 rows, the same one pass runs as streaming sweeps instead:
- *           a workgroup walks down the rows of whole tiles, waits only
- *           inside itself and needs no scratch (a form of this kind; the
- *           automatic schedule also takes it for smaller systems in large
- *           batches).  The number of
+ *           that solve and is reported by pent_check.  The number of
  *           segments per workgroup (4) can be set to 2, 4 or 8 with the
  *           environment variable PENT_ONEPASS_WAVES, read once per process
- *           (tuning).
+ *           (tuning; the automatic schedule then neither streams nor takes
+ *           resident tiles ahead of its kind).
+ * The automatic schedule runs one pass of its own in the place of kinds 2 to 4
+ * for large batches (from 5120 systems, in the resident tiles' place from
+ * 2560), where the matrix carries a back substitution's state less than 2^-72
+ * of itself over some 512 rows: streaming sweeps, in which a workgroup walks
+ * down the rows of whole tiles, waits only inside itself and needs no scratch.
+ * Ordinary data take 13 to 40% less time so than by kind 4.  A right-hand side
+ * with long stretches above its sources in which the solution falls by many
+ * orders of magnitude (compact support) can take up to a quarter more where n
+ * is below some 8000 rows: what the sweeps leave out there is added
+ * afterwards.  For such data kind 4 (64) is the schedule to force.
  * Returns PENT_INVALID_VALUE for an unknown kind or seg_rows. */
 int pent_set_schedule(pent_handle h, int kind, int seg_rows);
 
@@ -469,10 +479,21 @@ int pent_check(pent_handle h);
 int pent_autotune(pent_handle h, int64_t batch, int *kind_out, int *seg_rows_out, double *ms_out,
                   void *stream);
 
-/* The schedule pent_solve would use for `batch` systems on this handle
- * (kind as above; seg_rows is the segment height for kinds 2 and 4, the
- * prefetch depth for kind 1, 0 for kind 3).  Host-only, no HIP call. */
+/* The schedule of `batch` systems on this handle (kind as above; seg_rows is
+ * the segment height for kinds 2 and 4, the prefetch depth for kind 1, 0 for
+ * kind 3): by it the workspaces are sized, and pent_solve_tiled accepts a
+ * call.  What runs is that kind's kernels (PENT_FORM_SCHEDULE; kind 3's are the
+ * resident tiles) or, under the automatic schedule, one of the two forms that
+ * it has beside them.  Host-only, no HIP call. */
 int pent_query_schedule(pent_handle h, int64_t batch, int *kind, int *seg_rows);
+
+/* The form in which `batch` systems are solved: in place and batch-fastest
+ * (pent_solve; system_major == 0) or system-major (pent_solve_strided).
+ * Host-only, no HIP call. */
+#define PENT_FORM_SCHEDULE 0 /* the kernels of the schedule (system-major: one pass or one lane per system) */
+#define PENT_FORM_RESIDENT 1 /* whole systems resident in a workgroup, one kernel, no scratch */
+#define PENT_FORM_STREAM 2   /* streaming sweeps, one kernel */
+int pent_query_form(pent_handle h, int64_t batch, int system_major, int *form);
 
 /* ---------------------------------------------------------- measurement --
  * The copy ceiling of the batch-fastest single pass: dst = src for an

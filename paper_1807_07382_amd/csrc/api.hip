@@ -446,13 +446,17 @@ bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
 // systems at every n (us, streaming / before: n = 2048 58 / 56 at 5003, 57 /
 // 81 at 8192; n = 4096 110 / 112 and 110 / 159; n = 8192 230 / 224 and 214 /
 // 290).  In the place of the resident tiles (n above 2048, past a turn of theirs)
-// from half as many (n = 2500 x 4000 54 / 72, n = 4096 x 2560 52 / 75).  A
-// schedule forced to 64-row single pass streams by the same rule; any other
-// forced schedule is run as asked.
+// from half as many (n = 2500 x 4000 54 / 72, n = 4096 x 2560 52 / 75).  Those
+// are times of ordinary data.  Where a solution falls by more than 2^18 over
+// the rows of a chain, what was left out is added afterwards, and of a few
+// thousand rows that can be most (4096 x 65536 at sigma = 1: 831, by look-back
+// 951; with a top-hat in every system 1069 and 949; 2048 x 65536 418 / 478, with
+// sources in the bottom rows only 614 / 478; 8192 x 32768 814 / 1064 and 939 / 1065).
+// A forced schedule is run as asked: kind 4 is the look-back form, whose time
+// does not depend on the data.
 bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, StreamPlan *p)
 {
-    const bool single = kind == 4 && seg_rows == 64;
-    if ((!single && h->sched_kind != 0) || onepass_waves_override()) return false;
+    if (h->sched_kind != 0 || onepass_waves_override()) return false;
     if ((batch + 31) / 32 > INT32_MAX) return false;
     if (batch < (kind == 3 ? 2560 : 5120)) return false;
     return stream_plan(h, 32, p) || stream_plan(h, 64, p);
@@ -545,6 +549,17 @@ int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int6
     const int64_t summ_ld = (batch + 63) / 64 * 64;
     return hip_status(launch_part_sweep_io(h->d_fwd, h->d_bwd, seg, h->n, h->npad, seg_rows, f,
                                            f32, ldf, x, ldx, batch, (double *)summ, summ_ld, s));
+}
+
+// The form that solve_io runs in place (PENT_FORM_*).
+int solve_form(const pent_plan *h, int64_t batch)
+{
+    int kind, seg_rows;
+    io_schedule(h, batch, true, &kind, &seg_rows);
+    StreamPlan sp;
+    if (resident_route(h, kind, batch)) return PENT_FORM_RESIDENT;
+    if (stream_route(h, kind, seg_rows, batch, &sp)) return PENT_FORM_STREAM;
+    return kind == 3 ? PENT_FORM_RESIDENT : PENT_FORM_SCHEDULE;
 }
 
 // solve_io with its scratch taken from the stream-ordered allocator.
@@ -846,11 +861,12 @@ bool cyc_single_pass(pent_cyclic c, int64_t batch, bool cn)
            cyc_onepass_units(c->n, sr, batch) <= (int64_t)UINT32_MAX / 2;
 }
 
-// Systems from which the periodic single pass runs as streaming sweeps (us,
-// streaming / look-back, solve and step: N = 4096 x 5003 135 / 135 and 171 /
-// 139, x 8192 170 / 173 and 179 / 179, x 16384 212 / 322 and 219 / 329; N =
-// 1537 x 5003 62 / 61 and 67 / 63, x 16384 91 / 137 and 85 / 142).
-constexpr int64_t kCycStreamBatch = 8192;
+// Systems from which the periodic single pass runs as streaming sweeps (the step,
+// us, streaming / look-back, and the same with sources in the bottom rows only:
+// N = 1537 x 8192 68 / 67 and 97 / 66, x 10000 70 / 91 and 103 / 91, x 16384 89 / 140
+// and 125 / 138; N = 4096 x 8192 165 / 180 and 192 / 179, x 10000 170 / 208 and 207 /
+// 207, x 16384 220 / 327 and 254 / 328).
+constexpr int64_t kCycStreamBatch = 10000;
 
 // Tile width of the resident form for a periodic solve or step under the
 // automatic schedule, or 0 (us, solve and step, resident / look-back: N = 256 x 256
@@ -875,6 +891,13 @@ int cyc_resident_width(const pent_cyclic_s *c, int64_t batch)
     return resident_width(E->n, batch, E->cus);
 }
 
+// Whether a periodic solve or step that runs as one pass, and not in resident
+// tiles, runs as streaming sweeps.
+bool cyc_stream_route(const pent_cyclic_s *c, int64_t batch, StreamPlan *sp)
+{
+    return c->kind == 0 && batch >= kCycStreamBatch && c->ends > 0 && !onepass_waves_override() && stream_plan(c->E, 32, sp);
+}
+
 int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
                    int64_t batch, hipStream_t s)
 {
@@ -886,8 +909,7 @@ int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double 
                                                  c->d_cd, c->d_Z, c->d_aux, E->n, width, cn, F, ldf, X, ldx, batch, s,
                                                  c->uni ? c->uc : nullptr));
     }
-    if (c->seg_rows == 64 && batch >= kCycStreamBatch && c->ends > 0 && !onepass_waves_override() &&
-        stream_plan(c->E, 32, &sp)) {
+    if (cyc_stream_route(c, batch, &sp)) {
         const int cw = stream_tile_width(batch, c->E->cus);
         void *dx = nullptr;
         hipError_t e = scratch_alloc(&dx, cyc_stream_scratch_bytes(batch, cw), s);
@@ -1924,6 +1946,17 @@ int pent_cyclic_query_schedule(pent_cyclic c, int64_t batch, int cn, int *kind, 
     return ret(PENT_OK);
 }
 
+int pent_cyclic_query_form(pent_cyclic c, int64_t batch, int cn, int *form)
+{
+    if (!cvalid(c) || batch < 0 || !form) return ret(PENT_INVALID_VALUE);
+    StreamPlan sp;
+    *form = PENT_FORM_SCHEDULE;
+    if (!cyc_single_pass(c, batch, cn != 0)) return ret(PENT_OK);
+    if (cyc_resident_width(c, batch)) *form = PENT_FORM_RESIDENT;
+    else if (cyc_stream_route(c, batch, &sp)) *form = PENT_FORM_STREAM;
+    return ret(PENT_OK);
+}
+
 int pent_cyclic_check(pent_cyclic c)
 {
     if (!cvalid(c)) return ret(PENT_INVALID_VALUE);
@@ -2106,8 +2139,18 @@ int pent_set_refine_tolerance(pent_handle h, double tol)
 int pent_query_schedule(pent_handle h, int64_t batch, int *kind, int *seg_rows)
 {
     if (!valid(h) || batch < 0 || !kind || !seg_rows) return ret(PENT_INVALID_VALUE);
-    io_schedule(h, batch, true, kind, seg_rows);  // what an in-place pent_solve runs
+    io_schedule(h, batch, true, kind, seg_rows);
     if (*kind == 3) *seg_rows = 0;
+    return ret(PENT_OK);
+}
+
+int pent_query_form(pent_handle h, int64_t batch, int system_major, int *form)
+{
+    if (!valid(h) || batch < 0 || !form) return ret(PENT_INVALID_VALUE);
+    StreamPlan sp;
+    if (!system_major) *form = solve_form(h, batch);
+    else if (t_resident_route(h, batch)) *form = PENT_FORM_RESIDENT;
+    else *form = t_stream_route(h, batch, &sp) ? PENT_FORM_STREAM : PENT_FORM_SCHEDULE;
     return ret(PENT_OK);
 }
 

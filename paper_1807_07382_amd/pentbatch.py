@@ -28,6 +28,7 @@ NOT_SUPPORTED = 7
 TIMEOUT = 8
 
 # group solve modes (pent_group_solve)
+FORM_SCHEDULE, FORM_RESIDENT, FORM_STREAM = 0, 1, 2
 GROUP_FP64 = 0
 GROUP_MIXED = 1       # rejected with NOT_SUPPORTED (see the header)
 GROUP_PER_MATRIX = 2
@@ -76,6 +77,7 @@ SIGNATURES = {
     "pent_cyclic_cn_step": (_I, [_P, _P, _I64, _P, _I64, _I64, _P]),
     "pent_cyclic_set_schedule": (_I, [_P, _I, _I]),
     "pent_cyclic_query_schedule": (_I, [_P, _I64, _I, ctypes.POINTER(_I), ctypes.POINTER(_I)]),
+    "pent_cyclic_query_form": (_I, [_P, _I64, _I, ctypes.POINTER(_I)]),
     "pent_cyclic_check": (_I, [_P]),
     "pent_rewrite_workspace_size": (ctypes.c_size_t, [_I64, _I64]),
     "pent_solve_rewrite": (_I, [_I64, _P, _P, _P, _P, _P, _I64, _P, _I64, _I64, _P,
@@ -87,6 +89,7 @@ SIGNATURES = {
     "pent_set_schedule": (_I, [_P, _I, _I]),
     "pent_check": (_I, [_P]),
     "pent_query_schedule": (_I, [_P, _I64, ctypes.POINTER(_I), ctypes.POINTER(_I)]),
+    "pent_query_form": (_I, [_P, _I64, _I, ctypes.POINTER(_I)]),
     "pent_stream_copy": (_I, [_P, _I64, _P, _I64, _I64, _I64, _P]),
     "pent_stream_copy_shaped": (_I, [_P, _I64, _P, _I64, _I64, _I64, _I, _I, _P]),
     "pent_last_status": (_I, []),
@@ -300,18 +303,26 @@ class Plan:
 
     def autotune(self, batch: int, stream=None):
         """Time the schedules for ``batch`` systems and keep the fastest;
-        returns (kind, seg_rows, ms)."""
+        returns (kind, seg_rows, ms), kind 0 for the automatic one."""
         k, sr, ms = _I(0), _I(0), _D(0.0)
         _check(lib().pent_autotune(self._h, int(batch), ctypes.byref(k), ctypes.byref(sr),
                                    ctypes.byref(ms), _stream_ptr(stream)), "autotune")
         return int(k.value), int(sr.value), float(ms.value)
 
     def schedule_for(self, batch: int):
-        """(kind, seg_rows) pent_solve uses for ``batch`` systems."""
+        """(kind, seg_rows) of the schedule for ``batch`` systems; form_for
+        says in which form the automatic one runs it."""
         k, sr = _I(0), _I(0)
         _check(lib().pent_query_schedule(self._h, int(batch), ctypes.byref(k), ctypes.byref(sr)),
                "query_schedule")
         return int(k.value), int(sr.value)
+
+    def form_for(self, batch: int, system_major: bool = False) -> int:
+        """FORM_SCHEDULE, FORM_RESIDENT or FORM_STREAM: what runs for ``batch``
+        systems."""
+        f = _I(0)
+        _check(lib().pent_query_form(self._h, int(batch), int(bool(system_major)), ctypes.byref(f)), "query_form")
+        return int(f.value)
 
     def set_schedule(self, kind: int, seg_rows: int = 0):
         _check(lib().pent_set_schedule(self._h, int(kind), int(seg_rows)), "set_schedule")
@@ -593,6 +604,12 @@ class Cyclic:
                                                 ctypes.byref(k), ctypes.byref(sr)),
                "cyclic query_schedule")
         return int(k.value), int(sr.value)
+
+    def form_for(self, batch: int, cn: bool = False) -> int:
+        """As Plan.form_for."""
+        f = _I(0)
+        _check(lib().pent_cyclic_query_form(self._h, int(batch), int(bool(cn)), ctypes.byref(f)), "cyclic query_form")
+        return int(f.value)
 
     def check(self):
         """Raise PentError(TIMEOUT) if a single-pass wait ran out (blocking)."""

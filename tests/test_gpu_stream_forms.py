@@ -6,7 +6,8 @@ import pytest
 import oracle
 from paper_1807_07382_amd import pentbatch as pb
 from tests._gpu import U, colerr, d4_tol, print_case, torch_dev
-from tests.test_gpu_stream import probes, rand
+from tests.test_gpu_stream import cyc_lu, probes, rand
+from tests.test_oracle_pins import random_dd
 
 pytestmark = pytest.mark.gpu
 
@@ -38,7 +39,7 @@ def circulant_lu(stencil, n):
 def test_periodic_one_sided_reach(torch, stencil):
     """Solves and steps with matrices whose border reaches further up from the
     bottom than down from the top."""
-    n, m = 4100, 8200
+    n, m = 4100, 10011
     print_case(test="periodic_reach", stencil=stencil)
     C = rand(torch, (n, m), 5)
     X = torch.empty_like(C)
@@ -46,6 +47,7 @@ def test_periodic_one_sided_reach(torch, stencil):
     Cc = C[:, c].cpu().numpy()
     lu, A, kappa = circulant_lu(np.array(stencil, float), n)
     with pb.Cyclic.factor(*[np.full(n, float(v)) for v in stencil]) as cy:
+        assert cy.form_for(m) == (pb.FORM_STREAM if stencil[1] >= -13 and stencil[0] else pb.FORM_SCHEDULE)
         cy.cn_step(C, X)
         F = cy.solve_(C)
         cy.check()
@@ -93,6 +95,7 @@ def test_system_major_few_blocks(torch, n, m, ld, off, sigma):
     B = F.clone()
     F[5, n // 2] = float("nan")
     with pb.Plan.factor_d4(n, sigma) as p:
+        assert p.form_for(m, True) == (pb.FORM_STREAM if n <= 96 else pb.FORM_RESIDENT)
         p.solve_strided_(F[:, :n])
         p.check()
     assert torch.equal(F[:, n:], B[:, n:])
@@ -113,6 +116,7 @@ def test_system_major_far_tails(torch, n, m, sigma):
     tail_columns(F.t(), c[1:2], n // 2)
     ref = oracle.solve(oracle.assemble_d4(n, sigma), np.ascontiguousarray(F[c].T.cpu().numpy()))
     with pb.Plan.factor_d4(n, sigma) as p:
+        assert p.form_for(m, True) == (pb.FORM_RESIDENT if n <= 2048 else pb.FORM_SCHEDULE)
         p.solve_strided_(F)
         p.check()
     assert_tails(F[c].T.cpu().numpy(), ref, sigma, 128)
@@ -135,6 +139,7 @@ def test_grid_step_with_many_rows(torch, ny, ninst, nx, off):
     R = torch.empty(ny * ninst * nx + off, dtype=torch.float64, device="cuda")[off:].view(ny, ninst, nx)
     R2 = torch.empty((ny, ninst, nx), dtype=torch.float64, device="cuda")
     with pb.Plan.factor_d4(nx, sigma) as px, pb.Plan.factor_d4(ny, sigma) as py:
+        assert px.form_for(ny * ninst, True) == (pb.FORM_STREAM if nx <= 96 else pb.FORM_RESIDENT)
         pb.ch2d_rhs(C, R2, dt, h)
         px.solve_strided_(R2.view(ny * ninst, nx))
         pb.ch2d_step(px, py, C, R, dt, h)
@@ -177,6 +182,7 @@ def d4_extended(n, sigma, F):
 
 
 def refined(torch, p, F, steps, f32=False):
+    assert p.form_for(F.shape[1]) == pb.FORM_STREAM
     X = torch.empty(F.shape, dtype=torch.float64, device="cuda")
     p.solve_mixed(F.float() if f32 else F, X, steps)
     p.check()
@@ -248,8 +254,166 @@ def test_corrections_of_many_tiles(torch):
     X = torch.empty_like(F)
     c = np.array([0, 99_999, 100_000, 100_009, 100_010, m - 2, m - 1])
     with pb.Plan.factor_d4(n, sigma) as p:
+        assert p.form_for(m) == pb.FORM_STREAM
         p.solve_mixed(F, X, 1, eta)
         p.check()
     assert eta.max().item() <= 2 * U
     ref = d4_extended(n, sigma, F[:, c].cpu().numpy())
     assert np.max(colerr(X[:, c].cpu().numpy(), ref.astype(float))) <= 4 * U
+
+
+@pytest.mark.parametrize("n,m,pad", [(777, 12000, 0), (1500, 9001, 3), (2600, 6000, 16)])
+def test_general_matrix_and_bits_by_column(torch, n, m, pad):
+    """Non-symmetric matrices, rows on lines of their own and not; every
+    system has the same bits wherever it sits in the batch, and a system that
+    is zero but for one row does not change its neighbours'."""
+    print_case(test="stream_general", n=n, m=m, pad=pad)
+    dg = random_dd(n, seed=n)
+    B = rand(torch, (n, m + pad), 3)
+    F = B[:, :m]
+    perm = torch.randperm(m, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    c = probes(m, 48)
+    with pb.Plan.factor(*dg) as p:
+        assert p.form_for(m) == pb.FORM_STREAM
+        X = p.solve_(B.clone()[:, :m])
+        Y = p.solve_(F[:, perm].contiguous())
+        Z = F.clone()
+        tail_columns(Z, c, n - 1)
+        ref_tail = oracle.solve(dg, np.ascontiguousarray(Z[:, c].cpu().numpy()))
+        p.solve_(Z)
+        p.check()
+    assert torch.equal(X[:, perm], Y)
+    keep = np.setdiff1d(np.arange(m), c)
+    assert torch.equal(X[:, keep], Z[:, keep])
+    ref = oracle.solve(dg, np.ascontiguousarray(F[:, c].cpu().numpy()))
+    assert np.max(colerr(X[:, c].cpu().numpy(), ref)) <= 1e-13
+    for r in range(0, n, 64):
+        big = np.max(np.abs(ref_tail[r:r + 64]), axis=0)
+        err = np.max(np.abs(Z[r:r + 64][:, c].cpu().numpy() - ref_tail[r:r + 64]), axis=0)
+        assert np.all(err <= n * 1e-13 * big + 1e-290)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+def test_more_tiles_than_slots(torch, f32):
+    """More tiles to a workgroup than the 32 slots in which it notes what its
+    blocks left out, some with far tails, one with a NaN, a partial last one."""
+    n, m, sigma = 160, 64 * 256 * 33 + 21, 0.1
+    print_case(test="stream_many", f32=f32)
+    F = rand(torch, (n, m), 3).float()
+    F = F if f32 else F.double()
+    c = np.array([0, 63, 64 * 256 * 16, 64 * 256 * 32 + 5, m - 1])
+    tail_columns(F, c, n - 1)
+    F[n // 2, 200] = float("nan")
+    other = np.array([1, 62, 199, 201, 64 * 256 * 32 + 6, m - 2])
+    X = torch.empty((n, m), dtype=torch.float64, device="cuda")
+    with pb.Plan.factor_d4(n, sigma) as p:
+        assert p.form_for(m) == pb.FORM_STREAM
+        p.solve_mixed(F, X, 0)
+        p.check()
+    dg = oracle.assemble_d4(n, sigma)
+    assert not bool(torch.isfinite(X[:, 200]).any())
+    ref = oracle.solve(dg, np.ascontiguousarray(F[:, other].double().cpu().numpy()))
+    assert np.max(colerr(X[:, other].cpu().numpy(), ref)) <= d4_tol(sigma)
+    ref = oracle.solve(dg, np.ascontiguousarray(F[:, c].double().cpu().numpy()))
+    assert_tails(X[:, c].cpu().numpy(), ref, sigma, 32)
+
+
+# E rows on and off block edges, one to 32 rows in the last block; few and many
+# end blocks; tiles of 32 to 64 systems
+@pytest.mark.parametrize("n,m,pad,sigma", [(514, 10000, 0, 0.1), (515, 16400, 3, 1.0), (1027, 10000, 16, 50.0),
+                                           (1057, 10001, 0, 50.0), (2047, 12300, 0, 300.0), (4097, 10240, 0, 0.01)])
+def test_periodic_edges(torch, n, m, pad, sigma):
+    """Periodic solves and steps against an independent sparse LU (the bounds
+    are those of the periodic streaming test)."""
+    print_case(test="cyc_edges", n=n, m=m, pad=pad, sigma=sigma)
+    B = rand(torch, (n, m + pad), n + 1)
+    X = torch.full((n, m + pad), 7.0, dtype=torch.float64, device="cuda")
+    F = B.clone()
+    c = probes(m, 48)
+    Bc = B[:, c].cpu().numpy()
+    lu, A = cyc_lu(n, sigma)
+    with pb.Cyclic.factor_d4(n, sigma) as cy:
+        assert cy.form_for(m) == cy.form_for(m, True) == pb.FORM_STREAM
+        cy.solve_(F[:, :m])
+        cy.cn_step(B[:, :m], X[:, :m])
+        cy.check()
+    assert torch.equal(F[:, m:], B[:, m:]) and bool((X[:, m:] == 7.0).all())
+    assert np.max(colerr(F[:, c].cpu().numpy(), lu.solve(Bc))) <= d4_tol(sigma)
+    ref = lu.solve(2 * Bc - A @ Bc)
+    err = np.max(np.abs(X[:, c].cpu().numpy() - ref), axis=0)
+    assert np.all(err <= d4_tol(sigma) * (np.max(np.abs(ref), axis=0) + (2 + 16 * sigma) * np.max(np.abs(Bc), axis=0)))
+
+
+@pytest.mark.parametrize("n,m", [(1300, 10000), (1537, 16403)])
+def test_periodic_varying_rows(torch, n, m):
+    """Diagonals that differ from row to row (the step reads them per row), and
+    the look-back form of the same calls."""
+    print_case(test="cyc_rows", n=n, m=m)
+    g = np.random.Generator(np.random.PCG64(2))
+    dg = [g.uniform(-1, 1, n) for _ in range(5)]
+    dg[2] = 5.0 + g.uniform(0, 1, n)
+    A = np.zeros((n, n))
+    for o in range(-2, 3):
+        for r in range(n):
+            A[r, (r + o) % n] += dg[o + 2][r]
+    C = rand(torch, (n, m), 6)
+    X, Y = torch.empty_like(C), torch.empty_like(C)
+    c = probes(m, 64)
+    Cc = C[:, c].cpu().numpy()
+    with pb.Cyclic.factor(*dg) as cy:
+        assert cy.form_for(m) == cy.form_for(m, True) == pb.FORM_STREAM
+        cy.cn_step(C, X)
+        F = cy.solve_(C.clone())
+        cy.set_schedule(2, 64)
+        assert cy.form_for(m) == cy.form_for(m, True) == pb.FORM_SCHEDULE
+        cy.cn_step(C, Y)
+        cy.check()
+    kappa = np.linalg.cond(A, np.inf)
+    assert np.max(colerr(F[:, c].cpu().numpy(), np.linalg.solve(A, Cc))) <= 64 * U * kappa
+    ref = np.linalg.solve(A, 2 * Cc - A @ Cc)
+    tol = 64 * U * kappa * 12 * np.max(np.abs(Cc))
+    assert np.max(np.abs(X[:, c].cpu().numpy() - ref)) <= tol
+    assert float((X - Y).abs().max()) <= 2 * tol
+
+
+@pytest.mark.parametrize("row", [0, 600, 1199])
+def test_periodic_far_tails_and_non_finite(torch, row):
+    """The tails of one non-zero row both ways round, as by the look-back form,
+    in each stretch of rows; a NaN spoils its own system only."""
+    n, m, sigma = 1200, 10000, 20.0
+    print_case(test="cyc_tail", row=row)
+    F = rand(torch, (n, m), 9)
+    c = np.array([0, 17, 63, 64, m - 1])
+    tail_columns(F, c, row)
+    with pb.Cyclic.factor_d4(n, sigma) as cy:
+        assert cy.form_for(m) == pb.FORM_STREAM
+        X = cy.solve_(F.clone())
+        G = F.clone()
+        G[n // 2, 70] = float("nan")
+        Y = cy.solve_(G)
+        cy.set_schedule(2, 64)
+        Z = cy.solve_(F)
+        cy.check()
+    assert_tails(X[:, c].cpu().numpy(), Z[:, c].cpu().numpy(), sigma, 100)
+    assert not bool(torch.isfinite(Y[:, 70]).any())
+    keep = [j for j in range(m) if j != 70]
+    assert torch.equal(X[:, keep], Y[:, keep])
+
+
+@pytest.mark.parametrize("n,m", [(2100, 6000), (4096, 16384)])
+def test_forced_single_pass_is_look_back(torch, n, m):
+    """A forced schedule runs its own kernels, also at sizes that the automatic
+    one streams, and the automatic one gives its bits again afterwards."""
+    print_case(test="forced", n=n, m=m)
+    F = rand(torch, (n, m), 2)
+    with pb.Plan.factor_d4(n, 5.0) as p:
+        assert p.form_for(m) == pb.FORM_STREAM
+        X = p.solve_(F.clone())
+        p.set_schedule(4, 64)
+        assert p.form_for(m) == pb.FORM_SCHEDULE and p.schedule_for(m) == (4, 64)
+        Y = p.solve_(F.clone())
+        p.set_schedule(0, 0)
+        Z = p.solve_(F.clone())
+        p.check()
+    assert torch.equal(X, Z)
+    assert float((X - Y).abs().max() / X.abs().max()) <= 2 * d4_tol(5.0)
