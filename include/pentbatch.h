@@ -467,10 +467,11 @@ int pent_check(pent_handle h);
 
 /* Autotune the schedule of this handle for `batch` systems: one lane per
  * system at prefetch depths 8/16/32, partitioned with 16/32/64 rows per
- * lane, (n <= 4096) the resident tile, and the single pass with 32/64-row
- * segments are timed on a scratch buffer of n x batch (allocated and freed
- * here) and the fastest is set as the handle's schedule (for every later
- * batch size).  Results are kept per process, keyed by (device
+ * lane, (n <= 4096) the resident tile, the single pass with 32/64-row
+ * segments and, where it runs none of these (pent_query_form), the automatic
+ * schedule (reported as kind 0) are timed on a scratch buffer of n x batch
+ * (allocated and freed here) and the fastest is set as the handle's schedule
+ * (for every later batch size).  Results are kept per process, keyed by (device
  * architecture, n, batch, element type), and appended to the text file named
  * by the environment variable PENT_TUNE_CACHE, which later processes read
  * back (a line measured on another architecture is never used).  Blocking.

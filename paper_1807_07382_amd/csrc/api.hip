@@ -1561,8 +1561,8 @@ int pent_autotune(pent_handle h, int64_t batch, int *kind_out, int *seg_rows_out
     }
     // (kind, seg_rows): one lane per system at three prefetch depths, the
     // partitioned sweep at three segment heights, the resident tile, the
-    // single pass at two segment heights
-    const int cands[9][2] = {{1, 8}, {1, 16}, {1, 32}, {2, 16}, {2, 32}, {2, 64}, {3, 0}, {4, 32}, {4, 64}};
+    // single pass at two segment heights, and the automatic schedule
+    const int cands[10][2] = {{1, 8}, {1, 16}, {1, 32}, {2, 16}, {2, 32}, {2, 64}, {3, 0}, {4, 32}, {4, 64}, {0, 0}};
     double *F = nullptr;
     void *work = nullptr;
     const size_t nF = (size_t)h->n * batch;
@@ -1585,7 +1585,9 @@ int pent_autotune(pent_handle h, int64_t batch, int *kind_out, int *seg_rows_out
         if (c[0] == 4) query_onepass_cap(h, c[1]);
         int ek, es;
         io_schedule(h, batch, true, &ek, &es);
-        if (ek != c[0]) continue;  // not runnable at this size (falls back)
+        // not runnable at this size (falls back); the automatic schedule only
+        // where it runs none of the others
+        if (c[0] != 0 ? ek != c[0] : solve_form(h, batch) == (ek == 3 ? PENT_FORM_RESIDENT : PENT_FORM_SCHEDULE)) continue;
         double ms = 0.0;
         st = time_ms([&] { return solve_io(h, F, false, batch, F, batch, batch, work, s); }, s, 3, &ms);
         if (st == PENT_OK && ms < best) {

@@ -289,3 +289,23 @@ def test_graph_survives_rebind_and_destroy(torch, destroy_group):
     graph.close()
     if not destroy_group:
         g.close()
+
+
+@pytest.mark.parametrize("n,m,form", [(4200, 256, pb.FORM_RESIDENT), (2100, 16384, pb.FORM_STREAM)])
+def test_autotune_knows_the_automatic_schedule(torch, tmp_path, monkeypatch, n, m, form):
+    """Where the automatic schedule runs a form that no other one has, and that
+    one is the fastest, the tuner keeps it (kind 0), in the cache file too."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("PENT_TUNE_CACHE", str(cache))
+    print_case(test="autotune_auto", n=n, m=m)
+    with pb.Plan.factor_d4(n, 1.0) as p:
+        assert p.form_for(m) == form
+        p.set_schedule(4, 64)
+        kind, seg, ms = p.autotune(m)
+        assert (kind, seg) == (0, 0) and ms > 0
+        assert p.form_for(m) == form
+    assert cache.read_text().split()[1:6] == [str(n), str(m), "0", "0", "0"]
+    with pb.Plan.factor_d4(n, 1.0) as q:
+        q.set_schedule(2, 64)
+        assert q.autotune(m)[:2] == (0, 0)
+        assert q.form_for(m) == form
