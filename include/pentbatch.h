@@ -121,8 +121,9 @@ int pent_solve_noalloc(pent_handle h, double *F, int64_t batch, int64_t ld, void
  * single pass streams with fewer open DRAM pages than rows a whole batch
  * apart.  A partial last tile needs its 64 columns of storage; columns past
  * the batch are not written.  Results are the bits pent_solve gives the
- * same systems.  Runs as the single pass only: PENT_NOT_SUPPORTED (before
- * any HIP call) where pent_solve would use another schedule.
+ * same systems (it runs in the same form).  For the single-pass schedule only
+ * (kind 4 by pent_query_schedule): else PENT_NOT_SUPPORTED, before any HIP
+ * call.
  * PENT_INVALID_VALUE for a bad handle, batch < 0, ld or tile_stride too
  * small, or F == NULL with batch > 0.  Allocates stream-ordered scratch on
  * `stream`; a wait that runs out is reported by pent_check. */

@@ -1336,6 +1336,9 @@ int pent_solve_tiled(pent_handle h, double *F, int64_t batch, int64_t ld, int64_
     if (kind != 4) return ret(PENT_NOT_SUPPORTED);
     hipStream_t s = (hipStream_t)stream;
     StreamPlan sp;
+    if (resident_route(h, kind, batch))
+        return ret(hip_status(launch_resident(h->d_fwd, h->d_bwd, h->seg[seg_slot(32)].d_seg, h->seg[seg_slot(64)].d_seg, h->n,
+                                              resident_width(h->n, batch, h->cus), F, false, ld, F, ld, batch, s, tile_stride)));
     if (stream_route(h, kind, seg_rows, batch, &sp))
         return ret(hip_status(launch_stream(sp, h->n, F, false, ld, tile_stride, F, ld, tile_stride, batch, 64,
                                             h->d_err, s)));

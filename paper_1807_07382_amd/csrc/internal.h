@@ -460,7 +460,8 @@ hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32
 // Crank-Nicolson step.
 constexpr int64_t kResidentRows = 4096;  // the resident-tile schedule's (kind 3) most rows
 hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
-                           const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s);
+                           const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s,
+                           int64_t ts = 64);  // ts: from one 64 systems' storage to the next's
 // System-major solves and 2-D x sweeps, as launch_stream_t and _ch2d.
 hipError_t launch_resident_t(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n,
                              double *F, int64_t ld, int64_t batch, hipStream_t s);

@@ -375,7 +375,7 @@ __device__ __forceinline__ Place res_place(int w)
 template <int S, int NW, typename TI>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_resident(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *segw, int64_t n, const TI *F, int64_t ldf,
-    double *X, int64_t ldx, int64_t batch, int64_t ntiles)
+    double *X, int64_t ldx, int64_t batch, int64_t ntiles, int64_t ts)
 {
     __shared__ ResLds<S, kResWaves> sh;
     const int64_t tile = res_tile(ntiles);
@@ -384,8 +384,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
     const Place at = res_place<S>(w);
     const int64_t c0 = tile * S, blk = at.r0 / kResK;
     const bool act = c0 + at.s < batch, full = at.rw + 64 / S * kResK <= n && ldf <= kFullLd<S> && ldx <= kFullLd<S>;
+    const int64_t col = c0 / 64 * ts + c0 % 64;  // tiles of 64 systems ts apart (64: one array)
     double v[kResK];
-    res_load(v, F + c0, ldf, act ? at.s : batch - 1 - c0, at, n, full);  // idle lanes repeat the last column
+    res_load(v, F + col, ldf, act ? at.s : batch - 1 - c0, at, n, full);  // idle lanes repeat the last column
     if constexpr (S < 16) {
         narrow_sweeps<S>(v, fwd, bwd, seg32, w, waves, at.sub, blk, at.r0 < n, sh);
     } else {
@@ -395,7 +396,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
         res_forward<S>(v, rc, seg32, (CSeg)segw, w, at.sub, blk, sh);
         res_backward<S>(v, rc, seg32, (CSeg)segw, w, waves, at.sub, blk, at.r0 < n, sh, Plain());
     }
-    if (act) res_store(v, X + c0, ldx, at, n, full);
+    if (act) res_store(v, X + col, ldx, at, n, full);
 }
 
 // As above for E (m rows) and the border of a periodic matrix of m + 2 rows.
@@ -761,7 +762,7 @@ hipError_t launch_resident_ch2d(const FwdRec *fwd, const BwdRec *bwd, const SegR
 }
 
 hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg32, const SegRec *seg64, int64_t n, int width,
-                           const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s)
+                           const void *F, bool f32, int64_t ldf, double *X, int64_t ldx, int64_t batch, hipStream_t s, int64_t ts)
 {
     const ResLaunch g = res_launch(n, width, batch);
     auto go = [&](auto f) {
@@ -770,7 +771,7 @@ hipError_t launch_resident(const FwdRec *fwd, const BwdRec *bwd, const SegRec *s
         // (eight waves of four systems have 256 registers each; sixteen spill
         // 59 of theirs: 4096 x 154 23 us, with eight 18)
         if (width == 4) fn = g.block.x <= 512 ? k_resident<4, 8, TI> : k_resident<4, 16, TI>;
-        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const TI *)F, ldf, X, ldx, batch, g.ntiles);
+        hipLaunchKernelGGL(fn, g.grid, g.block, 0, s, fwd, bwd, seg32, seg64, n, (const TI *)F, ldf, X, ldx, batch, g.ntiles, ts);
         return hipGetLastError();
     };
     return f32 ? go(float()) : go(double());

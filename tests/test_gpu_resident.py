@@ -191,3 +191,28 @@ def test_resident_tile_schedule_any_batch(torch, n, m):
         p.solve_(B)
         p.check()
     assert np.max(colerr(B[:, c].cpu().numpy(), ref)) <= d4_tol(10.0)
+
+
+@pytest.mark.parametrize("n,m,gap", [(4097, 70, 0), (5000, 201, 32), (6656, 130, 1)])
+def test_resident_tiled_layout_same_bits(torch, n, m, gap):
+    """64-system tiles stored one after the other, at sizes where the single
+    pass' schedule runs in resident tiles: the bits of pent_solve, nothing
+    written past a partial tile's columns or between tiles."""
+    print_case(test="resident_tiled", n=n, m=m, gap=gap)
+    F = rand(torch, (n, m), 8)
+    nt, ts = (m + 63) // 64, 64 * n + gap
+    T = torch.full((nt, ts), 3.0, dtype=torch.float64, device="cuda")
+    for t in range(nt):
+        w = min(64, m - 64 * t)
+        T[t, :64 * n].view(n, 64)[:, :w] = F[:, 64 * t:64 * t + w]
+    with pb.Plan.factor_d4(n, 50.0) as p:
+        assert p.schedule_for(m)[0] == 4 and p.form_for(m) == pb.FORM_RESIDENT
+        st = pb.lib().pent_solve_tiled(p.handle, T.data_ptr(), m, 64, ts, torch.cuda.current_stream().cuda_stream)
+        assert st == pb.OK
+        X = p.solve_(F.clone())
+        p.check()
+    for t in range(nt):
+        w = min(64, m - 64 * t)
+        V = T[t, :64 * n].view(n, 64)
+        assert torch.equal(V[:, :w], X[:, 64 * t:64 * t + w])
+        assert bool((V[:, w:] == 3.0).all()) and bool((T[t, 64 * n:] == 3.0).all())
