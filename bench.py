@@ -45,14 +45,24 @@ PEAK_HBM_GBS = 8000.0
 BYTES_PER_UNKNOWN_FP64 = 16  # read f once, write x once
 
 
-SCHEDULE_NAMES = {1: "lane", 2: "partitioned", 3: "tile", 4: "onepass"}
+SCHEDULE_NAMES = {1: "lane", 2: "partitioned", 4: "onepass"}
 
 
-# kernel source files of each schedule (the counters go stale when one changes);
-# the single pass also runs as streaming sweeps
+# kernel source files of each schedule or form (the counters go stale when one changes)
 STREAM_SOURCES = ("stream.hip", "stream.h", "lookback.h")
-SCHEDULE_SOURCES = {"lane": ("sweep.hip",), "partitioned": ("sweep.hip",), "tile": ("resident.hip", "stream.h"),
-                    "onepass": ("onepass.hip",) + STREAM_SOURCES}
+SCHEDULE_SOURCES = {"lane": ("sweep.hip",), "partitioned": ("sweep.hip",), "resident": ("resident.hip", "stream.h"),
+                    "onepass": ("onepass.hip", "lookback.h"), "stream": STREAM_SOURCES}
+
+
+def form_name(plan, batch: int) -> str:
+    """What runs: "stream" or "resident" (the forms that the automatic schedule
+    has beside its own, and the resident tiles), else the schedule."""
+    from paper_1807_07382_amd import pentbatch as pb
+    form = plan.form_for(batch)
+    if form != pb.FORM_SCHEDULE:
+        return "stream" if form == pb.FORM_STREAM else "resident"
+    kind, seg = plan.schedule_for(batch)
+    return SCHEDULE_NAMES[kind] + (f"{seg}" if kind in (2, 4) else "")
 
 
 def kernel_source_hash(names) -> str:
@@ -134,7 +144,7 @@ def run_hyperdiff(args, torch):
     if args.schedule:
         kind, seg = (int(x) for x in args.schedule.split(","))
         plan.set_schedule(kind, seg)
-    sched = plan.schedule_for(batch)
+    sched_name = form_name(plan, batch)
     for _ in range(args.warmup):
         plan.solve_(T, stream)
     torch.cuda.synchronize()
@@ -156,7 +166,6 @@ def run_hyperdiff(args, torch):
     solves_s = batch * args.steps / (ms / 1e3)
     alg_bytes = BYTES_PER_UNKNOWN_FP64 * n * batch
     achieved = alg_bytes / (ms_step / 1e3) / 1e9
-    sched_name = SCHEDULE_NAMES[sched[0]] + (f"{sched[1]}" if sched[0] in (2, 4) else "")
     tr = traffic_for(sched_name, "hyperdiff")
     out = dict(
         metric=METRIC, value=solves_s, unit="RHS-solves/s", n_gpus=1, steps=args.steps,
@@ -215,8 +224,7 @@ def all_configs(args, torch):
         prec[f"sigma={sg:g}"] = precision_compare(torch, sg)
     # HBM bytes of one FP32-stream solve (k = 0) at N = 8192 x 131072 from the
     # committed counters, against its 12 B per unknown
-    prec["fp32_stream_refine0_traffic"] = traffic_for("onepass64_f32", "precision",
-                                                      SCHEDULE_SOURCES["onepass"])
+    prec["fp32_stream_refine0_traffic"] = traffic_for("stream_f32", "precision", STREAM_SOURCES)
     prec["note"] = ("FP32 is the storage precision of the right-hand-side stream; the factors, "
                     "every operation and x are FP64, so the k=0 solve already has FP64 accuracy "
                     "(same eta as the FP64 solve) and is the form that beats FP64 (12 instead of "
@@ -348,16 +356,15 @@ def precision_compare(torch, sigma, reps=10, seed=4):
     ref = oracle.solve(oracle.assemble_d4(n, sigma), f_sample)
     out = dict(workload="precision", n=n, systems=m, sigma=sigma)
     with pb.Plan.factor_d4(n, sigma) as plan:
-        # bytes per unknown of one solve: the single pass reads f once, the
+        # bytes per unknown of one solve: one pass reads f once, the
         # partitioned sweep twice; x is written once (FP64)
-        one = plan.schedule_for(m)[0] == 4
+        out["schedule"] = form_name(plan, m)
+        one = not out["schedule"].startswith("partitioned")
         solve64, solve32 = (16, 12) if one else (24, 16)
-        # one correction: fused on the single pass (f and x in, x out: 4 + 8
-        # + 8; by look-back, where the chain is too deep to stream, x is read
-        # twice: 8 more), else residual (f, x in; r out: 20) + correction
-        # solve + x += d (24)
-        refine1 = solve32 + (20 if one else 20 + solve64 + 24)
-        out["schedule"] = "single pass" if one else "partitioned"
+        # one correction: fused (f and x in, x out: 4 + 8 + 8; by look-back,
+        # where the chain is too deep to stream, x is read twice: 8 more),
+        # else residual (f, x in; r out: 20) + correction solve + x += d (24)
+        refine1 = solve32 + (20 if out["schedule"] == "stream" else 28 if one else 20 + solve64 + 24)
         nbytes = plan.mixed_workspace_size(m, 1, True)
         work = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
 
@@ -540,7 +547,7 @@ def run_plain(args, torch):
     torch.cuda.synchronize()
     ms = ev0.elapsed_time(ev1)
     plan.check()
-    sched = plan.schedule_for(F.shape[1])
+    sched_name = form_name(plan, F.shape[1])
     X = T.cpu().numpy()
     plan.close()
     import oracle
@@ -554,8 +561,7 @@ def run_plain(args, torch):
                 higher_is_better=True, scaling="weak", vs_baseline=None, dtype="f64",
                 data="synthetic", config=dict(workload="plain", n=n, systems=F.shape[1],
                                               sigma=sigma,
-                                              schedule=SCHEDULE_NAMES[sched[0]] +
-                                              (f"{sched[1]}" if sched[0] in (2, 4) else "")),
+                                              schedule=sched_name),
                 parity=dict(systems=F.shape[1], solves=args.warmup + args.steps,
                             max_rel_err_vs_oracle=err))
 
@@ -643,6 +649,7 @@ def run_periodic(args, torch):
         state["C"], state["R"] = cy.cn_steps_(state["C"], 1, state["R"], stream)
 
     form = cy.schedule_for(batch, cn=True)
+    streams = cy.form_for(batch, cn=True) == pb.FORM_STREAM
     for _ in range(args.warmup):
         step()
     ms = _timed(torch, stream, step, steps)
@@ -665,13 +672,13 @@ def run_periodic(args, torch):
                 scaling="weak", vs_baseline=None, dtype="f64", data="synthetic",
                 config=dict(workload="periodic", n=n, systems=batch, sigma=sigma,
                             scheme="Crank-Nicolson, periodic (bordering)",
-                            form=names[form[0]], seg_rows=form[1]),
+                            form="streaming sweeps" if streams else names[form[0]], seg_rows=form[1]),
                 other_form=dict(form=names[other], ms_per_step=ms_other),
                 roofline=dict(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s",
                               frac=gbs / PEAK_HBM_GBS,
-                              traffic=traffic_for("cyc_onepass64", "periodic",
+                              traffic=traffic_for("cyc_stream", "periodic",
                                                   ("cyclic.hip", "stream.h", "lookback.h"))
-                              if form == (2, 64) else None),
+                              if streams else None),
                 parity=dict(probe_systems=len(probe), max_rel_err_vs_oracle=err,
                             oracle_steps=args.warmup + steps))
 
