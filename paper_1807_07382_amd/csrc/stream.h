@@ -478,7 +478,9 @@ __device__ __forceinline__ void stream_repair(double *x, int64_t rs, bool act, i
     // once past the first of them no block of a chunk has anything
     const int top = sh.first[slot], low = sh.last[slot] + D;
     bool any = true;
-    for (int b1 = low < nblk - 2 ? low : nblk - 2; b1 >= 0 && (any || b1 >= top); b1 -= NW) {
+    // sixteens counted from the bottom, whatever the tile's other systems need:
+    // across their edges a state comes from memory, rounded otherwise
+    for (int b1 = nblk - 2 - (low < nblk - 2 ? (nblk - 2 - low) / NW * NW : 0); b1 >= 0 && (any || b1 >= top); b1 -= NW) {
         const int b = b1 - w;
         __syncthreads();
         if (b >= 0) {

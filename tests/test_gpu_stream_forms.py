@@ -417,3 +417,33 @@ def test_forced_single_pass_is_look_back(torch, n, m):
         p.check()
     assert torch.equal(X, Z)
     assert float((X - Y).abs().max() / X.abs().max()) <= 2 * d4_tol(5.0)
+
+
+# sources of one system each, at rows of their own, so that no two tiles have
+# the same blocks to add to
+@pytest.mark.parametrize("n,m,sigma", [(4096, 14000, 50.0), (3001, 9000, 5.0), (2100, 12001, 700.0)])
+def test_tail_bits_by_place(torch, n, m, sigma):
+    """A system's bits do not depend on which others share its tile, also where
+    the streaming sweeps add to it afterwards."""
+    print_case(test="tail_bits", n=n, m=m, sigma=sigma)
+    rows = torch.arange(m, device="cuda") * 7919 % (n - 200) + 200
+    F = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+    F[rows, torch.arange(m, device="cuda")] = 1.0
+    at, k = 7, m - 3000
+    part = F[:, at:at + k].contiguous()
+    with pb.Plan.factor_d4(n, sigma) as p:
+        assert p.form_for(m) == p.form_for(k) == pb.FORM_STREAM
+        X = p.solve_(F.clone())
+        assert torch.equal(X[:, at:at + k], p.solve_(part.clone()))
+        nt = (m + 63) // 64
+        T = torch.nn.functional.pad(F, (0, nt * 64 - m)).view(n, nt, 64).transpose(0, 1).contiguous()
+        assert pb.lib().pent_solve_tiled(p.handle, T.data_ptr(), m, 64, 64 * n, torch.cuda.current_stream().cuda_stream) == pb.OK
+        assert torch.equal(T.transpose(0, 1).reshape(n, nt * 64)[:, :m], X)
+        p.check()
+    with pb.Cyclic.factor_d4(n, sigma) as cy:
+        if cy.form_for(m, True) == cy.form_for(k, True) == pb.FORM_STREAM:
+            X, Y = torch.empty_like(F), torch.empty_like(part)
+            cy.cn_step(F, X)
+            cy.cn_step(part, Y)
+            assert torch.equal(X[:, at:at + k], Y)
+        cy.check()
