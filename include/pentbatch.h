@@ -392,8 +392,8 @@ int pent_cyclic_destroy(pent_cyclic c);
  *   kernel), kind 2 single pass with seg_rows in {32, 64} (still falls back
  *   to kind 1 when the blocks would not fit).  Under kind 0 the single pass
  *   runs in resident tiles or, from 10000 systems, as streaming sweeps where
- *   the matrix allows it (see pent_set_schedule, also for the data for which
- *   kind 2 is to be forced).
+ *   the matrix allows it (see pent_set_schedule; by look-back stands for kind
+ *   2 here).
  * pent_cyclic_query_schedule: the schedule of a solve (cn = 0) or step (cn =
  *   1) of `batch` systems: kind 1 or 2, seg_rows 0 unless kind 2.
  * pent_cyclic_query_form: the form in which it runs, PENT_FORM_SCHEDULE (the
@@ -451,11 +451,15 @@ int64_t pent_size(pent_handle h); /* n, or -1 for a bad handle */
  * 2560), where the matrix carries a back substitution's state less than 2^-72
  * of itself over some 512 rows: streaming sweeps, in which a workgroup walks
  * down the rows of whole tiles, waits only inside itself and needs no scratch.
- * Ordinary data take 13 to 40% less time so than by kind 4.  A right-hand side
- * with long stretches above its sources in which the solution falls by many
- * orders of magnitude (compact support) can take up to a quarter more where n
- * is below some 8000 rows: what the sweeps leave out there is added
- * afterwards.  For such data kind 4 (64) is the schedule to force.
+ * Ordinary data take 13 to 40% less time so than by kind 4.  Right-hand sides
+ * with long stretches above their sources in which the solution falls by many
+ * orders of magnitude (compact support) take more, since what the sweeps leave
+ * out there is added afterwards.  Calls of at least 60 million unknowns look at
+ * a sample of their right-hand sides first, and those that have such tails run
+ * by kind 4 (64): the results may then differ in rounding, all systems' alike.
+ * (It takes scratch memory: pent_solve and the periodic calls stream where
+ * there is none to be had, and in a stream capture.)  Smaller ones take up to
+ * half as long again so as by kind 4, and are the ones to force it for.
  * Returns PENT_INVALID_VALUE for an unknown kind or seg_rows. */
 int pent_set_schedule(pent_handle h, int kind, int seg_rows);
 
@@ -494,7 +498,7 @@ int pent_query_schedule(pent_handle h, int64_t batch, int *kind, int *seg_rows);
  * Host-only, no HIP call. */
 #define PENT_FORM_SCHEDULE 0 /* the kernels of the schedule (system-major: one pass or one lane per system) */
 #define PENT_FORM_RESIDENT 1 /* whole systems resident in a workgroup, one kernel, no scratch */
-#define PENT_FORM_STREAM 2   /* streaming sweeps, one kernel */
+#define PENT_FORM_STREAM 2   /* streaming sweeps (the largest calls: if their data suit them) */
 int pent_query_form(pent_handle h, int64_t batch, int system_major, int *form);
 
 /* ---------------------------------------------------------- measurement --

@@ -525,8 +525,72 @@ bool resident_route(const pent_plan *h, int kind, int64_t batch)
            !stream_plan(h, 64, &sp);
 }
 
+// Whether a streaming call looks for tails first (k_gate) and runs by look-back
+// if it finds them.  A system's tails go on until their values underflow, for
+// about fifteen times the rows of a chain; where that is less than a third of the
+// matrix streaming is ahead with what they cost it.  The look and the launch that
+// finds nothing to do take about 10 us, up to 4% of the smallest calls that have
+// it (us, without / with, and by look-back: n = 4096 x 65536 at sigma = 1 817 /
+// 828 / 950, at 50 and a top-hat in every system 1276 / 970 / 957; 2048 x 65536
+// 412 / 420 / 478, and 587 / 492 / 476; 3000 x 25000 285 / 291 / 330, and 442 /
+// 333 / 330; periodic step 4096 x 65536 901 / 915 / 1104, and 1402 / 1099 /
+// 1104).  Below, calls of localised data take up to half as long again as by
+// look-back (2048 x 20000 135 / 165, with sources in the bottom rows only 217 /
+// 165).
+constexpr int64_t kGateUnknowns = 60000000;
+bool tails_cost(int64_t n, int64_t batch, const StreamPlan &p)
+{
+    return n * batch >= kGateUnknowns && 45 * (int64_t)p.depth * p.rows > n;
+}
+bool stream_gated(const pent_plan *h, int kind, int seg_rows, int64_t batch, const StreamPlan &p)
+{
+    return kind == 4 && seg_rows == 64 && tails_cost(h->n, batch, p);
+}
+
+// A streaming solve of `batch` systems in tiles of cw, tsf and tsx apart (cw:
+// one array; else tiles of 64 stored by themselves).  Where it is gated, summ
+// is the scratch of the look-back solve (null: none to be had, so it streams).
+int solve_stream(pent_plan *h, const StreamPlan &p, int kind, int seg_rows, const void *f, bool f32, int64_t ldf, int64_t tsf,
+                 double *x, int64_t ldx, int64_t tsx, int64_t batch, int cw, void *summ, hipStream_t s)
+{
+    if (!summ || !stream_gated(h, kind, seg_rows, batch, p))
+        return hip_status(launch_stream(p, h->n, f, f32, ldf, tsf, x, ldx, tsx, batch, cw, h->d_err, s));
+    hipError_t e = launch_stream(p, h->n, f, f32, ldf, tsf, x, ldx, tsx, batch, cw, h->d_err, s, (unsigned int *)summ,
+                                 onepass_words(h->n, 64, batch));
+    if (e == hipSuccess)
+        e = launch_onepass(h->d_fwd, h->d_bwd, h->seg[seg_slot(64)].d_seg, h->n, 64, f, f32, ldf, x, ldx, batch, summ, h->d_err, s,
+                           tsf == cw ? 64 : tsf, tsx == cw ? 64 : tsx, true, true);
+    return hip_status(e);
+}
+
+// Scratch that a streaming call can do without: null where there is no memory
+// left for it, and in a stream capture, where the call is to allocate nothing.
+void *spare_scratch(size_t bytes, hipStream_t s)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    void *p = nullptr;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess && (cs != hipStreamCaptureStatusNone || scratch_alloc(&p, bytes, s) == hipSuccess))
+        return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+// The scratch of solve_io for (kind, seg_rows); null where it needs none.
+hipError_t solve_scratch(void **p, const pent_plan *h, int kind, int seg_rows, int64_t batch, hipStream_t s)
+{
+    StreamPlan sp;
+    *p = nullptr;
+    if (resident_route(h, kind, batch)) return hipSuccess;
+    const size_t bytes = summ_bytes(h, kind, seg_rows, batch);
+    if (stream_route(h, kind, seg_rows, batch, &sp)) {
+        if (stream_gated(h, kind, seg_rows, batch, sp)) *p = spare_scratch(bytes, s);
+        return hipSuccess;
+    }
+    return bytes ? scratch_alloc(p, bytes, s) : hipSuccess;
+}
+
 // x = A^{-1} f with FP64 arithmetic; f FP32 or FP64; summ: scratch of
-// summ_bytes() for the chosen schedule.
+// solve_scratch() for the chosen schedule.
 int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int64_t ldx,
              int64_t batch, void *summ, hipStream_t s, bool words_clear = false)
 {
@@ -537,7 +601,7 @@ int solve_io(pent_plan *h, const void *f, bool f32, int64_t ldf, double *x, int6
     const bool resident = resident_route(h, kind, batch);
     if (!resident && stream_route(h, kind, seg_rows, batch, &sp)) {
         const int cw = stream_tile_width(batch, h->cus);
-        return hip_status(launch_stream(sp, h->n, f, f32, ldf, cw, x, ldx, cw, batch, cw, h->d_err, s));
+        return solve_stream(h, sp, kind, seg_rows, f, f32, ldf, cw, x, ldx, cw, batch, cw, summ, s);
     }
     if (kind == 1)
         return hip_status(launch_lane_sweep(h->d_fwd, h->d_bwd, h->n, x, batch, ldx, seg_rows, s));
@@ -571,17 +635,12 @@ int solve_io_scratch(pent_plan *h, const double *f, int64_t ldf, double *x, int6
 {
     int kind, seg_rows;
     io_schedule(h, batch, (const void *)f == (const void *)x && ldf == ldx, &kind, &seg_rows);
-    StreamPlan sp;
-    const bool scratch = !resident_route(h, kind, batch) && !stream_route(h, kind, seg_rows, batch, &sp);
-    const size_t bytes = scratch ? summ_bytes(h, kind, seg_rows, batch) : 0;
-    void *summ = nullptr;
-    if (bytes) {
-        hipError_t e = scratch_alloc(&summ, bytes, s);
-        if (e != hipSuccess) return hip_status(e);
-    }
+    void *summ;
+    hipError_t e = solve_scratch(&summ, h, kind, seg_rows, batch, s);
+    if (e != hipSuccess) return hip_status(e);
     const int st = solve_io(h, f, false, ldf, x, ldx, batch, summ, s);
     if (summ) {
-        hipError_t e = hipFreeAsync(summ, s);
+        e = hipFreeAsync(summ, s);
         if (st == PENT_OK && e != hipSuccess) return hip_status(e);
     }
     return st;
@@ -914,12 +973,19 @@ int cyc_run_single(pent_cyclic c, bool cn, const double *F, int64_t ldf, double 
     }
     if (cyc_stream_route(c, batch, &sp)) {
         const int cw = stream_tile_width(batch, c->E->cus);
-        void *dx = nullptr;
-        hipError_t e = scratch_alloc(&dx, cyc_stream_scratch_bytes(batch, cw), s);
+        const size_t own = cyc_stream_scratch_bytes(batch, cw);
+        size_t other = align256(cyc_onepass_scratch_bytes(c->n, 64, batch));  // for look-back, ahead of its own
+        void *buf = c->seg_rows == 64 && tails_cost(c->n, batch, sp) ? spare_scratch(other + own, s) : nullptr;
+        const bool gate = buf != nullptr;
+        if (!gate) other = 0;
+        hipError_t e = gate ? hipSuccess : scratch_alloc(&buf, own, s);
         if (e != hipSuccess) return hip_status(e);
-        e = launch_cyc_stream(sp, c->d_cd, c->d_Z, c->d_W, c->d_aux, c->ends, c->n, cn, F, ldf, X, ldx, batch, cw, dx,
-                              c->E->d_err, s, c->uni ? c->uc : nullptr);
-        const hipError_t e2 = hipFreeAsync(dx, s);
+        e = launch_cyc_stream(sp, c->d_cd, c->d_Z, c->d_W, c->d_aux, c->ends, c->n, cn, F, ldf, X, ldx, batch, cw,
+                              (char *)buf + other, c->E->d_err, s, c->uni ? c->uc : nullptr, gate ? (unsigned int *)buf : nullptr);
+        if (e == hipSuccess && gate)
+            e = launch_cyc_onepass(c->E->d_fwd, c->E->d_bwd, c->E->seg[seg_slot(64)].d_seg, c->d_cd, c->d_Z, c->d_W, c->d_aux, c->n,
+                                   64, cn, F, ldf, X, ldx, batch, buf, c->E->d_err, s, c->uni ? c->uc : nullptr, true);
+        const hipError_t e2 = hipFreeAsync(buf, s);
         return hip_status(e != hipSuccess ? e : e2);
     }
     const SegRec *seg = seg_cache(c->E, c->seg_rows, &st);
@@ -1342,14 +1408,17 @@ int pent_solve_tiled(pent_handle h, double *F, int64_t batch, int64_t ld, int64_
     if (resident_route(h, kind, batch))
         return ret(hip_status(launch_resident(h->d_fwd, h->d_bwd, h->seg[seg_slot(32)].d_seg, h->seg[seg_slot(64)].d_seg, h->n,
                                               resident_width(h->n, batch, h->cus), F, false, ld, F, ld, batch, s, tile_stride)));
-    if (stream_route(h, kind, seg_rows, batch, &sp))
-        return ret(hip_status(launch_stream(sp, h->n, F, false, ld, tile_stride, F, ld, tile_stride, batch, 64,
-                                            h->d_err, s)));
     const SegRec *seg = seg_cache(h, seg_rows, &st);
     if (!seg) return ret(st);
-    void *summ = nullptr;
-    hipError_t e = scratch_alloc(&summ, summ_bytes(h, kind, seg_rows, batch), s);
+    const bool streams = stream_route(h, kind, seg_rows, batch, &sp);
+    void *summ;
+    hipError_t e = solve_scratch(&summ, h, kind, seg_rows, batch, s);
     if (e != hipSuccess) return ret(hip_status(e));
+    if (streams) {
+        st = solve_stream(h, sp, kind, seg_rows, F, false, ld, tile_stride, F, ld, tile_stride, batch, 64, summ, s);
+        if (summ) e = hipFreeAsync(summ, s);
+        return ret(st != PENT_OK ? st : hip_status(e));
+    }
     e = launch_onepass(h->d_fwd, h->d_bwd, seg, h->n, seg_rows, F, false, ld, F, ld, batch, summ,
                        h->d_err, s, tile_stride, tile_stride);
     const hipError_t e2 = hipFreeAsync(summ, s);
@@ -1806,14 +1875,10 @@ int pent_ch2d_step(pent_handle hx, pent_handle hy, double *C, double *R, int64_t
     int ykind, yseg;
     io_schedule(hy, ybatch, false, &ykind, &yseg);
     StreamPlan ysp;
-    const bool ystream = resident_route(hy, ykind, ybatch) ||
-                         stream_route(hy, ykind, yseg, ybatch, &ysp);  // one of the forms without scratch
-    const size_t ybytes = ystream ? 0 : summ_bytes(hy, ykind, yseg, ybatch);
-    void *ybuf = nullptr;
-    if (ybytes) {
-        const hipError_t e = scratch_alloc(&ybuf, ybytes, s);
-        if (e != hipSuccess) return ret(hip_status(e));
-    }
+    const bool ystream = resident_route(hy, ykind, ybatch) || stream_route(hy, ykind, yseg, ybatch, &ysp);
+    void *ybuf;
+    const hipError_t ye = solve_scratch(&ybuf, hy, ykind, yseg, ybatch, s);
+    if (ye != hipSuccess) return ret(hip_status(ye));
     int st = PENT_OK;
     bool ywords_clear = false;
     // x sweeps, system (y, k) being nx contiguous values: the single pass

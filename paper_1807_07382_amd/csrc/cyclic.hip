@@ -355,8 +355,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
     const double *__restrict__ Z_, const double *__restrict__ Wt_, const CycAux *__restrict__ aux,
     int64_t n, int ngroups, const double *Fin, int64_t ldf, double *X, int64_t ldx, int64_t batch,
     unsigned int *ctr, unsigned int *fst, unsigned int *bst, unsigned int *pst, unsigned int *tst,
-    double *ex, double *pex, double *tex, unsigned int *err, CycUni uc)
+    double *ex, double *pex, double *tex, unsigned int *err, CycUni uc, const unsigned int *gate)
 {
+    if (gate && *gate == 0) return;  // the streaming launch before this one ran the call
     PENT_GROUP_LDS(W);
     __shared__ double sp[W][2][64];
     __shared__ double sft[2][64];  // f_m, f_{m+1} of the tile (tail block), kept out of registers
@@ -648,13 +649,15 @@ struct CycExtra {
     }
 };
 
-template <bool CN, bool UNI, bool NT>
+template <bool CN, bool UNI, bool NT, bool GATED>
 __global__ __launch_bounds__(64 * kCsNW) __attribute__((amdgpu_waves_per_eu(kCsEU, kCsEU))) void k_cyc_stream(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, const double *__restrict__ cd,
     const double *Z, const double *Wt, const CycAux *__restrict__ aux, int T, int64_t n, int nblk, const double *F,
-    int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, int ntiles, double *dx, unsigned int *err, CycUni uc)
+    int64_t ldf, double *X, int64_t ldx, int64_t batch, int cw, int ntiles, double *dx, unsigned int *err, CycUni uc,
+    const unsigned int *gate)
 {
     using namespace st;
+    if (GATED && *gate != 0) return;  // left to the look-back launch after this one
     constexpr int K = kCsK, NW = kCsNW;
     __shared__ StreamLds<NW> sh;
     __shared__ CycLds cl;
@@ -925,7 +928,7 @@ hipError_t launch_cyc_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec
                               const CycAux *aux, int64_t n,
                               int seg_rows, bool cn, const double *Fin, int64_t ldf, double *X,
                               int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
-                              hipStream_t s, const double *uni)
+                              hipStream_t s, const double *uni, bool gated)
 {
     if (seg_rows != 32 && seg_rows != 64) return hipErrorInvalidValue;
     const int W = cyc_waves(seg_rows);
@@ -940,10 +943,13 @@ hipError_t launch_cyc_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec
     double *ex = (double *)((char *)scratch + wbytes);
     double *pex = ex + units * 8 * 64;
     double *tex = pex + units * 2 * 64;
-    hipLaunchKernelGGL(k_cyc_zero, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, w, words);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!gated) {
+        hipLaunchKernelGGL(k_cyc_zero, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, w, words);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     int ng = (int)ngroups;
+    const unsigned int *gate = gated ? gate_word(w) : nullptr;
     CycUni uc = {{0.0, 0.0, 0.0, 0.0, 0.0}};
     if (uni)
         for (int k = 0; k < 5; k++) uc.c[k] = uni[k];
@@ -951,7 +957,7 @@ hipError_t launch_cyc_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec
                     (void *)&aux, (void *)&n, (void *)&ng, (void *)&Fin, (void *)&ldf, (void *)&X,
                     (void *)&ldx, (void *)&batch, (void *)&ctr, (void *)&fst, (void *)&bst,
                     (void *)&pst, (void *)&tst, (void *)&ex, (void *)&pex, (void *)&tex,
-                    (void *)&err, (void *)&uc};
+                    (void *)&err, (void *)&uc, (void *)&gate};
     return hipLaunchKernel(cyc_fn_kw(seg_rows, W, cn, uni != nullptr), dim3((unsigned)units),
                            dim3(64 * W), args, 0, s);
 }
@@ -979,24 +985,34 @@ size_t cyc_stream_scratch_bytes(int64_t batch, int cw) { return (size_t)((batch 
 
 hipError_t launch_cyc_stream(const StreamPlan &p, const double *cd, const double *Z, const double *Wt, const CycAux *aux,
                              int T, int64_t n, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
-                             int64_t batch, int cw, void *scratch, unsigned int *err, hipStream_t s, const double *uni)
+                             int64_t batch, int cw, void *scratch, unsigned int *err, hipStream_t s, const double *uni,
+                             unsigned int *words)
 {
     const int64_t ntiles = (batch + cw - 1) / cw;
     const int nblk = (int)((n - 2 + kCsK - 1) / kCsK), nt = (int)ntiles, D = p.depth;
-    const int64_t grid = (ntiles < p.cus ? ntiles + 7 : p.cus) / 8 * 8;
+    const int64_t grid = stream_workgroups(batch, cw, p.cus);
     const bool lines = (uintptr_t)F % 128 == 0 && (uintptr_t)X % 128 == 0 && ldf % 16 == 0 && ldx % 16 == 0;
     CycUni uc = {{0.0, 0.0, 0.0, 0.0, 0.0}};
     if (uni)
         for (int k = 0; k < 5; k++) uc.c[k] = uni[k];
-    const void *fn;
-    if (!cn) fn = lines ? (const void *)k_cyc_stream<false, false, true> : (const void *)k_cyc_stream<false, false, false>;
-    else if (uni) fn = lines ? (const void *)k_cyc_stream<true, true, true> : (const void *)k_cyc_stream<true, true, false>;
-    else fn = lines ? (const void *)k_cyc_stream<true, false, true> : (const void *)k_cyc_stream<true, false, false>;
+    auto pick = [&](auto cn_, auto uni_) {
+        constexpr bool C = decltype(cn_)::value, U = decltype(uni_)::value;
+        return words ? (lines ? (const void *)k_cyc_stream<C, U, true, true> : (const void *)k_cyc_stream<C, U, false, true>)
+                     : (lines ? (const void *)k_cyc_stream<C, U, true, false> : (const void *)k_cyc_stream<C, U, false, false>);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    const void *fn = !cn ? pick(no, no) : uni ? pick(yes, yes) : pick(yes, no);
+    const unsigned int *gate = words ? gate_word(words) : nullptr;
+    if (words) {
+        const hipError_t e = launch_gate(F, false, ldf, 64, n, batch, p.depth, words, cyc_words(n, 64, batch), s);
+        if (e != hipSuccess) return e;
+    }
     double *dx = (double *)scratch;
     void *args[] = {(void *)&p.fwd, (void *)&p.bwd, (void *)&p.seg, (void *)&p.trunc, (void *)&D,    (void *)&cd,
                     (void *)&Z,     (void *)&Wt,    (void *)&aux,   (void *)&T,       (void *)&n,    (void *)&nblk,
                     (void *)&F,     (void *)&ldf,   (void *)&X,     (void *)&ldx,     (void *)&batch, (void *)&cw,
-                    (void *)&nt,    (void *)&dx,    (void *)&err,   (void *)&uc};
+                    (void *)&nt,    (void *)&dx,    (void *)&err,   (void *)&uc,      (void *)&gate};
     return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64 * kCsNW), args, 0, s);
 }
 

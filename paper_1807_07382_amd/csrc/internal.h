@@ -447,13 +447,24 @@ hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *se
                           int seg_rows, const void *Fin, bool f32, int64_t ldf, double *X,
                           int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
                           hipStream_t s, int64_t tsf = 64, int64_t tsx = 64,
-                          bool words_clear = false);  // words_clear: the status words are zero already
+                          bool words_clear = false,  // the status words are zero already
+                          bool gated = false);  // after a launch_stream with its words: returns at once if that ran the call
 
 // ---- streaming sweeps (stream.hip) ----
+// Rows between the samples by which tails are found: two in the rows of a chain
+// of `depth` 32-row blocks, and not more of them than there is room for.
+inline int64_t sample_stride(int64_t n, int depth) { return 16 * depth > (n + 63) / 64 ? 16 * depth : (n + 63) / 64; }
 int stream_tile_width(int64_t batch, int cus);
-// Tile t of cw <= 64 systems starts at F + t * tsf and X + t * tsx.
+// Decides whether a call with these right-hand sides streams, and says so in the
+// words of the look-back launch that runs it otherwise, all others of which it
+// clears (depth in 32-row blocks).
+hipError_t launch_gate(const void *F, bool f32, int64_t ld, int64_t ts, int64_t n, int64_t batch, int depth, unsigned int *words,
+                       int64_t nwords, hipStream_t s);
+// Tile t of cw <= 64 systems starts at F + t * tsf and X + t * tsx.  words (of a
+// look-back launch that follows, gated): gated, too.
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
-                         int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s);
+                         int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s,
+                         unsigned int *words = nullptr, int64_t nwords = 0);
 
 // Whole tiles of `width` (4, 16 or 32) systems, n <= 32768 / width rows, by one
 // workgroup each (resident.hip).  The periodic form: n = the rows of E, cn: the
@@ -539,7 +550,8 @@ hipError_t launch_cyc_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec
                               const CycAux *aux, int64_t n,
                               int seg_rows, bool cn, const double *Fin, int64_t ldf, double *X,
                               int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
-                              hipStream_t s, const double *uni = nullptr);
+                              hipStream_t s, const double *uni = nullptr,
+                              bool gated = false);  // as launch_onepass
 // The same as streaming sweeps (stream.h): p of 32-row segments of E, T =
 // cyc_stream_ends (0: too few rows for it).
 hipError_t launch_cyc_reach(const double *Wt, int64_t m, CycAux *aux, hipStream_t s);
@@ -548,7 +560,7 @@ size_t cyc_stream_scratch_bytes(int64_t batch, int cw);
 hipError_t launch_cyc_stream(const StreamPlan &p, const double *cd, const double *Z, const double *Wt, const CycAux *aux,
                              int T, int64_t n, bool cn, const double *F, int64_t ldf, double *X, int64_t ldx,
                              int64_t batch, int cw, void *scratch, unsigned int *err, hipStream_t s,
-                             const double *uni = nullptr);
+                             const double *uni = nullptr, unsigned int *words = nullptr);  // words: as launch_stream
 hipError_t launch_cyc_finish(const double *cd, int64_t n, const double *Z, CycAux *aux,
                              hipStream_t s);
 // etd: 5(n-2) diagonals of E^T; H: zrows x 2, ld 2, H[i][q] = A[n-2+q][i]

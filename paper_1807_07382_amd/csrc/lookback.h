@@ -241,6 +241,10 @@ __device__ __forceinline__ unsigned int *left_word(unsigned int *words, int wg)
     return words + (wg % kTicketLines) * kTicketStride + 1 + wg / kTicketLines;
 }
 
+// The word that says whether the streaming launch runs the call (0) or the
+// look-back launch after it (1); k_gate writes it.
+__host__ __device__ inline unsigned int *gate_word(unsigned int *words) { return words + 1; }
+
 // Whether any of the wgs words is set, to the whole workgroup.
 __device__ __forceinline__ bool any_left(unsigned int *words, int wgs)
 {

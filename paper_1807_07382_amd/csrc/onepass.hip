@@ -32,12 +32,16 @@ using namespace lb;
 // most 168 vector registers): for 64-row blocks this spills a few values,
 // and measured faster than two waves per SIMD without spills (more blocks
 // resident while carries are in flight).
-template <int K, int W, typename TI>
+// GATED: after a streaming launch that may have run the call already.  (Its
+// look costs the others 2%: 8192 x 16384 562 and 574 us.)
+template <int K, int W, bool GATED, typename TI>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) void k_onepass(
     const FwdRec *fwd_, const BwdRec *bwd_, const SegRec *seg_, int64_t n, int ngroups,
     const TI *Fin, int64_t ldf, double *X, int64_t ldx, int64_t batch, unsigned int *ctr,
-    unsigned int *fst, unsigned int *bst, double *ex, unsigned int *err, int64_t tsf, int64_t tsx)
+    unsigned int *fst, unsigned int *bst, double *ex, unsigned int *err, int64_t tsf, int64_t tsx,
+    const unsigned int *gate)
 {
+    if (GATED && *gate == 0) return;  // it did
     PENT_GROUP_LDS(W);
     __shared__ unsigned int s_unit;
     const CFwd fwd = (CFwd)fwd_;
@@ -473,14 +477,15 @@ __global__ void k_zero_words(unsigned int *p, int64_t count)
     if (i < count) p[i] = 0u;
 }
 
-template <int K, int W>
+template <int K, int W, bool GATED = false>
 const void *onepass_fn(bool f32)
 {
-    return f32 ? (const void *)k_onepass<K, W, float> : (const void *)k_onepass<K, W, double>;
+    return f32 ? (const void *)k_onepass<K, W, GATED, float> : (const void *)k_onepass<K, W, GATED, double>;
 }
 
-const void *onepass_fn_kw(int K, int W, bool f32)
+const void *onepass_fn_kw(int K, int W, bool f32, bool gated = false)
 {
+    if (gated) return W == 2 ? onepass_fn<64, 2, true>(f32) : W == 4 ? onepass_fn<64, 4, true>(f32) : onepass_fn<64, 8, true>(f32);
     if (K == 64) return W == 2 ? onepass_fn<64, 2>(f32) : W == 4 ? onepass_fn<64, 4>(f32) : onepass_fn<64, 8>(f32);
     return W == 2 ? onepass_fn<32, 2>(f32) : W == 4 ? onepass_fn<32, 4>(f32) : onepass_fn<32, 8>(f32);
 }
@@ -548,9 +553,9 @@ int onepass_capacity(int seg_rows)
 hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, int64_t n,
                           int seg_rows, const void *Fin, bool f32, int64_t ldf, double *X,
                           int64_t ldx, int64_t batch, void *scratch, unsigned int *err,
-                          hipStream_t s, int64_t tsf, int64_t tsx, bool words_clear)
+                          hipStream_t s, int64_t tsf, int64_t tsx, bool words_clear, bool gated)
 {
-    if (seg_rows != 32 && seg_rows != 64) return hipErrorInvalidValue;
+    if ((seg_rows != 32 && seg_rows != 64) || (gated && seg_rows != 64)) return hipErrorInvalidValue;
     const int W = onepass_waves(seg_rows);
     const int64_t ngroups = onepass_groups(n, seg_rows);
     const int64_t units = onepass_units(n, seg_rows, batch);
@@ -563,17 +568,19 @@ hipError_t launch_onepass(const FwdRec *fwd, const BwdRec *bwd, const SegRec *se
     const size_t wbytes = ((size_t)words * sizeof(unsigned int) + 255) / 256 * 256;
     double *ex = (double *)((char *)scratch + wbytes);
     hipError_t e = hipSuccess;
-    if (!words_clear) {
+    if (!words_clear && !gated) {
         hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, w, words);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const void *fn = onepass_fn_kw(seg_rows, W, f32);
+    const void *fn = onepass_fn_kw(seg_rows, W, f32, gated);
     const SegRec *segp = seg;
     int ng = (int)ngroups;
+    const unsigned int *gate = gated ? gate_word(w) : nullptr;
     void *args[] = {(void *)&fwd, (void *)&bwd, (void *)&segp, (void *)&n, (void *)&ng, (void *)&Fin,
                     (void *)&ldf, (void *)&X, (void *)&ldx, (void *)&batch, (void *)&ctr,
-                    (void *)&fst, (void *)&bst, (void *)&ex, (void *)&err, (void *)&tsf, (void *)&tsx};
+                    (void *)&fst, (void *)&bst, (void *)&ex, (void *)&err, (void *)&tsf, (void *)&tsx,
+                    (void *)&gate};
     e = hipLaunchKernel(fn, dim3((unsigned)units), dim3(64 * W), args, 0, s);
     return e;
 }

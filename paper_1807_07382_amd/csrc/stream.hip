@@ -17,12 +17,13 @@ using namespace st;
 // counter, N = 4096 x 65536).  That solve takes 800 us, 5.4 TB/s, as does a
 // bare copy through the same persistent blocks (770 to 830 us for any block
 // shape on this layout); the look-back single pass took 950.
-template <int K, int NW, int EU, bool NT, typename TI>
+template <int K, int NW, int EU, bool NT, bool GATED, typename TI>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU))) void k_stream(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, int64_t n, int nblk,
     const TI *F, int64_t ldf, int64_t tsf, double *X, int64_t ldx, int64_t tsx, int64_t batch, int cw, int ntiles,
-    unsigned int *err)
+    unsigned int *err, const unsigned int *gate)
 {
+    if (GATED && *gate != 0) return;  // left to the look-back launch after this one
     __shared__ StreamLds<NW> sh;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int lane = threadIdx.x & 63;
@@ -91,11 +92,65 @@ __device__ __forceinline__ void stream_residual(double (&v)[K], const double (&x
     });
 }
 
-// Growth from two samples to the next that k_find_left looks for.  In a tail it
+// Growth from two samples to the next that shows a tail.  In a tail it
 // is at least 2^18 (a correction's chain, kTruncFix) or 2^36 (a solve's) from
 // one sample to the next, while of 64 systems of random values one in 2^16 has
 // such a place.
 constexpr double kSteep = 0x1p-14;
+
+// Whether a call whose tails would cost streaming sweeps more than they save
+// runs by look-back as a whole: where in two of eight tiles of 64 systems, at
+// equal distances through the batch, one of 16 systems grows so between samples
+// or is zero in all of them (a source between two); up to 66 samples of each, rows
+// `stride` apart and the last one, tile t at F + t * ts.  One workgroup does, ahead of
+// the streaming launch: that one may work in place, so that its own workgroups
+// could not all look at the same right-hand sides.  The other workgroups clear
+// the rest of the look-back launch's status words.
+constexpr int kGateTiles = 8, kGateParts = 8, kGatePart = 9;
+template <typename TI>
+__global__ __launch_bounds__(16 * kGateParts * kGateTiles) void k_gate(const TI *F, int64_t ld, int64_t ts, int64_t n,
+                                                                      int64_t batch, int stride, unsigned int *words, int64_t nwords)
+{
+    if (blockIdx.x > 0) {
+        unsigned int *p = words + (int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
+        if (p < words + nwords && p != gate_word(words)) *p = 0;
+        return;
+    }
+    __shared__ unsigned int grows, some[kGateTiles];  // tiles with growth; a tile's systems with a value
+    if (threadIdx.x == 0) grows = 0;
+    if (threadIdx.x < kGateTiles) some[threadIdx.x] = 0;
+    __syncthreads();
+    const int p = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / (16 * kGateParts)));
+    const int cnt = (int)((n - 2) / stride) + 2, s0 = (int)(threadIdx.x / 16 % kGateParts) * kGatePart;
+    const int64_t t = (batch + 63) / 64 * p / kGateTiles;
+    int64_t col = p % 4 * 16 + (threadIdx.x & 15);
+    col = t * 64 + col < batch ? col : batch - 1 - t * 64;
+    const TI *c = F + t * ts + col;
+    double a[kGatePart + 2];
+#pragma unroll
+    for (int i = 0; i < kGatePart + 2; i++)
+        a[i] = fabs((double)c[(s0 + i < cnt - 1 ? (int64_t)(s0 + i) * stride : n - 1) * ld]);
+    bool here = false, value = false;
+#pragma unroll
+    for (int i = 0; i < kGatePart + 2; i++) value = value || a[i] != 0.0;
+#pragma unroll
+    for (int i = 0; i < kGatePart; i++)
+        here = here || (s0 + i + 2 < cnt && fmax(a[i], a[i + 1]) <= kSteep * a[i + 2] && a[i + 2] > 0.0 && a[i + 2] <= __DBL_MAX__);
+    unsigned long long m = __ballot(value);
+    m |= m >> 32;
+    m |= m >> 16;
+    const bool any = __ballot(here) != 0;
+    if ((threadIdx.x & 63) == 0) {
+        atomicOr(&some[p], (unsigned int)m & 0xFFFF);
+        if (any) atomicOr(&grows, 1u << p);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int votes = 0;
+    for (int i = 0; i < kGateTiles; i++) votes += (grows >> i & 1) != 0 || some[i] != 0xFFFF;
+    *gate_word(words) = votes >= 2;
+}
+
 constexpr int kSampleParts = 4, kSamplePart = 17;
 
 // Finds and marks the tiles that streaming sweeps had better leave to the
@@ -254,10 +309,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU)
     }
 }
 
-// Rows between the samples of find_left: two in the rows of a chain, and not
-// more than it has room for.
-int64_t sample_stride(int64_t n, int depth) { return std::max<int64_t>(16 * depth, (n + 63) / 64); }
-
 template <typename TI>
 hipError_t find_left(const TI *F, int64_t ldf, int64_t tsf, int64_t n, int64_t batch, int cw, const Left &left, hipStream_t s)
 {
@@ -272,12 +323,19 @@ inline bool on_lines(const void *p, int64_t pitch) { return (uintptr_t)p % 128 =
 
 template <int K, int NW, int EU, bool NT, typename TI>
 hipError_t launch_k(const StreamPlan &p, int64_t n, const void *F, int64_t ldf, int64_t tsf, double *X, int64_t ldx,
-                    int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
+                    int64_t tsx, int64_t batch, int cw, unsigned int *words, int64_t nwords, unsigned int *err, hipStream_t s)
 {
     const int64_t ntiles = (batch + cw - 1) / cw, nblk = (n + K - 1) / K;
     const int64_t grid = stream_workgroups(batch, cw, p.cus);
-    hipLaunchKernelGGL((k_stream<K, NW, EU, NT, TI>), dim3((unsigned)grid), dim3(64 * NW), 0, s, p.fwd, p.bwd, p.seg,
-                       p.trunc, p.depth, n, (int)nblk, (const TI *)F, ldf, tsf, X, ldx, tsx, batch, cw, (int)ntiles, err);
+    if (words) {
+        const hipError_t e = launch_gate(F, sizeof(TI) == sizeof(float), ldf, tsf == cw ? 64 : tsf, n, batch, K / 32 * p.depth,
+                                         words, nwords, s);
+        if (e != hipSuccess) return e;
+    }
+    const auto fn = words ? k_stream<K, NW, EU, NT, true, TI> : k_stream<K, NW, EU, NT, false, TI>;
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(64 * NW), 0, s, p.fwd, p.bwd, p.seg,
+                       p.trunc, p.depth, n, (int)nblk, (const TI *)F, ldf, tsf, X, ldx, tsx, batch, cw, (int)ntiles, err,
+                       words ? gate_word(words) : nullptr);
     return hipGetLastError();
 }
 
@@ -303,6 +361,19 @@ int stream_tile_width(int64_t batch, int cus)
         }
     }
     return best;
+}
+
+hipError_t launch_gate(const void *F, bool f32, int64_t ld, int64_t ts, int64_t n, int64_t batch, int depth, unsigned int *words,
+                       int64_t nwords, hipStream_t s)
+{
+    const int64_t wgs = 1 + (nwords + 16 * kGateParts * kGateTiles - 1) / (16 * kGateParts * kGateTiles);
+    const dim3 block(16 * kGateParts * kGateTiles);
+    const int stride = (int)sample_stride(n, depth);
+    if (f32)
+        hipLaunchKernelGGL(k_gate<float>, dim3((unsigned)wgs), block, 0, s, (const float *)F, ld, ts, n, batch, stride, words, nwords);
+    else
+        hipLaunchKernelGGL(k_gate<double>, dim3((unsigned)wgs), block, 0, s, (const double *)F, ld, ts, n, batch, stride, words, nwords);
+    return hipGetLastError();
 }
 
 hipError_t launch_stream_fix(const StreamPlan &p, int64_t n, const double *diag, const void *F, bool f32,
@@ -331,15 +402,16 @@ hipError_t launch_stream_fix(const StreamPlan &p, int64_t n, const double *diag,
 }
 
 hipError_t launch_stream(const StreamPlan &p, int64_t n, const void *F, bool f32, int64_t ldf, int64_t tsf, double *X,
-                         int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s)
+                         int64_t ldx, int64_t tsx, int64_t batch, int cw, unsigned int *err, hipStream_t s,
+                         unsigned int *words, int64_t nwords)
 {
     const size_t ef = f32 ? sizeof(float) : sizeof(double);
     const bool nt = on_lines(F, ldf * ef) && on_lines(X, ldx * 8) && tsf * ef % 64 == 0 && tsx * 8 % 128 == 0;
 #define PENT_STREAM_GO(K, NW, EU)                                                                                       \
-    return f32 ? (nt ? launch_k<K, NW, EU, true, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s)                \
-                     : launch_k<K, NW, EU, false, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s))              \
-               : (nt ? launch_k<K, NW, EU, true, double>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s)               \
-                     : launch_k<K, NW, EU, false, double>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, err, s))
+    return f32 ? (nt ? launch_k<K, NW, EU, true, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, words, nwords, err, s)                \
+                     : launch_k<K, NW, EU, false, float>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, words, nwords, err, s))              \
+               : (nt ? launch_k<K, NW, EU, true, double>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, words, nwords, err, s)               \
+                     : launch_k<K, NW, EU, false, double>(p, n, F, ldf, tsf, X, ldx, tsx, batch, cw, words, nwords, err, s))
     if (p.rows == 32) PENT_STREAM_GO(32, 16, 4);
     PENT_STREAM_GO(64, 12, 3);
 #undef PENT_STREAM_GO
