@@ -450,7 +450,7 @@ int64_t pent_size(pent_handle h); /* n, or -1 for a bad handle */
  * for large batches (from 5120 systems, in the resident tiles' place from
  * 2560), where the matrix carries a back substitution's state less than 2^-72
  * of itself over some 512 rows: streaming sweeps, in which a workgroup walks
- * down the rows of whole tiles, waits only inside itself and needs no scratch.
+ * down the rows of whole tiles and waits only inside itself.
  * Ordinary data take 13 to 40% less time so than by kind 4.  Right-hand sides
  * with long stretches above their sources in which the solution falls by many
  * orders of magnitude (compact support) take more, since what the sweeps leave

@@ -441,7 +441,7 @@ bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
 }
 
 // Whether a solve that io_schedule gave (kind, seg_rows) runs as the
-// streaming sweeps instead, which need no scratch: 32-row blocks where their
+// streaming sweeps instead: 32-row blocks where their
 // depth allows, else 64-row ones.  They put a tile on one compute unit and
 // walk down its rows, about 0.65 us per 32 of them at the least, so they want
 // many systems.  In the places of the single pass (and of the partitioned
@@ -454,7 +454,8 @@ bool stream_plan(const pent_plan *h, int rows, StreamPlan *p)
 // the rows of a chain, what was left out is added afterwards, and of a few
 // thousand rows that can be most (4096 x 65536 at sigma = 1: 831, by look-back
 // 951; with a top-hat in every system 1069 and 949; 2048 x 65536 418 / 478, with
-// sources in the bottom rows only 614 / 478; 8192 x 32768 814 / 1064 and 939 / 1065).
+// sources in the bottom rows only 614 / 478; 8192 x 32768 814 / 1064 and 939 / 1065);
+// the largest calls therefore look at their data first (stream_gated).
 // A forced schedule is run as asked: kind 4 is the look-back form, whose time
 // does not depend on the data.
 bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, StreamPlan *p)

@@ -545,9 +545,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3))) voi
 // state is.  The middle blocks' part is summed as they pass, and where it is
 // not negligible against what x_tail was formed from, the difference goes to
 // scratch (dx) and is applied after the workgroup's last block, as for the
-// truncated backward chain.  N = 4096 x 65536: solve 830 us, step 880, against
-// 1040 and 1090 by look-back (which waits 18 us of a unit's 49); a step costs
-// more than a plain solve (800) by the bottom blocks read twice, the border
+// truncated backward chain.  N = 4096 x 65536: solve 842 us, step 875 to 915, against
+// 1060 and 1100 by look-back (which waits 18 us of a unit's 49); a step costs
+// more than a plain solve (830) by the bottom blocks read twice, the border
 // products (18 us) and the values spilled for them.
 constexpr int kCsK = 32, kCsNW = 16, kCsEU = 4;
 

@@ -213,6 +213,8 @@ constexpr double kTruncTarget = 0x1p-72;
 // 32768 at 12, against 603 at 10), 833 us at 8 of 64 (868 at 9).
 constexpr int kStreamDepth32 = 10, kStreamDepth64 = 8, kStreamMaxDepth = 10;
 // ... and of a refinement correction, whose 12 waves hold two arrays each.
+// (its neglect is held against x, k_stream_fix; tiles in which that counts are
+// corrected by look-back)
 constexpr double kTruncFix = 0x1p-36;
 constexpr int kStreamDepthFix = 8;
 constexpr int64_t kStreamMaxRows = (int64_t)1 << 20;  // past it the depth is not searched for

@@ -125,7 +125,7 @@ __device__ __forceinline__ void load_backward(Rec<K> &r, const BwdRec *b, int64_
 // NT: loads and stores that pass the caches by, for rows on whole 128-byte
 // lines; where a line holds the columns of two tiles the L2 has to keep it
 // for the other (N = 256 x 20011 with an odd row stride: 17 us cached, 23 us
-// past the caches; N = 4096 x 65536, aligned: 860 and 800 us).
+// past the caches; N = 4096 x 65536, aligned: 7% less past them).
 template <int K, bool NT, typename TI>
 __device__ __forceinline__ void load_block(double (&v)[K], const TI *src, unsigned int lo, int64_t ld, int L)
 {
@@ -462,11 +462,11 @@ __device__ __forceinline__ void repair_rows(double *x, int64_t rs, int64_t r, F 
 // Values are read past the caches of the compute unit, in which lines loaded
 // earlier may still stand.  As much again is read and written as there are
 // rows with something to add, and that bounds it: 4096 x 65536 with a top-hat
-// in every system 1165 us against 790 for random ones, with a pulse in one
-// system of each tile 1043 (1079 with every system's rows read for it; the
-// periodic step 1230, 1303).
-// Bringing the states two turns ahead and 32 rows at once left both where
-// they are (1165, 1005).
+// in every system took 1069 us at sigma = 1 and 1276 at 50, against 831 and 855
+// for random ones, and with a pulse in one system of each tile 968 and 1139 (3%
+// more with every system's rows read for it).  Bringing the states two turns
+// ahead and 32 rows at once changed neither.  So the largest calls look for such
+// data first, and leave it to look-back (k_gate).
 template <int K, int NW, typename Off>
 __device__ __forceinline__ void stream_repair(double *x, int64_t rs, bool act, int64_t n, int nblk, int D,
                                               CSeg seg, CBwd bwd, CTrunc trunc, StreamLds<NW> &sh, int w, int slot, Off off)

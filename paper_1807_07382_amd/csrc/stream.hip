@@ -14,9 +14,10 @@ using namespace st;
 // (x).  HBM-bound: a wave's 32-row block lives 23 us of which its four sweeps
 // take 1.5; 10 are spent waiting for the blocks below to load and 12 issuing
 // loads and stores into a memory pipeline that is full (trace by the 100 MHz
-// counter, N = 4096 x 65536).  That solve takes 800 us, 5.4 TB/s, as does a
-// bare copy through the same persistent blocks (770 to 830 us for any block
-// shape on this layout); the look-back single pass took 950.
+// counter, N = 4096 x 65536).  That solve takes 817 to 833 us, 5.2 TB/s,
+// and a bare copy through the same persistent blocks 770 to 830 for any block
+// shape on this layout; the look-back single pass takes 950.
+// GATED: after k_gate, which may leave the call to a look-back launch (10 us).
 template <int K, int NW, int EU, bool NT, bool GATED, typename TI>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(EU, EU))) void k_stream(
     const FwdRec *fwd, const BwdRec *bwd, const SegRec *seg, const double *trunc, int D, int64_t n, int nblk,
