@@ -677,7 +677,7 @@ def run_periodic(args, torch):
                 roofline=dict(bound="hbm", achieved=gbs, peak=PEAK_HBM_GBS, unit="GB/s",
                               frac=gbs / PEAK_HBM_GBS,
                               traffic=traffic_for("cyc_stream", "periodic",
-                                                  ("cyclic.hip", "stream.h", "lookback.h"))
+                                                  ("cyclic.hip",) + STREAM_SOURCES)
                               if streams else None),
                 parity=dict(probe_systems=len(probe), max_rel_err_vs_oracle=err,
                             oracle_steps=args.warmup + steps))
