@@ -472,8 +472,9 @@ bool stream_route(const pent_plan *h, int kind, int seg_rows, int64_t batch, Str
 // and nothing is left out.  (Streams of longer matrices are the faster form for
 // some data only: 4096 x 16384 242, look-back 272, where the truncation leaves
 // nothing to add, but 500 where it does, and up to 2048 rows no faster than
-// resident tiles, 2048 x 32768 225 and 225, but 700.)  The x sweeps of a 2-D step go by the same two rules, so that they give the bits
-// of the separate passes.
+// resident tiles, 2048 x 32768 225 and 225, but 700.)  The x sweeps of a 2-D
+// step go by the same two rules, so that they give the bits of the separate
+// passes.
 bool t_stream_route(const pent_plan *h, int64_t batch, StreamPlan *p)
 {
     if (h->n > kStreamTRows || batch < 10000 || (batch + 31) / 32 > INT32_MAX) return false;
